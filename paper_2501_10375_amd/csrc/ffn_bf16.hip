@@ -20,7 +20,7 @@ namespace {
 // operand traffic can be in flight:
 //   full flavour:  256 slots x 256 weight rows, three 32 KB weight stages and two 32 KB slot stages.  The
 //       larger tile moves the fewest operand bytes per flop, which is what counts when the MFMAs are the
-//       work.  In the first GEMM a ragged tile issues only the MFMAs of its valid 32-slot fragments.
+//       work.  A ragged tile stages and computes only its valid 32-slot groups.
 //   ragged flavour (few routed rows per expert): 128 slots x 256 weight rows, three 48 KB stages, and
 //       empty slot fragments skipped.  Two K steps of both operands in flight hide the load latency that
 //       bounds a tile with little arithmetic, and half-height tiles pad cold experts less.
@@ -31,6 +31,8 @@ namespace {
 // below (the second GEMM by up to 25 %).
 constexpr int kRaggedRowsPerExpert1 = 128;  // mean routed rows per expert below which gemm1 runs ragged
 constexpr int kRaggedRowsPerExpert2 = 320;  // ... and gemm2
+// x of this many bytes and more is addressed with 64-bit row pointers (a lane offset plus the K offset must fit 32 bits).
+constexpr size_t kWideBytes = (size_t)15 << 28;
 constexpr int kWT = 2, kWW = 4;  // wavefront grid: slot groups x weight-row groups
 
 // y[t, :] = bf16( sum_j w[t, j] * out[slot_of[t, j], :] ), j ascending, fp32 sum, one rounding.
@@ -71,42 +73,15 @@ hipError_t allow_lds(Kernel k, int bytes, bool& configured) {
 // One persistent workgroup per CU (a multiple of the 8 XCDs); the kernels size their own work from `offs`.
 int persistent_grid() { return max(gg::kXcds, compute_units() / gg::kXcds * gg::kXcds); }
 
-// gemm1 (+ SwiGLU) in one pipeline shape.
-template <int BK, int STAGES, bool SKIP, int BT = gg::kBT, bool W3 = false>
-hipError_t launch_gemm1(const moe_shape_t& s, const uint16_t* x, const uint16_t* w1, const uint16_t* w3,
-                        const int32_t* offs, const int32_t* row_of_slot, void* act, int32_t* sync, float* partial,
-                        const StaleInput& alt, hipStream_t stream) {
-    using G1 = gg::Gemm<2, BK, STAGES, kWT, kWW, SKIP, BT, false, W3>;
-    auto k1 = gg::grouped_gemm_kernel<2, BK, STAGES, kWT, kWW, SKIP, BT, W3>;
-    auto k1_alt = gg::grouped_gemm1_alt_kernel<BK, STAGES, kWT, kWW, SKIP, BT, W3>;
-    static bool configured = false, configured_alt = false;
-    hipError_t e = allow_lds(k1, G1::kLdsBytes, configured);
-    if (e != hipSuccess) return e;
-    e = allow_lds(k1_alt, G1::kLdsBytes, configured_alt);
-    if (e != hipSuccess) return e;
-    if (alt.stale != nullptr)
-        k1_alt<<<persistent_grid(), G1::kThreads, G1::kLdsBytes, stream>>>(
-            x, static_cast<const uint16_t*>(alt.x_stale), alt.stale, w1, w3, offs, row_of_slot, s.n_experts, s.top_k, s.ffn,
-            s.hidden, act, sync, partial);
-    else
-        k1<<<persistent_grid(), G1::kThreads, G1::kLdsBytes, stream>>>(x, w1, w3, offs, row_of_slot, s.n_experts, s.top_k,
-                                                                       s.ffn, s.hidden, act, sync, partial);
-    stage_mark(stream, kStageGemm1);
-    return hipGetLastError();
-}
-
-// gemm2 in one pipeline shape.
-template <int BK, int STAGES, bool SKIP, int BT = gg::kBT, bool W3 = false>
-hipError_t launch_gemm2(const moe_shape_t& s, const uint16_t* act_in, const uint16_t* w2, const int32_t* offs,
-                        const int32_t* row_of_slot, float* out, int32_t* sync, float* partial, hipStream_t stream) {
-    using G2 = gg::Gemm<1, BK, STAGES, kWT, kWW, SKIP, BT, false, W3>;
-    auto k2 = gg::grouped_gemm_kernel<1, BK, STAGES, kWT, kWW, SKIP, BT, W3>;
+// One of the two GEMMs in flavour G.
+template <class G>
+hipError_t launch_gemm(const gg::GemmArgs& a, int stage, hipStream_t stream) {
+    auto kernel = gg::grouped_gemm_kernel<G>;
     static bool configured = false;
-    const hipError_t e = allow_lds(k2, G2::kLdsBytes, configured);
+    const hipError_t e = allow_lds(kernel, G::kLdsBytes, configured);
     if (e != hipSuccess) return e;
-    k2<<<persistent_grid(), G2::kThreads, G2::kLdsBytes, stream>>>(act_in, w2, nullptr, offs, row_of_slot, s.n_experts,
-                                                                   s.top_k, s.hidden, s.ffn, out, sync + gg::kSyncInts, partial);
-    stage_mark(stream, kStageGemm2);
+    kernel<<<persistent_grid(), G::kThreads, G::kLdsBytes, stream>>>(a);
+    stage_mark(stream, stage);
     return hipGetLastError();
 }
 
@@ -117,19 +92,42 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
                            const int32_t* row_of_slot, const int32_t* slot_of, void* act, float* out,
                            int32_t* sync, float* partial, const StaleInput& alt, hipStream_t stream) {
     static_assert(gg::kSyncInts == kGemmSyncInts && gg::kScratchBytes == kGemmScratchBytes, "workspace layout");
-    const uint16_t* xs = static_cast<const uint16_t*>(x);
-    const uint16_t* a16 = static_cast<const uint16_t*>(act);
-    const uint16_t *p1 = static_cast<const uint16_t*>(w1), *p3 = static_cast<const uint16_t*>(w3),
-                   *p2 = static_cast<const uint16_t*>(w2);
-    hipError_t e;
+    gg::GemmArgs g1{}, g2{};
+    g1.tok = static_cast<const uint16_t*>(x);
+    g1.wa = static_cast<const uint16_t*>(w1);
+    g1.wb = static_cast<const uint16_t*>(w3);
+    g1.offs = offs;
+    g1.row_of_slot = row_of_slot;
+    g1.E = s.n_experts;
+    g1.topk = s.top_k;
+    g1.N = s.ffn;
+    g1.K = s.hidden;
+    g1.dst = act;
+    g1.sync = sync;
+    g1.scratch = partial;
+    g1.tok_alt = static_cast<const uint16_t*>(alt.x_stale);
+    g1.alt_mask = alt.stale;
+    g2 = g1;
+    g2.tok = static_cast<const uint16_t*>(act);
+    g2.wa = static_cast<const uint16_t*>(w2);
+    g2.wb = nullptr;
+    g2.N = s.hidden;
+    g2.K = s.ffn;
+    g2.dst = out;
+    g2.sync = sync + gg::kSyncInts;
     const long routed = (long)tokens * s.top_k;
-    e = routed < (long)s.n_experts * kRaggedRowsPerExpert1
-            ? launch_gemm1<64, 3, true, 128>(s, xs, p1, p3, offs, row_of_slot, act, sync, partial, alt, stream)
-            : launch_gemm1<64, 2, false, 256, true>(s, xs, p1, p3, offs, row_of_slot, act, sync, partial, alt, stream);
+    const bool wide = (size_t)tokens * s.hidden * 2 >= kWideBytes;
+    hipError_t e;
+    if (routed < (long)s.n_experts * kRaggedRowsPerExpert1)
+        e = alt.stale != nullptr ? launch_gemm<gg::Gemm<2, 64, 3, kWT, kWW, true, 128, true>>(g1, kStageGemm1, stream)
+                                 : launch_gemm<gg::Gemm<2, 64, 3, kWT, kWW, true, 128>>(g1, kStageGemm1, stream);
+    else if (alt.stale != nullptr) e = launch_gemm<gg::FullGemm<2, true>>(g1, kStageGemm1, stream);
+    else if (wide) e = launch_gemm<gg::FullGemm<2, false, true>>(g1, kStageGemm1, stream);
+    else e = launch_gemm<gg::FullGemm<2>>(g1, kStageGemm1, stream);
     if (e != hipSuccess) return e;
     e = routed < (long)s.n_experts * kRaggedRowsPerExpert2
-            ? launch_gemm2<64, 3, true, 128>(s, a16, p2, offs, row_of_slot, out, sync, partial, stream)
-            : launch_gemm2<64, 2, false, 256, true>(s, a16, p2, offs, row_of_slot, out, sync, partial, stream);
+            ? launch_gemm<gg::Gemm<1, 64, 3, kWT, kWW, true, 128>>(g2, kStageGemm2, stream)
+            : launch_gemm<gg::FullGemm<1>>(g2, kStageGemm2, stream);
     if (e != hipSuccess) return e;
     combine_bf16<<<tokens, 256, 0, stream>>>(out, topk_w, slot_of, s.top_k, s.hidden, static_cast<uint16_t*>(y));
     stage_mark(stream, kStageCombine);

@@ -85,6 +85,42 @@ def test_bf16_ragged_fragments_of_full_tiles_every_token(oracle, T, H, F, E, k, 
     assert r["compared_tokens"] >= T - r["excluded"] - 2
 
 
+@pytest.mark.parametrize("T,H,F", [
+    (320, 64, 64), (352, 128, 192), (384, 192, 128), (401, 64, 320), (440, 320, 64), (470, 256, 128), (512, 128, 64),
+    (513, 192, 192), (545, 64, 128),
+])
+def test_bf16_slot_groups_and_short_k_loops(oracle, T, H, F):
+    """One expert, so the last slot tile of the call has T - 256 (or T - 512) rows: 1 to 8 groups of 32 slots,
+    among them single rows of a group; 1 to 5 K steps of 64 in each GEMM (the loop's first and last K steps are
+    separate code).  Every token is compared; the tolerance is the layer's (two roundings to bf16)."""
+    d, shape, out, res = _run(T, H, F, 1, 1, torch.bfloat16, seed=T)
+    r = check_layer(oracle, d, shape, res, torch.bfloat16, label=f"bf16 T={T} one expert")
+    print(r)
+    assert r["compared_tokens"] == T
+
+
+def test_bf16_hidden_states_of_more_than_4_gib(oracle):
+    """Row offsets of x past 32 bits: the first GEMM then addresses slot rows with 64-bit pointers.  Compared on
+    tokens from both ends of x (tokens are independent, so the oracle gets those rows alone)."""
+    H, F, E, k, dtype = 4096, 64, 2, 1, torch.bfloat16
+    T = (1 << 32) // (2 * H) + 300
+    d = synth.moe_layer_inputs(1, H, F, E, dtype, DEV, seed=5, with_next=False)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    x = torch.randn((T, H), generator=g, dtype=dtype, device=DEV)
+    idx = (torch.arange(T, device=DEV, dtype=torch.int32) % 3 == 0).int().reshape(T, 1)
+    w = torch.ones((T, 1), dtype=torch.float32, device=DEV)
+    y = torch.empty((T, H), dtype=dtype, device=DEV)
+    shape = moe.make_shape(H, F, E, k, dtype)
+    ws = moe.alloc_workspace(shape, T)
+    moe.moe_expert_ffn(shape, x, idx, w, d["w1"], d["w3"], d["w2"], y, ws)
+    torch.cuda.synchronize()
+    tok = torch.cat([torch.arange(0, 40), torch.arange(T // 2, T // 2 + 40), torch.arange(T - 350, T)])
+    h = host(d)
+    ref = oracle.expert_ffn(synth.to_numpy(x[tok.to(DEV)]), idx[tok.to(DEV)].cpu().numpy(),
+                            w[tok.to(DEV)].cpu().numpy().astype(np.float64), h["w1"], h["w3"], h["w2"])
+    assert output_error(to_f64(y[tok.to(DEV)]), ref) <= 2e-2
+
+
 @pytest.mark.parametrize("T,H,F,E,k", [
     (1, 256, 512, 8, 2), (5, 256, 512, 8, 2), (16, 256, 512, 8, 2), (8, 512, 1600, 16, 2), (3, 64, 64, 4, 1),
     (16, 128, 320, 8, 8), (7, 2048, 1024, 8, 2), (4, 128, 128, 64, 8), (9, 192, 256, 32, 2), (6, 8192, 128, 8, 2),
