@@ -15,38 +15,43 @@
 namespace moe {
 namespace {
 
-// Tile and pipeline shapes of the two GEMMs (slot rows per tile, K step, LDS stages).  Both move whole
-// 128-byte lines per global->LDS load instruction (K step 64); they differ in how much of a K step's
-// operand traffic can be in flight:
-//   full flavour:  256 slots x 256 weight rows, three 32 KB weight stages and two 32 KB slot stages.  The
-//       larger tile moves the fewest operand bytes per flop, which is what counts when the MFMAs are the
-//       work.  A ragged tile stages and computes only its valid 32-slot groups.
-//   ragged flavour (few routed rows per expert): 128 slots x 256 weight rows, three 48 KB stages, and
-//       empty slot fragments skipped.  Two K steps of both operands in flight hide the load latency that
-//       bounds a tile with little arithmetic, and half-height tiles pad cold experts less.
-// Each GEMM picks its flavour from the mean number of routed rows per expert (the counts themselves are
-// only known on the device).  Measured on the Mixtral- and Phi-shaped layers, 256 to 4096 tokens: the
-// first GEMM is faster in the full flavour from about 96-128 rows per expert on (7 % at 512 tokens of
-// the Mixtral shape, 10 % at 1536), the second from about 320 on (17 % at 1536 tokens), and slower
-// below (the second GEMM by up to 25 %).
-constexpr int kRaggedRowsPerExpert1 = 128;  // mean routed rows per expert below which gemm1 runs ragged
-constexpr int kRaggedRowsPerExpert2 = 320;  // ... and gemm2
 // x of this many bytes and more is addressed with 64-bit row pointers (a lane offset plus the K offset must fit 32 bits).
 constexpr size_t kWideBytes = (size_t)15 << 28;
-constexpr int kWT = 2, kWW = 4;  // wavefront grid: slot groups x weight-row groups
 
-// y[t, :] = bf16( sum_j w[t, j] * out[slot_of[t, j], :] ), j ascending, fp32 sum, one rounding.
+// y[t, :] = bf16( sum_j w[t, j] * out[slot_of[t, j], :] ), j ascending, fp32 sum, one rounding.  Where the second GEMM
+// split a tile along K, `out` holds its first piece; the others are added from the scratch memory in piece order first.
 __global__ __launch_bounds__(256) void combine_bf16(const float* __restrict__ out, const float* __restrict__ w,
-                                                    const int32_t* __restrict__ slot_of, int k, int H,
+                                                    const int32_t* __restrict__ slot_of, const int32_t* __restrict__ idx,
+                                                    const int32_t* __restrict__ offs, const gg::SplitTable* __restrict__ split,
+                                                    const float* __restrict__ pieces, int E, int k, int H,
                                                     uint16_t* __restrict__ y) {
     const int t = blockIdx.x;
+    const int parts = split->parts, slots = split->slots;
+    const int n_ft = (H + 255) / 256;
     for (int h = threadIdx.x * 8; h < H; h += 256 * 8) {
         float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         for (int j = 0; j < k; ++j) {
             const float wj = w[(size_t)t * k + j];
-            const float* src = out + (size_t)slot_of[(size_t)t * k + j] * H + h;
-            const float4 a = *reinterpret_cast<const float4*>(src);
-            const float4 b = *reinterpret_cast<const float4*>(src + 4);
+            const int slot = slot_of[(size_t)t * k + j];
+            const float* src = out + (size_t)slot * H + h;
+            float4 a = *reinterpret_cast<const float4*>(src);
+            float4 b = *reinterpret_cast<const float4*>(src + 4);
+            if (parts > 1) {
+                const int e = min(max(idx[(size_t)t * k + j], 0), E - 1);
+                const int first = offs[e], count = offs[e + 1] - first;
+                const int m = (slot - first) / slots, mt = (count + slots - 1) / slots;
+                const int tile = split->first_tile[e] + gg::TileList::position(mt, n_ft, m, h >> 8) - split->first_split;
+                if (tile >= 0) {
+                    const size_t stride = (size_t)split->piece_rows * 256;
+                    const float* p = pieces + (size_t)tile * (parts - 1) * stride + (size_t)(slot - first - m * slots) * 256 + (h & 255);
+                    for (int i = 1; i < parts; ++i, p += stride) {
+                        const float4 c = *reinterpret_cast<const float4*>(p);
+                        const float4 d = *reinterpret_cast<const float4*>(p + 4);
+                        a.x += c.x; a.y += c.y; a.z += c.z; a.w += c.w;
+                        b.x += d.x; b.y += d.y; b.z += d.z; b.w += d.w;
+                    }
+                }
+            }
             s[0] = fmaf(wj, a.x, s[0]); s[1] = fmaf(wj, a.y, s[1]);
             s[2] = fmaf(wj, a.z, s[2]); s[3] = fmaf(wj, a.w, s[3]);
             s[4] = fmaf(wj, b.x, s[4]); s[5] = fmaf(wj, b.y, s[5]);
@@ -73,7 +78,7 @@ hipError_t allow_lds(Kernel k, int bytes, bool& configured) {
 // One persistent workgroup per CU (a multiple of the 8 XCDs); the kernels size their own work from `offs`.
 int persistent_grid() { return max(gg::kXcds, compute_units() / gg::kXcds * gg::kXcds); }
 
-// One of the two GEMMs in flavour G.
+// One of the two GEMMs.
 template <class G>
 hipError_t launch_gemm(const gg::GemmArgs& a, int stage, hipStream_t stream) {
     auto kernel = gg::grouped_gemm_kernel<G>;
@@ -87,11 +92,15 @@ hipError_t launch_gemm(const gg::GemmArgs& a, int stage, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, const float* topk_w, const void* w1,
-                           const void* w3, const void* w2, void* y, const int32_t* offs,
+size_t gemm_scratch_bytes(const moe_shape_t& s, int tokens) {
+    return gg::scratch_units(tokens, s.top_k, s.n_experts, s.hidden) * gg::kUnitFloats * sizeof(float);
+}
+
+hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, const int32_t* topk_idx, const float* topk_w,
+                           const void* w1, const void* w3, const void* w2, void* y, const int32_t* offs,
                            const int32_t* row_of_slot, const int32_t* slot_of, void* act, float* out,
                            int32_t* sync, float* partial, const StaleInput& alt, hipStream_t stream) {
-    static_assert(gg::kSyncInts == kGemmSyncInts && gg::kScratchBytes == kGemmScratchBytes, "workspace layout");
+    static_assert(gg::kSyncInts == kGemmSyncInts, "workspace layout");
     gg::GemmArgs g1{}, g2{};
     g1.tok = static_cast<const uint16_t*>(x);
     g1.wa = static_cast<const uint16_t*>(w1);
@@ -104,7 +113,6 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
     g1.K = s.hidden;
     g1.dst = act;
     g1.sync = sync;
-    g1.scratch = partial;
     g1.tok_alt = static_cast<const uint16_t*>(alt.x_stale);
     g1.alt_mask = alt.stale;
     g2 = g1;
@@ -115,21 +123,19 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
     g2.K = s.ffn;
     g2.dst = out;
     g2.sync = sync + gg::kSyncInts;
-    const long routed = (long)tokens * s.top_k;
+    g2.scratch = partial;
+    g2.scratch_limit = (int)gg::scratch_units(tokens, s.top_k, s.n_experts, s.hidden);
     const bool wide = (size_t)tokens * s.hidden * 2 >= kWideBytes;
     hipError_t e;
-    if (routed < (long)s.n_experts * kRaggedRowsPerExpert1)
-        e = alt.stale != nullptr ? launch_gemm<gg::Gemm<2, 64, 3, kWT, kWW, true, 128, true>>(g1, kStageGemm1, stream)
-                                 : launch_gemm<gg::Gemm<2, 64, 3, kWT, kWW, true, 128>>(g1, kStageGemm1, stream);
-    else if (alt.stale != nullptr) e = launch_gemm<gg::FullGemm<2, true>>(g1, kStageGemm1, stream);
-    else if (wide) e = launch_gemm<gg::FullGemm<2, false, true>>(g1, kStageGemm1, stream);
-    else e = launch_gemm<gg::FullGemm<2>>(g1, kStageGemm1, stream);
+    if (alt.stale != nullptr) e = launch_gemm<gg::Gemm<2, true>>(g1, kStageGemm1, stream);
+    else if (wide) e = launch_gemm<gg::Gemm<2, false, true>>(g1, kStageGemm1, stream);
+    else e = launch_gemm<gg::Gemm<2>>(g1, kStageGemm1, stream);
     if (e != hipSuccess) return e;
-    e = routed < (long)s.n_experts * kRaggedRowsPerExpert2
-            ? launch_gemm<gg::Gemm<1, 64, 3, kWT, kWW, true, 128>>(g2, kStageGemm2, stream)
-            : launch_gemm<gg::FullGemm<1>>(g2, kStageGemm2, stream);
+    e = launch_gemm<gg::Gemm<1>>(g2, kStageGemm2, stream);
     if (e != hipSuccess) return e;
-    combine_bf16<<<tokens, 256, 0, stream>>>(out, topk_w, slot_of, s.top_k, s.hidden, static_cast<uint16_t*>(y));
+    combine_bf16<<<tokens, 256, 0, stream>>>(out, topk_w, slot_of, topk_idx, offs,
+                                             reinterpret_cast<const gg::SplitTable*>(g2.sync + gg::kXcds), partial, s.n_experts,
+                                             s.top_k, s.hidden, static_cast<uint16_t*>(y));
     stage_mark(stream, kStageCombine);
     return hipGetLastError();
 }

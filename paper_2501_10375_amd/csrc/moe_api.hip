@@ -33,7 +33,7 @@ WorkspaceLayout workspace_layout(const moe_shape_t& s, int tokens) {
     L.act = off;         off = align_up(off + A * (size_t)s.ffn * esz);
     L.out = off;         off = align_up(off + A * (size_t)s.hidden * sizeof(float));
     L.partial = off;
-    if (s.dtype == MOE_BF16 && tokens > kStreamMaxTokens) off = align_up(off + kGemmScratchBytes);
+    if (s.dtype == MOE_BF16 && tokens > kStreamMaxTokens) off = align_up(off + gemm_scratch_bytes(s, tokens));
     L.total = off;
     return L;
 }
@@ -213,7 +213,7 @@ hipError_t run_ffn(const moe_shape_t& s, int tokens, const void* x, const int32_
         return launch_ffn_f32(s, tokens, static_cast<const float*>(x), w, static_cast<const float*>(w1),
                               static_cast<const float*>(w3), static_cast<const float*>(w2), static_cast<float*>(y),
                               ws.offs, ws.row_of_slot, ws.slot_of, static_cast<float*>(ws.act), ws.out, alt, stream);
-    return launch_ffn_bf16(s, tokens, x, w, w1, w3, w2, y, ws.offs, ws.row_of_slot, ws.slot_of, ws.act, ws.out,
+    return launch_ffn_bf16(s, tokens, x, idx, w, w1, w3, w2, y, ws.offs, ws.row_of_slot, ws.slot_of, ws.act, ws.out,
                            ws.sync, ws.partial, alt, stream);
 }
 

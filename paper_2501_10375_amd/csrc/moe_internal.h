@@ -25,14 +25,13 @@ constexpr int kStreamMaxTokens = 32;
 
 // Rows (tokens) per M-tile of the grouped GEMMs; an M-tile never spans two experts.
 constexpr int kTileTokensF32 = 64;
-constexpr int kTileTokensBf16 = 256;
 
 // The two blocks of flags and counters come first, at offsets that depend on nothing: calls of any
 // size on one workspace then never put other data where a decode-size call keeps its launch count
 // and arrival flags.
 struct WorkspaceLayout {
     size_t dec_flags;    // uint32 [kDecodeFlagInts]  arrival flags, launch count and status word of the decode kernel's two grid-wide rendezvous
-    size_t sync;         // int32 [kSyncInts]    tile hand-out and split-tile arrival counters of the two grouped GEMMs
+    size_t sync;         // int32 [kSyncInts]    tile hand-out counters of the two grouped GEMMs, table of split tiles
     size_t hist;         // int32 [n_blocks, E]  per-block selection histogram
     size_t hist_next;    // int32 [n_blocks, E]  same for the next-layer gate
     size_t offs;         // int32 [E + 1]        exclusive scan of counts
@@ -41,7 +40,7 @@ struct WorkspaceLayout {
     size_t route_end;    // bytes needed by routing-only calls
     size_t act;          // dtype [A, F]         silu(W1 x) * (W3 x)
     size_t out;          // fp32  [A, H]         per-assignment expert output
-    size_t partial;      // fp32  [8 * 32, 256, 256]  pieces of K-split tiles (bf16 prefill path only)
+    size_t partial;      // fp32  pieces of K-split tiles (bf16 prefill path only; see gemm_scratch_bytes)
     size_t total;        // bytes needed by the whole layer
 };
 
@@ -83,11 +82,12 @@ hipError_t launch_hist_from_idx(const moe_shape_t& s, int tokens, const int32_t*
 // Sum block histograms into counts (counts may be null), and when
 // row_of_slot/slot_of are given build offs and the stable token->expert
 // permutation.
-// Counters and scratch of the persistent grouped GEMMs (see grouped_gemm_bf16.h): per launch 8 tile
-// hand-out counters (one per XCD) + 8 x 32 split-tile arrival counters, and one 256 x 256 fp32 piece per workgroup.
-constexpr int kGemmSyncInts = 8 + 8 * 32;
+// Counters of the persistent grouped GEMMs (see grouped_gemm_bf16.h): per launch 8 tile hand-out counters (one per XCD)
+// and the table of the second GEMM's split tiles.
+constexpr int kGemmSyncInts = 8 + 8 + 64;
 constexpr int kSyncInts = 2 * kGemmSyncInts;  // gemm1 and gemm2
-constexpr size_t kGemmScratchBytes = (size_t)8 * 32 * 256 * 256 * sizeof(float);
+// Bytes of scratch memory the second GEMM may need for the pieces of K-split tiles.
+size_t gemm_scratch_bytes(const moe_shape_t& s, int tokens);
 // `sync` (may be null) is a block of kSyncInts counters that is cleared for the GEMMs that follow.
 // For long calls the histograms in `hist` are replaced by their per-block prefixes.
 hipError_t launch_finalize(const moe_shape_t& s, int tokens, int32_t* hist, const int32_t* idx,
@@ -114,7 +114,7 @@ hipError_t launch_ffn_f32(const moe_shape_t& s, int tokens, const float* x, cons
                           float* act, float* out, const StaleInput& alt, hipStream_t stream);
 
 // Grouped expert FFN, bf16 storage, MFMA (prefill-size calls).
-hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, const float* topk_w,
+hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, const int32_t* topk_idx, const float* topk_w,
                            const void* w1, const void* w3, const void* w2, void* y,
                            const int32_t* offs, const int32_t* row_of_slot, const int32_t* slot_of,
                            void* act, float* out, int32_t* sync, float* partial, const StaleInput& alt,

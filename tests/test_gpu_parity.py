@@ -99,6 +99,22 @@ def test_bf16_slot_groups_and_short_k_loops(oracle, T, H, F):
     assert r["compared_tokens"] == T
 
 
+@pytest.mark.parametrize("T,H,F,E,k", [
+    (70, 320, 1856, 5, 3),      # 29 K steps in the second GEMM: two parts at most; the last feature tile is a quarter one
+    (257, 64, 3584, 1, 1),      # one expert: a full slot tile and one with a single row, cut into up to 4 parts
+    (900, 512, 5504, 4, 2),     # 86 K steps that the parts do not divide; slot tiles of unequal height
+    (34, 4096, 896, 64, 8),     # more tiles than compute units: whole tiles first, then 14-step pieces of the coldest experts
+    (1200, 2048, 1792, 6, 2),   # hot experts whose slot tiles are shared, leftover tiles among them
+])
+def test_bf16_second_gemm_pieces_every_token(oracle, T, H, F, E, k):
+    """The second GEMM cuts the tiles left over after its last full round along K; their pieces are added by the kernel
+    that combines a token's selections.  Every token is compared."""
+    d, shape, out, res = _run(T, H, F, E, k, torch.bfloat16, seed=T + E)
+    r = check_layer(oracle, d, shape, res, torch.bfloat16, label=f"bf16 T={T} pieces")
+    print(r)
+    assert r["compared_tokens"] >= T - r["excluded"] - 2
+
+
 def test_bf16_hidden_states_of_more_than_4_gib(oracle):
     """Row offsets of x past 32 bits: the first GEMM then addresses slot rows with 64-bit pointers.  Compared on
     tokens from both ends of x (tokens are independent, so the oracle gets those rows alone)."""
