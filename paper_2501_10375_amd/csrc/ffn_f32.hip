@@ -2,147 +2,193 @@
 // (expert execution of DAOP Sec. II-A / Algorithm 1's local expert execution,
 // with the Mixtral expert  y = W2 ( silu(W1 x) * (W3 x) )  the paper builds on).
 //
-// This is the exact-arithmetic configuration: fp32 in, fp32 FMA accumulation,
-// nothing narrowed.  Plain LDS-tiled kernels, 64 x 64 output tile, 4 x 4
-// outputs per thread; rows of an M-tile are gathered through the permutation
-// and never span two experts.
+// This is the exact-arithmetic configuration: fp32 in, fp32 accumulation, nothing narrowed.  Rows of a
+// unit are gathered through the permutation and never span two experts.
+//
+// The sizes of this configuration are small (hidden and ffn of a few hundred to a few thousand), so a call
+// lasts as long as its chain of memory latencies, not as its arithmetic.  The two GEMMs are therefore
+// organised to have few dependent steps:
+//   * v_mfma_f32_16x16x4_f32: its operands are one float per lane, row lane % 16 and K element lane / 16.
+//     Which four of sixteen K elements an MFMA multiplies is free as long as both operands agree, so a lane
+//     loads four consecutive floats of its row (16 bytes) and feeds them to four MFMAs.  That is the layout
+//     the rows have in memory: no LDS staging and no barrier in the loop.
+//   * the four wavefronts of a workgroup split K; their partial sums meet in LDS once, in wavefront order.
+//   * a workgroup makes 16 features of up to 16 * NC slots; NC grows with the call (see pick_groups()), so
+//     that a small call is spread over the chip and a large one re-reads its operands less often.
+//   * each wavefront has kAhead K steps of loads in flight.
+// Measured against the LDS-tiled FMA kernels these replaced (64 x 64 outputs, K in steps of 16 between two
+// barriers), first and second GEMM:
+//   64 tokens, hidden 256, ffn 512, 8 experts top-2:        33 + 34 -> 9 + 7 us
+//   100 tokens, hidden 512, ffn 1024, 8 experts top-2:      64 + 65 -> 21 + 13 us
+//   512 tokens, hidden 1024, ffn 2048, 4 experts top-4:    262 + 185 -> 227 + 131 us (76 and 66 TFLOP/s)
+// and half as far from a 64-bit layer (y: 6.0e-7 -> 3.1e-7, 1.2e-6 -> 6.0e-7 at the first and the last), because a
+// running sum is a quarter as long.
+#include <type_traits>
+
 #include "moe_internal.h"
 
 namespace moe {
 namespace {
 
-constexpr int BM = kTileTokensF32;  // tokens (slots) per tile
-constexpr int BN = 64;              // output features per tile
-constexpr int BK = 16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-// Maps a linear M-tile index to (expert, first slot, valid rows).  Uniform per workgroup.
-__device__ inline bool find_mtile(const int32_t* __restrict__ offs, int E, int mt, int& e, int& slot0, int& rows) {
-    int acc = 0;
-    for (int i = 0; i < E; ++i) {
-        const int c = offs[i + 1] - offs[i];
-        const int nt = (c + BM - 1) / BM;
-        if (mt < acc + nt) {
-            const int local = (mt - acc) * BM;
-            e = i;
-            slot0 = offs[i] + local;
-            rows = min(BM, c - local);
-            return true;
-        }
-        acc += nt;
+constexpr int kWaves = 4;
+constexpr int kRows = 16;    // rows of an MFMA operand
+constexpr int kStepK = 16;   // K elements of a step: 16 bytes a lane
+constexpr int kAhead = 4;    // steps in flight
+constexpr int kPair = 2;     // steps requested together: 128 bytes of a row, a whole cache line
+
+// Unit u of the call: up to `unit_rows` slots of one expert.  Lane e looks after expert e; every wavefront finds
+// the same answer.  False if there is no such unit.
+__device__ inline bool find_unit(const int32_t* __restrict__ offs, int E, int unit_rows, int u, int& e, int& slot0, int& rows) {
+    const int lane = threadIdx.x & 63;
+    const int first = lane < E ? offs[lane] : 0;
+    const int count = lane < E ? offs[lane + 1] - first : 0;
+    const int units = (count + unit_rows - 1) / unit_rows;
+    int end = units;  // inclusive sum
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+        const int v = __shfl_up(end, d, 64);
+        if (lane >= d) end += v;
     }
-    return false;
+    const uint64_t mine = __ballot(u >= end - units && u < end);
+    if (mine == 0) return false;
+    const int r = __ffsll((long long)mine) - 1;
+    const int local = (u - __builtin_amdgcn_readlane(end - units, r)) * unit_rows;
+    e = r;
+    slot0 = __builtin_amdgcn_readlane(first, r) + local;
+    rows = min(unit_rows, __builtin_amdgcn_readlane(count, r) - local);
+    return true;
 }
 
-// Loads a [64 rows x 16 k] tile, one float4 per thread, and stores it k-major in LDS.
-__device__ inline void stage_tile(float (*dst)[BM + 4], const float* __restrict__ rowptr, int kq, int r) {
-    const float4 v = *reinterpret_cast<const float4*>(rowptr + kq * 4);
-    dst[kq * 4 + 0][r] = v.x;
-    dst[kq * 4 + 1][r] = v.y;
-    dst[kq * 4 + 2][r] = v.z;
-    dst[kq * 4 + 3][r] = v.w;
+// Work of this workgroup.  Workgroups go to the XCDs in turn, blockIdx.x % 8; the units are cut into 8 contiguous
+// chunks, and one XCD takes a chunk at one feature tile, so that units of one expert read their weight rows through the
+// same L2.  Which chunk it takes moves on with the feature tile: the last ones may hold fewer units.
+__device__ inline bool my_work(int tiles, int& tile, int& unit) {
+    tile = blockIdx.z * gridDim.y + blockIdx.y;
+    unit = (int)((blockIdx.x + blockIdx.y) & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    return tile < tiles;
 }
 
-// act[slot, f] = silu(x_row . w1[e,f,:]) * (x_row . w3[e,f,:])
-__global__ __launch_bounds__(256) void gemm1_swiglu_f32(const float* __restrict__ x, const float* __restrict__ w1,
-                                                        const float* __restrict__ w3,
-                                                        const int32_t* __restrict__ offs,
-                                                        const int32_t* __restrict__ row_of_slot, int E, int k, int H,
-                                                        int F, float* __restrict__ act,
+// acc[m][c] += (16 weight rows m) . (16 rows of column group c) over `steps` K steps; w[m] and x[c] are this lane's
+// first 16 bytes (row lane % 16, K element 4 * (lane / 16)).
+template <int NM, int NC>
+__device__ inline void dot_rows(const float* const (&w)[NM], const float* const (&x)[NC], int steps, f32x4 (&acc)[NM][NC]) {
+    f32x4 wf[kAhead][NM], xf[kAhead][NC];
+    auto load = [&](int i, int s) {
+        const size_t off = (size_t)min(s, steps - 1) * kStepK;  // requests past the end re-read the last step (never used)
+#pragma unroll
+        for (int m = 0; m < NM; ++m) wf[i][m] = *reinterpret_cast<const f32x4*>(w[m] + off);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) xf[i][c] = *reinterpret_cast<const f32x4*>(x[c] + off);
+    };
+    auto multiply = [&](int i) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int m = 0; m < NM; ++m)
+                    acc[m][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[i][m][q], xf[i][c][q], acc[m][c], 0, 0, 0);
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) load(i, i);
+    int s = 0;
+    for (; s + kAhead < steps; s += kAhead) {
+#pragma unroll
+        for (int i = 0; i < kAhead; i += kPair) {
+#pragma unroll
+            for (int j = i; j < i + kPair; ++j) multiply(j);
+#pragma unroll
+            for (int j = i; j < i + kPair; ++j) load(j, s + kAhead + j);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+        if (s + i < steps) multiply(i);
+}
+
+// A workgroup makes FR * 16 features.
+// NM = 2 (gemm1): dst[slot, f] = silu(x_row . wa[e, f]) * (x_row . wb[e, f]), x_row gathered through row_of_slot;
+// NM = 1 (gemm2): dst[slot, n] = src[slot] . wa[e, n].
+template <int NM, int FR, int NC_MAX>
+__global__ __launch_bounds__(kWaves * 64) void gemm_f32(const float* __restrict__ src, const float* __restrict__ wa,
+                                                        const float* __restrict__ wb, const int32_t* __restrict__ offs,
+                                                        const int32_t* __restrict__ row_of_slot, int E, int k, int N, int K,
+                                                        float* __restrict__ dst,
                                                         const float* __restrict__ x_stale,
                                                         const uint8_t* __restrict__ stale) {
-    __shared__ float As[BK][BM + 4];
-    __shared__ float B1s[BK][BN + 4];
-    __shared__ float B3s[BK][BN + 4];
-    int e, slot0, rows;
-    if (!find_mtile(offs, E, blockIdx.x, e, slot0, rows)) return;
-    const int f0 = blockIdx.y * BN;
-    const int tid = threadIdx.x;
-    const int lr = tid >> 2, kq = tid & 3;  // staging: row 0..63, k quarter 0..3
-    const int srow = min(lr, rows - 1);     // rows past the end re-read a valid row; never stored
-    const int assignment = row_of_slot[slot0 + srow];  // t * k + j
-    const int token = assignment / k;
-    // a pre-calculated selection reads the earlier hidden state of its token
-    const float* xa = ((stale != nullptr && stale[assignment] != 0) ? x_stale : x) + (size_t)token * H;
-    const float* b1 = w1 + ((size_t)e * F + f0 + lr) * H;
-    const float* b3 = w3 + ((size_t)e * F + f0 + lr) * H;
-    const int tm = (tid >> 4) * 4, tn = (tid & 15) * 4;
-    float g[4][4] = {}, u[4][4] = {};
-    for (int k0 = 0; k0 < H; k0 += BK) {
-        stage_tile(As, xa + k0, kq, lr);
-        stage_tile(B1s, b1 + k0, kq, lr);
-        stage_tile(B3s, b3 + k0, kq, lr);
-        __syncthreads();
+    __shared__ f32x4 part[kWaves][NM * FR][NC_MAX][64];
+    int tile, unit, e, slot0, rows;
+    if (!my_work(N / (FR * kRows), tile, unit)) return;
+    if (!find_unit(offs, E, NC_MAX * kRows, unit, e, slot0, rows)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int row = lane & 15, kq = lane >> 4;
+    const int n0 = tile * FR * kRows;
+    const int steps = K / kStepK / kWaves;  // K is a multiple of 64: the wavefronts take equal contiguous runs
+    const size_t at = (size_t)wave * steps * kStepK + kq * 4;
+    const float* w[NM * FR];
 #pragma unroll
-        for (int kk = 0; kk < BK; ++kk) {
-            float a[4], p[4], q[4];
+    for (int m = 0; m < NM * FR; ++m) w[m] = (m < FR ? wa : wb) + ((size_t)e * N + n0 + (m % FR) * kRows + row) * K + at;
+    // the unit's column groups, as many as it has
+    auto run = [&](auto nc) {
+        constexpr int NC = decltype(nc)::value;
+        const float* x[NC];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = As[kk][tm + i];
-                p[i] = B1s[kk][tn + i];
-                q[i] = B3s[kk][tn + i];
+        for (int c = 0; c < NC; ++c) {
+            const int slot = slot0 + min(c * kRows + row, rows - 1);  // rows past the end re-read a valid row; never stored
+            if constexpr (NM == 2) {
+                const int assignment = row_of_slot[slot];  // t * k + j
+                // a pre-calculated selection reads the earlier hidden state of its token
+                x[c] = ((stale != nullptr && stale[assignment] != 0) ? x_stale : src) + (size_t)(assignment / k) * K + at;
+            } else {
+                x[c] = src + (size_t)slot * K + at;
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    g[i][j] = fmaf(a[i], p[j], g[i][j]);
-                    u[i][j] = fmaf(a[i], q[j], u[i][j]);
-                }
         }
-        __syncthreads();
+        f32x4 acc[NM * FR][NC];
+#pragma unroll
+        for (int m = 0; m < NM * FR; ++m)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[m][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        dot_rows<NM * FR, NC>(w, x, steps, acc);
+#pragma unroll
+        for (int m = 0; m < NM * FR; ++m)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) part[wave][m][c][lane] = acc[m][c];
+    };
+    const int groups = (rows + kRows - 1) / kRows;
+    if constexpr (NC_MAX >= 4) {
+        if (groups == 4) run(std::integral_constant<int, 4>{});
+        if (groups == 3) run(std::integral_constant<int, 3>{});
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (tm + i < rows) {
-            float4 o;
-            float* op = &o.x;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) op[j] = g[i][j] / (1.f + expf(-g[i][j])) * u[i][j];
-            *reinterpret_cast<float4*>(act + (size_t)(slot0 + tm + i) * F + f0 + tn) = o;
-        }
+    if constexpr (NC_MAX >= 2) {
+        if (groups == 2) run(std::integral_constant<int, 2>{});
     }
-}
-
-// out[slot, h] = act[slot, :] . w2[e, h, :]
-__global__ __launch_bounds__(256) void gemm2_f32(const float* __restrict__ act, const float* __restrict__ w2,
-                                                 const int32_t* __restrict__ offs, int E, int H, int F,
-                                                 float* __restrict__ out) {
-    __shared__ float As[BK][BM + 4];
-    __shared__ float Bs[BK][BN + 4];
-    int e, slot0, rows;
-    if (!find_mtile(offs, E, blockIdx.x, e, slot0, rows)) return;
-    const int h0 = blockIdx.y * BN;
-    const int tid = threadIdx.x;
-    const int lr = tid >> 2, kq = tid & 3;
-    const int srow = min(lr, rows - 1);
-    const float* aa = act + (size_t)(slot0 + srow) * F;
-    const float* bb = w2 + ((size_t)e * H + h0 + lr) * F;
-    const int tm = (tid >> 4) * 4, tn = (tid & 15) * 4;
-    float c[4][4] = {};
-    for (int k0 = 0; k0 < F; k0 += BK) {
-        stage_tile(As, aa + k0, kq, lr);
-        stage_tile(Bs, bb + k0, kq, lr);
-        __syncthreads();
+    if (groups == 1) run(std::integral_constant<int, 1>{});
+    __syncthreads();
+    // MFMA result: lane holds column (slot) lane % 16 and rows (features) 4 * (lane / 16) .. + 3.  A wavefront sums one
+    // 16 x 16 result at a time.
+    for (int item = wave; item < groups * FR; item += kWaves) {
+        const int c = item / FR, f = item % FR;
+        const int slot = c * kRows + row;
+        if (slot >= rows) continue;
+        f32x4 sum[NM];
 #pragma unroll
-        for (int kk = 0; kk < BK; ++kk) {
-            float a[4], p[4];
+        for (int m = 0; m < NM; ++m) {
+            sum[m] = part[0][m * FR + f][c][lane];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = As[kk][tm + i];
-                p[i] = Bs[kk][tn + i];
+            for (int v = 1; v < kWaves; ++v) {
+                const f32x4 o = part[v][m * FR + f][c][lane];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum[m][i] += o[i];
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) c[i][j] = fmaf(a[i], p[j], c[i][j]);
         }
-        __syncthreads();
-    }
+        f32x4 o = sum[0];
+        if constexpr (NM == 2) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (tm + i < rows)
-            *reinterpret_cast<float4*>(out + (size_t)(slot0 + tm + i) * H + h0 + tn) =
-                make_float4(c[i][0], c[i][1], c[i][2], c[i][3]);
+            for (int i = 0; i < 4; ++i) o[i] = sum[0][i] / (1.f + expf(-sum[0][i])) * sum[1][i];
+        }
+        *reinterpret_cast<f32x4*>(dst + (size_t)(slot0 + slot) * N + n0 + f * kRows + kq * 4) = o;
     }
 }
 
@@ -165,20 +211,53 @@ __global__ __launch_bounds__(256) void combine_f32(const float* __restrict__ out
     }
 }
 
+// Column groups of 16 slots a workgroup takes: the most that still leave kMinWorkgroups of them, counting an expert's
+// last unit as half full.  More groups re-read the weights less often; fewer keep more of the chip busy.
+// (Measured at 256 and 4096 as well, second GEMM: 300 tokens, hidden 512, ffn 2048, 8 experts 57 / 47 / 47 us at 256 / 1024 /
+// 4096, first GEMM 60 / 59 / 66; 512 tokens, hidden 1024, ffn 2048, 4 experts top-4, second GEMM 132 / 127 / 183.)
+constexpr int kMinWorkgroups = 1024;
+int pick_groups(int routed, int experts, int features) {
+    for (int nc = 4; nc > 1; nc /= 2)
+        if ((long)(routed / (nc * kRows) + (min(experts, routed) + 1) / 2) * (features / kRows) >= kMinWorkgroups) return nc;
+    return 1;
+}
+
+struct F32Gemm {
+    const float *src, *wa, *wb;
+    const int32_t *offs, *row_of_slot;
+    int E, k, N, K, routed;
+    float* dst;
+    StaleInput alt;
+};
+
+template <int NM, int FR, int NC>
+void launch_groups(const F32Gemm& g, hipStream_t stream) {
+    const int units = g.routed / (NC * kRows) + min(g.E, g.routed);  // sum of the experts' ceil(rows / unit) at most
+    const int tiles = g.N / (FR * kRows), y = min(tiles, 1 << 15);           // (a grid's y ends at 65535)
+    const dim3 grid((units + 7) / 8 * 8, y, (tiles + y - 1) / y);
+    gemm_f32<NM, FR, NC><<<grid, kWaves * 64, 0, stream>>>(g.src, g.wa, g.wb, g.offs, g.row_of_slot, g.E, g.k, g.N, g.K, g.dst,
+                                                       static_cast<const float*>(g.alt.x_stale), g.alt.stale);
+}
+
+template <int NM>
+void launch_gemm_f32(const F32Gemm& g, hipStream_t stream) {
+    const int nc = pick_groups(g.routed, g.E, g.N);
+    if (nc == 4) launch_groups<NM, NM == 1 ? 2 : 1, 4>(g, stream);
+    else if (nc == 2) launch_groups<NM, 1, 2>(g, stream);
+    else launch_groups<NM, 1, 1>(g, stream);
+}
+
 }  // namespace
 
 hipError_t launch_ffn_f32(const moe_shape_t& s, int tokens, const float* x, const float* topk_w, const float* w1,
                           const float* w3, const float* w2, float* y, const int32_t* offs,
                           const int32_t* row_of_slot, const int32_t* slot_of, float* act, float* out,
                           const StaleInput& alt, hipStream_t stream) {
-    const int A = tokens * s.top_k;
-    const int max_mtiles = (A + BM - 1) / BM + s.n_experts;
-    gemm1_swiglu_f32<<<dim3(max_mtiles, s.ffn / BN), 256, 0, stream>>>(x, w1, w3, offs, row_of_slot, s.n_experts,
-                                                                       s.top_k, s.hidden, s.ffn, act,
-                                                                       static_cast<const float*>(alt.x_stale), alt.stale);
+    F32Gemm g{x, w1, w3, offs, row_of_slot, s.n_experts, s.top_k, s.ffn, s.hidden, tokens * s.top_k, act, alt};
+    launch_gemm_f32<2>(g, stream);
     stage_mark(stream, kStageGemm1);
-    gemm2_f32<<<dim3(max_mtiles, s.hidden / BN), 256, 0, stream>>>(act, w2, offs, s.n_experts, s.hidden, s.ffn,
-                                                                  out);
+    g = {act, w2, nullptr, offs, row_of_slot, s.n_experts, s.top_k, s.hidden, s.ffn, tokens * s.top_k, out, {nullptr, nullptr}};
+    launch_gemm_f32<1>(g, stream);
     stage_mark(stream, kStageGemm2);
     combine_f32<<<tokens, 256, 0, stream>>>(out, topk_w, slot_of, s.top_k, s.hidden, y);
     stage_mark(stream, kStageCombine);

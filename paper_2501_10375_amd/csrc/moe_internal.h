@@ -23,9 +23,6 @@ constexpr int kDecodeMaxTokens = 16;
 // the 256-row MFMA tiles (measured: 617 vs 737 us at 32 tokens; at 64 tokens it loses, 863 vs 782 us).
 constexpr int kStreamMaxTokens = 32;
 
-// Rows (tokens) per M-tile of the grouped GEMMs; an M-tile never spans two experts.
-constexpr int kTileTokensF32 = 64;
-
 // The two blocks of flags and counters come first, at offsets that depend on nothing: calls of any
 // size on one workspace then never put other data where a decode-size call keeps its launch count
 // and arrival flags.

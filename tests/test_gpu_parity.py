@@ -177,6 +177,24 @@ def test_fp32_path(oracle, T, H, F, E, k):
     print(r)
 
 
+@pytest.mark.parametrize("T,H,F,E,k,zipf", [
+    (1, 64, 64, 4, 1, None),         # one slot, one K step a wavefront in both GEMMs
+    (17, 128, 320, 1, 1, None),      # 17 slots of one expert: a full 16-slot group and a single row; 2 and 5 K steps
+    (16, 192, 64, 8, 8, None),       # every expert has all 16 tokens
+    (95, 64, 2048, 2, 2, None),      # 95 slots an expert in units of 64 or 32: ragged last units; 32 K steps
+    (260, 320, 1024, 3, 2, 1.2),     # units of 64 slots in the first GEMM, of 16 in the second
+    (700, 512, 2048, 4, 3, 1.2),     # units of 64 slots in both, one to four groups in the last ones
+    (33, 64, 64, 64, 8, 0.5),        # 64 experts; 128 selections to rank in a block
+    (40, 4096, 64, 33, 5, 1.2),      # four blocks of experts in the router, more than one chunk of its K steps
+    (37, 1088, 128, 17, 2, 1.2),     # router: 68 K steps over 16 wavefronts, two blocks of experts, the second with one
+])
+def test_fp32_units_groups_and_router_blocks(oracle, T, H, F, E, k, zipf):
+    d, shape, out, res = _run(T, H, F, E, k, torch.float32, zipf=zipf)
+    r = check_layer(oracle, d, shape, res, torch.float32, label=f"fp32 units T={T}")
+    # fp32 sums of n terms are off by less than n * 2^-24 of their terms' size; a tenth of the general tolerance covers H + F
+    assert r["err"] <= 1e-5, r
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("T", [9, 30, 64, 150])
 def test_layer_equals_route_predict_ffn_bitwise(dtype, T):
