@@ -645,7 +645,7 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
         const bool leftover = item >= n_whole;
         const int p = leftover ? parts : 1;
         const int q = item - n_whole;  // piece number (leftover tiles only)
-        const int t = leftover ? q / p : item % members, part = leftover ? q - t * p : 0;
+        const int part = leftover ? q / rem : 0, t = leftover ? q - part * rem : item % members;
         int round = (item / members) * kXcds + xcd;
         if (!leftover) {
             const int l0 = (int)((long)round * light_rounds / n_rounds), l1 = (int)((long)(round + 1) * light_rounds / n_rounds);

@@ -32,6 +32,43 @@ __global__ __launch_bounds__(64) void hist_from_idx_kernel(const int32_t* __rest
     if (tid < E) hist[(size_t)blockIdx.x * E + tid] = h[tid];
 }
 
+// Inclusive sum over the lanes of a wavefront.
+__device__ inline int lane_prefix(int v) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+        const int u = __shfl_up(v, d, 64);
+        if (lane >= d) v += u;
+    }
+    return v;
+}
+
+// Ranks the n_local selections (at most 128, one per thread of the first two wavefronts; expert `e` in thread tid)
+// among those of the same expert: slot = base[e] + selections of e before it.  A wavefront finds the lanes of the same
+// expert from six ballots, one per bit of the expert's number (a loop over the selections before a thread's own cost
+// up to 96 LDS reads in a row; with it and a running sum over 64 experts 1003 tokens took 11.7 us, now 8.1); the second wavefront starts from the first
+// one's counts.  Call with all threads of the workgroup; `first_half` is scratch, `base` has been written and synchronised.
+__device__ inline void rank_selections(int n_local, int e, int a0, const int* base, int* first_half,
+                                       int32_t* __restrict__ row_of_slot, int32_t* __restrict__ slot_of) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const bool on = tid < n_local;
+    uint64_t same = __ballot(on);
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+        const bool bit = ((e >> b) & 1) != 0;
+        const uint64_t m = __ballot(bit);
+        same &= bit ? m : ~m;
+    }
+    const int before = __popcll(same & ((1ull << lane) - 1ull));
+    if (on && tid < 64 && before == 0) first_half[e] = __popcll(same);  // an expert's first selection leaves the count
+    __syncthreads();
+    if (on) {
+        const int slot = base[e] + before + (tid >= 64 ? first_half[e] : 0);
+        slot_of[a0 + tid] = slot;
+        row_of_slot[slot] = a0 + tid;
+    }
+}
+
 // grid = max(1, n_blocks) workgroups of 256 threads.
 __global__ __launch_bounds__(256) void finalize_kernel(const int32_t* __restrict__ hist, int n_blocks, int E,
                                                        int k, int tokens, const int32_t* __restrict__ idx,
@@ -42,10 +79,16 @@ __global__ __launch_bounds__(256) void finalize_kernel(const int32_t* __restrict
     __shared__ int total[64];
     __shared__ int before[64];
     __shared__ int base[64];
-    __shared__ int local_e[kRouteTokensPerBlock * 8];
+    __shared__ int first_half[64];
     const int tid = threadIdx.x;
     const int blk = blockIdx.x;
+    static_assert(kRouteTokensPerBlock * 8 <= 128, "two wavefronts rank a block's selections");
+    const int a0 = blk * kRouteTokensPerBlock * k;
+    const int n_local = min(tokens * k, a0 + kRouteTokensPerBlock * k) - a0;
+    // requested before the histograms, used after them
+    const int my_e = row_of_slot != nullptr && tid < n_local ? min(max(idx[a0 + tid], 0), E - 1) : 0;
     if (tid < 64) {
+        first_half[tid] = 0;
         total[tid] = 0;
         before[tid] = 0;
     }
@@ -74,31 +117,20 @@ __global__ __launch_bounds__(256) void finalize_kernel(const int32_t* __restrict
         }
     }
     __syncthreads();
-    if (tid == 0) {
-        int run = 0;
-        for (int e = 0; e < E; ++e) {
-            base[e] = run + before[e];
-            if (blk == 0 && offs != nullptr) offs[e] = run;
-            run += total[e];
+    if (tid < 64) {  // (lanes of experts that do not exist hold zero)
+        const int mine = total[tid], end = lane_prefix(mine);
+        base[tid] = end - mine + before[tid];
+        if (blk == 0 && offs != nullptr && tid < E) {
+            offs[tid] = end - mine;
+            if (tid == E - 1) offs[E] = end;
         }
-        if (blk == 0 && offs != nullptr) offs[E] = run;
     }
     if (blk == 0 && counts != nullptr && tid < E) counts[tid] = (accumulate ? counts[tid] : 0) + total[tid];
     if (blk == 0 && sync != nullptr)
         for (int i = tid; i < kSyncInts; i += 256) sync[i] = 0;
     if (row_of_slot == nullptr) return;
-    const int a0 = blk * kRouteTokensPerBlock * k;
-    const int n_local = min(tokens * k, a0 + kRouteTokensPerBlock * k) - a0;
-    if (tid < n_local) local_e[tid] = min(max(idx[a0 + tid], 0), E - 1);
     __syncthreads();
-    if (tid < n_local) {
-        const int e = local_e[tid];
-        int rank = 0;
-        for (int i = 0; i < tid; ++i) rank += (local_e[i] == e);
-        const int slot = base[e] + rank;
-        slot_of[a0 + tid] = slot;
-        row_of_slot[slot] = a0 + tid;
-    }
+    rank_selections(n_local, my_e, a0, base, first_half, row_of_slot, slot_of);
 }
 
 // ---- long calls: the fused kernel above sweeps all block histograms in every workgroup, which is
@@ -157,21 +189,15 @@ __global__ __launch_bounds__(256) void rank_kernel(const int32_t* __restrict__ p
                                                    int E, int k, int tokens, const int32_t* __restrict__ idx,
                                                    int32_t* __restrict__ row_of_slot, int32_t* __restrict__ slot_of) {
     __shared__ int base[64];
-    __shared__ int local_e[kRouteTokensPerBlock * 8];
+    __shared__ int first_half[64];
     const int tid = threadIdx.x, blk = blockIdx.x;
     if (tid < E) base[tid] = offs[tid] + prefix[(size_t)blk * E + tid];
+    if (tid < 64) first_half[tid] = 0;
     const int a0 = blk * kRouteTokensPerBlock * k;
     const int n_local = min(tokens * k, a0 + kRouteTokensPerBlock * k) - a0;
-    if (tid < n_local) local_e[tid] = min(max(idx[a0 + tid], 0), E - 1);
+    const int my_e = tid < n_local ? min(max(idx[a0 + tid], 0), E - 1) : 0;
     __syncthreads();
-    if (tid < n_local) {
-        const int e = local_e[tid];
-        int rank = 0;
-        for (int i = 0; i < tid; ++i) rank += (local_e[i] == e);
-        const int slot = base[e] + rank;
-        slot_of[a0 + tid] = slot;
-        row_of_slot[slot] = a0 + tid;
-    }
+    rank_selections(n_local, my_e, a0, base, first_half, row_of_slot, slot_of);
 }
 
 }  // namespace
