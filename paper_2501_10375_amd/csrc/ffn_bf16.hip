@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256) void combine_bf16(const float* __restrict__ ou
                                                     const float* __restrict__ pieces, int E, int k, int H,
                                                     uint16_t* __restrict__ y) {
     const int t = blockIdx.x;
-    const int parts = split->parts, slots = split->slots;
+    const int parts = split->parts, slots = split->slots, n_split = split->n_split;
     const int n_ft = (H + 255) / 256;
     for (int h = threadIdx.x * 8; h < H; h += 256 * 8) {
         float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -41,7 +41,7 @@ __global__ __launch_bounds__(256) void combine_bf16(const float* __restrict__ ou
                 const int first = offs[e], count = offs[e + 1] - first;
                 const int m = (slot - first) / slots, mt = (count + slots - 1) / slots;
                 const int tile = split->first_tile[e] + gg::TileList::position(mt, n_ft, m, h >> 8) - split->first_split;
-                if (tile >= 0) {
+                if (tile >= 0 && tile < n_split) {
                     const size_t stride = (size_t)split->piece_rows * 256;
                     const float* p = pieces + (size_t)tile * (parts - 1) * stride + (size_t)(slot - first - m * slots) * 256 + (h & 255);
                     for (int i = 1; i < parts; ++i, p += stride) {

@@ -45,15 +45,17 @@ constexpr int kMaxWgsPerXcd = 32;  // persistent grid: at most 8 x 32 workgroups
 // A K-split tile of the second GEMM leaves its first piece in the output and the others in the scratch memory, in rows of
 // 256 columns, the pieces of a tile one after the other; the kernel that combines a token's selections adds them.  The
 // table tells it where they are: slots per tile, parts per split tile, number of the first split tile, rows a piece
-// has room for, and per expert the number of its first tile.
+// has room for, how many tiles are split, and per expert the number of its first tile.
 struct SplitTable {
-    int slots, parts, first_split, piece_rows;
-    int pad[4];
+    int slots, parts, first_split, piece_rows, n_split;
+    int pad[3];
     int first_tile[64];
 };
 constexpr int kSyncInts = kXcds + (int)(sizeof(SplitTable) / sizeof(int));
 // K parts a leftover tile can be cut into, and the shortest part in K steps of 64.
 constexpr int kMaxParts = 6, kMinPartKSteps = 14;
+// Shortest K (steps of 64) at which a workgroup whose XCD has nothing left looks for work elsewhere, see persistent().
+constexpr int kMinStealKSteps = 48;
 // Scratch memory for those pieces, in units of 32 rows: 64 MiB for calls whose tiles are few or low (an expert sees a token
 // once), up to 128 MiB for the others (the parts are chosen to fit).
 constexpr size_t kUnitFloats = 32 * 256;
@@ -585,6 +587,17 @@ struct GemmArgs {
 // which is what a round was measured to take, within 10 % from 77 to 4096 tokens of the Mixtral and Phi shapes
 // (2048 tokens, Mixtral: 545 us with whole tiles, 416 so; Phi: 311 us with 256 slots, 256 us with 192).
 // The first GEMM has many short tiles (4096 tokens: 15 rounds); cutting its leftover tiles gained nothing.
+//
+// Which tiles are left over: the last ones, those of the coldest experts, except in a second GEMM of one full round.
+// There the full round would be all hot tiles, bound by the MFMAs, and the leftovers all cold ones, bound by memory, with nothing
+// to interleave; so the leftovers are taken from around the border of the two kinds in their proportion (2048 tokens of the
+// Phi shape: 297 -> 277 us; with more full rounds it only moves hot tiles to the end, 3500 tokens: 372 -> 387 us, first
+// GEMM at 600 tokens: 326 -> 335 us).
+//
+// A workgroup whose XCD has handed out all its items takes one from the XCD with most left.  The look at the counters costs
+// each GEMM about 1.5 us at its end and tiles taken over share fewer lines, so calls with short tiles do without
+// (4096 tokens of the Mixtral shape: both GEMMs 2168 -> 2164 us; 1500 tokens, first GEMM 609 -> 602; 22 K steps, the 64-expert
+// shape at 1003 tokens: 100.5 -> 103 us with it).
 template <class G>
 __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     TileList list(a.offs, a.E, (a.N + G::kBF - 1) / G::kBF);
@@ -621,8 +634,8 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     const int full_rounds = total / per_super_round;
     const int left = total - full_rounds * per_super_round;
     const int chunk = (left + kXcds - 1) / kXcds;
-    const int rem = max(0, min(left, (xcd + 1) * chunk) - xcd * chunk);
-    const int first_left = full_rounds * per_super_round;
+    const bool amid = G::kMats == 1 && full_rounds == 1;  // (see above)
+    const int first_left = amid ? list.heavy - (int)((long)left * list.heavy / total) : total - left;
     if (G::kMats == 1 && blockIdx.x == 0 && threadIdx.x < 64) {
         SplitTable* table = reinterpret_cast<SplitTable*>(a.sync + kXcds);
         if (threadIdx.x == 0) {
@@ -630,28 +643,71 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
             table->parts = parts;
             table->first_split = first_left;
             table->piece_rows = piece_units * 32;
+            table->n_split = left;
         }
         if (threadIdx.x < a.E) table->first_tile[list.expert] = list.first_tile;
     }
-    // Work items of this XCD in hand-out order: its whole tiles, then the pieces of its leftover tiles.
+    // Work items of an XCD in hand-out order: its whole tiles, then the pieces of its leftover tiles.
     const int n_whole = full_rounds * members;
-    const int n_items = n_whole + rem * parts;
-    // rounds of `members` tiles that lie in the heavy part of the list / in the rest
+    auto left_of = [&](int x) { return max(0, min(left, (x + 1) * chunk) - x * chunk); };
+    // rounds of `members` whole tiles that lie in the heavy part of the list / in the rest
     const int n_rounds = full_rounds * kXcds;
-    const int heavy_rounds = min(n_rounds, list.heavy / members);
+    const int heavy_rounds = min(n_rounds, min(list.heavy, first_left) / members);
     const int light_rounds = n_rounds - heavy_rounds;
     int item = member;  // the counter hands out items `members`, `members` + 1, ...
-    while (item < n_items) {
+    int from = xcd;     // whose items
+    for (;;) {
+        if (item >= n_whole + left_of(from) * parts) {
+            if (KT < kMinStealKSteps) break;
+            // That XCD's items are all handed out: go on with one of the XCD that has most left.  (Not in the word that
+            // tile() hands over: another wavefront may still have to read that.)
+            int* handoff = reinterpret_cast<int*>(lds + G::kHandoffOffset);
+            if (threadIdx.x < 64) {
+                const int lane = threadIdx.x;
+                const int items = lane < kXcds ? n_whole + left_of(lane) * parts - members : 0;
+                int got = -1, victim = 0;
+                for (;;) {  // a try that loses the race has seen the victim's last item go: the sum of `open` falls every time
+                    int open = lane < kXcds ? items - __hip_atomic_load(&a.sync[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+                    int most = 0;
+                    for (int x = 0; x < kXcds; ++x) {
+                        const int o = __builtin_amdgcn_readlane(open, x);
+                        if (o > most) { most = o; victim = x; }
+                    }
+                    if (most == 0) break;
+                    int n = 0;
+                    if (lane == 0) n = __hip_atomic_fetch_add(&a.sync[victim], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    n = __builtin_amdgcn_readfirstlane(n);
+                    if (n < __builtin_amdgcn_readlane(items, victim)) {
+                        got = n;
+                        break;
+                    }
+                }
+                if (lane == 0) {
+                    handoff[1] = got;
+                    handoff[2] = victim;
+                }
+            }
+            lds_barrier();
+            const int got = __builtin_amdgcn_readfirstlane(handoff[1]);
+            from = __builtin_amdgcn_readfirstlane(handoff[2]);
+            if (got < 0) break;
+            item = members + got;
+        }
+        const int rem = left_of(from);
         const bool leftover = item >= n_whole;
         const int p = leftover ? parts : 1;
         const int q = item - n_whole;  // piece number (leftover tiles only)
         const int part = leftover ? q / rem : 0, t = leftover ? q - part * rem : item % members;
-        int round = (item / members) * kXcds + xcd;
+        int round = (item / members) * kXcds + from;
         if (!leftover) {
             const int l0 = (int)((long)round * light_rounds / n_rounds), l1 = (int)((long)(round + 1) * light_rounds / n_rounds);
             round = l1 > l0 ? heavy_rounds + ((l0 & 1) != 0 ? light_rounds - 1 - l0 / 2 : l0 / 2) : round - l0;
         }
-        const int tile_index = leftover ? first_left + xcd * chunk + t : round * members + t;
+        int tile_index = first_left + from * chunk + t;
+        if (!leftover) {
+            tile_index = round * members + t;
+            if (tile_index >= first_left) tile_index += left;
+        }
         int e, slot0, rows, ft;
         list.find(tile_index, e, slot0, rows, ft);
         const int kt0 = (int)((long)KT * part / p), kt1 = (int)((long)KT * (part + 1) / p);
@@ -659,11 +715,11 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
         float* out = static_cast<float*>(a.dst) + (size_t)slot0 * a.N + ft * G::kBF;
         size_t out_stride = a.N;
         if (part > 0) {
-            out = a.scratch + (size_t)(((xcd * chunk + t) * (p - 1) + part - 1) * piece_units) * kUnitFloats;
+            out = a.scratch + (size_t)(((from * chunk + t) * (p - 1) + part - 1) * piece_units) * kUnitFloats;
             out_stride = 256;
         }
         item = members + G::tile(a.tok, a.wa, a.wb, a.row_of_slot, a.topk, a.N, a.K, static_cast<uint16_t*>(a.dst), lds, e, slot0,
-                                 rows, ft, kt0, kt1, out, out_stride, a.sync + xcd, a.tok_alt, a.alt_mask);
+                                 rows, ft, kt0, kt1, out, out_stride, a.sync + from, a.tok_alt, a.alt_mask);
     }
 }
 

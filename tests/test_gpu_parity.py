@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2501_10375_amd import moe, synth
-from parity_util import check_layer, check_routing, host, output_error, to_f64
+from parity_util import check_layer, check_routing, host, output_error, tile_aware_sample, to_f64
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -193,6 +193,30 @@ def test_fp32_units_groups_and_router_blocks(oracle, T, H, F, E, k, zipf):
     r = check_layer(oracle, d, shape, res, torch.float32, label=f"fp32 units T={T}")
     # fp32 sums of n terms are off by less than n * 2^-24 of their terms' size; a tenth of the general tolerance covers H + F
     assert r["err"] <= 1e-5, r
+
+
+@pytest.mark.parametrize("T,F,E,zipf", [
+    (1100, 1024, 12, 1.5),     # second GEMM: one full round and whole leftover tiles from the middle of the list; no work taken over
+    (1100, 3072, 12, 1.5),     # 48 K steps: leftover tiles may be cut, and work is taken over between XCDs
+    (2600, 3072, 4, 1.2),      # the same with few experts of many slot tiles
+    (5000, 3072, 3, 0.5),      # two full rounds: the leftover tiles are the last ones
+])
+def test_bf16_leftover_tiles_of_the_second_gemm(oracle, T, F, E, zipf):
+    H, k, dtype = 4096, 2, torch.bfloat16
+    d, shape, out, res = _run(T, H, F, E, k, dtype, zipf=zipf, predict=False)
+    torch.cuda.synchronize()
+    sample = tile_aware_sample(res["idx"].cpu().numpy(), E, 16, n_cold=0)
+    # every token against a second call with its rows in another order: other tiles, other pieces, sums equal to the
+    # last bits of fp32, so a bf16 result may round to its neighbour
+    check_layer(oracle, d, shape, res, dtype, tokens=sample, label=f"leftover T={T} F={F} E={E}", predict=False)
+    perm = torch.randperm(T, generator=torch.Generator().manual_seed(1)).to(DEV)
+    d2 = dict(d, x=d["x"][perm].contiguous())
+    out2 = moe.LayerOutputs(shape, T, dtype, DEV, predict=False)
+    res2 = moe.run_layer(shape, d2, out2, predict=False)
+    torch.cuda.synchronize()
+    assert torch.equal(res2["idx"], res["idx"][perm])
+    a, b = res["y"][perm].float(), res2["y"].float()
+    assert torch.all((a - b).abs() <= 2.0 ** -7 * a.abs().clamp_min(a.square().mean().sqrt()))
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
