@@ -157,3 +157,26 @@ def test_predict_degraded_matches_oracle(oracle, dtype, T, H, E, k):
             if T <= 16:
                 assert torch.equal(plain, idx)
     print("tokens whose selection was degraded:", changed)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_predict_degraded_is_the_same_however_tokens_share_workgroups(dtype):
+    """One call long enough for 16 tokens a workgroup against calls on its slices with two (odd lengths included)."""
+    T, H, E, k = 6 * 256 + 5, 128, 24, 3
+    d = synth.moe_layer_inputs(T, H, 64, E, dtype, DEV)
+    shape = moe.make_shape(H, 64, E, k, dtype)
+    on = torch.from_numpy((np.arange(E) % 5 == 0).astype(np.uint8)).to(DEV)
+
+    def predict(x):
+        idx = torch.empty((x.shape[0], k), dtype=torch.int32, device=DEV)
+        w = torch.empty((x.shape[0], k), dtype=torch.float32, device=DEV)
+        policy.daop_predict_degraded(shape, x, d["wg_next"], d["bias_next"], on, idx, w)
+        return idx, w
+
+    idx, w = predict(d["x"])
+    at = 0
+    for n in (1, 2, 3, 1021, T - 1027):
+        i, v = predict(d["x"][at:at + n].contiguous())
+        torch.cuda.synchronize()
+        assert torch.equal(i, idx[at:at + n]) and torch.equal(v, w[at:at + n])
+        at += n
