@@ -15,9 +15,6 @@
 namespace moe {
 namespace {
 
-// x of this many bytes and more is addressed with 64-bit row pointers (a lane offset plus the K offset must fit 32 bits).
-constexpr size_t kWideBytes = (size_t)15 << 28;
-
 // y[t, :] = bf16( sum_j w[t, j] * out[slot_of[t, j], :] ), j ascending, fp32 sum, one rounding.  Where the second GEMM
 // split a tile along K, `out` holds its first piece; the others are added from the scratch memory in piece order first.
 __global__ __launch_bounds__(256) void combine_bf16(const float* __restrict__ out, const float* __restrict__ w,
@@ -125,13 +122,15 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
     g2.sync = sync + gg::kSyncInts;
     g2.scratch = partial;
     g2.scratch_limit = (int)gg::scratch_units(tokens, s.top_k, s.n_experts, s.hidden);
-    const bool wide = (size_t)tokens * s.hidden * 2 >= kWideBytes;
     hipError_t e;
-    if (alt.stale != nullptr) e = launch_gemm<gg::Gemm<2, true>>(g1, kStageGemm1, stream);
-    else if (wide) e = launch_gemm<gg::Gemm<2, false, true>>(g1, kStageGemm1, stream);
+    // (with tok_alt slot rows are addressed with pointers anyway: only the weight rows decide)
+    if (gg::needs_wide(alt.stale != nullptr ? 0 : (size_t)tokens * s.hidden * 2, gg::Gemm<2>::kBF, s.hidden))
+        e = launch_gemm<gg::Gemm<2, false, true>>(g1, kStageGemm1, stream);
+    else if (alt.stale != nullptr) e = launch_gemm<gg::Gemm<2, true>>(g1, kStageGemm1, stream);
     else e = launch_gemm<gg::Gemm<2>>(g1, kStageGemm1, stream);
     if (e != hipSuccess) return e;
-    e = launch_gemm<gg::Gemm<1>>(g2, kStageGemm2, stream);
+    e = gg::needs_wide(0, 256, s.ffn) ? launch_gemm<gg::Gemm<1, false, true>>(g2, kStageGemm2, stream)
+                                      : launch_gemm<gg::Gemm<1>>(g2, kStageGemm2, stream);
     if (e != hipSuccess) return e;
     combine_bf16<<<tokens, 256, 0, stream>>>(out, topk_w, slot_of, topk_idx, offs,
                                              reinterpret_cast<const gg::SplitTable*>(g2.sync + gg::kXcds), partial, s.n_experts,

@@ -208,10 +208,12 @@ __device__ inline int swizzled(int row, int chunk) { return chunk ^ ((row >> 1) 
 // 32-slot groups: slots are dealt to the two slot groups of wavefronts in fragments of 16, and every wavefront
 // stages 8 rows of each 32-slot group, so all four wavefronts get shorter by the same amount.
 //
-// WIDE: slot rows are addressed with 64-bit pointers (x of 4 GiB or more).
+// ALT (first GEMM): a slot's row comes from tok_alt where alt_mask says so; slot rows are addressed with 64-bit pointers.
+// WIDE: every operand is addressed with 64-bit pointers, and tok_alt is used if there is one.  For operands that a 32-bit
+// lane offset does not reach: x of kWideBytes or more, or a tile of weight or slot rows of that size (see needs_wide()).
 template <int NMAT, bool ALT = false, bool WIDE = false>
 struct Gemm {
-    static_assert((!ALT && !WIDE) || NMAT == 2, "only the first GEMM gathers rows of x");
+    static_assert(!(ALT && WIDE) && (!ALT || NMAT == 2), "only the first GEMM gathers rows of x");
     static constexpr int kThreads = 256, kMats = NMAT;
     static constexpr int kBF = 256 / NMAT;            // features per tile (per matrix)
     static constexpr int kF = 8;                      // 16-row fragments of each operand per wavefront
@@ -287,15 +289,21 @@ struct Gemm {
         const size_t w_first = ((size_t)e * N + n0) * K;
         const u32x4 base_a = descriptor(wa + w_first);
         const u32x4 base_b = descriptor(NMAT == 2 ? wb + w_first : wa + w_first);
-        uint32_t w_off[kWOffs];
+        const uint32_t row_bytes = (uint32_t)K * 2u;
+        uint32_t w_off[WIDE ? 1 : kWOffs];
+        const char* w_ptr[WIDE ? 8 : 1];
 #pragma unroll
-        for (int q = 0; q < kWOffs; ++q) {
-            const int f = min(q * 32 + lrow, N - 1 - n0);  // features past the end re-read the last one
-            w_off[q] = (uint32_t)f * (uint32_t)(K * 2) + (uint32_t)chunk * 16;
+        for (int q = 0; q < (WIDE ? 8 : kWOffs); ++q) {
+            const int f = min((q % kWOffs) * 32 + lrow, N - 1 - n0);  // features past the end re-read the last one
+            if constexpr (WIDE)
+                w_ptr[q] = reinterpret_cast<const char*>((NMAT == 2 && q >= 4 ? wb : wa) + w_first) + (size_t)f * row_bytes + (size_t)chunk * 16;
+            else
+                w_off[q] = (uint32_t)f * row_bytes + (uint32_t)chunk * 16;
         }
         const uint32_t wave_lds = lds0 + (uint32_t)wave * 1024;
         auto weight_load = [&](int q, uint32_t k_off) {
-            load_lane(NMAT == 2 && q >= 4 ? base_b : base_a, w_off[q % kWOffs], k_off);
+            if constexpr (WIDE) load_ptr(w_ptr[q] + k_off);
+            else load_lane(NMAT == 2 && q >= 4 ? base_b : base_a, w_off[q % kWOffs], k_off);
         };
         // Weights of the first two K steps are requested before the slot rows are looked up.
 #pragma unroll
@@ -311,12 +319,16 @@ struct Gemm {
         for (int q = 0; q < 8; ++q) {
             const int r = min(q * 32 + lrow, rows - 1);   // rows past the end re-read the last valid row
             if constexpr (NMAT == 1) {
-                s_off[q] = (uint32_t)r * (uint32_t)(K * 2) + (uint32_t)chunk * 16;
+                if constexpr (WIDE)
+                    s_ptr[q] = reinterpret_cast<const char*>(tok_base + (size_t)slot0 * K) + (size_t)r * row_bytes + (size_t)chunk * 16;
+                else
+                    s_off[q] = (uint32_t)r * row_bytes + (uint32_t)chunk * 16;
             } else {
                 const int assignment = row_of_slot[slot0 + r];   // t * topk + j
-                const size_t at = (size_t)(assignment / topk) * (size_t)(K * 2) + (size_t)chunk * 16;
+                const size_t at = (size_t)(assignment / topk) * row_bytes + (size_t)chunk * 16;
                 if constexpr (WIDE || ALT) {
-                    const uint16_t* rows_from = (ALT && alt_mask[assignment] != 0) ? tok_alt : tok_base;
+                    const bool from_alt = (ALT || alt_mask != nullptr) && alt_mask[assignment] != 0;
+                    const uint16_t* rows_from = from_alt ? tok_alt : tok_base;
                     s_ptr[q] = reinterpret_cast<const char*>(rows_from) + at;
                 } else {
                     s_off[q] = (uint32_t)at;
@@ -548,6 +560,15 @@ struct Gemm {
     }
 };
 
+// Operands of this many bytes and more are addressed with 64-bit pointers: a lane offset plus the K offset must fit 32 bits and
+// stay below the bound of the buffer descriptor.
+constexpr size_t kWideBytes = (size_t)15 << 28;
+// Whether a GEMM needs the WIDE kernel: `gathered` is the size of the tensor that slot rows are gathered from (0 where they
+// are a tile's consecutive rows), `tile_rows` the weight or slot rows that are addressed from one base.
+constexpr bool needs_wide(size_t gathered, size_t tile_rows, size_t k_elements) {
+    return gathered >= kWideBytes || tile_rows * k_elements * 2 >= kWideBytes;
+}
+
 // tok: gemm1 -> x [T, K] rows gathered via row_of_slot / topk; gemm2 -> act [A, K], rows = slots.
 // wa, wb: [E, N, K]; dst: gemm1 -> bf16 [A, N]; gemm2 -> fp32 [A, N].
 struct GemmArgs {
@@ -609,7 +630,7 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     int slots = 256, parts = 1, piece_units = 0;
     if constexpr (G::kMats == 1) {
         const int most_rows = __builtin_amdgcn_readlane(list.count, 0);
-        int best = 0x7fffffff;
+        int64_t best = INT64_MAX;
         for (int s = 256; s >= 128; s -= 32) {
             const int tiles = list.tiles_for(s);
             const int full = tiles / per_super_round;
@@ -619,7 +640,7 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
             const int units = (min(s, most_rows) + 31) / 32;
             for (int p = 1; p <= kMaxParts && (p == 1 || KT / p >= kMinPartKSteps); ++p) {
                 if (p > 1 && (chunk == 0 || left * (p - 1) * units > a.scratch_limit)) break;
-                const int cost = full * (KT * step + 600) + (chunk * p + members - 1) / members * (KT / p * step + 600);
+                const int64_t cost = full * ((int64_t)KT * step + 600) + (chunk * p + members - 1) / members * ((int64_t)(KT / p) * step + 600);
                 if (cost < best) {
                     best = cost;
                     slots = s;

@@ -137,6 +137,62 @@ def test_bf16_hidden_states_of_more_than_4_gib(oracle):
     assert output_error(to_f64(y[tok.to(DEV)]), ref) <= 2e-2
 
 
+def _swiglu_expert_rows(x, w1, w3, w2, chunk=1 << 20):
+    """One expert on a few rows as plain torch: fp32 products, fp64 sums, the intermediate rounded to bf16."""
+    H, F = w1.shape[1], w1.shape[0]
+    g = torch.zeros((x.shape[0], F), dtype=torch.float64, device=x.device)
+    u = torch.zeros_like(g)
+    for h in range(0, H, chunk):
+        for f in range(0, F, chunk):
+            xs = x[:, h:h + chunk].float()
+            g[:, f:f + chunk] += (xs @ w1[f:f + chunk, h:h + chunk].float().T).double()
+            u[:, f:f + chunk] += (xs @ w3[f:f + chunk, h:h + chunk].float().T).double()
+    act = (torch.nn.functional.silu(g) * u).to(torch.bfloat16)
+    y = torch.zeros((x.shape[0], H), dtype=torch.float32, device=x.device)
+    for h in range(0, H, chunk):
+        s = torch.zeros((x.shape[0], min(chunk, H - h)), dtype=torch.float64, device=x.device)
+        for f in range(0, F, chunk):
+            s += (act[:, f:f + chunk].float() @ w2[h:h + chunk, f:f + chunk].float().T).double()
+        y[:, h:h + chunk] = s.float()
+    return y
+
+
+@pytest.mark.parametrize("T,H,F", [
+    (257, 256, (1 << 23) + (1 << 20)),   # second GEMM: 256 rows of act or of w2 span more than 4 GiB
+    (34, (1 << 24) + (1 << 20), 128),    # first GEMM: 128 rows of w1 or w3 do
+])
+def test_bf16_rows_of_a_tile_span_more_than_4_gib(T, H, F):
+    """Very long rows are accepted and computed like any other: offsets within a tile then exceed 32 bits.  The second
+    call takes every other selection from another tensor (moe_expert_ffn_precalc).  Rows of the tile's end are compared."""
+    g = torch.Generator(device=DEV).manual_seed(F)
+
+    def normal(shape, std):
+        return torch.randn(shape, generator=g, dtype=torch.bfloat16, device=DEV).mul_(std)
+
+    x, x_stale = normal((T, H), 1.0), normal((T, H), 1.0)
+    w1, w3, w2 = normal((1, F, H), H ** -0.5), normal((1, F, H), H ** -0.5), normal((1, H, F), F ** -0.5)
+    idx = torch.zeros((T, 1), dtype=torch.int32, device=DEV)
+    w = torch.ones((T, 1), dtype=torch.float32, device=DEV)
+    shape = moe.make_shape(H, F, 1, 1, torch.bfloat16)
+    ws = moe.alloc_workspace(shape, T)
+    y = torch.empty_like(x)
+    stale = (torch.arange(T, device=DEV) % 2).to(torch.uint8).reshape(T, 1)
+    tok = torch.tensor([0, 1, T - 3, T - 2, T - 1], device=DEV)
+    mixed = torch.where(stale[tok] != 0, x_stale[tok], x[tok])
+    for precalc, rows in ((False, x[tok]), (True, mixed)):
+        y.fill_(float("nan"))
+        if precalc:
+            moe.moe_expert_ffn_precalc(shape, x, x_stale, stale, idx, w, w1, w3, w2, y, ws)
+        else:
+            moe.moe_expert_ffn(shape, x, idx, w, w1, w3, w2, y, ws)
+        ref = _swiglu_expert_rows(rows, w1[0], w3[0], w2[0])
+        torch.cuda.synchronize()
+        got = y[tok].float()
+        err = ((got - ref).abs() / ref.abs().clamp_min(ref.square().mean().sqrt())).max().item()
+        assert err <= 2e-2, (precalc, err)
+        assert torch.isfinite(y[:, ::1 << 12]).all()
+
+
 @pytest.mark.parametrize("T,H,F,E,k", [
     (1, 256, 512, 8, 2), (5, 256, 512, 8, 2), (16, 256, 512, 8, 2), (8, 512, 1600, 16, 2), (3, 64, 64, 4, 1),
     (16, 128, 320, 8, 8), (7, 2048, 1024, 8, 2), (4, 128, 128, 64, 8), (9, 192, 256, 32, 2), (6, 8192, 128, 8, 2),
