@@ -236,12 +236,23 @@ struct Gemm {
     // acc += a . b with the accumulator in AGPRs, in place.  (From the builtin, in a kernel with as many loops as this
     // one, the compiler gives the result another register than the operand and then spends the loop moving accumulators
     // between the two halves of the register file: 340 moves per 128 MFMAs.)  The compiler waits for the LDS reads of a
-    // and b, as it does for any use; what it does not know is that the instruction is an MFMA, so settle() has to follow
-    // the last one before an accumulator is used by anything else (and must stand between setting one and the first).
+    // and b, as it does for any use; what it does not know is that the instruction is an MFMA, so between setting an
+    // accumulator and the first one, and between the last one and any other use, there has to be settle(), held in its
+    // place by pin(): asm statements keep their order among each other, but an access to a register that they don't name may
+    // cross them.  What C++ cannot forbid is that the compiler moves a register between two MFMAs;
+    // tests/test_isa_hazards.py reads the built kernels for that.
     static __device__ inline void mfma_acc(f32x4& acc, bf16x8 a, bf16x8 b) {
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
     }
     static __device__ inline void settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }  // 19 wait states at most
+    // Every write of the accumulators above this comes before it, every use below it after.
+    template <int TFE>
+    static __device__ inline void pin(f32x4 (&acc)[kF][TFE]) {
+#pragma unroll
+        for (int j = 0; j < kF; ++j)
+#pragma unroll
+            for (int i = 0; i < TFE; ++i) asm volatile("" : "+a"(acc[j][i]));
+    }
     // An accumulator element.  (Read where it is used: left to the compiler, all 256 are copied to VGPRs at once.)
     static __device__ inline float from_acc(float a) {
         float v;
@@ -362,6 +373,7 @@ struct Gemm {
         for (int j = 0; j < kF; ++j)
 #pragma unroll
             for (int i = 0; i < TFE; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        pin(acc);
         settle();
 
             constexpr int kM = kF * TFE, kR = kF + TFE;
@@ -467,6 +479,7 @@ struct Gemm {
         // Ask for the next work item now; the answer is needed only after the epilogue.
         if (tid == 0) next_item = __hip_atomic_fetch_add(handed_out, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         settle();
+        pin(acc);
 
         // ---- epilogue: transpose through LDS so that global stores are whole contiguous rows.
         // MFMA 16x16 result: lane holds column (slot) lane % 16 and rows (features) 4 * (lane / 16) + c.
