@@ -36,11 +36,13 @@ __global__ __launch_bounds__(256) void combine_bf16(const float* __restrict__ ou
             if (parts > 1) {
                 const int e = min(max(idx[(size_t)t * k + j], 0), E - 1);
                 const int first = offs[e], count = offs[e + 1] - first;
-                const int m = (slot - first) / slots, mt = (count + slots - 1) / slots;
-                const int tile = split->first_tile[e] + gg::TileList::position(mt, n_ft, m, h >> 8) - split->first_split;
+                const int m = (slot - first) / slots;
+                const gg::TileList::Place at = gg::TileList::place(count, slots, n_ft, m, h >> 8);
+                const int tile = split->first_tile[e] + at.tile - split->first_split;
                 if (tile >= 0 && tile < n_split) {
-                    const size_t stride = (size_t)split->piece_rows * 256;
-                    const float* p = pieces + (size_t)tile * (parts - 1) * stride + (size_t)(slot - first - m * slots) * 256 + (h & 255);
+                    const size_t stride = (size_t)split->n_units * gg::kUnitFloats;
+                    const float* p = pieces + (size_t)(split->units_before[e] + at.unit - split->first_unit) * gg::kUnitFloats +
+                                     (size_t)(slot - first - m * slots) * 256 + (h & 255);
                     for (int i = 1; i < parts; ++i, p += stride) {
                         const float4 c = *reinterpret_cast<const float4*>(p);
                         const float4 d = *reinterpret_cast<const float4*>(p + 4);
@@ -89,15 +91,12 @@ hipError_t launch_gemm(const gg::GemmArgs& a, int stage, hipStream_t stream) {
 
 }  // namespace
 
-size_t gemm_scratch_bytes(const moe_shape_t& s, int tokens) {
-    return gg::scratch_units(tokens, s.top_k, s.n_experts, s.hidden) * gg::kUnitFloats * sizeof(float);
-}
-
 hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, const int32_t* topk_idx, const float* topk_w,
                            const void* w1, const void* w3, const void* w2, void* y, const int32_t* offs,
                            const int32_t* row_of_slot, const int32_t* slot_of, void* act, float* out,
                            int32_t* sync, float* partial, const StaleInput& alt, hipStream_t stream) {
-    static_assert(gg::kSyncInts == kGemmSyncInts, "workspace layout");
+    static_assert(gg::kXcds <= kGemmSyncInts && gg::kScratchFloats * sizeof(float) + sizeof(gg::SplitTable) <= kGemmScratchBytes,
+                  "workspace layout");
     gg::GemmArgs g1{}, g2{};
     g1.tok = static_cast<const uint16_t*>(x);
     g1.wa = static_cast<const uint16_t*>(w1);
@@ -119,9 +118,9 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
     g2.N = s.hidden;
     g2.K = s.ffn;
     g2.dst = out;
-    g2.sync = sync + gg::kSyncInts;
+    g2.sync = sync + kGemmSyncInts;
     g2.scratch = partial;
-    g2.scratch_limit = (int)gg::scratch_units(tokens, s.top_k, s.n_experts, s.hidden);
+    g2.table = reinterpret_cast<gg::SplitTable*>(partial + gg::kScratchFloats);
     hipError_t e;
     // (with tok_alt slot rows are addressed with pointers anyway: only the weight rows decide)
     if (gg::needs_wide(alt.stale != nullptr ? 0 : (size_t)tokens * s.hidden * 2, gg::Gemm<2>::kBF, s.hidden))
@@ -133,8 +132,7 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
                                       : launch_gemm<gg::Gemm<1>>(g2, kStageGemm2, stream);
     if (e != hipSuccess) return e;
     combine_bf16<<<tokens, 256, 0, stream>>>(out, topk_w, slot_of, topk_idx, offs,
-                                             reinterpret_cast<const gg::SplitTable*>(g2.sync + gg::kXcds), partial, s.n_experts,
-                                             s.top_k, s.hidden, static_cast<uint16_t*>(y));
+                                             g2.table, partial, s.n_experts, s.top_k, s.hidden, static_cast<uint16_t*>(y));
     stage_mark(stream, kStageCombine);
     return hipGetLastError();
 }

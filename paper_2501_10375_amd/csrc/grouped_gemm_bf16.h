@@ -39,51 +39,51 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 constexpr int kXcds = 8;
 constexpr int kMaxWgsPerXcd = 32;  // persistent grid: at most 8 x 32 workgroups
 
-// Layout of the int32 `sync` block a GEMM launch uses:
-//   [0, 8)    tiles handed out so far in each XCD (see persistent()); all zero when the kernel starts
-//   [8, ...)  SplitTable (second GEMM only)
+// A launch uses kXcds counters (`sync`): the tiles handed out so far in each XCD (see persistent()); all zero when it starts.
+
 // A K-split tile of the second GEMM leaves its first piece in the output and the others in the scratch memory, in rows of
-// 256 columns, the pieces of a tile one after the other; the kernel that combines a token's selections adds them.  The
-// table tells it where they are: slots per tile, parts per split tile, number of the first split tile, rows a piece
-// has room for, how many tiles are split, and per expert the number of its first tile.
+// 256 columns, a tile's rows rounded up to whole units of 32.  All first pieces there come first, then all second ones; within
+// them the tiles follow each other in the order of the tile list without gaps.  The kernel that combines a token's
+// selections adds them.  The table tells it where they are: slots per tile, parts per split tile, number of the first split
+// tile, how many are split, the units before the first of them and in all of them, and per expert the number of its first tile
+// and the units before it.
+constexpr int kUnitRows = 32;
 struct SplitTable {
-    int slots, parts, first_split, piece_rows, n_split;
-    int pad[3];
-    int first_tile[64];
+    int slots, parts, first_split, n_split, first_unit, n_units;
+    int pad[2];
+    int first_tile[64], units_before[64];
 };
-constexpr int kSyncInts = kXcds + (int)(sizeof(SplitTable) / sizeof(int));
 // K parts a leftover tile can be cut into, and the shortest part in K steps of 64.
 constexpr int kMaxParts = 6, kMinPartKSteps = 14;
 // Shortest K (steps of 64) at which a workgroup whose XCD has nothing left looks for work elsewhere, see persistent().
 constexpr int kMinStealKSteps = 48;
-// Scratch memory for those pieces, in units of 32 rows: 64 MiB for calls whose tiles are few or low (an expert sees a token
-// once), up to 128 MiB for the others (the parts are chosen to fit).
-constexpr size_t kUnitFloats = 32 * 256;
-constexpr size_t kMinScratchUnits = 2048, kMaxScratchUnits = 4096;
-inline size_t scratch_units(size_t tokens, size_t top_k, size_t experts, size_t out_features) {
-    const size_t routed = tokens * top_k;
-    const size_t tiles = (routed / 128 + (experts < routed ? experts : routed)) * ((out_features + 255) / 256);
-    const size_t left = tiles < kXcds * kMaxWgsPerXcd ? tiles : (size_t)kXcds * kMaxWgsPerXcd;
-    const size_t units = left * (kMaxParts - 1) * (((tokens < 256 ? tokens : 256) + 31) / 32);
-    return units < kMinScratchUnits ? kMinScratchUnits : units < kMaxScratchUnits ? units : kMaxScratchUnits;
-}
+// Scratch memory for those pieces: enough to cut any 255 tiles of 256 rows into two parts, and low tiles into more.  The parts
+// are chosen to fit.  (Twice as much let 129 to 170 full tiles have three.)  The tables follow the pieces.
+constexpr size_t kUnitFloats = kUnitRows * 256;
+constexpr int kScratchUnits = 255 * 8;
+constexpr size_t kScratchFloats = kScratchUnits * kUnitFloats;
 
 // Tile list.  The number of tiles depends on the routing (sum over experts of ceil(count / 256) slot tiles, times the
 // feature tiles) and is only known on the device: every wavefront derives the list from `offs` when the kernel starts
 // and keeps it across its lanes (at most 64 experts), so that looking a tile up is a ballot and a few scalar
 // operations.
 //
-// Order: experts by descending row count.  Within an expert blocks of kFtBlock feature tiles, within a block its slot
-// tiles in groups of at most kGroup of nearly equal size, within a group feature tile by feature tile.  32 consecutive
+// Order: experts by descending row count.  Within an expert its slot tiles in groups of at most kGroup
+// of nearly equal size, within a group feature tile by feature tile and within a feature tile slot tile by slot tile.  32 consecutive
 // tiles (what the 32 CUs of an XCD work on at one time) are then about 8 slot tiles x 4 feature tiles of one
 // expert: 12 distinct operand tiles feed 32 workgroups through the XCD's L2, and the groups of an expert with more
 // than 8 slot tiles meet the same weights at about the same time.
 constexpr int kGroup = 8;
 
-__device__ inline int wave_total(int v) {
+// Sums over the lanes of a wavefront, all of them at once (a sum by itself is six LDS round trips).
+template <int N>
+__device__ inline void wave_totals(int (&v)[N]) {
 #pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-    return __builtin_amdgcn_readfirstlane(v);
+    for (int d = 32; d > 0; d >>= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], d, 64);
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = __builtin_amdgcn_readfirstlane(v[i]);
 }
 __device__ inline int wave_inclusive_sum(int v) {
     const int lane = threadIdx.x & 63;
@@ -101,6 +101,7 @@ struct TileList {
     int total, heavy;         // tiles; tiles of experts with two slot tiles or more (they come first)
     // lane r: the expert of rank r
     int expert, count, first_slot, first_tile;
+    int units, first_unit;    // units of 32 rows of all tiles, and before an expert's (count_units())
 
     __device__ TileList(const int32_t* __restrict__ offs, int E, int n_ftiles) : n_ft(n_ftiles) {
         const int lane = threadIdx.x & 63;
@@ -111,17 +112,20 @@ struct TileList {
             const int ci = __builtin_amdgcn_readlane(c, i);
             if (lane < E) rank += (ci > c || (ci == c && i < lane)) ? 1 : 0;
         }
+        units = first_unit = 0;
         expert = __builtin_amdgcn_ds_permute(rank * 4, lane);
         count = __builtin_amdgcn_ds_permute(rank * 4, c);
         first_slot = __builtin_amdgcn_ds_permute(rank * 4, o);
     }
 
-    // Tiles of all experts together for slot tiles of `s` rows.
-    __device__ int tiles_for(int s) const { return wave_total(count > 0 ? (count + s - 1) / s : 0) * n_ft; }
+    static __device__ int units_of(int rows) { return rows > 0 ? (rows + kUnitRows - 1) / kUnitRows : 0; }
+
+    // Slot tiles of `s` rows of this lane's expert.
+    __device__ int slot_tiles(int s) const { return count > 0 ? (count + s - 1) / s : 0; }
 
     __device__ void build(int slots_per_tile) {
         slots = slots_per_tile;
-        const int tiles = count > 0 ? (count + slots - 1) / slots * n_ft : 0;
+        const int tiles = slot_tiles(slots) * n_ft;
         const int tile_sum = wave_inclusive_sum(tiles);
         first_tile = tile_sum - tiles;
         total = __builtin_amdgcn_readlane(tile_sum, 63);
@@ -129,7 +133,15 @@ struct TileList {
         heavy = n_heavy > 0 ? __builtin_amdgcn_readlane(tile_sum, n_heavy - 1) : 0;
     }
 
-    __device__ void find(int id, int& e, int& slot0, int& rows, int& ft) const {
+    __device__ void count_units() {
+        const int own = units_of(count) * n_ft;
+        const int sum = wave_inclusive_sum(own);
+        first_unit = sum - own;
+        units = __builtin_amdgcn_readlane(sum, 63);
+    }
+
+    // Tile `id`, and the units of the tiles before it (valid after count_units()).
+    __device__ void find(int id, int& e, int& slot0, int& rows, int& ft, int& unit) const {
         const int r = __popcll(__ballot(first_tile <= id && count > 0)) - 1;
         const int c = __builtin_amdgcn_readlane(count, r);
         e = __builtin_amdgcn_readlane(expert, r);
@@ -145,18 +157,28 @@ struct TileList {
         const int g = in / (gs * n_ft);
         const int in_grp = in - g * (gs * n_ft);
         ft = in_grp / gs;
-        const int m = (b ? 0 : big * (size + 1)) + g * gs + (in_grp - ft * gs);
+        const int from = (b ? 0 : big * (size + 1)) + g * gs;  // the group's first slot tile
+        const int m = from + (in_grp - ft * gs);
         slot0 = __builtin_amdgcn_readlane(first_slot, r) + m * slots;
         rows = min(slots, c - m * slots);
+        unit = __builtin_amdgcn_readlane(first_unit, r) + local * (slots / kUnitRows) - (from + gs == mt ? ft * units_missing(c, mt, slots) : 0);
     }
-    // Inverse of find() within an expert of mt slot tiles: position of (slot tile m, feature tile ft).
-    static __device__ int position(int mt, int n_ft, int m, int ft) {
+    // What the last slot tile of an expert of c rows lacks of slots / 32 units.
+    static __device__ int units_missing(int c, int mt, int slots) { return slots / kUnitRows - units_of(c - (mt - 1) * slots); }
+
+    // Inverse of find() within an expert of c rows: number of (slot tile m, feature tile ft), and the units before it.
+    struct Place {
+        int tile, unit;
+    };
+    static __device__ Place place(int c, int slots, int n_ft, int m, int ft) {
+        const int mt = (c + slots - 1) / slots;
         const int groups = (mt + kGroup - 1) / kGroup;
         const int size = mt / groups, big = mt - size * groups;
         const bool b = m < big * (size + 1);
         const int gs = b ? size + 1 : size;
         const int from = b ? m / gs * gs : big * (size + 1) + (m - big * (size + 1)) / gs * gs;  // the group's first slot tile
-        return from * n_ft + ft * gs + m - from;
+        const int tile = from * n_ft + ft * gs + m - from;
+        return {tile, tile * (slots / kUnitRows) - (from + gs == mt ? ft * units_missing(c, mt, slots) : 0)};
     }
 };
 
@@ -590,8 +612,8 @@ struct GemmArgs {
     int E, topk, N, K;
     void* dst;
     int32_t* sync;
-    float* scratch;              // second GEMM: pieces of split tiles, scratch_limit units
-    int scratch_limit;
+    float* scratch;              // second GEMM: pieces of split tiles, kScratchUnits units ...
+    SplitTable* table;           // ... and where they are
     const uint16_t* tok_alt;     // gemm1 with per-selection input rows (ALT), else null
     const uint8_t* alt_mask;
 };
@@ -640,25 +662,31 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     const int members = min((int)gridDim.x / kXcds, kMaxWgsPerXcd);
     if (member >= members) return;
     const int per_super_round = kXcds * members;
-    int slots = 256, parts = 1, piece_units = 0;
+    int slots = 256, parts = 1;
     if constexpr (G::kMats == 1) {
         const int most_rows = __builtin_amdgcn_readlane(list.count, 0);
+        int sums[6] = {TileList::units_of(list.count)};
+#pragma unroll
+        for (int i = 1; i < 6; ++i) sums[i] = list.slot_tiles(288 - i * 32);
+        wave_totals(sums);
+        const int all_units = sums[0] * list.n_ft;
         int64_t best = INT64_MAX;
-        for (int s = 256; s >= 128; s -= 32) {
-            const int tiles = list.tiles_for(s);
+#pragma unroll
+        for (int i = 1; i < 6; ++i) {
+            const int s = 288 - i * 32;
+            const int tiles = sums[i] * list.n_ft;
             const int full = tiles / per_super_round;
             const int left = tiles - full * per_super_round;
             const int chunk = (left + kXcds - 1) / kXcds;
             const int step = 75 + 7 * s / 32;
-            const int units = (min(s, most_rows) + 31) / 32;
+            const int units = min(left * TileList::units_of(min(s, most_rows)), all_units);  // of the leftover tiles, at most
             for (int p = 1; p <= kMaxParts && (p == 1 || KT / p >= kMinPartKSteps); ++p) {
-                if (p > 1 && (chunk == 0 || left * (p - 1) * units > a.scratch_limit)) break;
+                if (p > 1 && (chunk == 0 || units * (p - 1) > kScratchUnits)) break;
                 const int64_t cost = full * ((int64_t)KT * step + 600) + (chunk * p + members - 1) / members * ((int64_t)(KT / p) * step + 600);
                 if (cost < best) {
                     best = cost;
                     slots = s;
                     parts = p;
-                    piece_units = units;
                 }
             }
         }
@@ -670,16 +698,29 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     const int chunk = (left + kXcds - 1) / kXcds;
     const bool amid = G::kMats == 1 && full_rounds == 1;  // (see above)
     const int first_left = amid ? list.heavy - (int)((long)left * list.heavy / total) : total - left;
+    int first_unit = 0, n_units = 0;  // of the leftover tiles
+    if (parts > 1) {
+        int e, slot0, rows, ft;
+        list.count_units();
+        list.find(first_left, e, slot0, rows, ft, first_unit);
+        n_units = list.units;
+        if (first_left + left < total) list.find(first_left + left, e, slot0, rows, ft, n_units);
+        n_units -= first_unit;
+    }
     if (G::kMats == 1 && blockIdx.x == 0 && threadIdx.x < 64) {
-        SplitTable* table = reinterpret_cast<SplitTable*>(a.sync + kXcds);
+        SplitTable* table = a.table;
         if (threadIdx.x == 0) {
             table->slots = slots;
             table->parts = parts;
             table->first_split = first_left;
-            table->piece_rows = piece_units * 32;
             table->n_split = left;
+            table->first_unit = first_unit;
+            table->n_units = n_units;
         }
-        if (threadIdx.x < a.E) table->first_tile[list.expert] = list.first_tile;
+        if (threadIdx.x < a.E) {
+            table->first_tile[list.expert] = list.first_tile;
+            table->units_before[list.expert] = list.first_unit;
+        }
     }
     // Work items of an XCD in hand-out order: its whole tiles, then the pieces of its leftover tiles.
     const int n_whole = full_rounds * members;
@@ -742,14 +783,14 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
             tile_index = round * members + t;
             if (tile_index >= first_left) tile_index += left;
         }
-        int e, slot0, rows, ft;
-        list.find(tile_index, e, slot0, rows, ft);
+        int e, slot0, rows, ft, unit;
+        list.find(tile_index, e, slot0, rows, ft, unit);
         const int kt0 = (int)((long)KT * part / p), kt1 = (int)((long)KT * (part + 1) / p);
         // where the fp32 rows of the second GEMM go
         float* out = static_cast<float*>(a.dst) + (size_t)slot0 * a.N + ft * G::kBF;
         size_t out_stride = a.N;
         if (part > 0) {
-            out = a.scratch + (size_t)(((from * chunk + t) * (p - 1) + part - 1) * piece_units) * kUnitFloats;
+            out = a.scratch + (size_t)((part - 1) * n_units + unit - first_unit) * kUnitFloats;
             out_stride = 256;
         }
         item = members + G::tile(a.tok, a.wa, a.wb, a.row_of_slot, a.topk, a.N, a.K, static_cast<uint16_t*>(a.dst), lds, e, slot0,

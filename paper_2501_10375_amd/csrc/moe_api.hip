@@ -33,7 +33,7 @@ WorkspaceLayout workspace_layout(const moe_shape_t& s, int tokens) {
     L.act = off;         off = align_up(off + A * (size_t)s.ffn * esz);
     L.out = off;         off = align_up(off + A * (size_t)s.hidden * sizeof(float));
     L.partial = off;
-    if (s.dtype == MOE_BF16 && tokens > kStreamMaxTokens) off = align_up(off + gemm_scratch_bytes(s, tokens));
+    if (s.dtype == MOE_BF16 && tokens > kStreamMaxTokens) off = align_up(off + kGemmScratchBytes);
     L.total = off;
     return L;
 }

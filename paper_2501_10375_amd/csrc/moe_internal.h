@@ -28,7 +28,7 @@ constexpr int kStreamMaxTokens = 32;
 // and arrival flags.
 struct WorkspaceLayout {
     size_t dec_flags;    // uint32 [kDecodeFlagInts]  arrival flags, launch count and status word of the decode kernel's two grid-wide rendezvous
-    size_t sync;         // int32 [kSyncInts]    tile hand-out counters of the two grouped GEMMs, table of split tiles
+    size_t sync;         // int32 [kSyncInts]    tile hand-out counters of the two grouped GEMMs
     size_t hist;         // int32 [n_blocks, E]  per-block selection histogram
     size_t hist_next;    // int32 [n_blocks, E]  same for the next-layer gate
     size_t offs;         // int32 [E + 1]        exclusive scan of counts
@@ -37,7 +37,7 @@ struct WorkspaceLayout {
     size_t route_end;    // bytes needed by routing-only calls
     size_t act;          // dtype [A, F]         silu(W1 x) * (W3 x)
     size_t out;          // fp32  [A, H]         per-assignment expert output
-    size_t partial;      // fp32  pieces of K-split tiles (bf16 prefill path only; see gemm_scratch_bytes)
+    size_t partial;      // fp32  pieces of K-split tiles and their table (bf16 prefill path only)
     size_t total;        // bytes needed by the whole layer
 };
 
@@ -79,12 +79,12 @@ hipError_t launch_hist_from_idx(const moe_shape_t& s, int tokens, const int32_t*
 // Sum block histograms into counts (counts may be null), and when
 // row_of_slot/slot_of are given build offs and the stable token->expert
 // permutation.
-// Counters of the persistent grouped GEMMs (see grouped_gemm_bf16.h): per launch 8 tile hand-out counters (one per XCD)
-// and the table of the second GEMM's split tiles.
-constexpr int kGemmSyncInts = 8 + 8 + 64;
+// Counters of the persistent grouped GEMMs (see grouped_gemm_bf16.h): per launch 8 tile hand-out counters, one per XCD, on
+// cache lines of their own.  (With this block the smallest workspace has the 4096 bytes that moe_decode_status asks for.)
+constexpr int kGemmSyncInts = 80;
 constexpr int kSyncInts = 2 * kGemmSyncInts;  // gemm1 and gemm2
-// Bytes of scratch memory the second GEMM may need for the pieces of K-split tiles.
-size_t gemm_scratch_bytes(const moe_shape_t& s, int tokens);
+// Scratch memory of the GEMMs for the pieces of K-split tiles and the table of where they are.
+constexpr size_t kGemmScratchBytes = 64u << 20;
 // `sync` (may be null) is a block of kSyncInts counters that is cleared for the GEMMs that follow.
 // For long calls the histograms in `hist` are replaced by their per-block prefixes.
 hipError_t launch_finalize(const moe_shape_t& s, int tokens, int32_t* hist, const int32_t* idx,

@@ -244,6 +244,24 @@ def test_workspace_keeps_flags_and_counters_at_fixed_offsets(L):
         assert n.value >= n0.value
 
 
+@pytest.mark.parametrize("shape,tokens,layer_bytes,route_bytes", [
+    (dict(hidden=4096, ffn=14336), 77, 74054400, 5376), (dict(hidden=4096, ffn=14336), 512, 113261312, 13568),
+    (dict(hidden=4096, ffn=14336), 4096, 436294400, 85248), (dict(hidden=4096, ffn=14336), 32, 2887936, 4352),
+    (dict(hidden=4096, ffn=6400, n_experts=16), 2048, 186700544, 52480),
+    (dict(hidden=2048, ffn=1408, n_experts=64, top_k=6), 33, 69297152, 7168),
+    (dict(hidden=2048, ffn=1408, n_experts=64, top_k=6), 1003, 133441024, 84480),
+    (dict(hidden=256, ffn=512), 40, 67277568, 4864), (dict(hidden=256, ffn=512, dtype=0), 64, 398080, 4864),
+])
+def test_a_workspace_that_was_large_enough_stays_so(L, shape, tokens, layer_bytes, route_bytes):
+    """Callers keep buffers of sizes that they asked for once: a call must not need more than it did (the sizes here)."""
+    n = ctypes.c_size_t(0)
+    s = _shape(**shape)
+    assert L.moe_workspace_bytes(ctypes.byref(s), tokens, ctypes.byref(n)) == 0
+    assert n.value <= layer_bytes
+    assert L.moe_route_workspace_bytes(ctypes.byref(s), tokens, ctypes.byref(n)) == 0
+    assert n.value <= route_bytes
+
+
 def test_static_scratch_entry_point_validates_on_the_host(L):
     """moe_layer_static checks its arguments and the size limit of its static buffer before any device work."""
     from paper_2501_10375_amd import moe

@@ -105,6 +105,9 @@ def test_bf16_slot_groups_and_short_k_loops(oracle, T, H, F):
     (900, 512, 5504, 4, 2),     # 86 K steps that the parts do not divide; slot tiles of unequal height
     (34, 4096, 896, 64, 8),     # more tiles than compute units: whole tiles first, then 14-step pieces of the coldest experts
     (1200, 2048, 1792, 6, 2),   # hot experts whose slot tiles are shared, leftover tiles among them
+    (2700, 320, 1792, 2, 1),    # more slot tiles an expert than a group holds, the last ones ragged, all cut
+    (2300, 256, 2048, 3, 2),    # the same with a single feature tile and two groups of different size
+    (333, 576, 5376, 7, 3),     # ragged single slot tiles of every expert, pieces without gaps between them
 ])
 def test_bf16_second_gemm_pieces_every_token(oracle, T, H, F, E, k):
     """The second GEMM cuts the tiles left over after its last full round along K; their pieces are added by the kernel
