@@ -15,53 +15,158 @@
 namespace moe {
 namespace {
 
+// Where a selection's row is, and where its pieces are if its tile was split (in every feature tile ft: tile number relative to the
+// first split tile tile + ft * tile_step, and likewise units of the scratch memory).
+struct CombineRow {
+    float w;
+    int slot, tile, tile_step, unit, unit_step, row;
+};
+
+__device__ inline float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+
+__device__ inline void accumulate(float (&s)[8], float w, float4 a, float4 b) {
+    s[0] = fmaf(w, a.x, s[0]); s[1] = fmaf(w, a.y, s[1]);
+    s[2] = fmaf(w, a.z, s[2]); s[3] = fmaf(w, a.w, s[3]);
+    s[4] = fmaf(w, b.x, s[4]); s[5] = fmaf(w, b.y, s[5]);
+    s[6] = fmaf(w, b.z, s[6]); s[7] = fmaf(w, b.w, s[7]);
+}
+
+__device__ inline void store_row(uint16_t* p, const float (&s)[8]) {
+    uint4 pk;
+    pk.x = pack_bf16x2(s[0], s[1]);
+    pk.y = pack_bf16x2(s[2], s[3]);
+    pk.z = pack_bf16x2(s[4], s[5]);
+    pk.w = pack_bf16x2(s[6], s[7]);
+    *reinterpret_cast<uint4*>(p) = pk;
+}
+
+// A selection's 8 values at column h, P parts added in their order.  The loads of all parts are requested together.
+template <int P>
+struct PartRows {
+    float4 a[P], b[P];
+    bool split;
+    __device__ inline void load(const float* out, const float* pieces, const CombineRow& r, int n_split, size_t stride, int H, int h) {
+        const int ft = h >> 8;
+        split = (unsigned)(r.tile + ft * r.tile_step) < (unsigned)n_split;
+        const float* src = out + (size_t)r.slot * H + h;
+        a[0] = *reinterpret_cast<const float4*>(src);
+        b[0] = *reinterpret_cast<const float4*>(src + 4);
+        if (__ballot(split) == 0) return;
+        const float* p = split ? pieces + (size_t)(r.unit + ft * r.unit_step) * gg::kUnitFloats + (size_t)r.row * 256 + (h & 255) : src;
+#pragma unroll
+        for (int i = 1; i < P; ++i) {
+            a[i] = *reinterpret_cast<const float4*>(p);
+            b[i] = *reinterpret_cast<const float4*>(p + 4);
+            p += split ? stride : 0;
+        }
+    }
+    __device__ inline void sum(float4& x, float4& y) const {
+        x = a[0];
+        y = b[0];
+        if (split) {
+#pragma unroll
+            for (int i = 1; i < P; ++i) {
+                x = add4(x, a[i]);
+                y = add4(y, b[i]);
+            }
+        }
+    }
+};
+
+// Tile and unit of a row of expert e at feature tile 0, relative to the first split tile, and what a feature tile adds.
+__device__ inline CombineRow combine_row(const gg::SplitTable* __restrict__ split, const int32_t* __restrict__ offs, int e, int slot,
+                                         int H) {
+    const int first = offs[e], count = offs[e + 1] - first, slots = split->slots;
+    const int m = (slot - first) / slots;
+    const gg::TileList::Place at = gg::TileList::place(count, slots, (H + 255) / 256, m);
+    CombineRow r;
+    r.slot = slot;
+    r.tile = split->first_tile[e] + at.tile - split->first_split;
+    r.tile_step = at.tile_step;
+    r.unit = split->units_before[e] + at.unit - split->first_unit;
+    r.unit_step = at.unit_step;
+    r.row = slot - first - m * slots;
+    return r;
+}
+
 // y[t, :] = bf16( sum_j w[t, j] * out[slot_of[t, j], :] ), j ascending, fp32 sum, one rounding.  Where the second GEMM
 // split a tile along K, `out` holds its first piece; the others are added from the scratch memory in piece order first.
+//
+// Long calls are bound by memory and want many wavefronts; short ones by the chain of loads, which with split tiles is one
+// memory round trip per piece.  AHEAD (short calls) looks the rows up once per token, through LDS, and requests the rows and all
+// pieces of two selections before it uses the first, at 118 registers instead of 34: 66 tokens, hidden 3008, 3 selections of 6
+// parts 16.2 -> 9.9 us; 195 tokens, hidden 2944, 4 selections of 5 parts 19.8 -> 12.6; but 1500 tokens, hidden 2048, 12.5 -> 14.8.
+template <bool AHEAD>
 __global__ __launch_bounds__(256) void combine_bf16(const float* __restrict__ out, const float* __restrict__ w,
                                                     const int32_t* __restrict__ slot_of, const int32_t* __restrict__ idx,
                                                     const int32_t* __restrict__ offs, const gg::SplitTable* __restrict__ split,
                                                     const float* __restrict__ pieces, int E, int k, int H,
                                                     uint16_t* __restrict__ y) {
     const int t = blockIdx.x;
-    const int parts = split->parts, slots = split->slots, n_split = split->n_split;
-    const int n_ft = (H + 255) / 256;
-    for (int h = threadIdx.x * 8; h < H; h += 256 * 8) {
-        float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int j = 0; j < k; ++j) {
-            const float wj = w[(size_t)t * k + j];
-            const int slot = slot_of[(size_t)t * k + j];
-            const float* src = out + (size_t)slot * H + h;
-            float4 a = *reinterpret_cast<const float4*>(src);
-            float4 b = *reinterpret_cast<const float4*>(src + 4);
-            if (parts > 1) {
-                const int e = min(max(idx[(size_t)t * k + j], 0), E - 1);
-                const int first = offs[e], count = offs[e + 1] - first;
-                const int m = (slot - first) / slots;
-                const gg::TileList::Place at = gg::TileList::place(count, slots, n_ft, m, h >> 8);
-                const int tile = split->first_tile[e] + at.tile - split->first_split;
-                if (tile >= 0 && tile < n_split) {
-                    const size_t stride = (size_t)split->n_units * gg::kUnitFloats;
-                    const float* p = pieces + (size_t)(split->units_before[e] + at.unit - split->first_unit) * gg::kUnitFloats +
-                                     (size_t)(slot - first - m * slots) * 256 + (h & 255);
-                    for (int i = 1; i < parts; ++i, p += stride) {
-                        const float4 c = *reinterpret_cast<const float4*>(p);
-                        const float4 d = *reinterpret_cast<const float4*>(p + 4);
-                        a.x += c.x; a.y += c.y; a.z += c.z; a.w += c.w;
-                        b.x += d.x; b.y += d.y; b.z += d.z; b.w += d.w;
+    const int parts = split->parts, n_split = split->n_split;
+    const size_t stride = (size_t)split->n_units * gg::kUnitFloats;
+    const int h_first = (blockIdx.y * 256 + threadIdx.x) * 8, h_step = gridDim.y * 256 * 8;
+    if (!AHEAD || parts <= 1) {
+        for (int h = h_first; h < H; h += h_step) {
+            float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < k; ++j) {
+                const int slot = slot_of[(size_t)t * k + j];
+                const float* src = out + (size_t)slot * H + h;
+                float4 a = *reinterpret_cast<const float4*>(src);
+                float4 b = *reinterpret_cast<const float4*>(src + 4);
+                if (!AHEAD && parts > 1) {
+                    const int ft = h >> 8;
+                    const CombineRow r = combine_row(split, offs, min(max(idx[(size_t)t * k + j], 0), E - 1), slot, H);
+                    if ((unsigned)(r.tile + ft * r.tile_step) < (unsigned)n_split) {
+                        const float* p = pieces + (size_t)(r.unit + ft * r.unit_step) * gg::kUnitFloats + (size_t)r.row * 256 + (h & 255);
+                        for (int i = 1; i < parts; ++i, p += stride) {
+                            a = add4(a, *reinterpret_cast<const float4*>(p));
+                            b = add4(b, *reinterpret_cast<const float4*>(p + 4));
+                        }
                     }
                 }
+                accumulate(s, w[(size_t)t * k + j], a, b);
             }
-            s[0] = fmaf(wj, a.x, s[0]); s[1] = fmaf(wj, a.y, s[1]);
-            s[2] = fmaf(wj, a.z, s[2]); s[3] = fmaf(wj, a.w, s[3]);
-            s[4] = fmaf(wj, b.x, s[4]); s[5] = fmaf(wj, b.y, s[5]);
-            s[6] = fmaf(wj, b.z, s[6]); s[7] = fmaf(wj, b.w, s[7]);
+            store_row(y + (size_t)t * H + h, s);
         }
-        uint4 pk;
-        pk.x = pack_bf16x2(s[0], s[1]);
-        pk.y = pack_bf16x2(s[2], s[3]);
-        pk.z = pack_bf16x2(s[4], s[5]);
-        pk.w = pack_bf16x2(s[6], s[7]);
-        *reinterpret_cast<uint4*>(y + (size_t)t * H + h) = pk;
+        return;
+    }
+    __shared__ CombineRow rows[8];
+    if ((int)threadIdx.x < k) {
+        const size_t a = (size_t)t * k + threadIdx.x;
+        rows[threadIdx.x] = combine_row(split, offs, min(max(idx[a], 0), E - 1), slot_of[a], H);
+        rows[threadIdx.x].w = w[a];
+    }
+    __syncthreads();
+    auto run = [&](auto parts_c) {
+        constexpr int P = decltype(parts_c)::value;
+        for (int h = h_first; h < H; h += h_step) {
+            float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < k; j += 2) {
+                const bool two = j + 1 < k;
+                PartRows<P> r0, r1;
+                r0.load(out, pieces, rows[j], n_split, stride, H, h);
+                if (two) r1.load(out, pieces, rows[j + 1], n_split, stride, H, h);
+                float4 a, b;
+                r0.sum(a, b);
+                accumulate(s, rows[j].w, a, b);
+                if (two) {
+                    r1.sum(a, b);
+                    accumulate(s, rows[j + 1].w, a, b);
+                }
+            }
+            store_row(y + (size_t)t * H + h, s);
+        }
+    };
+    if constexpr (AHEAD) {
+        static_assert(gg::kMaxParts == 6, "one version per number of parts");
+        switch (parts) {
+            case 2: run(std::integral_constant<int, 2>{}); break;
+            case 3: run(std::integral_constant<int, 3>{}); break;
+            case 4: run(std::integral_constant<int, 4>{}); break;
+            case 5: run(std::integral_constant<int, 5>{}); break;
+            default: run(std::integral_constant<int, 6>{}); break;
+        }
     }
 }
 
@@ -131,8 +236,12 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
     e = gg::needs_wide(0, 256, s.ffn) ? launch_gemm<gg::Gemm<1, false, true>>(g2, kStageGemm2, stream)
                                       : launch_gemm<gg::Gemm<1>>(g2, kStageGemm2, stream);
     if (e != hipSuccess) return e;
-    combine_bf16<<<tokens, 256, 0, stream>>>(out, topk_w, slot_of, topk_idx, offs,
-                                             g2.table, partial, s.n_experts, s.top_k, s.hidden, static_cast<uint16_t*>(y));
+    const int column_blocks = (s.hidden + 2047) / 2048;
+    // AHEAD up to three workgroups a CU: 720 of them (360 tokens, hidden 4096) 17.0 -> 15.1 us, 1000 to 1050 are equal (14.1; 10.5 and
+    // 10.4), 1200 take 11.8 without and 13.3 with it.
+    const bool ahead = (long)tokens * column_blocks <= 3 * compute_units();
+    (ahead ? combine_bf16<true> : combine_bf16<false>)<<<dim3(tokens, ahead ? column_blocks : 1), 256, 0, stream>>>(
+        out, topk_w, slot_of, topk_idx, offs, g2.table, partial, s.n_experts, s.top_k, s.hidden, static_cast<uint16_t*>(y));
     stage_mark(stream, kStageCombine);
     return hipGetLastError();
 }

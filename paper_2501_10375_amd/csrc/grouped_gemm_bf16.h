@@ -166,19 +166,20 @@ struct TileList {
     // What the last slot tile of an expert of c rows lacks of slots / 32 units.
     static __device__ int units_missing(int c, int mt, int slots) { return slots / kUnitRows - units_of(c - (mt - 1) * slots); }
 
-    // Inverse of find() within an expert of c rows: number of (slot tile m, feature tile ft), and the units before it.
+    // Inverse of find() within an expert of c rows: where slot tile m stands, number and units before it at feature tile 0, and
+    // what each further feature tile adds.
     struct Place {
-        int tile, unit;
+        int tile, tile_step, unit, unit_step;
     };
-    static __device__ Place place(int c, int slots, int n_ft, int m, int ft) {
+    static __device__ Place place(int c, int slots, int n_ft, int m) {
         const int mt = (c + slots - 1) / slots;
         const int groups = (mt + kGroup - 1) / kGroup;
         const int size = mt / groups, big = mt - size * groups;
         const bool b = m < big * (size + 1);
         const int gs = b ? size + 1 : size;
         const int from = b ? m / gs * gs : big * (size + 1) + (m - big * (size + 1)) / gs * gs;  // the group's first slot tile
-        const int tile = from * n_ft + ft * gs + m - from;
-        return {tile, tile * (slots / kUnitRows) - (from + gs == mt ? ft * units_missing(c, mt, slots) : 0)};
+        const int tile = from * n_ft + m - from, full = slots / kUnitRows;
+        return {tile, gs, tile * full, gs * full - (from + gs == mt ? units_missing(c, mt, slots) : 0)};
     }
 };
 
