@@ -53,8 +53,8 @@ struct SplitTable {
     int pad[2];
     int first_tile[64], units_before[64];
 };
-// K parts a leftover tile can be cut into, and the shortest part in K steps of 64.
-constexpr int kMaxParts = 6, kMinPartKSteps = 14;
+// K parts a leftover tile can be cut into, and the fewest K steps of 64 that a part has.
+constexpr int kMaxParts = 6, kMinPartKSteps = 3;
 // Shortest K (steps of 64) at which a workgroup whose XCD has nothing left looks for work elsewhere, see persistent().
 constexpr int kMinStealKSteps = 48;
 // Scratch memory for those pieces: enough to cut any 255 tiles of 256 rows into two parts, and low tiles into more.  The parts
@@ -619,6 +619,49 @@ struct GemmArgs {
     const uint8_t* alt_mask;
 };
 
+// Slots per tile and parts of a leftover tile for the second GEMM.  A smaller tile costs less per round, but there are more of
+// them; more parts make a shorter last round, but each is a prologue and an epilogue, and rows that are written and read again.
+// Lane l prices one of the 30 plans (slots 256 - 32 * (l / 6), l % 6 + 1 parts); the first of the cheapest is taken.  In 10 ns:
+//   the larger of   full rounds x (K steps x (90 + 6 x slots / 32) + 400) and the same for the rounds of pieces  (MFMAs)
+//            and    the active experts' weights at 6.6 TB/s + 600 a round                                       (memory)
+//   + 300 + 2 a unit of 32 rows of pieces, if there are any.
+// Fitted to all plans of 72 shapes, 33 to 3400 tokens, 4 to 64 experts, 8 to 224 K steps, the combination's time included, and
+// with 36 others: chosen plans are 1.3 % above the best on average and 8.6 % at most.  (The MFMA term alone, with 14 K
+// steps or more a part, as it was: 4.4 % and 46 %; Phi shape, 200 tokens, 152 + 12 us in four parts where 131 + 6 is had in one;
+// 16 experts, hidden 640, ffn 1728, 627 tokens: 34 -> 23 us.)  The lanes do it side by side because 30 prices one after the
+// other take 2 us.
+__device__ inline void choose_plan(const TileList& list, int N, int KT, int members, int& slots, int& parts) {
+    static_assert(kMaxParts == 6, "30 plans");
+    const int lane = threadIdx.x & 63;
+    const int i = min(lane / 6, 4), p = lane - lane / 6 * 6 + 1, s = 256 - 32 * i;
+    int sums[6] = {TileList::units_of(list.count)};
+#pragma unroll
+    for (int n = 0; n < 5; ++n) sums[n + 1] = list.slot_tiles(256 - 32 * n);
+    const int most_rows = __builtin_amdgcn_readlane(list.count, 0);
+    const int active = __popcll(__ballot(list.count > 0));
+    wave_totals(sums);
+    int tiles = sums[1];
+#pragma unroll
+    for (int n = 1; n < 5; ++n) tiles = i == n ? sums[n + 1] : tiles;
+    tiles *= list.n_ft;
+    const int full = tiles / (kXcds * members), left = tiles - full * (kXcds * members);
+    const int chunk = (left + kXcds - 1) / kXcds;
+    const int units = min(left * TileList::units_of(min(s, most_rows)), sums[0] * list.n_ft);  // of the leftover tiles, at most
+    const int rounds = (chunk * p + members - 1) / members;
+    const bool allowed = p == 1 || (chunk > 0 && units * (p - 1) <= kScratchUnits && KT >= p * kMinPartKSteps);
+    const float step = 90 + 6 * s / 32;
+    const float work = full * (KT * step + 400.f) + rounds * ((KT + p - 1) / p * step + 400.f);
+    const float stream = active * (float)N * KT * (1.f / 516.f) + (full + rounds) * 600.f;
+    float cost = fmaxf(work, stream) + (p > 1 ? 300.f + 2.f * units * (p - 1) : 0.f);
+    if (lane >= 30 || !allowed) cost = INFINITY;
+    float best = cost;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) best = fminf(best, __shfl_xor(best, d, 64));
+    const int winner = __ffsll((long long)__ballot(cost == best)) - 1;
+    slots = __builtin_amdgcn_readlane(s, winner);
+    parts = __builtin_amdgcn_readlane(p, winner);
+}
+
 // Persistent schedule: the grid is one workgroup per CU.  Workgroup b belongs to XCD b % 8 (the
 // hardware deals workgroups round-robin to the XCDs) and is its member b / 8.  An XCD works
 // through the tile list in rounds of `members` consecutive tiles, so that its workgroups work on
@@ -638,23 +681,21 @@ struct GemmArgs {
 //
 // Second GEMM: it has few tiles with many K steps (2048 tokens of the Mixtral shape: 320 tiles of 224 K steps for 256
 // CUs), so what the last round costs matters.  The tiles left over after the last full round are cut along K into
-// `parts` pieces, handed out like tiles; see SplitTable for their sums.  Slots per tile (a smaller tile costs less per
-// round, but there are more of them) and parts are chosen for the least sum of
-//   full rounds x (K steps x (0.75 + 0.07 x slots / 32) us + 6 us) and the same for the rounds of pieces,
-// which is what a round was measured to take, within 10 % from 77 to 4096 tokens of the Mixtral and Phi shapes
-// (2048 tokens, Mixtral: 545 us with whole tiles, 416 so; Phi: 311 us with 256 slots, 256 us with 192).
+// `parts` pieces, handed out like tiles; see SplitTable for their sums, choose_plan() for their number.
 // The first GEMM has many short tiles (4096 tokens: 15 rounds); cutting its leftover tiles gained nothing.
 //
-// Which tiles are left over: the last ones, those of the coldest experts, except in a second GEMM of one full round.
-// There the full round would be all hot tiles, bound by the MFMAs, and the leftovers all cold ones, bound by memory, with nothing
-// to interleave; so the leftovers are taken from around the border of the two kinds in their proportion (2048 tokens of the
-// Phi shape: 297 -> 277 us; with more full rounds it only moves hot tiles to the end, 3500 tokens: 372 -> 387 us, first
-// GEMM at 600 tokens: 326 -> 335 us).
+// Which tiles are left over: the last ones, those of the coldest experts, except in a second GEMM of one full round of which
+// hot tiles alone would fill 7 tenths or more.  Such a round is bound by the MFMAs and the leftovers by memory, with little to
+// interleave; so the leftovers are taken from around the border of the two kinds in their proportion.  Phi shape, second GEMM,
+// leftovers at the end / amid: 900, 1300 and 1500 tokens (160 of 256 hot tiles) 193 / 202, 211 / 222, 221 / 232 us; 1700, 2048 and
+// 2300 tokens (192 and more) 270 / 253, 298 / 276, 322 / 292; Mixtral shape, 2600 tokens 511 / 493.  (With more full rounds it
+// only moves hot tiles to the end, 3500 tokens: 372 -> 387 us, first GEMM at 600 tokens: 326 -> 335 us).
 //
-// A workgroup whose XCD has handed out all its items takes one from the XCD with most left.  The look at the counters costs
-// each GEMM about 1.5 us at its end and tiles taken over share fewer lines, so calls with short tiles do without
-// (4096 tokens of the Mixtral shape: both GEMMs 2168 -> 2164 us; 1500 tokens, first GEMM 609 -> 602; 22 K steps, the 64-expert
-// shape at 1003 tokens: 100.5 -> 103 us with it).
+// A workgroup whose XCD has handed out all its items takes one from the XCD with most left, in calls with at least 48 K steps.
+// The look at the counters costs each GEMM about 1.5 us at its end and tiles taken over share fewer lines: 22 K steps, the
+// 64-expert shape at 1003 tokens, first GEMM 100.5 -> 103 us with it.  Between 32 and 64 K steps it does not matter (eight
+// shapes, hidden and ffn 2048 to 3584: within 2 % either way).  With 64 and 100 of the Phi shape, 700 tokens, 523 -> 509 us; 64 and
+// 224 of the Mixtral shape, 512 tokens, 630 -> 625, 4096 tokens, both GEMMs, 2168 -> 2164.
 template <class G>
 __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     TileList list(a.offs, a.E, (a.N + G::kBF - 1) / G::kBF);
@@ -664,40 +705,13 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     if (member >= members) return;
     const int per_super_round = kXcds * members;
     int slots = 256, parts = 1;
-    if constexpr (G::kMats == 1) {
-        const int most_rows = __builtin_amdgcn_readlane(list.count, 0);
-        int sums[6] = {TileList::units_of(list.count)};
-#pragma unroll
-        for (int i = 1; i < 6; ++i) sums[i] = list.slot_tiles(288 - i * 32);
-        wave_totals(sums);
-        const int all_units = sums[0] * list.n_ft;
-        int64_t best = INT64_MAX;
-#pragma unroll
-        for (int i = 1; i < 6; ++i) {
-            const int s = 288 - i * 32;
-            const int tiles = sums[i] * list.n_ft;
-            const int full = tiles / per_super_round;
-            const int left = tiles - full * per_super_round;
-            const int chunk = (left + kXcds - 1) / kXcds;
-            const int step = 75 + 7 * s / 32;
-            const int units = min(left * TileList::units_of(min(s, most_rows)), all_units);  // of the leftover tiles, at most
-            for (int p = 1; p <= kMaxParts && (p == 1 || KT / p >= kMinPartKSteps); ++p) {
-                if (p > 1 && (chunk == 0 || units * (p - 1) > kScratchUnits)) break;
-                const int64_t cost = full * ((int64_t)KT * step + 600) + (chunk * p + members - 1) / members * ((int64_t)(KT / p) * step + 600);
-                if (cost < best) {
-                    best = cost;
-                    slots = s;
-                    parts = p;
-                }
-            }
-        }
-    }
+    if constexpr (G::kMats == 1) choose_plan(list, a.N, KT, members, slots, parts);
     list.build(slots);
     const int total = list.total;
     const int full_rounds = total / per_super_round;
     const int left = total - full_rounds * per_super_round;
     const int chunk = (left + kXcds - 1) / kXcds;
-    const bool amid = G::kMats == 1 && full_rounds == 1;  // (see above)
+    const bool amid = G::kMats == 1 && full_rounds == 1 && list.heavy * 10 >= 7 * per_super_round;  // (see above)
     const int first_left = amid ? list.heavy - (int)((long)left * list.heavy / total) : total - left;
     int first_unit = 0, n_units = 0;  // of the leftover tiles
     if (parts > 1) {

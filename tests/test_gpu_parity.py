@@ -108,6 +108,9 @@ def test_bf16_slot_groups_and_short_k_loops(oracle, T, H, F):
     (2700, 320, 1792, 2, 1),    # more slot tiles an expert than a group holds, the last ones ragged, all cut
     (2300, 256, 2048, 3, 2),    # the same with a single feature tile and two groups of different size
     (333, 576, 5376, 7, 3),     # ragged single slot tiles of every expert, pieces without gaps between them
+    (64, 512, 1152, 2, 2),      # 18 K steps, 6 parts of 3
+    (50, 2112, 1216, 3, 1),     # 19 K steps: parts of unequal length
+    (290, 640, 320, 4, 2),      # 5 K steps: whole tiles only
 ])
 def test_bf16_second_gemm_pieces_every_token(oracle, T, H, F, E, k):
     """The second GEMM cuts the tiles left over after its last full round along K; their pieces are added by the kernel
