@@ -170,6 +170,61 @@ __global__ __launch_bounds__(256) void combine_bf16(const float* __restrict__ ou
     }
 }
 
+// Second half of a first GEMM whose tiles were all cut (CUT): act[slot, f] = silu(g) * u, g and u the sums over the tile's pieces
+// in their order.  Four features a thread, all of their pieces requested together.  Bound by the latency of its two round
+// trips (tables, pieces).
+__global__ __launch_bounds__(256) void sum_swiglu_bf16(const float* __restrict__ pieces, const gg::SplitTable* __restrict__ split,
+                                                       const int32_t* __restrict__ offs, int E, int F, int routed,
+                                                       uint16_t* __restrict__ act) {
+    __shared__ int first[65], tile_units[64];
+    const int tid = threadIdx.x;
+    if (tid <= E) first[tid] = offs[tid];
+    if (tid < E) tile_units[tid] = split->units_before[tid];
+    const int parts = split->parts, slots = split->slots;
+    const size_t stride = (size_t)split->n_units * gg::kUnitFloats;
+    __syncthreads();
+    const int64_t item = (int64_t)blockIdx.x * 256 + tid;
+    const int slot = (int)(item / (F / 4)), f = (int)(item - (int64_t)slot * (F / 4)) * 4;
+    if (slot >= routed) return;
+    int e = 0;  // the last expert whose first slot is not behind this one
+#pragma unroll
+    for (int d = 32; d > 0; d /= 2)
+        if (e + d < E && first[e + d] <= slot) e += d;
+    const int count = first[e + 1] - first[e], m = (slot - first[e]) / slots, ft = f >> 7;
+    const gg::TileList::Place at = gg::TileList::place(count, slots, (F + 127) / 128, m);
+    const float* src = pieces + (size_t)(tile_units[e] + at.unit + ft * at.unit_step) * gg::kUnitFloats +
+                       (size_t)(slot - first[e] - m * slots) * 256 + (f & 127);
+    auto run = [&](auto parts_c) {
+        constexpr int P = decltype(parts_c)::value;
+        float4 g[P], u[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            g[i] = *reinterpret_cast<const float4*>(src + i * stride);
+            u[i] = *reinterpret_cast<const float4*>(src + i * stride + 128);
+        }
+#pragma unroll
+        for (int i = 1; i < P; ++i) {
+            g[0] = add4(g[0], g[i]);
+            u[0] = add4(u[0], u[i]);
+        }
+        uint2 pk;
+        pk.x = pack_bf16x2(swiglu(g[0].x, u[0].x), swiglu(g[0].y, u[0].y));
+        pk.y = pack_bf16x2(swiglu(g[0].z, u[0].z), swiglu(g[0].w, u[0].w));
+        *reinterpret_cast<uint2*>(act + (size_t)slot * F + f) = pk;
+    };
+    static_assert(gg::kMaxCutParts == 8, "one version per number of parts");
+    switch (parts) {
+        case 1: run(std::integral_constant<int, 1>{}); break;
+        case 2: run(std::integral_constant<int, 2>{}); break;
+        case 3: run(std::integral_constant<int, 3>{}); break;
+        case 4: run(std::integral_constant<int, 4>{}); break;
+        case 5: run(std::integral_constant<int, 5>{}); break;
+        case 6: run(std::integral_constant<int, 6>{}); break;
+        case 7: run(std::integral_constant<int, 7>{}); break;
+        default: run(std::integral_constant<int, 8>{}); break;
+    }
+}
+
 // Raises a kernel's dynamic LDS limit once (idempotent; a race only repeats it).
 template <typename Kernel>
 hipError_t allow_lds(Kernel k, int bytes, bool& configured) {
@@ -184,13 +239,12 @@ int persistent_grid() { return max(gg::kXcds, compute_units() / gg::kXcds * gg::
 
 // One of the two GEMMs.
 template <class G>
-hipError_t launch_gemm(const gg::GemmArgs& a, int stage, hipStream_t stream) {
+hipError_t launch_gemm(const gg::GemmArgs& a, hipStream_t stream) {
     auto kernel = gg::grouped_gemm_kernel<G>;
     static bool configured = false;
     const hipError_t e = allow_lds(kernel, G::kLdsBytes, configured);
     if (e != hipSuccess) return e;
     kernel<<<persistent_grid(), G::kThreads, G::kLdsBytes, stream>>>(a);
-    stage_mark(stream, stage);
     return hipGetLastError();
 }
 
@@ -200,7 +254,7 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
                            const void* w1, const void* w3, const void* w2, void* y, const int32_t* offs,
                            const int32_t* row_of_slot, const int32_t* slot_of, void* act, float* out,
                            int32_t* sync, float* partial, const StaleInput& alt, hipStream_t stream) {
-    static_assert(gg::kXcds <= kGemmSyncInts && gg::kScratchFloats * sizeof(float) + sizeof(gg::SplitTable) <= kGemmScratchBytes,
+    static_assert(gg::kXcds <= kGemmSyncInts && gg::kScratchFloats * sizeof(float) + 2 * sizeof(gg::SplitTable) <= kGemmScratchBytes,
                   "workspace layout");
     gg::GemmArgs g1{}, g2{};
     g1.tok = static_cast<const uint16_t*>(x);
@@ -214,6 +268,8 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
     g1.K = s.hidden;
     g1.dst = act;
     g1.sync = sync;
+    g1.scratch = partial;
+    g1.table = reinterpret_cast<gg::SplitTable*>(partial + gg::kScratchFloats);
     g1.tok_alt = static_cast<const uint16_t*>(alt.x_stale);
     g1.alt_mask = alt.stale;
     g2 = g1;
@@ -224,17 +280,26 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
     g2.K = s.ffn;
     g2.dst = out;
     g2.sync = sync + kGemmSyncInts;
-    g2.scratch = partial;
-    g2.table = reinterpret_cast<gg::SplitTable*>(partial + gg::kScratchFloats);
+    g2.table = g1.table + 1;
+    const bool alternate = alt.stale != nullptr;
+    const int routed = tokens * s.top_k;
+    const long most_tiles = (long)((s.ffn + 127) / 128) * (routed / 256 + min(s.n_experts, routed));
     hipError_t e;
-    // (with tok_alt slot rows are addressed with pointers anyway: only the weight rows decide)
-    if (gg::needs_wide(alt.stale != nullptr ? 0 : (size_t)tokens * s.hidden * 2, gg::Gemm<2>::kBF, s.hidden))
-        e = launch_gemm<gg::Gemm<2, false, true>>(g1, kStageGemm1, stream);
-    else if (alt.stale != nullptr) e = launch_gemm<gg::Gemm<2, true>>(g1, kStageGemm1, stream);
-    else e = launch_gemm<gg::Gemm<2>>(g1, kStageGemm1, stream);
+    const bool wide = gg::needs_wide((size_t)tokens * s.hidden * 2, gg::Gemm<2>::kBF, s.hidden);
+    if (wide) {  // (with and without tok_alt alike: with nothing taken from it the results have the same bits)
+        e = launch_gemm<gg::Gemm<2, false, true>>(g1, stream);
+    } else if (most_tiles <= gg::kMaxCutTiles && s.hidden / 64 >= gg::kMinCutKSteps) {
+        e = alternate ? launch_gemm<gg::Gemm<2, true, false, true>>(g1, stream) : launch_gemm<gg::Gemm<2, false, false, true>>(g1, stream);
+        const int64_t threads = (int64_t)routed * (s.ffn / 4);
+        sum_swiglu_bf16<<<(unsigned)((threads + 255) / 256), 256, 0, stream>>>(partial, g1.table, offs, s.n_experts, s.ffn, routed,
+                                                                              static_cast<uint16_t*>(act));
+    } else {
+        e = alternate ? launch_gemm<gg::Gemm<2, true>>(g1, stream) : launch_gemm<gg::Gemm<2>>(g1, stream);
+    }
+    stage_mark(stream, kStageGemm1);
     if (e != hipSuccess) return e;
-    e = gg::needs_wide(0, 256, s.ffn) ? launch_gemm<gg::Gemm<1, false, true>>(g2, kStageGemm2, stream)
-                                      : launch_gemm<gg::Gemm<1>>(g2, kStageGemm2, stream);
+    e = gg::needs_wide(0, 256, s.ffn) ? launch_gemm<gg::Gemm<1, false, true>>(g2, stream) : launch_gemm<gg::Gemm<1>>(g2, stream);
+    stage_mark(stream, kStageGemm2);
     if (e != hipSuccess) return e;
     const int column_blocks = (s.hidden + 2047) / 2048;
     // AHEAD up to three workgroups a CU: 720 of them (360 tokens, hidden 4096) 17.0 -> 15.1 us, 1000 to 1050 are equal (14.1; 10.5 and

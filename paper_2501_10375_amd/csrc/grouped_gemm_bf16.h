@@ -234,9 +234,13 @@ __device__ inline int swizzled(int row, int chunk) { return chunk ^ ((row >> 1) 
 // ALT (first GEMM): a slot's row comes from tok_alt where alt_mask says so; slot rows are addressed with 64-bit pointers.
 // WIDE: every operand is addressed with 64-bit pointers, and tok_alt is used if there is one.  For operands that a 32-bit
 // lane offset does not reach: x of kWideBytes or more, or a tile of weight or slot rows of that size (see needs_wide()).
-template <int NMAT, bool ALT = false, bool WIDE = false>
+// CUT (first GEMM): every tile is cut along K, see choose_cut(); the sums of both matrices go to the scratch memory in fp32, 128
+// columns of each side by side, and another kernel adds the pieces and applies SwiGLU.
+template <int NMAT, bool ALT = false, bool WIDE = false, bool CUT = false>
 struct Gemm {
     static_assert(!(ALT && WIDE) && (!ALT || NMAT == 2), "only the first GEMM gathers rows of x");
+    static_assert(!CUT || (NMAT == 2 && !WIDE), "the second GEMM cuts by itself");
+    static constexpr bool kCut = CUT;
     static constexpr int kThreads = 256, kMats = NMAT;
     static constexpr int kBF = 256 / NMAT;            // features per tile (per matrix)
     static constexpr int kF = 8;                      // 16-row fragments of each operand per wavefront
@@ -509,7 +513,7 @@ struct Gemm {
         // LDS rows are XOR-swizzled in 16-byte units so that the row-wise read-back is conflict free.
         // load_group(i, v): the results of slot fragment i, v[j] for weight fragment j.
         auto epilogue = [&](auto load_group) {
-            if constexpr (NMAT == 2) {
+            if constexpr (NMAT == 2 && !CUT) {
                 // [256 slots][128 features] bf16, 256-byte rows, unit v of row r at position v ^ (r & 15)
 #pragma unroll
                 for (int i = 0; i < TFE; ++i) {
@@ -539,7 +543,7 @@ struct Gemm {
                     }
                 }
             } else {
-                // two 32-slot groups at a time: [64 slots][256 features] fp32, 1 KB rows, unit v of row r at v ^ (r & 63)
+                // two 32-slot groups at a time: [64 slots][256 columns] fp32, 1 KB rows, unit v of row r at v ^ (r & 63)
 #pragma unroll
                 for (int i2 = 0; i2 < TFE; i2 += 2) {
                     if (i2 > 0) lds_barrier();
@@ -550,14 +554,14 @@ struct Gemm {
                         const int lr = (2 * (i - i2) + wt) * 16 + frow;
 #pragma unroll
                         for (int j = 0; j < kF; ++j) {
-                            const int unit = (wq * 128 + j * 16 + fpiece * 4) >> 2;
+                            const int unit = ((NMAT == 2 ? (j / 4) * 128 + wq * 64 + (j % 4) * 16 : wq * 128 + j * 16) + fpiece * 4) >> 2;
                             *reinterpret_cast<f32x4*>(lds + lr * 1024 + ((unit ^ (lr & 63)) << 4)) = v[j];
                         }
                     }
                     lds_barrier();
                     for (int lr = wave; lr < 64; lr += kThreads / 64) {
                         const int row = i2 * 32 + lr;
-                        const int n = n0 + lane * 4;
+                        const int n = n0 + (lane * 4 & (kBF - 1));
                         if (row < rows && n < N) {
                             const f32x4 v = *reinterpret_cast<const f32x4*>(lds + lr * 1024 + ((lane ^ (lr & 63)) << 4));
                             *reinterpret_cast<f32x4*>(out + (size_t)row * out_stride + lane * 4) = v;
@@ -613,7 +617,7 @@ struct GemmArgs {
     int E, topk, N, K;
     void* dst;
     int32_t* sync;
-    float* scratch;              // second GEMM: pieces of split tiles, kScratchUnits units ...
+    float* scratch;              // second GEMM, CUT: pieces of split tiles, kScratchUnits units ...
     SplitTable* table;           // ... and where they are
     const uint16_t* tok_alt;     // gemm1 with per-selection input rows (ALT), else null
     const uint8_t* alt_mask;
@@ -662,6 +666,34 @@ __device__ inline void choose_plan(const TileList& list, int N, int KT, int memb
     parts = __builtin_amdgcn_readlane(p, winner);
 }
 
+// Parts of the first GEMM's tiles in calls of few tiles (CUT): priced as in choose_plan(), for one height of tiles and with all
+// parts in the scratch memory.  Lane l prices l + 1 parts.
+constexpr int kMaxCutParts = 8;
+// Most tiles that such a call can have, which the launcher knows from the token count, and the fewest K steps.  Few tiles leave most CUs
+// idle for a whole K loop; cut, they keep them busy for part of one, but the other kernel takes 6 us.  First GEMM, whole / cut:
+// 16 tiles of 64 K steps 51 / 23 us, 32 52 / 31, 84 56 / 47, 96 of 48 56 / 51, 48 of 24 27 / 22, 88 of 25 29 / 27; but 128 of 64 with few
+// rows, which as they are stream at 4 TB/s, 70 / 79, 128 of 32 36 / 38, 64 of 16 20 / 21, 32 of 16 15 / 17.
+constexpr int kMaxCutTiles = 96, kMinCutKSteps = 24;
+
+__device__ inline void choose_cut(const TileList& list, int N, int KT, int members, int& parts) {
+    const int p = (threadIdx.x & 63) + 1;
+    const int most_rows = __builtin_amdgcn_readlane(list.count, 0);
+    const int active = __popcll(__ballot(list.count > 0));
+    int sums[2] = {TileList::units_of(list.count), list.slot_tiles(256)};
+    wave_totals(sums);
+    const int units = sums[0] * list.n_ft, chunk = (sums[1] * list.n_ft + kXcds - 1) / kXcds;
+    const int rounds = (chunk * p + members - 1) / members;
+    const float step = 90 + 6 * TileList::units_of(min(256, most_rows));
+    const float work = rounds * ((KT + p - 1) / p * step + 400.f);
+    const float stream = active * 2.f * N * KT * (1.f / 516.f) + rounds * 600.f;
+    float cost = fmaxf(work, stream) + 2.f * units * p;
+    if (p > 1 && (p > kMaxCutParts || units * p > kScratchUnits || KT < p * kMinPartKSteps)) cost = INFINITY;
+    float best = cost;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) best = fminf(best, __shfl_xor(best, d, 64));
+    parts = __ffsll((long long)__ballot(cost == best));
+}
+
 // Persistent schedule: the grid is one workgroup per CU.  Workgroup b belongs to XCD b % 8 (the
 // hardware deals workgroups round-robin to the XCDs) and is its member b / 8.  An XCD works
 // through the tile list in rounds of `members` consecutive tiles, so that its workgroups work on
@@ -682,7 +714,8 @@ __device__ inline void choose_plan(const TileList& list, int N, int KT, int memb
 // Second GEMM: it has few tiles with many K steps (2048 tokens of the Mixtral shape: 320 tiles of 224 K steps for 256
 // CUs), so what the last round costs matters.  The tiles left over after the last full round are cut along K into
 // `parts` pieces, handed out like tiles; see SplitTable for their sums, choose_plan() for their number.
-// The first GEMM has many short tiles (4096 tokens: 15 rounds); cutting its leftover tiles gained nothing.
+// The first GEMM has many short tiles (4096 tokens: 15 rounds); cutting its leftover tiles gained nothing.  For calls in which it
+// has few, see choose_cut().
 //
 // Which tiles are left over: the last ones, those of the coldest experts, except in a second GEMM of one full round of which
 // hot tiles alone would fill 7 tenths or more.  Such a round is bound by the MFMAs and the leftovers by memory, with little to
@@ -706,15 +739,30 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     const int per_super_round = kXcds * members;
     int slots = 256, parts = 1;
     if constexpr (G::kMats == 1) choose_plan(list, a.N, KT, members, slots, parts);
+    if constexpr (G::kCut) choose_cut(list, a.N, KT, members, parts);
     list.build(slots);
+    if constexpr (G::kMats == 2 && !G::kCut) {
+        // A call whose tiles are one round takes the lowest ones with which it still is: a K step takes less time (hidden 4096,
+        // ffn 2048, 8 experts, 256 tokens 77 -> 67 us; hidden 3584, ffn 1088, 8 experts, 509 tokens 72 -> 63; no shape is slower).
+        if (list.total <= per_super_round && __builtin_amdgcn_readlane(list.count, 0) > 128) {
+            int tiles[4];
+#pragma unroll
+            for (int n = 0; n < 4; ++n) tiles[n] = list.slot_tiles(128 + 32 * n);
+            wave_totals(tiles);
+#pragma unroll
+            for (int n = 3; n >= 0; --n)
+                if (tiles[n] * list.n_ft <= per_super_round) slots = 128 + 32 * n;
+            list.build(slots);
+        }
+    }
     const int total = list.total;
-    const int full_rounds = total / per_super_round;
+    const int full_rounds = G::kCut ? 0 : total / per_super_round;  // (CUT: every tile counts as left over)
     const int left = total - full_rounds * per_super_round;
     const int chunk = (left + kXcds - 1) / kXcds;
     const bool amid = G::kMats == 1 && full_rounds == 1 && list.heavy * 10 >= 7 * per_super_round;  // (see above)
     const int first_left = amid ? list.heavy - (int)((long)left * list.heavy / total) : total - left;
     int first_unit = 0, n_units = 0;  // of the leftover tiles
-    if (parts > 1) {
+    if (parts > 1 || G::kCut) {
         int e, slot0, rows, ft;
         list.count_units();
         list.find(first_left, e, slot0, rows, ft, first_unit);
@@ -722,7 +770,7 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
         if (first_left + left < total) list.find(first_left + left, e, slot0, rows, ft, n_units);
         n_units -= first_unit;
     }
-    if (G::kMats == 1 && blockIdx.x == 0 && threadIdx.x < 64) {
+    if ((G::kMats == 1 || G::kCut) && blockIdx.x == 0 && threadIdx.x < 64) {
         SplitTable* table = a.table;
         if (threadIdx.x == 0) {
             table->slots = slots;
@@ -801,11 +849,11 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
         int e, slot0, rows, ft, unit;
         list.find(tile_index, e, slot0, rows, ft, unit);
         const int kt0 = (int)((long)KT * part / p), kt1 = (int)((long)KT * (part + 1) / p);
-        // where the fp32 rows of the second GEMM go
+        // where fp32 rows go
         float* out = static_cast<float*>(a.dst) + (size_t)slot0 * a.N + ft * G::kBF;
         size_t out_stride = a.N;
-        if (part > 0) {
-            out = a.scratch + (size_t)((part - 1) * n_units + unit - first_unit) * kUnitFloats;
+        if (part > 0 || G::kCut) {
+            out = a.scratch + (size_t)((G::kCut ? part : part - 1) * n_units + unit - first_unit) * kUnitFloats;
             out_stride = 256;
         }
         item = members + G::tile(a.tok, a.wa, a.wb, a.row_of_slot, a.topk, a.N, a.K, static_cast<uint16_t*>(a.dst), lds, e, slot0,

@@ -143,6 +143,39 @@ def test_bf16_hidden_states_of_more_than_4_gib(oracle):
     assert output_error(to_f64(y[tok.to(DEV)]), ref) <= 2e-2
 
 
+@pytest.mark.parametrize("T,H,F,E,k", [
+    (33, 1536, 64, 1, 1),        # one tile, half a feature tile; 24 K steps: the shortest rows that are cut, 8 parts
+    (100, 4096, 512, 8, 2),      # 32 tiles, 8 parts of 8 K steps
+    (70, 1664, 320, 5, 3),       # 26 K steps: parts of unequal length; the last feature tile is half
+    (64, 2048, 2048, 8, 2),      # 128 tiles: the most that are cut
+    (64, 2048, 2112, 8, 2),      # one more feature tile: not cut
+    (2500, 1536, 192, 4, 3),     # several slot tiles an expert, the last ones ragged
+    (4000, 1536, 128, 1, 1),     # more slot tiles than a group of the tile list holds
+    (40, 1536, 128, 64, 1),      # experts without rows
+])
+def test_bf16_first_gemm_pieces_every_token(oracle, T, H, F, E, k):
+    """In calls of few tiles the first GEMM cuts all of them along K and another kernel adds the pieces and applies SwiGLU.
+    Every token is compared, and every selection of moe_expert_ffn_precalc once with mixed inputs."""
+    d, shape, out, res = _run(T, H, F, E, k, torch.bfloat16, seed=T + E)
+    r = check_layer(oracle, d, shape, res, torch.bfloat16, label=f"bf16 T={T} first GEMM cut")
+    print(r)
+    assert r["compared_tokens"] >= T - r["excluded"] - 2
+    x_stale = synth.normal((T, H), 99, 3, 1.0, torch.bfloat16, DEV)
+    g = torch.Generator().manual_seed(T)
+    stale = (torch.rand((T, k), generator=g) < 0.4).to(torch.uint8).to(DEV)
+    y = torch.empty_like(d["x"])
+    for mask, want in ((torch.zeros_like(stale), None), (stale, "mixed")):
+        moe.moe_expert_ffn_precalc(shape, d["x"], x_stale, mask, res["idx"], res["w"], d["w1"], d["w3"], d["w2"], y, out.workspace)
+        torch.cuda.synchronize()
+        if want is None:
+            assert torch.equal(y, res["y"])
+        else:
+            h = host(d)
+            ref = oracle.expert_ffn_precalc(h["x"], synth.to_numpy(x_stale), mask.cpu().numpy(), res["idx"].cpu().numpy(),
+                                            res["w"].cpu().numpy().astype(np.float64), h["w1"], h["w3"], h["w2"])
+            assert output_error(to_f64(y), ref) <= 2e-2
+
+
 def _swiglu_expert_rows(x, w1, w3, w2, chunk=1 << 20):
     """One expert on a few rows as plain torch: fp32 products, fp64 sums, the intermediate rounded to bf16."""
     H, F = w1.shape[1], w1.shape[0]
