@@ -9,6 +9,8 @@
 // Decode-size calls (at most 16 tokens) are a chain of memory latencies rather
 // than a stream: one workgroup routes the whole call with the hidden dimension
 // split over its wavefronts (route_device.h) and writes the counts itself.
+#include <type_traits>
+
 #include "moe_internal.h"
 #include "route_device.h"
 
@@ -32,9 +34,12 @@ struct RouteParams {
 // expert e on lane e for the softmax and the top-k.
 //
 // At these sizes (a gate of 64 to 512 KB, 16 tokens a workgroup) the kernel is a chain of latencies, so every load of
-// kChunk steps is requested before the first one is used, and unconditionally: rows and steps that do not exist re-read
-// one that does and are zeroed afterwards (a load under a branch waits for its own memory round trip).  The two gates
-// of a call go to different workgroups (x comes from the L2 the second time) while those fit the chip at one a CU, and
+// up to kChunk steps is requested before the first one is used, and unconditionally: rows that do not exist re-read one that
+// does (a load under a branch waits for its own memory round trip).  There is a version for every number of steps, so that a
+// wavefront of a short hidden dimension asks for no step twice (all eight always, one gate, 8 experts: hidden 512 11.7 -> 6.9 us,
+// 2048 11.7 -> 9.1) and addresses are constants from the row's start (with an address a step, 64 experts spilled registers:
+// hidden 2048, 1003 tokens 19.3 -> 16.2 us; fp32 with 64 experts has registers for one step only, hidden 1024 21.0 -> 17.0).
+// The two gates of a call go to different workgroups (x comes from the L2 the second time) while those fit the chip at one a CU, and
 // are done one after the other by the same workgroup beyond that (4096 tokens: 23 us so, 27 us in two rounds).
 // Measured, both gates: 1003 tokens, 64 experts, hidden 2048: 28 -> 17 us; 32 and 77 tokens, 8 experts, hidden 4096:
 // 17 -> 12 us; fp32, 512 tokens, 64 experts, hidden 1024: 208 -> 20 us (a wavefront per token read the whole gate).
@@ -61,22 +66,22 @@ __device__ inline f32x4 total_of(const f32x4 (&acc)[4]) {
     for (int i = 0; i < 4; ++i) r[i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
     return r;
 }
-__device__ inline u32x4 keep_if(bool on, u32x4 v) {
-    u32x4 r;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = on ? v[i] : 0u;
-    return r;
+// f(n) with n, at most N, as a constant.
+template <int N, class F>
+__device__ inline void for_count(int n, F f) {
+    if (n == N) f(std::integral_constant<int, N>{});
+    else if constexpr (N > 1) for_count<N - 1>(n, f);
 }
 
 template <typename scalar_t, int NBG>
 __global__ __launch_bounds__(1024) void route_mfma_kernel(RouteParams p) {
     constexpr bool kF32 = sizeof(scalar_t) == 4;
     constexpr int kSums = kF32 ? 4 : 1;
-    constexpr int kChunk = NBG == 1 ? 8 : NBG == 4 && kF32 ? 2 : 4;  // steps whose operands are in registers at a time
+    constexpr int kChunk = NBG == 1 ? 8 : NBG == 4 && kF32 ? 1 : 4;  // steps whose operands are in registers at a time
     constexpr int kStep = 64 / (int)sizeof(scalar_t), kLane = 16 / (int)sizeof(scalar_t);
     __shared__ int hist[2][64];
     __shared__ f32x4 part[16][NBG][64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid < 128) hist[tid >> 6][tid & 63] = 0;
     const int H = p.hidden, E = p.n_experts, T = p.tokens;
     const int t0 = blockIdx.x * kRouteTokensPerBlock;
@@ -101,23 +106,26 @@ __global__ __launch_bounds__(1024) void route_mfma_kernel(RouteParams p) {
         for (int nb = 0; nb < NBG; ++nb)
 #pragma unroll
             for (int q = 0; q < kSums; ++q) acc[nb][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int s0 = s_begin; s0 < s_end; s0 += kChunk) {
-            u32x4 xa[kChunk], wb[NBG][kChunk];
+        auto steps = [&](auto n_c, int s0) {
+            constexpr int N = decltype(n_c)::value;
+            u32x4 xa[N], wb[NBG][N];
+            const scalar_t* xs = xrow + (size_t)s0 * kStep;
 #pragma unroll
-            for (int i = 0; i < kChunk; ++i) {
-                const size_t at = (size_t)min(s0 + i, s_end - 1) * kStep;
-                xa[i] = *reinterpret_cast<const u32x4*>(xrow + at);
+            for (int i = 0; i < N; ++i) xa[i] = *reinterpret_cast<const u32x4*>(xs + i * kStep);
 #pragma unroll
-                for (int nb = 0; nb < NBG; ++nb) wb[nb][i] = *reinterpret_cast<const u32x4*>(wrow[nb] + at);
+            for (int nb = 0; nb < NBG; ++nb) {
+                const scalar_t* ws = wrow[nb] + (size_t)s0 * kStep;
+#pragma unroll
+                for (int i = 0; i < N; ++i) wb[nb][i] = *reinterpret_cast<const u32x4*>(ws + i * kStep);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < kChunk; ++i) {
-                const bool real = s0 + i < s_end;  // both operands are zeroed: they may hold infinities
-                const u32x4 a = keep_if(real, xa[i]);
+            for (int i = 0; i < N; ++i)
 #pragma unroll
-                for (int nb = 0; nb < NBG; ++nb) mfma_step(a, keep_if(real, wb[nb][i]), acc[nb]);
-            }
+                for (int nb = 0; nb < NBG; ++nb) mfma_step(xa[i], wb[nb][i], acc[nb]);
+        };
+        for (int s0 = s_begin; s0 < s_end; s0 += kChunk) {
+            for_count<kChunk>(min(kChunk, s_end - s0), [&](auto n) { steps(n, s0); });
         }
 
         // MFMA result: lane holds column (expert in block) lane & 15 and rows (tokens) 4 * (lane / 16) + r.

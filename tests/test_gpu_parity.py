@@ -290,6 +290,23 @@ def test_fp32_units_groups_and_router_blocks(oracle, T, H, F, E, k, zipf):
     assert r["err"] <= 1e-5, r
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("E", [7, 21, 61])
+@pytest.mark.parametrize("H", [64, 448, 1024, 1536, 2304, 2624, 3008, 3584, 4160])
+def test_router_steps_per_wavefront(oracle, H, E, dtype):
+    """Sixteen wavefronts share the K steps: 0 to 10 (bf16) or 17 (fp32) steps each, in chunks of 1, 4 or 8 with every remainder."""
+    T, k = 35, 3
+    d = synth.moe_layer_inputs(T, H, 64, E, dtype, DEV, seed=H + E)
+    shape = moe.make_shape(H, 64, E, k, dtype)
+    idx = torch.empty((T, k), dtype=torch.int32, device=DEV)
+    w = torch.empty((T, k), dtype=torch.float32, device=DEV)
+    counts = torch.empty(E, dtype=torch.int32, device=DEV)
+    moe.moe_route(shape, d["x"], d["wg"], d["bias"], idx, w, counts, False, moe.alloc_workspace(shape, T, route_only=True))
+    torch.cuda.synchronize()
+    h = host(d)
+    check_routing(idx, w, counts, oracle.route(h["x"], h["wg"], h["bias"], k), E, f"H={H} E={E}")
+
+
 @pytest.mark.parametrize("T,F,E,zipf", [
     (1100, 1024, 12, 1.5),     # second GEMM: one full round and whole leftover tiles from the middle of the list; no work taken over
     (1100, 3072, 12, 1.5),     # 48 K steps: leftover tiles may be cut, and work is taken over between XCDs
