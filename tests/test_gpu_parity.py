@@ -290,6 +290,42 @@ def test_fp32_units_groups_and_router_blocks(oracle, T, H, F, E, k, zipf):
     assert r["err"] <= 1e-5, r
 
 
+@pytest.mark.parametrize("T,H,F,E,k", [
+    (800, 1024, 1024, 4, 2),    # both GEMMs: one wavefront sums K alone, 64 slots x 128 features
+    (700, 576, 1600, 3, 3),     # the shortest long K; features that are no multiple of 128
+    (900, 640, 512, 2, 1),      # only the first GEMM has a long K
+    (2000, 64, 192, 8, 2),      # K 64 and 192: short K, 32 slots
+    (3000, 128, 64, 5, 4),      # features of the second GEMM that are no multiple of 128; K 128 and 64
+    (300, 192, 2112, 1, 1),     # short and long K, one expert, ragged last units
+])
+def test_fp32_kernels_for_long_calls_give_the_same_bits(oracle, T, H, F, E, k):
+    """A slot's sums have one order in all fp32 GEMM kernels: a long call equals the calls on its slices bit for bit, with
+    selections evaluated on another input among them.  A few tokens are compared with the oracle as well."""
+    d = synth.moe_layer_inputs(T, H, F, E, torch.float32, DEV, seed=T, with_next=False)
+    shape = moe.make_shape(H, F, E, k, torch.float32)
+    g = torch.Generator().manual_seed(T)
+    idx = torch.stack([torch.randperm(E, generator=g)[:k] for _ in range(T)]).int().to(DEV)
+    w = torch.softmax(torch.rand((T, k), generator=g), 1).to(DEV)
+    x_stale = synth.normal((T, H), 5, 3, 1.0, torch.float32, DEV)
+    stale = (torch.rand((T, k), generator=g) < 0.4).to(torch.uint8).to(DEV)
+    ws = moe.alloc_workspace(shape, T)
+
+    def run(lo, hi):
+        y = torch.empty((2, hi - lo, H), device=DEV)
+        part = [t[lo:hi].clone() for t in (d["x"], x_stale, stale, idx, w)]
+        moe.moe_expert_ffn(shape, part[0], part[3], part[4], d["w1"], d["w3"], d["w2"], y[0], ws)
+        moe.moe_expert_ffn_precalc(shape, *part, d["w1"], d["w3"], d["w2"], y[1], ws)
+        return y
+
+    whole = run(0, T)
+    assert torch.equal(whole, torch.cat([run(lo, min(T, lo + 37)) for lo in range(0, T, 37)], 1))
+    tok = np.unique(np.linspace(0, T - 1, 12).astype(int))
+    h = host(d)
+    ref = oracle.expert_ffn(h["x"], idx.cpu().numpy(), w.cpu().numpy().astype(np.float64), h["w1"], h["w3"], h["w2"], tokens=tok)
+    # fp32 sums of n terms are off by less than n * 2^-24 of their terms' size
+    assert output_error(to_f64(whole[0])[tok], ref) <= 1e-5
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("E", [7, 21, 61])
 @pytest.mark.parametrize("H", [64, 448, 1024, 1536, 2304, 2624, 3008, 3584, 4160])
