@@ -184,7 +184,8 @@ __global__ __launch_bounds__(256) void memory_init_kernel(int L, int E, const in
 }
 
 // ---- prediction with graceful degradation --------------------------------------------------------
-// One workgroup per 16 tokens, the decode-size routing code with the placement mask.
+// One workgroup per `per_block` tokens (2 or 16, see daop_predict_degraded), the decode-size routing code with the placement
+// mask.
 template <typename scalar_t>
 __global__ __launch_bounds__(kSmallRouteThreads) void predict_degraded_kernel(const scalar_t* __restrict__ x,
                                                                                const scalar_t* __restrict__ wg,
