@@ -86,16 +86,48 @@ def check_layer(oracle, d_gpu, shape, out, dtype, tokens=None, label="", predict
     return {"excluded": n_excl, "excluded_pred": n_excl_pred, "err": err, "compared_tokens": int(tok.size)}
 
 
-def tile_aware_sample(idx: np.ndarray, n_experts: int, n_even: int, tile: int = 256, n_cold: int = 2,
+UNIT_ROWS, SCRATCH_UNITS, SCRATCH_BYTES = 32, 255 * 8, 64 << 20
+
+
+def second_gemm_plan(workspace: torch.Tensor, shape, tokens: int) -> dict:
+    """What the last bf16 call of more than 32 tokens on `workspace` did in its second GEMM, read from the table that the
+    kernel leaves behind the pieces in the workspace: slots per tile, parts per split tile, number of the first split tile
+    in the tile list and how many are split."""
+    table_bytes = 4 * (8 + 2 * 64)
+    at = moe.moe_workspace_bytes(shape, tokens) - SCRATCH_BYTES + SCRATCH_UNITS * UNIT_ROWS * 256 * 4 + table_bytes
+    t = workspace[at:at + 16].cpu().numpy().view(np.int32)
+    plan = {"slots": int(t[0]), "parts": int(t[1]), "first": int(t[2]), "count": int(t[3])}
+    assert plan["slots"] in (128, 160, 192, 224, 256) and 1 <= plan["parts"] <= 6, plan
+    return plan
+
+
+def second_gemm_tiles(counts: np.ndarray, hidden: int, slots: int) -> list:
+    """(expert, slot tile) of every tile of the second GEMM in the order of its tile list: experts by descending row count
+    (equal counts: lower index first), their slot tiles in groups of at most 8 of nearly equal size, within a group feature tile by
+    feature tile."""
+    n_ft, tiles = (hidden + 255) // 256, []
+    for e in sorted(range(len(counts)), key=lambda e: (-counts[e], e)):
+        mt = -(-int(counts[e]) // slots)
+        groups = -(-mt // 8)
+        first = 0
+        for g in range(groups):
+            size = mt // groups + (1 if g < mt % groups else 0)
+            tiles += [(e, first + m) for _ in range(n_ft) for m in range(size)]
+            first += size
+    return tiles
+
+
+def tile_aware_sample(idx: np.ndarray, n_experts: int, n_even: int, plan: dict | None = None, hidden: int = 0, n_cold: int = 2,
                       fragment: int = 32) -> np.ndarray:
     """Tokens on which to compare the layer output of a long call, chosen from where the grouped GEMMs
-    put them.  Selections are grouped per expert in (token, j) order (a stable sort), `tile` slots to
-    a slot tile.  The sample holds
-      * every token routed to one of the `n_cold` least-used experts (their few, ragged slot tiles are
-        the ones whose K range is split between workgroups when they fall into the last round),
-      * the first and last slot of every slot tile of every expert,
+    put them.  Selections are grouped per expert in (token, j) order (a stable sort); the first GEMM has 256 slots to
+    a slot tile (in calls of this size), the second `plan["slots"]` (see second_gemm_plan; every height it can choose where
+    there is no plan).  The sample holds
+      * the first and last slot of every slot tile of every expert, in both GEMMs,
+      * one more slot of every slot tile that the second GEMM split along K or left over,
       * for the most-used expert's first and last slot tile, one slot at the start and one at the end of
         every `fragment`-slot group (every fragment position of a tile, full and ragged),
+      * every token routed to one of the `n_cold` least-used experts,
       * `n_even` evenly spaced tokens.
     idx: int [T, k] selected experts."""
     T, k = idx.shape
@@ -104,20 +136,24 @@ def tile_aware_sample(idx: np.ndarray, n_experts: int, n_even: int, tile: int = 
     counts = np.bincount(flat, minlength=n_experts)
     starts = np.concatenate([[0], np.cumsum(counts)])
     chosen = set(np.unique(np.linspace(0, T - 1, max(n_even, 1)).astype(int)).tolist())
+
+    def add(e, slot):
+        chosen.add(int(order[starts[e] + min(slot, int(counts[e]) - 1)] // k))
+
     used = [e for e in np.argsort(counts, kind="stable") if counts[e] > 0]
     for e in used[:n_cold]:
         chosen.update((order[starts[e]:starts[e + 1]] // k).tolist())
-    for e in used:
-        c = int(counts[e])
-        for s0 in range(0, c, tile):
-            last = min(c, s0 + tile) - 1
-            chosen.add(int(order[starts[e] + s0] // k))
-            chosen.add(int(order[starts[e] + last] // k))
-    if used:
+    for tile in {256, plan["slots"]} if plan else range(128, 257, 32):
+        for e in used:
+            for s0 in range(0, int(counts[e]), tile):
+                add(e, s0)
+                add(e, s0 + tile - 1)
         e = used[-1]
-        c = int(counts[e])
-        for s0 in {0, (c - 1) // tile * tile}:
-            for f0 in range(s0, min(c, s0 + tile), fragment):
-                chosen.add(int(order[starts[e] + f0] // k))
-                chosen.add(int(order[starts[e] + min(c, f0 + fragment) - 1] // k))
+        for s0 in {0, (int(counts[e]) - 1) // tile * tile}:
+            for f0 in range(s0, min(int(counts[e]), s0 + tile), fragment):
+                add(e, f0)
+                add(e, f0 + fragment - 1)
+    split = second_gemm_tiles(counts, hidden, plan["slots"])[plan["first"]:plan["first"] + plan["count"]] if plan else ()
+    for e, m in set(split):
+        add(e, m * plan["slots"] + (7 * m + 11 * int(e)) % plan["slots"])
     return np.array(sorted(chosen), dtype=np.int64)

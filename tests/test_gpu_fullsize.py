@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2501_10375_amd import moe, synth
-from parity_util import check_layer, tile_aware_sample
+from parity_util import check_layer, second_gemm_plan, tile_aware_sample
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -43,7 +43,9 @@ def _layer(oracle, d, c, T, n_sample, label, tile_aware=False):
     if n_sample >= T:
         tokens = None
     elif tile_aware:
-        tokens = tile_aware_sample(res["idx"].cpu().numpy(), c["E"], n_sample)
+        plan = second_gemm_plan(out.workspace, shape, T)
+        print(label, plan)
+        tokens = tile_aware_sample(res["idx"].cpu().numpy(), c["E"], n_sample, plan, c["H"])
     else:
         tokens = np.unique(np.linspace(0, T - 1, n_sample).astype(int))
     r = check_layer(oracle, call, shape, res, torch.bfloat16, tokens=tokens, label=label)

@@ -5,7 +5,8 @@ import pytest
 import torch
 
 from paper_2501_10375_amd import moe, synth
-from parity_util import check_layer, check_routing, host, output_error, tile_aware_sample, to_f64
+from parity_util import (check_layer, check_routing, host, output_error, second_gemm_plan, second_gemm_tiles, tile_aware_sample,
+                         to_f64)
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -27,7 +28,7 @@ def test_config0_tiny_fp32_layer(oracle):
 
 
 @pytest.mark.parametrize("T,H,F,E,k", [
-    (300, 256, 512, 8, 2),     # several 128-slot tiles per expert, ragged tails
+    (300, 256, 512, 8, 2),     # about 75 rows an expert: ragged slot tiles of one to several 32-slot groups
     (129, 128, 192, 4, 2),     # F not a multiple of the 128 feature tile
     (77, 64, 64, 16, 2),       # smallest legal widths, many cold experts
     (200, 256, 256, 8, 1),     # top-1
@@ -53,9 +54,8 @@ def test_bf16_prefill_path(oracle, T, H, F, E, k):
     (3000, 256, 2048, 2, 2),   # more tiles than compute units: one full round, then a split round
 ])
 def test_bf16_full_tile_flavour_every_token(oracle, T, H, F, E, k):
-    """Calls with at least 512 routed rows per expert run both GEMMs in the full-tile flavour (256-slot
-    tiles, three weight stages and two slot stages), the one long prefill calls run.  Narrow layers let
-    the oracle check every token, so every wavefront's fragment rows and every epilogue position of
+    """Calls with at least 512 routed rows per expert, as long prefill calls have them: full slot tiles of up to 256 slots.
+    Narrow layers let the oracle check every token, so every wavefront's fragment rows and every epilogue position of
     the 256 x 256 tile is compared, including tiles whose K range is split between workgroups."""
     assert T * k >= E * 512
     d, shape, out, res = _run(T, H, F, E, k, torch.bfloat16)
@@ -65,18 +65,17 @@ def test_bf16_full_tile_flavour_every_token(oracle, T, H, F, E, k):
 
 
 @pytest.mark.parametrize("T,H,F,E,k,seed", [
-    (200, 256, 256, 2, 2, 0),    # 200 rows per expert: gemm1 in the full-tile flavour, gemm2 in the ragged one
+    (200, 256, 256, 2, 2, 0),    # 200 rows per expert: one ragged tile of seven 32-slot groups each
     (150, 256, 384, 4, 4, 1),    # hot expert: a full slot tile and a short one; cold experts: one or two fragments
-    (330, 320, 448, 2, 2, 2),    # both GEMMs full-tile, second slot tile of every expert ragged
-    (140, 128, 640, 1, 1, 3),    # one expert with 140 rows: 5 valid fragments, 3 and 2 per wavefront group
-    (520, 192, 256, 8, 2, 4),    # 130 rows per expert on average: cold experts far below one fragment per group
+    (330, 320, 448, 2, 2, 2),    # second slot tile of every expert ragged
+    (140, 128, 640, 1, 1, 3),    # one expert with 140 rows: five 32-slot groups, the last of 12 rows
+    (520, 192, 256, 8, 2, 4),    # 130 rows per expert on average: cold experts below one group
     (300, 256, 512, 2, 1, 5),    # top-1, about 150 rows per expert
 ])
 def test_bf16_ragged_fragments_of_full_tiles_every_token(oracle, T, H, F, E, k, seed):
-    """From 128 routed rows per expert on gemm1 runs in the full-tile flavour, whose ragged slot tiles
-    issue only the MFMAs of their valid 32-slot fragments (a main loop per fragment count, chosen per
-    wavefront), while gemm2 stays in the ragged flavour below 320 rows per expert.  Every token is
-    compared, so every fragment count a wavefront can have (1 to 4) is exercised over these shapes."""
+    """A ragged slot tile computes and stages only the 32-slot groups that have slots (a main loop per number of
+    groups, 1 to 8).  Every token is compared; the numbers of groups that these shapes leave out are in
+    test_bf16_slot_groups_and_short_k_loops."""
     assert E * 128 <= T * k
     d, shape, out, res = _run(T, H, F, E, k, torch.bfloat16, seed=seed)
     counts = res["counts"].cpu().tolist()
@@ -121,11 +120,13 @@ def test_bf16_second_gemm_pieces_every_token(oracle, T, H, F, E, k):
     assert r["compared_tokens"] >= T - r["excluded"] - 2
 
 
-def test_bf16_hidden_states_of_more_than_4_gib(oracle):
-    """Row offsets of x past 32 bits: the first GEMM then addresses slot rows with 64-bit pointers.  Compared on
+@pytest.mark.parametrize("gib,precalc", [(3, False), (4, False), (4, True)])
+def test_bf16_hidden_states_of_many_gib(oracle, gib, precalc):
+    """Row offsets of x around 32 bits: at 3 GiB lane offsets have their top bit set; past 3.75 GiB the first GEMM
+    addresses slot rows with 64-bit pointers, of two tensors with selections pre-calculated on another input.  Compared on
     tokens from both ends of x (tokens are independent, so the oracle gets those rows alone)."""
     H, F, E, k, dtype = 4096, 64, 2, 1, torch.bfloat16
-    T = (1 << 32) // (2 * H) + 300
+    T = (gib << 30) // (2 * H) + 300
     d = synth.moe_layer_inputs(1, H, F, E, dtype, DEV, seed=5, with_next=False)
     g = torch.Generator(device=DEV).manual_seed(9)
     x = torch.randn((T, H), generator=g, dtype=dtype, device=DEV)
@@ -134,7 +135,13 @@ def test_bf16_hidden_states_of_more_than_4_gib(oracle):
     y = torch.empty((T, H), dtype=dtype, device=DEV)
     shape = moe.make_shape(H, F, E, k, dtype)
     ws = moe.alloc_workspace(shape, T)
-    moe.moe_expert_ffn(shape, x, idx, w, d["w1"], d["w3"], d["w2"], y, ws)
+    if precalc:
+        x_stale = torch.randn((T, H), generator=g, dtype=dtype, device=DEV)
+        stale = (torch.arange(T, device=DEV) % 2).to(torch.uint8).reshape(T, 1)
+        moe.moe_expert_ffn_precalc(shape, x, x_stale, stale, idx, w, d["w1"], d["w3"], d["w2"], y, ws)
+        x = torch.where(stale != 0, x_stale, x)  # what each selection was evaluated on
+    else:
+        moe.moe_expert_ffn(shape, x, idx, w, d["w1"], d["w3"], d["w2"], y, ws)
     torch.cuda.synchronize()
     tok = torch.cat([torch.arange(0, 40), torch.arange(T // 2, T // 2 + 40), torch.arange(T - 350, T)])
     h = host(d)
@@ -290,6 +297,24 @@ def test_fp32_units_groups_and_router_blocks(oracle, T, H, F, E, k, zipf):
     assert r["err"] <= 1e-5, r
 
 
+@pytest.mark.parametrize("T,H,F,E,zipf", [
+    (600, 3072, 3072, 8, 1.2),   # 48 K steps: the fewest with which work is taken over
+    (150, 4096, 6400, 16, 1.5),  # 64 and 100 K steps, single slot tiles
+    (1500, 4096, 3584, 6, 0.5),  # several rounds in both GEMMs
+])
+def test_bf16_work_taken_over_between_xcds_repeats_bit_for_bit(T, H, F, E, zipf):
+    """Which workgroup makes a tile depends on timing there; the plan, and with it every sum, depends on the counts alone."""
+    d, shape, out, res = _run(T, H, F, E, 2, torch.bfloat16, zipf=zipf, predict=False)
+    torch.cuda.synchronize()
+    first = res["y"].clone()
+    for i in range(8):
+        out.workspace.fill_(255 if i % 2 else 0)
+        out.y.fill_(0)
+        res = moe.run_layer(shape, d, out, predict=False)
+        torch.cuda.synchronize()
+        assert torch.equal(res["y"], first), i
+
+
 @pytest.mark.parametrize("T,H,F,E,k", [
     (800, 1024, 1024, 4, 2),    # both GEMMs: one wavefront sums K alone, 64 slots x 128 features
     (700, 576, 1600, 3, 3),     # the shortest long K; features that are no multiple of 128
@@ -345,15 +370,20 @@ def test_router_steps_per_wavefront(oracle, H, E, dtype):
 
 @pytest.mark.parametrize("T,F,E,zipf", [
     (1100, 1024, 12, 1.5),     # second GEMM: one full round and whole leftover tiles from the middle of the list; no work taken over
-    (1100, 3072, 12, 1.5),     # 48 K steps: leftover tiles may be cut, and work is taken over between XCDs
-    (2600, 3072, 4, 1.2),      # the same with few experts of many slot tiles
+    (1100, 3072, 12, 1.5),     # one full round with few hot tiles: the coldest are left over and cut; 48 K steps: work is taken over
+    (2600, 3072, 4, 1.2),      # one full round of hot tiles alone, leftover tiles cut
     (5000, 3072, 3, 0.5),      # two full rounds: the leftover tiles are the last ones
 ])
 def test_bf16_leftover_tiles_of_the_second_gemm(oracle, T, F, E, zipf):
     H, k, dtype = 4096, 2, torch.bfloat16
     d, shape, out, res = _run(T, H, F, E, k, dtype, zipf=zipf, predict=False)
     torch.cuda.synchronize()
-    sample = tile_aware_sample(res["idx"].cpu().numpy(), E, 16, n_cold=0)
+    plan = second_gemm_plan(out.workspace, shape, T)
+    counts = res["counts"].cpu().numpy()
+    tiles = second_gemm_tiles(counts, H, plan["slots"])
+    print(plan, "tiles", len(tiles), "hot", sum(counts[e] > plan["slots"] for e, _ in tiles), counts)
+    assert plan["count"] == len(tiles) % 256 and 0 <= plan["first"] <= len(tiles) - plan["count"]
+    sample = tile_aware_sample(res["idx"].cpu().numpy(), E, 16, plan, H, n_cold=0)
     # every token against a second call with its rows in another order: other tiles, other pieces, sums equal to the
     # last bits of fp32, so a bf16 result may round to its neighbour
     check_layer(oracle, d, shape, res, dtype, tokens=sample, label=f"leftover T={T} F={F} E={E}", predict=False)
@@ -486,7 +516,7 @@ def test_decode_rendezvous_reports_when_it_gives_up(oracle):
     (1, 256, 512, 8, 2, torch.bfloat16), (8, 512, 1024, 8, 2, torch.bfloat16), (16, 128, 320, 8, 8, torch.bfloat16),
     (24, 256, 512, 8, 2, torch.bfloat16),      # two column groups of the streaming kernel
     (6, 8192, 128, 8, 2, torch.bfloat16),      # hidden size past the register-resident token operand
-    (300, 256, 512, 8, 2, torch.bfloat16),     # ragged 128-slot tiles
+    (300, 256, 512, 8, 2, torch.bfloat16),     # ragged slot tiles
     (1100, 256, 512, 2, 2, torch.bfloat16),    # full 256-slot tiles, split-K round
     (64, 256, 512, 8, 2, torch.float32), (5, 64, 128, 4, 2, torch.float32),
 ])
