@@ -16,6 +16,7 @@ DEV = "cuda"
     (8, 512, 1600, 16, 2),    # decode size, tiles that do not divide the grid
     (24, 256, 512, 8, 2),     # routing kernels + the streaming expert kernel
     (300, 256, 512, 8, 2),    # prefill path: routing, permutation, grouped GEMMs with a split last round, combine
+    (100, 1536, 512, 8, 2),   # the first GEMM's tiles cut along K as well, summed by a kernel of their own
 ])
 def test_layer_call_replays_from_a_graph(T, H, F, E, k):
     dtype = torch.bfloat16
