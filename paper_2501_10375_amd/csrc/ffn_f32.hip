@@ -329,7 +329,8 @@ void launch_units(Kernel kernel, const F32Gemm& g, int unit_rows, int tile_featu
 
 // gemm_f32_alone where there is work for every CU without cutting K over wavefronts, counted in 64 x 64 outputs with an
 // expert's last 64 rows as half full.  Split / alone, us:
-//   long K, 64 slots x 128 features, from 380 of them and 32 rows an expert on.  First GEMM, K 4096: 2048 tokens 4119 / 2367, 256 tokens (768) 832 / 526; K 2048: 384 of them 212 / 147, 224 118 / 118; K 1024: 1088 231 / 154, 320 93 / 92 and
+//   long K, 64 slots x 128 features, from 380 of them and 32 rows an expert on (and not for 64 features: half of every workgroup
+//   would have none, K 4096 (407) 441 / 515).  First GEMM, K 4096: 2048 tokens 4119 / 2367, 256 tokens (768) 832 / 526; K 2048: 384 of them 212 / 147, 224 118 / 118; K 1024: 1088 231 / 154, 320 93 / 92 and
 //   256 61 / 67; but K 4096 with 16 rows an expert 325 / 348, K 960 with 25 216 / 227, K 512 (528) 45 / 53, K 256 (1056) 72 / 82.
 //   short K, 32 slots x 64 features (first) or x 128 (second), from as many of them as K has elements on: what the split
 //   costs per output no longer hides behind the contraction.  K 64: 20000 tokens 39 / 20, second 22 / 14; hidden 4096 from ffn 64, 3000
@@ -339,7 +340,7 @@ constexpr int kLongK = 576, kShortK = 192, kMinLongTiles = 380, kMinLongRows = 3
 template <int NM>
 void launch_gemm_f32(const F32Gemm& g, hipStream_t stream) {
     const long tiles = (long)(g.routed / (4 * kRows) + (min(g.E, g.routed) + 1) / 2) * (g.N / (4 * kRows));
-    if (g.K >= kLongK && tiles >= kMinLongTiles && g.routed >= kMinLongRows * g.E)
+    if (g.K >= kLongK && tiles >= kMinLongTiles && g.routed >= kMinLongRows * g.E && g.N >= 2 * kWaves * kRows)
         return launch_units(gemm_f32_alone<NM, 2, 4, 1>, g, 4 * kRows, 2 * kWaves * kRows, stream);
     if (g.K <= kShortK && tiles >= g.K)
         return launch_units(gemm_f32_alone<NM, 3 - NM, 2, NM == 2 ? 4 : 3>, g, 2 * kRows, (3 - NM) * kWaves * kRows, stream);
