@@ -85,6 +85,8 @@ __device__ inline void wave_totals(int (&v)[N]) {
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = __builtin_amdgcn_readfirstlane(v[i]);
 }
+// A value that is the same in all lanes, in a scalar register.
+__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ inline int wave_inclusive_sum(int v) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -183,6 +185,20 @@ struct TileList {
     }
 };
 
+// tok: gemm1 -> x [T, K] rows gathered via row_of_slot / topk; gemm2 -> act [A, K], rows = slots.
+// wa, wb: [E, N, K]; dst: gemm1 -> bf16 [A, N]; gemm2 -> fp32 [A, N].
+struct GemmArgs {
+    const uint16_t *tok, *wa, *wb;
+    const int32_t *offs, *row_of_slot;
+    int E, topk, N, K;
+    void* dst;
+    int32_t* sync;
+    float* scratch;              // second GEMM, CUT: pieces of split tiles, kScratchUnits units ...
+    SplitTable* table;           // ... and where they are
+    const uint16_t* tok_alt;     // gemm1 with per-selection input rows (ALT), else null
+    const uint8_t* alt_mask;
+};
+
 template <int N>
 __device__ inline void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
@@ -194,6 +210,13 @@ __device__ inline void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Orders a wavefront's own LDS traffic (which the hardware does by itself; this is for the compiler).
+__device__ inline void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
 // LDS swizzle: the 16-byte piece `chunk` (of 8) of tile row `row` is stored at piece position
@@ -240,14 +263,14 @@ template <int NMAT, bool ALT = false, bool WIDE = false, bool CUT = false>
 struct Gemm {
     static_assert(!(ALT && WIDE) && (!ALT || NMAT == 2), "only the first GEMM gathers rows of x");
     static_assert(!CUT || (NMAT == 2 && !WIDE), "the second GEMM cuts by itself");
-    static constexpr bool kCut = CUT;
+    static constexpr bool kCut = CUT, kFp32 = NMAT == 1 || CUT;
     static constexpr int kThreads = 256, kMats = NMAT;
     static constexpr int kBF = 256 / NMAT;            // features per tile (per matrix)
     static constexpr int kF = 8;                      // 16-row fragments of each operand per wavefront
     static constexpr int kStage = 32768;              // one operand tile: 256 rows of 128 bytes
     static constexpr uint32_t kSlotBase = 3 * kStage; // weights: three stages from 0, slots: two stages from here
     static constexpr int kLdsBytes = 5 * kStage;
-    static constexpr int kHandoffOffset = kSlotBase + kStage;  // first load into this stage follows a tile's first barrier
+    static constexpr int kRowsOffset = 1024;          // row numbers of the next item's slots, 256 bytes a wavefront, behind the item's number
 
     typedef __attribute__((address_space(3))) const unsigned char* lds_ptr;
     using Yes = std::true_type;
@@ -259,6 +282,7 @@ struct Gemm {
     static __device__ inline void load_lane(u32x4 base, uint32_t lane_off, uint32_t off) {
         asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(lane_off), "s"(base), "s"(off) : "memory");
     }
+    static __device__ inline void load_word(const char* p) { asm volatile("global_load_lds_dword %0, off" ::"v"(p) : "memory"); }
     static __device__ inline void load_ptr(const char* p) { asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(p) : "memory"); }
     // acc += a . b with the accumulator in AGPRs, in place.  (From the builtin, in a kernel with as many loops as this
     // one, the compiler gives the result another register than the operand and then spends the loop moving accumulators
@@ -299,84 +323,162 @@ struct Gemm {
         return d;
     }
 
-    static __device__ int tile(const uint16_t* __restrict__ tok_base, const uint16_t* __restrict__ wa,
-                               const uint16_t* __restrict__ wb, const int32_t* __restrict__ row_of_slot, int topk,
-                               int N, int K, uint16_t* __restrict__ dst, unsigned char* lds, int e, int slot0, int rows,
-                               int ft, int kt_begin, int kt_end, float* __restrict__ out, size_t out_stride,
-                               int32_t* __restrict__ handed_out,
-                               const uint16_t* __restrict__ tok_alt, const uint8_t* __restrict__ alt_mask) {
-        const int n0 = ft * kBF;
+    // One work item: a tile, or a piece of one.
+    struct Item {
+        int e, slot0, rows, ft, kt_begin, k_steps;
+        float* out;          // where fp32 rows go
+        uint32_t out_stride;
+        int from;            // XCD whose list it is from
+    };
+
+    // Works through items, beginning with `item`.  claim(from) takes the number of the next one off a list (one lane), settle_claim(n, item,
+    // from) turns it into an item's number and its list (wavefront 0; -1: none left), and decode(item, from, Item&) says what that is.
+    //
+    // The wavefronts go from tile to tile without emptying the memory pipe: the next item is claimed two K steps before the end of a
+    // tile; when the last operands have been read, its first weights, the row numbers of its slots and then its first slot rows are
+    // requested, and the results of the finished tile are stored while they arrive.  The results go through LDS in an 8 KB
+    // region per wavefront inside slot stage 1, so that the only barriers between two tiles are the one after the last operand reads
+    // (which also publishes the next item) and the one before the first.  (With the claim, the look-up and all requests after the stores a
+    // tile cost 6 us more than its K steps, 3 now.  While all CUs stream, others use the bandwidth meanwhile: whole layer, Phi shape, 200
+    // tokens 381 -> 368 us, 64 experts of hidden 2048 and ffn 1408, 3000 tokens 437 -> 429, Mixtral shape 512 to 4096 tokens 0.3 to 0.7 %.)
+    template <class Claim, class SettleClaim, class Decode>
+    static __device__ inline void run(const GemmArgs& a, unsigned char* lds, Item cur, const Claim& claim, const SettleClaim& settle_claim,
+                                      const Decode& decode) {
+        const int N = a.N, K = a.K;
+        const lds_ptr lds3 = (lds_ptr)lds;
+        const uint32_t lds0 = (uint32_t)(uintptr_t)lds3;
+        const uint32_t row_bytes = (uint32_t)K * 2u;
+        const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int wt = wave & 1, wq = wave >> 1;      // slot group, weight-row group
+        const uint32_t wave_lds = lds0 + (uint32_t)wave * 1024;
+        auto next_w = [](uint32_t s) { return s == 2 * kStage ? 0u : s + kStage; };
+
+        // ---- staging: load q of wavefront w covers rows q * 32 + w * 8 .. + 7 of an operand tile, lane l the 16-byte
+        // piece that belongs at position l % 8 of row l / 8 (see swizzled(); the same for every q).
+        constexpr int kWOffs = 8 / NMAT;              // both matrices use the same lane offsets
+        u32x4 base_a, base_b, base_s;
+        uint32_t w_off[WIDE ? 1 : kWOffs];
+        const char* w_ptr[WIDE ? 8 : 1];
+        uint32_t s_off[WIDE || ALT ? 1 : 8];
+        const char* s_ptr[WIDE || ALT ? 8 : 1];
+        auto weight_load = [&](int q, uint32_t k_off) __attribute__((always_inline)) {
+            if constexpr (WIDE) load_ptr(w_ptr[q] + k_off);
+            else load_lane(NMAT == 2 && q >= 4 ? base_b : base_a, w_off[q % kWOffs], k_off);
+        };
+        auto slot_load = [&](int q, uint32_t k_off) __attribute__((always_inline)) {
+            if constexpr (WIDE || ALT) load_ptr(s_ptr[q] + k_off);
+            else load_lane(base_s, s_off[q], k_off);
+        };
+        auto weight_stage = [&](uint32_t stage, uint32_t k_off) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                set_lds_target(wave_lds + stage + q * 4096);
+                wait_state();
+                weight_load(q, k_off);
+            }
+        };
+        auto slot_stage0 = [&](const Item& t) __attribute__((always_inline)) {
+            const int groups = (t.rows + 31) / 32;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (q >= groups) break;
+                set_lds_target(wave_lds + kSlotBase + q * 4096);
+                wait_state();
+                slot_load(q, (uint32_t)t.kt_begin * 128);
+            }
+        };
+        // First requests of an item: the row numbers of its slots (first GEMM), which go to the weight stage `w0` + 2 (not used
+        // before its third K step), and its first weights, into stage w0.  The second GEMM's slot rows are consecutive rows: the first ones go out as well.
+        auto request_first = [&](const Item& t, uint32_t w0) __attribute__((always_inline)) {
+            int tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));
+            const int lane = tid & 63;
+            const int lrow = wave * 8 + (lane >> 3);
+            const int chunk = swizzled(lrow, lane & 7);
+            if constexpr (NMAT == 2) {  // lane l: the row that lanes 8 * (l % 8) ... of load l / 8 fetch
+                const int r = min((lane >> 3) * 32 + wave * 8 + (lane & 7), t.rows - 1);  // rows past the end re-read the last valid row
+                set_lds_target(lds0 + next_w(next_w(w0)) + kRowsOffset + (uint32_t)wave * 256);
+                wait_state();
+                load_word(reinterpret_cast<const char*>(a.row_of_slot + t.slot0 + r));
+            }
+            const int n0 = t.ft * kBF;
+            const size_t w_first = ((size_t)t.e * N + n0) * K;
+            base_a = descriptor(a.wa + w_first);
+            base_b = descriptor(NMAT == 2 ? a.wb + w_first : a.wa + w_first);
+#pragma unroll
+            for (int q = 0; q < (WIDE ? 8 : kWOffs); ++q) {
+                const int f = min((q % kWOffs) * 32 + lrow, N - 1 - n0);  // features past the end re-read the last one
+                if constexpr (WIDE)
+                    w_ptr[q] = reinterpret_cast<const char*>((NMAT == 2 && q >= 4 ? a.wb : a.wa) + w_first) + (size_t)f * row_bytes + (size_t)chunk * 16;
+                else
+                    w_off[q] = (uint32_t)f * row_bytes + (uint32_t)chunk * 16;
+            }
+            weight_stage(w0, (uint32_t)t.kt_begin * 128);
+            if constexpr (NMAT == 1) {
+                base_s = descriptor(a.tok + (size_t)t.slot0 * K);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int r = min(q * 32 + lrow, t.rows - 1);
+                    if constexpr (WIDE)
+                        s_ptr[q] = reinterpret_cast<const char*>(a.tok + (size_t)t.slot0 * K) + (size_t)r * row_bytes + (size_t)chunk * 16;
+                    else
+                        s_off[q] = (uint32_t)r * row_bytes + (uint32_t)chunk * 16;
+                }
+                slot_stage0(t);
+            }
+        };
+        // First GEMM: looks the slot rows up and requests those of the first K step.  At most eight loads (the weights) are younger than the row numbers.
+        auto request_slots = [&](const Item& t, uint32_t w0) __attribute__((always_inline)) {
+            if constexpr (NMAT == 2) {
+                int tid = threadIdx.x;
+                asm volatile("" : "+v"(tid));
+                const int lane = tid & 63;
+                const int chunk = swizzled(wave * 8 + (lane >> 3), lane & 7);
+                wait_vmcnt<8>();
+                const int assignment = *reinterpret_cast<__attribute__((address_space(3))) const int*>(
+                    lds3 + next_w(next_w(w0)) + kRowsOffset + wave * 256 + lane * 4);   // t * topk + j
+                const int token = assignment / a.topk;
+                if constexpr (WIDE || ALT) {
+                    const bool from_alt = (ALT || a.alt_mask != nullptr) && a.alt_mask[assignment] != 0;
+                    uint64_t tok = reinterpret_cast<uint64_t>(a.tok), alt = reinterpret_cast<uint64_t>(a.tok_alt);
+                    asm volatile("" : "+s"(tok), "+s"(alt));  // (else the two are picked from an array in scratch memory)
+                    const uint64_t at = (from_alt ? alt : tok) + (uint64_t)token * row_bytes;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        const int src = (q * 8 + (lane >> 3)) * 4;
+                        const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)at);
+                        const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)(at >> 32));
+                        s_ptr[q] = reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo) + chunk * 16;
+                    }
+                } else {
+                    base_s = descriptor(a.tok);
+                    const uint32_t at = (uint32_t)token * row_bytes;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        s_off[q] = (uint32_t)__builtin_amdgcn_ds_bpermute((q * 8 + (lane >> 3)) * 4, (int)at) + (uint32_t)chunk * 16;
+                }
+                slot_stage0(t);
+            }
+        };
+
+        uint32_t w0 = 0;  // weight stage of an item's first K step
+        request_first(cur, w0);
+        request_slots(cur, w0);
+        for (;;) {
         // (opaque, so that the compiler computes lane addresses where they are used instead of keeping those of every
         // version of the epilogue in registers across the whole kernel)
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         const int lane = tid & 63;
-        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int wt = wave & 1, wq = wave >> 1;      // slot group, weight-row group
-        const lds_ptr lds3 = (lds_ptr)lds;
-        const uint32_t lds0 = (uint32_t)(uintptr_t)lds3;
-        const int KT = kt_end - kt_begin;
-        const uint32_t k_first = (uint32_t)kt_begin * 128;
-        const int n_groups = __builtin_amdgcn_readfirstlane((rows + 31) / 32);  // TFE
-
-        // ---- staging: load q of wavefront w covers rows q * 32 + w * 8 .. + 7 of an operand tile, lane l the 16-byte
-        // piece that belongs at position l % 8 of row l / 8 (see swizzled(); the same for every q).
-        const int lrow = wave * 8 + (lane >> 3);
-        const int chunk = swizzled(lrow, lane & 7);
-        constexpr int kWOffs = 8 / NMAT;              // both matrices use the same lane offsets
-        const size_t w_first = ((size_t)e * N + n0) * K;
-        const u32x4 base_a = descriptor(wa + w_first);
-        const u32x4 base_b = descriptor(NMAT == 2 ? wb + w_first : wa + w_first);
-        const uint32_t row_bytes = (uint32_t)K * 2u;
-        uint32_t w_off[WIDE ? 1 : kWOffs];
-        const char* w_ptr[WIDE ? 8 : 1];
-#pragma unroll
-        for (int q = 0; q < (WIDE ? 8 : kWOffs); ++q) {
-            const int f = min((q % kWOffs) * 32 + lrow, N - 1 - n0);  // features past the end re-read the last one
-            if constexpr (WIDE)
-                w_ptr[q] = reinterpret_cast<const char*>((NMAT == 2 && q >= 4 ? wb : wa) + w_first) + (size_t)f * row_bytes + (size_t)chunk * 16;
-            else
-                w_off[q] = (uint32_t)f * row_bytes + (uint32_t)chunk * 16;
+        const int KT = cur.k_steps;
+        const uint32_t k_first = (uint32_t)cur.kt_begin * 128;
+        if (KT > 1) {
+            weight_stage(next_w(w0), k_first + 128);
+            wait_vmcnt<8>();
+        } else {
+            wait_vmcnt<0>();
         }
-        const uint32_t wave_lds = lds0 + (uint32_t)wave * 1024;
-        auto weight_load = [&](int q, uint32_t k_off) {
-            if constexpr (WIDE) load_ptr(w_ptr[q] + k_off);
-            else load_lane(NMAT == 2 && q >= 4 ? base_b : base_a, w_off[q % kWOffs], k_off);
-        };
-        // Weights of the first two K steps are requested before the slot rows are looked up.
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            set_lds_target(wave_lds + q * 4096);
-            wait_state();
-            weight_load(q, k_first);
-        }
-        const u32x4 base_s = descriptor(NMAT == 2 ? tok_base : tok_base + (size_t)slot0 * K);
-        uint32_t s_off[WIDE || ALT ? 1 : 8];
-        const char* s_ptr[WIDE || ALT ? 8 : 1];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int r = min(q * 32 + lrow, rows - 1);   // rows past the end re-read the last valid row
-            if constexpr (NMAT == 1) {
-                if constexpr (WIDE)
-                    s_ptr[q] = reinterpret_cast<const char*>(tok_base + (size_t)slot0 * K) + (size_t)r * row_bytes + (size_t)chunk * 16;
-                else
-                    s_off[q] = (uint32_t)r * row_bytes + (uint32_t)chunk * 16;
-            } else {
-                const int assignment = row_of_slot[slot0 + r];   // t * topk + j
-                const size_t at = (size_t)(assignment / topk) * row_bytes + (size_t)chunk * 16;
-                if constexpr (WIDE || ALT) {
-                    const bool from_alt = (ALT || alt_mask != nullptr) && alt_mask[assignment] != 0;
-                    const uint16_t* rows_from = from_alt ? tok_alt : tok_base;
-                    s_ptr[q] = reinterpret_cast<const char*>(rows_from) + at;
-                } else {
-                    s_off[q] = (uint32_t)at;
-                }
-            }
-        }
-        auto slot_load = [&](int q, uint32_t k_off) {
-            if constexpr (WIDE || ALT) load_ptr(s_ptr[q] + k_off);
-            else load_lane(base_s, s_off[q], k_off);
-        };
+        lds_barrier();
 
         // ---- operand fragments: 16 rows x 32 K elements, lane l holds row l % 16, piece l / 16 of the half K step.
         // Row r, piece p sits at r * 128 + ((p ^ ((r >> 1) & 7)) << 4): fragments are 2048 bytes apart (the swizzle
@@ -389,19 +491,20 @@ struct Gemm {
         const uint32_t s_read = kSlotBase + (uint32_t)wt * 2048 + in_row;
         constexpr auto w_frag = [](int j) constexpr { return (uint32_t)(NMAT == 2 ? (j / 4) * 16384 + (j % 4) * 2048 : j * 2048); };
 
-        int next_item = 0;
+        Item next;
+        bool more_items = false;
         // The whole tile for TFE valid 32-slot groups.  Everything from the accumulators to the stores is inside, so
         // that the eight versions have no code in common behind their loops (where they join, the compiler would have
         // to agree on registers for 256 accumulators and spills instead).
-        auto run = [&](auto tfe_c) {
+        auto tile = [&](auto tfe_c) __attribute__((always_inline)) {
             constexpr int TFE = decltype(tfe_c)::value;
-        f32x4 acc[kF][TFE];  // [weight fragment][slot fragment]
+            f32x4 acc[kF][TFE];  // [weight fragment][slot fragment]
 #pragma unroll
-        for (int j = 0; j < kF; ++j)
+            for (int j = 0; j < kF; ++j)
 #pragma unroll
-            for (int i = 0; i < TFE; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        pin(acc);
-        settle();
+                for (int i = 0; i < TFE; ++i) acc[j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            pin(acc);
+            settle();
 
             constexpr int kM = kF * TFE, kR = kF + TFE;
             bf16x8 wf[2][kF], tf[2][TFE];
@@ -409,7 +512,7 @@ struct Gemm {
             // at w_stage / s_stage into buffer 1 - mbuf, and the loads of one operand (LOADS 1: TFE slot loads, 2: 8
             // weight loads) for a later K step.
             auto half_step = [&](auto mfma, auto mbuf_c, auto read, int half, uint32_t w_stage, uint32_t s_stage, auto loads,
-                                 uint32_t target, uint32_t k_off) {
+                                 uint32_t target, uint32_t k_off) __attribute__((always_inline)) {
                 constexpr int mbuf = decltype(mbuf_c)::value, rbuf = 1 - mbuf;
                 constexpr int LOADS = decltype(loads)::value;
                 constexpr int n_loads = LOADS == 1 ? TFE : LOADS == 2 ? 8 : 1;
@@ -453,26 +556,9 @@ struct Gemm {
             using Slots = std::integral_constant<int, 1>;
             using Weights = std::integral_constant<int, 2>;
 
-#pragma unroll
-            for (int q = 0; q < TFE; ++q) {
-                set_lds_target(wave_lds + kSlotBase + q * 4096);
-                wait_state();
-                slot_load(q, k_first);
-            }
-            if (KT > 1) {
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    set_lds_target(wave_lds + kStage + q * 4096);
-                    wait_state();
-                    weight_load(q, k_first + 128);
-                }
-                wait_vmcnt<8>();
-            } else {
-                wait_vmcnt<0>();
-            }
-            lds_barrier();
             // first half of K step 0 into buffer 0; slots of K step 1 requested
-            half_step(No{}, Buf1{}, Yes{}, 0, 0u, 0u, None{}, 0u, 0u);
+            uint32_t w_stage = w0, s_stage = 0;                // of K step kt
+            half_step(No{}, Buf1{}, Yes{}, 0, w_stage, s_stage, None{}, 0u, 0u);
             if (KT > 1) {
 #pragma unroll
                 for (int q = 0; q < TFE; ++q) {
@@ -481,16 +567,15 @@ struct Gemm {
                     slot_load(q, k_first + 128);
                 }
             }
-            uint32_t w_stage = 0, s_stage = 0;                 // of K step kt
             uint32_t k_off = k_first + 256;                    // of K step kt + 2
-            auto next_w = [](uint32_t s) { return s == 2 * kStage ? 0u : s + kStage; };
-            auto k_step = [&](auto more) {                      // second half of K step kt, first half of K step kt + 1
+            auto k_step = [&](auto more) __attribute__((always_inline)) {  // second half of K step kt, first half of K step kt + 1
                 const uint32_t w1 = next_w(w_stage), w2 = next_w(w1), s1 = s_stage ^ kStage;
                 // Stage w2 held K step kt - 1, which every wavefront had read before the last barrier.
                 half_step(Yes{}, Buf0{}, Yes{}, 1, w_stage, s_stage, std::conditional_t<decltype(more)::value, Weights, None>{},
                           wave_lds + w2, k_off);
-                // Outstanding, oldest first: weights of K step kt + 1, its slots, weights of K step kt + 2.
+                // Outstanding, oldest first: weights of K step kt + 1, its slots, weights of K step kt + 2, or the first wavefront's claim.
                 if constexpr (decltype(more)::value) wait_vmcnt<8>();
+                else if (wave == 0) wait_vmcnt<1>();
                 else wait_vmcnt<0>();
                 lds_barrier();
                 half_step(Yes{}, Buf1{}, Yes{}, 0, w1, s1, std::conditional_t<decltype(more)::value, Slots, None>{},
@@ -500,103 +585,114 @@ struct Gemm {
                 k_off += 128;
             };
             for (int kt = 0; kt + 2 < KT; ++kt) k_step(Yes{});
+            // The next item is claimed now; the answer is needed after the last K step.
+            int claimed = 0;
+            if (tid == 0) claimed = claim(cur.from);
             if (KT > 1) k_step(No{});
             half_step(Yes{}, Buf0{}, Yes{}, 1, w_stage, s_stage, None{}, 0u, 0u);
             half_step(Yes{}, Buf1{}, No{}, 0, 0u, 0u, None{}, 0u, 0u);
-        // Ask for the next work item now; the answer is needed only after the epilogue.
-        if (tid == 0) next_item = __hip_atomic_fetch_add(handed_out, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        settle();
-        pin(acc);
+            settle();
+            pin(acc);
 
-        // ---- epilogue: transpose through LDS so that global stores are whole contiguous rows.
-        // MFMA 16x16 result: lane holds column (slot) lane % 16 and rows (features) 4 * (lane / 16) + c.
-        // LDS rows are XOR-swizzled in 16-byte units so that the row-wise read-back is conflict free.
-        // load_group(i, v): the results of slot fragment i, v[j] for weight fragment j.
-        auto epilogue = [&](auto load_group) {
+            // ---- the next item: its number and list in the weight stage that the last two K steps did not use
+            const uint32_t handoff = next_w(w_stage);
+            asm volatile("" ::"v"(claimed));  // (every wavefront waits here: where the answer may be outstanding, the main loop gets waits for it)
+            if (wave == 0) {
+                int item, from = cur.from;
+                settle_claim(claimed, item, from);
+                if (tid == 0) *reinterpret_cast<int2*>(lds + handoff) = make_int2(item, from);
+            }
+            lds_barrier();  // every wavefront is done reading operand tiles; no load is outstanding
+            const int2 got = *reinterpret_cast<const int2*>(lds + handoff);
+            const int item = __builtin_amdgcn_readfirstlane(got.x);
+            w0 = next_w(handoff);  // (so that the stage with the number is the last to be written again)
+            more_items = item >= 0;
+            if (more_items) {
+                decode(item, __builtin_amdgcn_readfirstlane(got.y), next);
+                request_first(next, w0);
+            }
+
+            // ---- epilogue: transpose through LDS so that global stores are whole 128-byte lines, each wavefront by itself.
+            // MFMA 16x16 result: lane holds column (slot) lane % 16 and rows (features) 4 * (lane / 16) + c.
+            // LDS rows are XOR-swizzled in 16-byte units so that both ways are conflict free.
+            unsigned char* own = lds + kSlotBase + kStage + wave * 8192;
+            const int n0 = cur.ft * kBF;
             if constexpr (NMAT == 2 && !CUT) {
-                // [256 slots][128 features] bf16, 256-byte rows, unit v of row r at position v ^ (r & 15)
+                // [up to 64 slots][64 features] bf16, 128-byte rows, unit v of row r at position v ^ ((r >> 1) & 7)
+                const int n = n0 + wq * 64 + (lane & 7) * 8;
 #pragma unroll
-                for (int i = 0; i < TFE; ++i) {
-                    __builtin_amdgcn_sched_barrier(0);  // one fragment's values in registers at a time
-                    f32x4 v[kF];
-                    load_group(i, v);
-                    const int row = (2 * i + wt) * 16 + frow;
+                for (int i4 = 0; i4 < TFE; i4 += 4) {
 #pragma unroll
-                    for (int j = 0; j < kF / 2; ++j) {
-                        const int col = wq * 64 + j * 16 + fpiece * 4;  // feature in tile
-                        float o[4];
+                    for (int i = i4; i < i4 + 4 && i < TFE; ++i) {
+                        __builtin_amdgcn_sched_barrier(0);  // one fragment's values in registers at a time
+                        const int lr = (i - i4) * 16 + frow;
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) o[c] = swiglu(v[j][c], v[kF / 2 + j][c]);
-                        uint2 pk;
-                        pk.x = pack_bf16x2(o[0], o[1]);
-                        pk.y = pack_bf16x2(o[2], o[3]);
-                        *reinterpret_cast<uint2*>(lds + row * 256 + (((col >> 3) ^ (row & 15)) << 4) + (col & 4) * 2) = pk;
+                        for (int j = 0; j < kF / 2; ++j) {
+                            float o[4];
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) o[c] = swiglu(from_acc(acc[j][i][c]), from_acc(acc[kF / 2 + j][i][c]));
+                            uint2 pk;
+                            pk.x = pack_bf16x2(o[0], o[1]);
+                            pk.y = pack_bf16x2(o[2], o[3]);
+                            *reinterpret_cast<uint2*>(own + lr * 128 + (((j * 2 + (fpiece >> 1)) ^ ((lr >> 1) & 7)) << 4) + (fpiece & 1) * 8) = pk;
+                        }
                     }
-                }
-                lds_barrier();
-                for (int row = tid >> 4; row < rows; row += kThreads / 16) {
-                    const int unit = tid & 15;
-                    const int n = n0 + unit * 8;
-                    if (n < N) {
-                        const u32x4 v = *reinterpret_cast<const u32x4*>(lds + row * 256 + ((unit ^ (row & 15)) << 4));
-                        *reinterpret_cast<u32x4*>(dst + (size_t)(slot0 + row) * N + n) = v;
-                    }
+                    wave_order();
+                    if (i4 == 0 && more_items) request_slots(next, w0);
+#pragma unroll
+                    for (int i = i4; i < i4 + 4 && i < TFE; ++i)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            const int lr = (i - i4) * 16 + h * 8 + (lane >> 3);
+                            const int row = (2 * i + wt) * 16 + h * 8 + (lane >> 3);
+                            const u32x4 v = *reinterpret_cast<const u32x4*>(own + lr * 128 + (((lane & 7) ^ ((lr >> 1) & 7)) << 4));
+                            if (row < cur.rows && n < N)
+                                *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.dst) + (size_t)(cur.slot0 + row) * N + n) = v;
+                        }
+                    wave_order();
                 }
             } else {
-                // two 32-slot groups at a time: [64 slots][256 columns] fp32, 1 KB rows, unit v of row r at v ^ (r & 63)
+                // [16 slots][128 columns] fp32, 512-byte rows, unit v of row r at v ^ r.  Columns: NMAT == 1 wq * 128 + 0 .. 127;
+                // NMAT == 2 64 of each matrix, wq * 64 + 0 .. 63 and 128 + wq * 64 + 0 .. 63.
+                const int unit = lane & 31;
+                const int col = NMAT == 1 ? wq * 128 + unit * 4 : (unit >> 4) * 128 + wq * 64 + (unit & 15) * 4;
+                const bool stores = n0 + (col & (kBF - 1)) < N;
+                if (more_items) request_slots(next, w0);
 #pragma unroll
-                for (int i2 = 0; i2 < TFE; i2 += 2) {
-                    if (i2 > 0) lds_barrier();
+                for (int i = 0; i < TFE; ++i) {
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int i = i2; i < i2 + 2 && i < TFE; ++i) {
-                        f32x4 v[kF];
-                        load_group(i, v);
-                        const int lr = (2 * (i - i2) + wt) * 16 + frow;
+                    for (int j = 0; j < kF; ++j) {
+                        f32x4 v;
 #pragma unroll
-                        for (int j = 0; j < kF; ++j) {
-                            const int unit = ((NMAT == 2 ? (j / 4) * 128 + wq * 64 + (j % 4) * 16 : wq * 128 + j * 16) + fpiece * 4) >> 2;
-                            *reinterpret_cast<f32x4*>(lds + lr * 1024 + ((unit ^ (lr & 63)) << 4)) = v[j];
-                        }
+                        for (int c = 0; c < 4; ++c) v[c] = from_acc(acc[j][i][c]);
+                        *reinterpret_cast<f32x4*>(own + frow * 512 + (((j * 4 + fpiece) ^ frow) << 4)) = v;
                     }
-                    lds_barrier();
-                    for (int lr = wave; lr < 64; lr += kThreads / 64) {
-                        const int row = i2 * 32 + lr;
-                        const int n = n0 + (lane * 4 & (kBF - 1));
-                        if (row < rows && n < N) {
-                            const f32x4 v = *reinterpret_cast<const f32x4*>(lds + lr * 1024 + ((lane ^ (lr & 63)) << 4));
-                            *reinterpret_cast<f32x4*>(out + (size_t)row * out_stride + lane * 4) = v;
-                        }
+                    wave_order();
+#pragma unroll
+                    for (int h = 0; h < 8; ++h) {
+                        const int lr = h * 2 + (lane >> 5);
+                        const int row = (2 * i + wt) * 16 + lr;
+                        const f32x4 v = *reinterpret_cast<const f32x4*>(own + lr * 512 + ((unit ^ lr) << 4));
+                        if (row < cur.rows && stores) *reinterpret_cast<f32x4*>(cur.out + (size_t)row * cur.out_stride + col) = v;
                     }
+                    wave_order();
                 }
             }
         };
-        lds_barrier();  // every wavefront is done reading operand tiles; no load is outstanding
-        epilogue([&](int i, f32x4 (&v)[kF]) {
-#pragma unroll
-            for (int j = 0; j < kF; ++j)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) v[j][c] = from_acc(acc[j][i][c]);
-        });
-        };
-        switch (n_groups) {
-            case 1: run(std::integral_constant<int, 1>{}); break;
-            case 2: run(std::integral_constant<int, 2>{}); break;
-            case 3: run(std::integral_constant<int, 3>{}); break;
-            case 4: run(std::integral_constant<int, 4>{}); break;
-            case 5: run(std::integral_constant<int, 5>{}); break;
-            case 6: run(std::integral_constant<int, 6>{}); break;
-            case 7: run(std::integral_constant<int, 7>{}); break;
-            default: run(std::integral_constant<int, 8>{}); break;
+        switch (__builtin_amdgcn_readfirstlane((cur.rows + 31) / 32)) {
+            case 1: tile(std::integral_constant<int, 1>{}); break;
+            case 2: tile(std::integral_constant<int, 2>{}); break;
+            case 3: tile(std::integral_constant<int, 3>{}); break;
+            case 4: tile(std::integral_constant<int, 4>{}); break;
+            case 5: tile(std::integral_constant<int, 5>{}); break;
+            case 6: tile(std::integral_constant<int, 6>{}); break;
+            case 7: tile(std::integral_constant<int, 7>{}); break;
+            default: tile(std::integral_constant<int, 8>{}); break;
         }
-
-        // ---- hand the next item's number to every wavefront.  The first barrier also keeps the next
-        // tile's loads from landing in LDS that a slower wavefront is still reading back above; the word
-        // sits in the stage that no load is written to before the next tile's first barrier.
-        lds_barrier();
-        int* handoff = reinterpret_cast<int*>(lds + kHandoffOffset);
-        if (tid == 0) *handoff = next_item;
-        lds_barrier();
-        return __builtin_amdgcn_readfirstlane(*handoff);
+        if (!more_items) return;
+        cur = next;
+        }
     }
 };
 
@@ -608,20 +704,6 @@ constexpr size_t kWideBytes = (size_t)15 << 28;
 constexpr bool needs_wide(size_t gathered, size_t tile_rows, size_t k_elements) {
     return gathered >= kWideBytes || tile_rows * k_elements * 2 >= kWideBytes;
 }
-
-// tok: gemm1 -> x [T, K] rows gathered via row_of_slot / topk; gemm2 -> act [A, K], rows = slots.
-// wa, wb: [E, N, K]; dst: gemm1 -> bf16 [A, N]; gemm2 -> fp32 [A, N].
-struct GemmArgs {
-    const uint16_t *tok, *wa, *wb;
-    const int32_t *offs, *row_of_slot;
-    int E, topk, N, K;
-    void* dst;
-    int32_t* sync;
-    float* scratch;              // second GEMM, CUT: pieces of split tiles, kScratchUnits units ...
-    SplitTable* table;           // ... and where they are
-    const uint16_t* tok_alt;     // gemm1 with per-selection input rows (ALT), else null
-    const uint8_t* alt_mask;
-};
 
 // Slots per tile and parts of a leftover tile for the second GEMM.  A smaller tile costs less per round, but there are more of
 // them; more parts make a shorter last round, but each is a prologue and an epilogue, and rows that are written and read again.
@@ -792,73 +874,95 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     const int n_rounds = full_rounds * kXcds;
     const int heavy_rounds = min(n_rounds, min(list.heavy, first_left) / members);
     const int light_rounds = n_rounds - heavy_rounds;
-    int item = member;  // the counter hands out items `members`, `members` + 1, ...
-    int from = xcd;     // whose items
-    for (;;) {
-        if (item >= n_whole + left_of(from) * parts) {
-            if (KT < kMinStealKSteps) break;
-            // That XCD's items are all handed out: go on with one of the XCD that has most left.  (Not in the word that
-            // tile() hands over: another wavefront may still have to read that.)
-            int* handoff = reinterpret_cast<int*>(lds + G::kHandoffOffset);
-            if (threadIdx.x < 64) {
-                const int lane = threadIdx.x;
-                const int items = lane < kXcds ? n_whole + left_of(lane) * parts - members : 0;
-                int got = -1, victim = 0;
-                for (;;) {  // a try that loses the race has seen the victim's last item go: the sum of `open` falls every time
-                    int open = lane < kXcds ? items - __hip_atomic_load(&a.sync[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-                    int most = 0;
-                    for (int x = 0; x < kXcds; ++x) {
-                        const int o = __builtin_amdgcn_readlane(open, x);
-                        if (o > most) { most = o; victim = x; }
-                    }
-                    if (most == 0) break;
-                    int n = 0;
-                    if (lane == 0) n = __hip_atomic_fetch_add(&a.sync[victim], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    n = __builtin_amdgcn_readfirstlane(n);
-                    if (n < __builtin_amdgcn_readlane(items, victim)) {
-                        got = n;
-                        break;
-                    }
-                }
-                if (lane == 0) {
-                    handoff[1] = got;
-                    handoff[2] = victim;
-                }
-            }
-            lds_barrier();
-            const int got = __builtin_amdgcn_readfirstlane(handoff[1]);
-            from = __builtin_amdgcn_readfirstlane(handoff[2]);
-            if (got < 0) break;
-            item = members + got;
-        }
-        const int rem = left_of(from);
-        const bool leftover = item >= n_whole;
-        const int p = leftover ? parts : 1;
-        const int q = item - n_whole;  // piece number (leftover tiles only)
-        const int part = leftover ? q / rem : 0, t = leftover ? q - part * rem : item % members;
-        int round = (item / members) * kXcds + from;
-        if (!leftover) {
-            const int l0 = (int)((long)round * light_rounds / n_rounds), l1 = (int)((long)(round + 1) * light_rounds / n_rounds);
+    // round * light_rounds / n_rounds by multiplication (any spacing does that takes every light round once, in order)
+    const uint32_t light_step = n_rounds > 0 ? (uint32_t)(((uint64_t)(uint32_t)light_rounds << 32) / (uint32_t)n_rounds) + 1u : 0u;
+    auto light_before = [&](int round) { return light_rounds == n_rounds ? round : (int)__umulhi((uint32_t)round, light_step); };
+    // Item `item` of XCD `from`, see above.
+    auto decode = [&](int item, int from, typename G::Item& t) __attribute__((always_inline)) {
+        int tile_index, part = 0;
+        if (item >= n_whole) {
+            const int rem = left_of(from), q = item - n_whole;  // piece number
+            part = q / rem;
+            tile_index = first_left + from * chunk + q - part * rem;
+            t.kt_begin = uniform(KT * part / parts);
+            t.k_steps = uniform(KT * (part + 1) / parts) - t.kt_begin;
+        } else {
+            int round = item / members;
+            const int at = item - round * members;
+            round = round * kXcds + from;
+            const int l0 = light_before(round), l1 = light_before(round + 1);
             round = l1 > l0 ? heavy_rounds + ((l0 & 1) != 0 ? light_rounds - 1 - l0 / 2 : l0 / 2) : round - l0;
-        }
-        int tile_index = first_left + from * chunk + t;
-        if (!leftover) {
-            tile_index = round * members + t;
+            tile_index = round * members + at;
             if (tile_index >= first_left) tile_index += left;
+            t.kt_begin = 0;
+            t.k_steps = KT;
         }
-        int e, slot0, rows, ft, unit;
-        list.find(tile_index, e, slot0, rows, ft, unit);
-        const int kt0 = (int)((long)KT * part / p), kt1 = (int)((long)KT * (part + 1) / p);
-        // where fp32 rows go
-        float* out = static_cast<float*>(a.dst) + (size_t)slot0 * a.N + ft * G::kBF;
-        size_t out_stride = a.N;
-        if (part > 0 || G::kCut) {
-            out = a.scratch + (size_t)((G::kCut ? part : part - 1) * n_units + unit - first_unit) * kUnitFloats;
-            out_stride = 256;
+        int unit;
+        list.find(tile_index, t.e, t.slot0, t.rows, t.ft, unit);
+        t.slot0 = uniform(t.slot0);
+        t.rows = uniform(t.rows);
+        t.ft = uniform(t.ft);
+        t.from = from;
+        if constexpr (G::kFp32) {
+            t.out = static_cast<float*>(a.dst) + (size_t)t.slot0 * a.N + t.ft * G::kBF;
+            t.out_stride = (uint32_t)a.N;
+            if (part > 0 || G::kCut) {
+                t.out = a.scratch + (size_t)uniform((G::kCut ? part : part - 1) * n_units + unit - first_unit) * kUnitFloats;
+                t.out_stride = 256;
+            }
         }
-        item = members + G::tile(a.tok, a.wa, a.wb, a.row_of_slot, a.topk, a.N, a.K, static_cast<uint16_t*>(a.dst), lds, e, slot0,
-                                 rows, ft, kt0, kt1, out, out_stride, a.sync + from, a.tok_alt, a.alt_mask);
+    };
+    // The counters hand out items `members`, `members` + 1, ...; a workgroup's first one is its member number.
+    auto claim = [&](int from) __attribute__((always_inline)) {
+        int counter = from;
+        asm volatile("" : "+v"(counter));  // (at an address that the compiler knows to be uniform it reads the result at once, and waits)
+        return __hip_atomic_fetch_add(&a.sync[counter], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto settle_claim = [&](int claimed, int& item, int& from) __attribute__((always_inline)) {
+        item = members + __builtin_amdgcn_readfirstlane(claimed);
+        if (item < n_whole + left_of(from) * parts) return;
+        // That XCD's items are all handed out: go on with one of the XCD that has most left.
+        item = -1;
+        if (KT < kMinStealKSteps) return;
+        const int lane = threadIdx.x & 63;
+        const int items = lane < kXcds ? n_whole + left_of(lane) * parts - members : 0;
+        for (;;) {  // a try that loses the race has seen the victim's last item go: the sum of `open` falls every time
+            int open = lane < kXcds ? items - __hip_atomic_load(&a.sync[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+            int most = 0;
+            for (int x = 0; x < kXcds; ++x) {
+                const int o = __builtin_amdgcn_readlane(open, x);
+                if (o > most) { most = o; from = x; }
+            }
+            if (most == 0) return;
+            int n = 0;
+            if (lane == 0) n = __hip_atomic_fetch_add(&a.sync[from], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            n = __builtin_amdgcn_readfirstlane(n);
+            if (n < __builtin_amdgcn_readlane(items, from)) {
+                item = members + n;
+                return;
+            }
+        }
+    };
+    int item = member, from = xcd;
+    if (item >= n_whole + left_of(from) * parts) {
+        // (the XCD has fewer items than workgroups: this one looks elsewhere at once)
+        int* handoff = reinterpret_cast<int*>(lds);
+        if (threadIdx.x < 64) {
+            settle_claim(item - members, item, from);
+            if (threadIdx.x == 0) {
+                handoff[0] = item;
+                handoff[1] = from;
+            }
+        }
+        lds_barrier();
+        item = __builtin_amdgcn_readfirstlane(handoff[0]);
+        from = __builtin_amdgcn_readfirstlane(handoff[1]);
+        lds_barrier();  // (loads into this memory follow)
+        if (item < 0) return;
     }
+    typename G::Item first;
+    decode(item, from, first);
+    G::run(a, lds, first, claim, settle_claim, decode);
 }
 
 template <class G>
