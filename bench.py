@@ -268,20 +268,26 @@ def prefill_leg(model, T, steps, warmup, d=None):
     # bytes: each active expert's weights once, x in, y out, the bf16 intermediate written and read
     bytes_layer = active * 3.0 * H * F * 2 + 2.0 * T * H * 2 + 2.0 * A * F * 2
     t_mfma, t_hbm = flops_layer / (PEAK_BF16_TFLOPS * 1e12), bytes_layer / (PEAK_HBM_GBS * 1e9)
-    flops_gemm1 = 4.0 * A * H * F
+    # the dominant kernel: the first grouped GEMM, or in calls of middle size the one that runs both (its second GEMM reads the
+    # intermediate, one more matrix per expert, and writes fp32 rows)
+    linked = st["fused"][1] > 0
+    kernel = "linked_grouped_gemm<gemm1+swiglu, gemm2>" if linked else "grouped_gemm_bf16<gemm1+swiglu>"
+    flops_gemm1 = (6.0 if linked else 4.0) * A * H * F
     bytes_gemm1 = active * 2.0 * H * F * 2 + A * H * 2.0 + A * F * 2.0
-    g1_ms = st["gemm1"][0]
+    if linked:
+        bytes_gemm1 += active * 1.0 * H * F * 2 + A * F * 2.0 + A * H * 4.0
+    g1_ms = st["fused" if linked else "gemm1"][0]
     mfma_bound = flops_gemm1 / (PEAK_BF16_TFLOPS * 1e12) >= bytes_gemm1 / (PEAK_HBM_GBS * 1e9)
     key = f"{model}_prefill_T{T}_gemm1"
     traffic, traffic_source = read_traffic(key)
     if mfma_bound:
         ach = flops_gemm1 / (g1_ms * 1e-3) / 1e12
-        roofline = {"bound": "mfma", "kernel": "grouped_gemm_bf16<gemm1+swiglu>", "achieved": ach, "peak": PEAK_BF16_TFLOPS,
+        roofline = {"bound": "mfma", "kernel": kernel, "achieved": ach, "peak": PEAK_BF16_TFLOPS,
                     "unit": "TFLOP/s", "frac": ach / PEAK_BF16_TFLOPS, "traffic": traffic, "traffic_source": traffic_source,
                     "kernel_ms": g1_ms, "algorithmic_flops_per_launch": flops_gemm1}
     else:
         ach = bytes_gemm1 / (g1_ms * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "kernel": "grouped_gemm_bf16<gemm1+swiglu>", "achieved": ach, "peak": PEAK_HBM_GBS,
+        roofline = {"bound": "hbm", "kernel": kernel, "achieved": ach, "peak": PEAK_HBM_GBS,
                     "unit": "GB/s", "frac": ach / PEAK_HBM_GBS, "traffic": traffic, "traffic_source": traffic_source,
                     "kernel_ms": g1_ms, "algorithmic_bytes_per_launch": bytes_gemm1,
                     "frac_of_mfma_peak": flops_gemm1 / (g1_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS}

@@ -47,9 +47,11 @@
  *     other kernel (another stream, another process) occupies compute units
  *     for the duration of the call.  A workgroup whose wait runs out writes
  *     NaN into its part of y and raises a status word that moe_decode_status
- *     reads; the call itself has long returned MOE_OK by then.  (The
- *     prefill-size grouped GEMM is persistent too, but no workgroup of it
- *     ever waits for another.)
+ *     reads; the call itself has long returned MOE_OK by then.  (Longer
+ *     bf16 calls need no residency: where both of their GEMMs run in one
+ *     kernel, a workgroup waits only for tiles that running ones have taken.
+ *     That wait is bounded and reported in the same way; it can only run
+ *     out when something else writes the workspace during the call.)
  *   - Determinism: no floating-point atomics are used; two calls on the same
  *     inputs give bitwise identical outputs.  moe_layer gives bitwise the same
  *     outputs as moe_route (+ moe_predict_next) followed by moe_expert_ffn.
@@ -213,8 +215,8 @@ int moe_layer_static(const moe_shape_t* shape, int32_t tokens, const void* x, co
                      float* topk_w, int32_t* counts, int32_t accumulate, int32_t* pred_idx, void* hip_stream);
 
 /*
- * Whether a decode-size call on `workspace` gave up a rendezvous (see the
- * conventions above: bf16 calls of at most 32 tokens need the whole grid
+ * Whether a bf16 call on `workspace` gave up a rendezvous (see the
+ * conventions above: those of at most 32 tokens need the whole grid
  * resident at once; a workgroup whose bounded wait runs out stores NaN instead
  * of its part of y and raises a status word in the workspace, which stays
  * raised until it is reset).  Copies that word back: *gave_up (HOST pointer) =

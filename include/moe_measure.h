@@ -24,9 +24,10 @@ extern "C" {
  * recorded on the caller's stream between the kernels of each entry-point
  * call made by THIS thread between begin and end.  Stages: 0 routing (gate,
  * softmax, top-k, prediction), 1 counts + permutation, 2 grouped GEMM1 +
- * SwiGLU, 3 grouped GEMM2, 4 combine, 5 the single kernel that runs a bf16
- * call of at most 16 tokens (routing when the entry point routes, both
- * GEMMs, combine).  begin allocates events for up to max_calls calls (later calls
+ * SwiGLU, 3 grouped GEMM2, 4 combine, 5 a kernel that runs both GEMMs: of a bf16
+ * call of at most 16 tokens everything (routing when the entry point routes,
+ * combine), of one of at most 32 tokens the combine, and in longer calls of
+ * middle size just the two grouped GEMMs (stages 2 and 3 are not recorded then).  begin allocates events for up to max_calls calls (later calls
  * are not recorded); end synchronises with the last recorded event, writes
  * the mean milliseconds per launch of each stage and the number of launches
  * averaged (either pointer may be NULL), and frees the events.
@@ -81,9 +82,9 @@ int moe_calibrate_read_stream(const void* device_buffer, size_t bytes, float* mi
                               void* hip_stream);
 
 /*
- * Test aid: the number of polling rounds a rendezvous of the decode-size
- * kernel waits before it gives up (process-wide; default 4194304).  With 0
- * every rendezvous gives up at once, which lets a test see the failure report
+ * Test aid: the number of polling rounds that a rendezvous of the decode-size
+ * kernel, or a workgroup of a kernel that runs both grouped GEMMs, waits before
+ * it gives up (process-wide; default 4194304).  With 0 every one gives up at once, which lets a test see the failure report
  * of moe_decode_status while every kernel still runs to its end: the affected
  * calls write NaN into y and raise the status word.  Not for production use.
  * Errors: MOE_ERR_SHAPE (negative).

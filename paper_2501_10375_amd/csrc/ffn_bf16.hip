@@ -237,7 +237,7 @@ hipError_t allow_lds(Kernel k, int bytes, bool& configured) {
 // One persistent workgroup per CU (a multiple of the 8 XCDs); the kernels size their own work from `offs`.
 int persistent_grid() { return max(gg::kXcds, compute_units() / gg::kXcds * gg::kXcds); }
 
-// One of the two GEMMs.
+// One of the two GEMMs in a launch of its own.
 template <class G>
 hipError_t launch_gemm(const gg::GemmArgs& a, hipStream_t stream) {
     auto kernel = gg::grouped_gemm_kernel<G>;
@@ -248,13 +248,25 @@ hipError_t launch_gemm(const gg::GemmArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
+// Both in one.
+template <bool ALT>
+hipError_t launch_linked(const gg::GemmArgs& a, const gg::GemmArgs& b, int32_t* done, uint32_t* status, hipStream_t stream) {
+    using First = gg::Gemm<2, ALT, false, false, true>;
+    auto kernel = gg::linked_grouped_gemm_kernel<First>;
+    static bool configured = false;
+    const hipError_t e = allow_lds(kernel, First::kLdsBytes, configured);
+    if (e != hipSuccess) return e;
+    kernel<<<persistent_grid(), First::kThreads, First::kLdsBytes, stream>>>(a, b, done, status, decode_spin_limit());
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, const int32_t* topk_idx, const float* topk_w,
                            const void* w1, const void* w3, const void* w2, void* y, const int32_t* offs,
                            const int32_t* row_of_slot, const int32_t* slot_of, void* act, float* out,
-                           int32_t* sync, float* partial, const StaleInput& alt, hipStream_t stream) {
-    static_assert(gg::kXcds <= kGemmSyncInts && gg::kScratchFloats * sizeof(float) + 2 * sizeof(gg::SplitTable) <= kGemmScratchBytes,
+                           int32_t* sync, uint32_t* status, float* partial, const StaleInput& alt, hipStream_t stream) {
+    static_assert(gg::kXcds + 64 <= kGemmSyncInts && gg::kScratchFloats * sizeof(float) + 2 * sizeof(gg::SplitTable) <= kGemmScratchBytes,
                   "workspace layout");
     gg::GemmArgs g1{}, g2{};
     g1.tok = static_cast<const uint16_t*>(x);
@@ -285,21 +297,29 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
     const int routed = tokens * s.top_k;
     const long most_tiles = (long)((s.ffn + 127) / 128) * (routed / 256 + min(s.n_experts, routed));
     hipError_t e;
-    const bool wide = gg::needs_wide((size_t)tokens * s.hidden * 2, gg::Gemm<2>::kBF, s.hidden);
-    if (wide) {  // (with and without tok_alt alike: with nothing taken from it the results have the same bits)
-        e = launch_gemm<gg::Gemm<2, false, true>>(g1, stream);
-    } else if (most_tiles <= gg::kMaxCutTiles && s.hidden / 64 >= gg::kMinCutKSteps) {
-        e = alternate ? launch_gemm<gg::Gemm<2, true, false, true>>(g1, stream) : launch_gemm<gg::Gemm<2, false, false, true>>(g1, stream);
-        const int64_t threads = (int64_t)routed * (s.ffn / 4);
-        sum_swiglu_bf16<<<(unsigned)((threads + 255) / 256), 256, 0, stream>>>(partial, g1.table, offs, s.n_experts, s.ffn, routed,
-                                                                              static_cast<uint16_t*>(act));
+    const bool wide2 = gg::needs_wide(0, 256, s.ffn), wide1 = wide2 || gg::needs_wide((size_t)tokens * s.hidden * 2, gg::Gemm<2>::kBF, s.hidden);
+    const bool cut = !wide1 && most_tiles <= gg::kMaxCutTiles && s.hidden / 64 >= gg::kMinCutKSteps;
+    const bool link = !wide1 && most_tiles * 4 > persistent_grid() * 5 && (double)routed * s.hidden * s.ffn <= gg::kMaxLinkedMacs;
+    if (link) {
+        int32_t* done = sync + gg::kXcds;
+        e = alternate ? launch_linked<true>(g1, g2, done, status, stream) : launch_linked<false>(g1, g2, done, status, stream);
+        stage_mark(stream, kStageFused);
     } else {
-        e = alternate ? launch_gemm<gg::Gemm<2, true>>(g1, stream) : launch_gemm<gg::Gemm<2>>(g1, stream);
+        if (wide1) {  // (with and without tok_alt alike: with nothing taken from it the results have the same bits)
+            e = launch_gemm<gg::Gemm<2, false, true>>(g1, stream);
+        } else if (cut) {
+            e = alternate ? launch_gemm<gg::Gemm<2, true, false, true>>(g1, stream) : launch_gemm<gg::Gemm<2, false, false, true>>(g1, stream);
+            const int64_t threads = (int64_t)routed * (s.ffn / 4);
+            sum_swiglu_bf16<<<(unsigned)((threads + 255) / 256), 256, 0, stream>>>(partial, g1.table, offs, s.n_experts, s.ffn, routed,
+                                                                                  static_cast<uint16_t*>(act));
+        } else {
+            e = alternate ? launch_gemm<gg::Gemm<2, true>>(g1, stream) : launch_gemm<gg::Gemm<2>>(g1, stream);
+        }
+        stage_mark(stream, kStageGemm1);
+        if (e != hipSuccess) return e;
+        e = wide2 ? launch_gemm<gg::Gemm<1, false, true>>(g2, stream) : launch_gemm<gg::Gemm<1>>(g2, stream);
+        stage_mark(stream, kStageGemm2);
     }
-    stage_mark(stream, kStageGemm1);
-    if (e != hipSuccess) return e;
-    e = gg::needs_wide(0, 256, s.ffn) ? launch_gemm<gg::Gemm<1, false, true>>(g2, stream) : launch_gemm<gg::Gemm<1>>(g2, stream);
-    stage_mark(stream, kStageGemm2);
     if (e != hipSuccess) return e;
     const int column_blocks = (s.hidden + 2047) / 2048;
     // AHEAD up to three workgroups a CU: 720 of them (360 tokens, hidden 4096) 17.0 -> 15.1 us, 1000 to 1050 are equal (14.1; 10.5 and

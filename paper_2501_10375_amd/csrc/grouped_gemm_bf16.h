@@ -19,7 +19,9 @@
 //     LDS reads of other stages; completion is enforced by hand: s_waitcnt vmcnt(n) on the issuing
 //     wavefront, then a workgroup barrier, before any wavefront reads the stage.  One barrier per K step.
 //   * Persistent schedule, one workgroup per CU, tiles handed out in rounds per XCD so the
-//     workgroups of an XCD share operand tiles through its L2 (see persistent()).
+//     workgroups of an XCD share operand tiles through its L2 (see persistent()).  A workgroup requests the first operands of its
+//     next tile before it stores the results of the last one (see Gemm::run()).
+//   * Calls of middle size run both GEMMs in one launch (see Link).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,6 +30,11 @@
 #include <type_traits>
 
 #include "bf16_utils.h"
+#include "moe_internal.h"
+
+// Everything is compiled into its kernel: what a call would return counts as different from lane to lane.
+#define GG_INLINE __attribute__((always_inline)) inline
+#define GG_LAMBDA __attribute__((always_inline))
 
 namespace moe {
 namespace gg {
@@ -77,7 +84,7 @@ constexpr int kGroup = 8;
 
 // Sums over the lanes of a wavefront, all of them at once (a sum by itself is six LDS round trips).
 template <int N>
-__device__ inline void wave_totals(int (&v)[N]) {
+__device__ GG_INLINE void wave_totals(int (&v)[N]) {
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1)
 #pragma unroll
@@ -86,8 +93,8 @@ __device__ inline void wave_totals(int (&v)[N]) {
     for (int i = 0; i < N; ++i) v[i] = __builtin_amdgcn_readfirstlane(v[i]);
 }
 // A value that is the same in all lanes, in a scalar register.
-__device__ inline int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ inline int wave_inclusive_sum(int v) {
+__device__ GG_INLINE int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ GG_INLINE int wave_inclusive_sum(int v) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int d = 1; d < 64; d *= 2) {
@@ -105,7 +112,7 @@ struct TileList {
     int expert, count, first_slot, first_tile;
     int units, first_unit;    // units of 32 rows of all tiles, and before an expert's (count_units())
 
-    __device__ TileList(const int32_t* __restrict__ offs, int E, int n_ftiles) : n_ft(n_ftiles) {
+    __device__ GG_INLINE TileList(const int32_t* __restrict__ offs, int E) {
         const int lane = threadIdx.x & 63;
         const int o = lane < E ? offs[lane] : 0;
         const int c = lane < E ? offs[lane + 1] - o : -1;
@@ -114,18 +121,18 @@ struct TileList {
             const int ci = __builtin_amdgcn_readlane(c, i);
             if (lane < E) rank += (ci > c || (ci == c && i < lane)) ? 1 : 0;
         }
-        units = first_unit = 0;
+        n_ft = slots = total = heavy = first_tile = units = first_unit = 0;
         expert = __builtin_amdgcn_ds_permute(rank * 4, lane);
         count = __builtin_amdgcn_ds_permute(rank * 4, c);
         first_slot = __builtin_amdgcn_ds_permute(rank * 4, o);
     }
 
-    static __device__ int units_of(int rows) { return rows > 0 ? (rows + kUnitRows - 1) / kUnitRows : 0; }
+    static __device__ GG_INLINE int units_of(int rows) { return rows > 0 ? (rows + kUnitRows - 1) / kUnitRows : 0; }
 
     // Slot tiles of `s` rows of this lane's expert.
-    __device__ int slot_tiles(int s) const { return count > 0 ? (count + s - 1) / s : 0; }
+    __device__ GG_INLINE int slot_tiles(int s) const { return count > 0 ? (count + s - 1) / s : 0; }
 
-    __device__ void build(int slots_per_tile) {
+    __device__ GG_INLINE void build(int slots_per_tile) {
         slots = slots_per_tile;
         const int tiles = slot_tiles(slots) * n_ft;
         const int tile_sum = wave_inclusive_sum(tiles);
@@ -135,16 +142,16 @@ struct TileList {
         heavy = n_heavy > 0 ? __builtin_amdgcn_readlane(tile_sum, n_heavy - 1) : 0;
     }
 
-    __device__ void count_units() {
+    __device__ GG_INLINE void count_units() {
         const int own = units_of(count) * n_ft;
         const int sum = wave_inclusive_sum(own);
         first_unit = sum - own;
         units = __builtin_amdgcn_readlane(sum, 63);
     }
 
-    // Tile `id`, and the units of the tiles before it (valid after count_units()).
-    __device__ void find(int id, int& e, int& slot0, int& rows, int& ft, int& unit) const {
-        const int r = __popcll(__ballot(first_tile <= id && count > 0)) - 1;
+    // Tile `id` (r: its expert's rank), and the units of the tiles before it (valid after count_units()).
+    __device__ GG_INLINE void find(int id, int& r, int& e, int& slot0, int& rows, int& ft, int& unit) const {
+        r = __popcll(__ballot(first_tile <= id && count > 0)) - 1;
         const int c = __builtin_amdgcn_readlane(count, r);
         e = __builtin_amdgcn_readlane(expert, r);
         const int local = id - __builtin_amdgcn_readlane(first_tile, r);
@@ -166,14 +173,14 @@ struct TileList {
         unit = __builtin_amdgcn_readlane(first_unit, r) + local * (slots / kUnitRows) - (from + gs == mt ? ft * units_missing(c, mt, slots) : 0);
     }
     // What the last slot tile of an expert of c rows lacks of slots / 32 units.
-    static __device__ int units_missing(int c, int mt, int slots) { return slots / kUnitRows - units_of(c - (mt - 1) * slots); }
+    static __device__ GG_INLINE int units_missing(int c, int mt, int slots) { return slots / kUnitRows - units_of(c - (mt - 1) * slots); }
 
     // Inverse of find() within an expert of c rows: where slot tile m stands, number and units before it at feature tile 0, and
     // what each further feature tile adds.
     struct Place {
         int tile, tile_step, unit, unit_step;
     };
-    static __device__ Place place(int c, int slots, int n_ft, int m) {
+    static __device__ GG_INLINE Place place(int c, int slots, int n_ft, int m) {
         const int mt = (c + slots - 1) / slots;
         const int groups = (mt + kGroup - 1) / kGroup;
         const int size = mt / groups, big = mt - size * groups;
@@ -200,20 +207,35 @@ struct GemmArgs {
 };
 
 template <int N>
-__device__ inline void wait_vmcnt() {
+__device__ GG_INLINE void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
+// Waits for all but the `stores` (2, 4, ..., 16) and eight loads that were issued last.
+__device__ GG_INLINE void wait_stores(int stores) {
+    switch (stores) {
+        case 2: wait_vmcnt<10>(); break;
+        case 4: wait_vmcnt<12>(); break;
+        case 6: wait_vmcnt<14>(); break;
+        case 8: wait_vmcnt<16>(); break;
+        case 10: wait_vmcnt<18>(); break;
+        case 12: wait_vmcnt<20>(); break;
+        case 14: wait_vmcnt<22>(); break;
+        case 16: wait_vmcnt<24>(); break;
+        default: wait_vmcnt<8>(); break;
+    }
+}
+
 // Workgroup barrier that orders LDS traffic only (no wait on outstanding global loads).
-__device__ inline void lds_barrier() {
+__device__ GG_INLINE void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Orders a wavefront's own LDS traffic (which the hardware does by itself; this is for the compiler).
-__device__ inline void wave_order() {
+__device__ GG_INLINE void wave_order() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
@@ -223,7 +245,49 @@ __device__ inline void wave_order() {
 // swizzled(row, chunk) of that row.  The LDS has 64 four-byte banks (256 bytes per cycle), so a
 // ds_read_b128 serves 16 lanes per cycle; the lanes of one MFMA operand read sit on 16
 // consecutive rows at the same chunk, and the XOR below spreads them over all 64 banks.
-__device__ inline int swizzled(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
+__device__ GG_INLINE int swizzled(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
+
+// Both GEMMs in one launch (LINKED): a workgroup that finds no more tiles of the first GEMM goes on with the second one's, so neither
+// the workgroups that end the first early nor the next kernel's start cost anything.  A tile of the second GEMM needs all of its
+// expert's tiles of the first: `done` counts those per expert, and a workgroup looks at it before it requests the tile's first
+// slot rows (its weights are on their way by then).  act is stored through to memory, a tile is counted when all of its stores
+// have been acknowledged, and act is not read by anybody in this launch before that, so that no cache can hold an older copy.
+//
+// A workgroup only waits for tiles that others have already taken, and they wait for nobody in the first GEMM: in every XCD's list and,
+// when that is empty, the others', there is no tile left when it goes on.  So the wait ends whatever part of the grid is
+// resident.  It is bounded all the same (memory that an overlapping call clears must not hang the GPU): when it runs out
+// the status word is raised and the tile's results are NaN.
+//
+// Which calls: those whose first GEMM has more than five quarters of a round of tiles (with about one there is nothing to fill, and handing act
+// over costs 3 to 8 us: hidden 3584, ffn 1088, 2000 tokens 143 us apart / 151 linked; hidden and ffn 2048, 16 experts, 500 tokens, 1.1
+// rounds 137 / 139; 1.4 rounds, hidden 4096, ffn 2048, 1000 tokens 203 / 200) and at most 1.6e11 products of a routed row and a weight.  Beyond, the chip is at its power
+// limit, where time that is saved comes back as clock that is lost, and workgroups that enter the second GEMM at different times share
+// fewer lines of its tall tiles.  Whole layer, apart / linked: Mixtral shape 200 tokens 526 / 511 us, 512 616 / 593, 1024 776 / 764,
+// but 1400 (1.64e11) 932 / 945, 2048 1214 / 1235; Phi shape 700 tokens 481 / 474, 2048 757 / 749, 3500 1037 / 1024, 6000 1622 / 1624; 64 experts of
+// hidden 2048 and ffn 1408, 1003 tokens 276 / 269, 3000 429 / 413; hidden 3008, ffn 5632, 12 experts, 200 tokens 290 / 261.
+constexpr double kMaxLinkedMacs = 1.6e11;
+struct Link {
+    int32_t* done;       // tiles of the first GEMM that are stored, per expert (null: not linked)
+    uint32_t* status;
+    int spin_limit;
+    int need, expert;    // lane r: of the expert of rank r
+    uint64_t ready;      // ranks whose act is complete
+    bool gave_up;
+
+    __device__ GG_INLINE void finish(int e) { __hip_atomic_fetch_add(&done[e], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ GG_INLINE void await(int rank) {
+        for (int n = 0; (ready >> rank & 1) == 0; ++n) {
+            if (n == spin_limit) {
+                if (threadIdx.x == 0) __hip_atomic_store(status, kDecodeGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                gave_up = true;
+                break;
+            }
+            if (n > 0) __builtin_amdgcn_s_sleep(8);
+            ready = __ballot(need == 0 || __hip_atomic_load(&done[expert], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= need);
+        }
+        asm volatile("" ::: "memory");
+    }
+};
 
 // ---- one tile: up to 256 slots x 256 weight rows, one wavefront per SIMD.
 //
@@ -259,11 +323,13 @@ __device__ inline int swizzled(int row, int chunk) { return chunk ^ ((row >> 1) 
 // lane offset does not reach: x of kWideBytes or more, or a tile of weight or slot rows of that size (see needs_wide()).
 // CUT (first GEMM): every tile is cut along K, see choose_cut(); the sums of both matrices go to the scratch memory in fp32, 128
 // columns of each side by side, and another kernel adds the pieces and applies SwiGLU.
-template <int NMAT, bool ALT = false, bool WIDE = false, bool CUT = false>
+// LINKED: both GEMMs run in one kernel, see Link.
+template <int NMAT, bool ALT = false, bool WIDE = false, bool CUT = false, bool LINKED = false>
 struct Gemm {
     static_assert(!(ALT && WIDE) && (!ALT || NMAT == 2), "only the first GEMM gathers rows of x");
     static_assert(!CUT || (NMAT == 2 && !WIDE), "the second GEMM cuts by itself");
-    static constexpr bool kCut = CUT, kFp32 = NMAT == 1 || CUT;
+    static_assert(!LINKED || (!WIDE && !CUT), "the other versions run in kernels of their own");
+    static constexpr bool kLinked = LINKED, kCut = CUT, kFp32 = NMAT == 1 || CUT;
     static constexpr int kThreads = 256, kMats = NMAT;
     static constexpr int kBF = 256 / NMAT;            // features per tile (per matrix)
     static constexpr int kF = 8;                      // 16-row fragments of each operand per wavefront
@@ -277,13 +343,13 @@ struct Gemm {
     using No = std::false_type;
 
     // M0 (the LDS address of the load that follows in a later slot; nothing in the loop writes it in between) ...
-    static __device__ inline void set_lds_target(uint32_t lds_base) { asm volatile("s_mov_b32 m0, %0" ::"s"(lds_base) : "memory"); }
+    static __device__ GG_INLINE void set_lds_target(uint32_t lds_base) { asm volatile("s_mov_b32 m0, %0" ::"s"(lds_base) : "memory"); }
     // ... and the load itself: 16 bytes per lane from base + lane offset + scalar offset to M0 + lane * 16.
-    static __device__ inline void load_lane(u32x4 base, uint32_t lane_off, uint32_t off) {
+    static __device__ GG_INLINE void load_lane(u32x4 base, uint32_t lane_off, uint32_t off) {
         asm volatile("buffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(lane_off), "s"(base), "s"(off) : "memory");
     }
-    static __device__ inline void load_word(const char* p) { asm volatile("global_load_lds_dword %0, off" ::"v"(p) : "memory"); }
-    static __device__ inline void load_ptr(const char* p) { asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(p) : "memory"); }
+    static __device__ GG_INLINE void load_word(const char* p) { asm volatile("global_load_lds_dword %0, off" ::"v"(p) : "memory"); }
+    static __device__ GG_INLINE void load_ptr(const char* p) { asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(p) : "memory"); }
     // acc += a . b with the accumulator in AGPRs, in place.  (From the builtin, in a kernel with as many loops as this
     // one, the compiler gives the result another register than the operand and then spends the loop moving accumulators
     // between the two halves of the register file: 340 moves per 128 MFMAs.)  The compiler waits for the LDS reads of a
@@ -292,28 +358,29 @@ struct Gemm {
     // place by pin(): asm statements keep their order among each other, but an access to a register that they don't name may
     // cross them.  What C++ cannot forbid is that the compiler moves a register between two MFMAs;
     // tests/test_isa_hazards.py reads the built kernels for that.
-    static __device__ inline void mfma_acc(f32x4& acc, bf16x8 a, bf16x8 b) {
+    static __device__ GG_INLINE void mfma_acc(f32x4& acc, bf16x8 a, bf16x8 b) {
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
     }
-    static __device__ inline void settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }  // 19 wait states at most
+    static __device__ GG_INLINE void settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }  // 19 wait states at most
     // Every write of the accumulators above this comes before it, every use below it after.
     template <int TFE>
-    static __device__ inline void pin(f32x4 (&acc)[kF][TFE]) {
+    static __device__ GG_INLINE void pin(f32x4 (&acc)[kF][TFE]) {
 #pragma unroll
         for (int j = 0; j < kF; ++j)
 #pragma unroll
             for (int i = 0; i < TFE; ++i) asm volatile("" : "+a"(acc[j][i]));
     }
     // An accumulator element.  (Read where it is used: left to the compiler, all 256 are copied to VGPRs at once.)
-    static __device__ inline float from_acc(float a) {
+    static __device__ GG_INLINE float from_acc(float a) {
         float v;
         asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
         return v;
     }
-    static __device__ inline void wait_state() { asm volatile("s_nop 0" ::: "memory"); }
+    static constexpr int kWriteThrough = 16;  // cache policy bit sc1
+    static __device__ GG_INLINE void wait_state() { asm volatile("s_nop 0" ::: "memory"); }
 
     // Buffer descriptor of the memory from `p` on (wave-uniform), without a bound of its own.
-    static __device__ inline u32x4 descriptor(const void* p) {
+    static __device__ GG_INLINE u32x4 descriptor(const void* p) {
         const uint64_t a = reinterpret_cast<uint64_t>(p);
         u32x4 d;
         d[0] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
@@ -325,7 +392,7 @@ struct Gemm {
 
     // One work item: a tile, or a piece of one.
     struct Item {
-        int e, slot0, rows, ft, kt_begin, k_steps;
+        int rank, e, slot0, rows, ft, kt_begin, k_steps;
         float* out;          // where fp32 rows go
         uint32_t out_stride;
         int from;            // XCD whose list it is from
@@ -342,8 +409,8 @@ struct Gemm {
     // tile cost 6 us more than its K steps, 3 now.  While all CUs stream, others use the bandwidth meanwhile: whole layer, Phi shape, 200
     // tokens 381 -> 368 us, 64 experts of hidden 2048 and ffn 1408, 3000 tokens 437 -> 429, Mixtral shape 512 to 4096 tokens 0.3 to 0.7 %.)
     template <class Claim, class SettleClaim, class Decode>
-    static __device__ inline void run(const GemmArgs& a, unsigned char* lds, Item cur, const Claim& claim, const SettleClaim& settle_claim,
-                                      const Decode& decode) {
+    static __device__ GG_INLINE void run(const GemmArgs& a, unsigned char* lds, Item cur, const Claim& claim, const SettleClaim& settle_claim,
+                                      const Decode& decode, Link& link) {
         const int N = a.N, K = a.K;
         const lds_ptr lds3 = (lds_ptr)lds;
         const uint32_t lds0 = (uint32_t)(uintptr_t)lds3;
@@ -351,7 +418,7 @@ struct Gemm {
         const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
         const int wt = wave & 1, wq = wave >> 1;      // slot group, weight-row group
         const uint32_t wave_lds = lds0 + (uint32_t)wave * 1024;
-        auto next_w = [](uint32_t s) { return s == 2 * kStage ? 0u : s + kStage; };
+        auto next_w = [](uint32_t s) GG_LAMBDA { return s == 2 * kStage ? 0u : s + kStage; };
 
         // ---- staging: load q of wavefront w covers rows q * 32 + w * 8 .. + 7 of an operand tile, lane l the 16-byte
         // piece that belongs at position l % 8 of row l / 8 (see swizzled(); the same for every q).
@@ -361,15 +428,15 @@ struct Gemm {
         const char* w_ptr[WIDE ? 8 : 1];
         uint32_t s_off[WIDE || ALT ? 1 : 8];
         const char* s_ptr[WIDE || ALT ? 8 : 1];
-        auto weight_load = [&](int q, uint32_t k_off) __attribute__((always_inline)) {
+        auto weight_load = [&](int q, uint32_t k_off) GG_LAMBDA {
             if constexpr (WIDE) load_ptr(w_ptr[q] + k_off);
             else load_lane(NMAT == 2 && q >= 4 ? base_b : base_a, w_off[q % kWOffs], k_off);
         };
-        auto slot_load = [&](int q, uint32_t k_off) __attribute__((always_inline)) {
+        auto slot_load = [&](int q, uint32_t k_off) GG_LAMBDA {
             if constexpr (WIDE || ALT) load_ptr(s_ptr[q] + k_off);
             else load_lane(base_s, s_off[q], k_off);
         };
-        auto weight_stage = [&](uint32_t stage, uint32_t k_off) __attribute__((always_inline)) {
+        auto weight_stage = [&](uint32_t stage, uint32_t k_off) GG_LAMBDA {
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 set_lds_target(wave_lds + stage + q * 4096);
@@ -377,7 +444,7 @@ struct Gemm {
                 weight_load(q, k_off);
             }
         };
-        auto slot_stage0 = [&](const Item& t) __attribute__((always_inline)) {
+        auto slot_stage0 = [&](const Item& t) GG_LAMBDA {
             const int groups = (t.rows + 31) / 32;
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
@@ -389,7 +456,7 @@ struct Gemm {
         };
         // First requests of an item: the row numbers of its slots (first GEMM), which go to the weight stage `w0` + 2 (not used
         // before its third K step), and its first weights, into stage w0.  The second GEMM's slot rows are consecutive rows: the first ones go out as well.
-        auto request_first = [&](const Item& t, uint32_t w0) __attribute__((always_inline)) {
+        auto request_first = [&](const Item& t, uint32_t w0) GG_LAMBDA {
             int tid = threadIdx.x;
             asm volatile("" : "+v"(tid));
             const int lane = tid & 63;
@@ -424,11 +491,12 @@ struct Gemm {
                     else
                         s_off[q] = (uint32_t)r * row_bytes + (uint32_t)chunk * 16;
                 }
+                if constexpr (LINKED) link.await(t.rank);
                 slot_stage0(t);
             }
         };
         // First GEMM: looks the slot rows up and requests those of the first K step.  At most eight loads (the weights) are younger than the row numbers.
-        auto request_slots = [&](const Item& t, uint32_t w0) __attribute__((always_inline)) {
+        auto request_slots = [&](const Item& t, uint32_t w0) GG_LAMBDA {
             if constexpr (NMAT == 2) {
                 int tid = threadIdx.x;
                 asm volatile("" : "+v"(tid));
@@ -462,6 +530,7 @@ struct Gemm {
         };
 
         uint32_t w0 = 0;  // weight stage of an item's first K step
+        int finished = -1, stores = 0;  // first GEMM, LINKED: expert of the item before this one, and its stores
         request_first(cur, w0);
         request_slots(cur, w0);
         for (;;) {
@@ -472,13 +541,17 @@ struct Gemm {
         const int lane = tid & 63;
         const int KT = cur.k_steps;
         const uint32_t k_first = (uint32_t)cur.kt_begin * 128;
+        bool counted = !(LINKED && NMAT == 2) || KT <= 2;
         if (KT > 1) {
             weight_stage(next_w(w0), k_first + 128);
-            wait_vmcnt<8>();
+            if (counted) wait_vmcnt<8>();
+            else wait_stores(stores);  // the first item's stores go through to memory: not waited for before the first K step
         } else {
             wait_vmcnt<0>();
         }
         lds_barrier();
+        if constexpr (LINKED && NMAT == 2)
+            if (counted && tid == 0 && finished >= 0) link.finish(finished);
 
         // ---- operand fragments: 16 rows x 32 K elements, lane l holds row l % 16, piece l / 16 of the half K step.
         // Row r, piece p sits at r * 128 + ((p ^ ((r >> 1) & 7)) << 4): fragments are 2048 bytes apart (the swizzle
@@ -496,7 +569,7 @@ struct Gemm {
         // The whole tile for TFE valid 32-slot groups.  Everything from the accumulators to the stores is inside, so
         // that the eight versions have no code in common behind their loops (where they join, the compiler would have
         // to agree on registers for 256 accumulators and spills instead).
-        auto tile = [&](auto tfe_c) __attribute__((always_inline)) {
+        auto tile = [&](auto tfe_c) GG_LAMBDA {
             constexpr int TFE = decltype(tfe_c)::value;
             f32x4 acc[kF][TFE];  // [weight fragment][slot fragment]
 #pragma unroll
@@ -512,7 +585,7 @@ struct Gemm {
             // at w_stage / s_stage into buffer 1 - mbuf, and the loads of one operand (LOADS 1: TFE slot loads, 2: 8
             // weight loads) for a later K step.
             auto half_step = [&](auto mfma, auto mbuf_c, auto read, int half, uint32_t w_stage, uint32_t s_stage, auto loads,
-                                 uint32_t target, uint32_t k_off) __attribute__((always_inline)) {
+                                 uint32_t target, uint32_t k_off) GG_LAMBDA {
                 constexpr int mbuf = decltype(mbuf_c)::value, rbuf = 1 - mbuf;
                 constexpr int LOADS = decltype(loads)::value;
                 constexpr int n_loads = LOADS == 1 ? TFE : LOADS == 2 ? 8 : 1;
@@ -568,7 +641,7 @@ struct Gemm {
                 }
             }
             uint32_t k_off = k_first + 256;                    // of K step kt + 2
-            auto k_step = [&](auto more) __attribute__((always_inline)) {  // second half of K step kt, first half of K step kt + 1
+            auto k_step = [&](auto more) GG_LAMBDA {  // second half of K step kt, first half of K step kt + 1
                 const uint32_t w1 = next_w(w_stage), w2 = next_w(w1), s1 = s_stage ^ kStage;
                 // Stage w2 held K step kt - 1, which every wavefront had read before the last barrier.
                 half_step(Yes{}, Buf0{}, Yes{}, 1, w_stage, s_stage, std::conditional_t<decltype(more)::value, Weights, None>{},
@@ -584,7 +657,16 @@ struct Gemm {
                 s_stage = s1;
                 k_off += 128;
             };
-            for (int kt = 0; kt + 2 < KT; ++kt) k_step(Yes{});
+            int kt = 0;
+            for (int until = counted ? KT - 2 : 1;;) {
+                for (; kt < until; ++kt) k_step(Yes{});
+                if (counted) break;
+                // The stores of the item before were older than what the first K step has waited for, in every wavefront.
+                if constexpr (LINKED && NMAT == 2)
+                    if (tid == 0 && finished >= 0) link.finish(finished);
+                counted = true;
+                until = KT - 2;
+            }
             // The next item is claimed now; the answer is needed after the last K step.
             int claimed = 0;
             if (tid == 0) claimed = claim(cur.from);
@@ -594,6 +676,10 @@ struct Gemm {
             settle();
             pin(acc);
 
+            if constexpr (LINKED && NMAT == 2) {
+                finished = cur.e;
+                stores = 2 * TFE;
+            }
             // ---- the next item: its number and list in the weight stage that the last two K steps did not use
             const uint32_t handoff = next_w(w_stage);
             asm volatile("" ::"v"(claimed));  // (every wavefront waits here: where the answer may be outstanding, the main loop gets waits for it)
@@ -620,6 +706,8 @@ struct Gemm {
             if constexpr (NMAT == 2 && !CUT) {
                 // [up to 64 slots][64 features] bf16, 128-byte rows, unit v of row r at position v ^ ((r >> 1) & 7)
                 const int n = n0 + wq * 64 + (lane & 7) * 8;
+                const __amdgpu_buffer_rsrc_t act_rows = __builtin_amdgcn_make_buffer_rsrc(
+                    static_cast<uint16_t*>(a.dst) + (size_t)cur.slot0 * N, 0, (int)((uint32_t)cur.rows * N * 2u), 0x00020000);
 #pragma unroll
                 for (int i4 = 0; i4 < TFE; i4 += 4) {
 #pragma unroll
@@ -646,7 +734,9 @@ struct Gemm {
                             const int lr = (i - i4) * 16 + h * 8 + (lane >> 3);
                             const int row = (2 * i + wt) * 16 + h * 8 + (lane >> 3);
                             const u32x4 v = *reinterpret_cast<const u32x4*>(own + lr * 128 + (((lane & 7) ^ ((lr >> 1) & 7)) << 4));
-                            if (row < cur.rows && n < N)
+                            if constexpr (LINKED)  // (always issued, see wait_stores(): what does not exist lies past the end of the buffer)
+                                __builtin_amdgcn_raw_buffer_store_b128(v, act_rows, n < N ? ((uint32_t)row * N + n) * 2u : ~15u, 0, kWriteThrough);
+                            else if (row < cur.rows && n < N)
                                 *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.dst) + (size_t)(cur.slot0 + row) * N + n) = v;
                         }
                     wave_order();
@@ -673,7 +763,9 @@ struct Gemm {
                     for (int h = 0; h < 8; ++h) {
                         const int lr = h * 2 + (lane >> 5);
                         const int row = (2 * i + wt) * 16 + lr;
-                        const f32x4 v = *reinterpret_cast<const f32x4*>(own + lr * 512 + ((unit ^ lr) << 4));
+                        f32x4 v = *reinterpret_cast<const f32x4*>(own + lr * 512 + ((unit ^ lr) << 4));
+                        if constexpr (LINKED)
+                            if (link.gave_up) v = f32x4{NAN, NAN, NAN, NAN};
                         if (row < cur.rows && stores) *reinterpret_cast<f32x4*>(cur.out + (size_t)row * cur.out_stride + col) = v;
                     }
                     wave_order();
@@ -690,8 +782,13 @@ struct Gemm {
             case 7: tile(std::integral_constant<int, 7>{}); break;
             default: tile(std::integral_constant<int, 8>{}); break;
         }
-        if (!more_items) return;
+        if (!more_items) break;
         cur = next;
+        }
+        if constexpr (LINKED && NMAT == 2) {
+            wait_vmcnt<0>();
+            lds_barrier();  // (and nobody reads the last item's number any more)
+            if (threadIdx.x == 0) link.finish(finished);
         }
     }
 };
@@ -716,7 +813,7 @@ constexpr bool needs_wide(size_t gathered, size_t tile_rows, size_t k_elements) 
 // steps or more a part, as it was: 4.4 % and 46 %; Phi shape, 200 tokens, 152 + 12 us in four parts where 131 + 6 is had in one;
 // 16 experts, hidden 640, ffn 1728, 627 tokens: 34 -> 23 us.)  The lanes do it side by side because 30 prices one after the
 // other take 2 us.
-__device__ inline void choose_plan(const TileList& list, int N, int KT, int members, int& slots, int& parts) {
+__device__ GG_INLINE void choose_plan(const TileList& list, int N, int KT, int members, int& slots, int& parts) {
     static_assert(kMaxParts == 6, "30 plans");
     const int lane = threadIdx.x & 63;
     const int i = min(lane / 6, 4), p = lane - lane / 6 * 6 + 1, s = 256 - 32 * i;
@@ -757,7 +854,7 @@ constexpr int kMaxCutParts = 8;
 // rows, which as they are stream at 4 TB/s, 70 / 79, 128 of 32 36 / 38, 64 of 16 20 / 21, 32 of 16 15 / 17.
 constexpr int kMaxCutTiles = 96, kMinCutKSteps = 24;
 
-__device__ inline void choose_cut(const TileList& list, int N, int KT, int members, int& parts) {
+__device__ GG_INLINE void choose_cut(const TileList& list, int N, int KT, int members, int& parts) {
     const int p = (threadIdx.x & 63) + 1;
     const int most_rows = __builtin_amdgcn_readlane(list.count, 0);
     const int active = __popcll(__ballot(list.count > 0));
@@ -811,13 +908,13 @@ __device__ inline void choose_cut(const TileList& list, int N, int KT, int membe
 // 64-expert shape at 1003 tokens, first GEMM 100.5 -> 103 us with it.  Between 32 and 64 K steps it does not matter (eight
 // shapes, hidden and ffn 2048 to 3584: within 2 % either way).  With 64 and 100 of the Phi shape, 700 tokens, 523 -> 509 us; 64 and
 // 224 of the Mixtral shape, 512 tokens, 630 -> 625, 4096 tokens, both GEMMs, 2168 -> 2164.
+// Returns the slots per tile.
 template <class G>
-__device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
-    TileList list(a.offs, a.E, (a.N + G::kBF - 1) / G::kBF);
+__device__ GG_INLINE int persistent(const GemmArgs& a, unsigned char* lds, TileList list, Link& link) {
+    list.n_ft = (a.N + G::kBF - 1) / G::kBF;
     const int KT = a.K / 64;
     const int xcd = blockIdx.x % kXcds, member = blockIdx.x / kXcds;
     const int members = min((int)gridDim.x / kXcds, kMaxWgsPerXcd);
-    if (member >= members) return;
     const int per_super_round = kXcds * members;
     int slots = 256, parts = 1;
     if constexpr (G::kMats == 1) choose_plan(list, a.N, KT, members, slots, parts);
@@ -845,11 +942,11 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     const int first_left = amid ? list.heavy - (int)((long)left * list.heavy / total) : total - left;
     int first_unit = 0, n_units = 0;  // of the leftover tiles
     if (parts > 1 || G::kCut) {
-        int e, slot0, rows, ft;
+        int r, e, slot0, rows, ft;
         list.count_units();
-        list.find(first_left, e, slot0, rows, ft, first_unit);
+        list.find(first_left, r, e, slot0, rows, ft, first_unit);
         n_units = list.units;
-        if (first_left + left < total) list.find(first_left + left, e, slot0, rows, ft, n_units);
+        if (first_left + left < total) list.find(first_left + left, r, e, slot0, rows, ft, n_units);
         n_units -= first_unit;
     }
     if ((G::kMats == 1 || G::kCut) && blockIdx.x == 0 && threadIdx.x < 64) {
@@ -869,16 +966,16 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
     }
     // Work items of an XCD in hand-out order: its whole tiles, then the pieces of its leftover tiles.
     const int n_whole = full_rounds * members;
-    auto left_of = [&](int x) { return max(0, min(left, (x + 1) * chunk) - x * chunk); };
+    auto left_of = [&](int x) GG_LAMBDA { return max(0, min(left, (x + 1) * chunk) - x * chunk); };
     // rounds of `members` whole tiles that lie in the heavy part of the list / in the rest
     const int n_rounds = full_rounds * kXcds;
     const int heavy_rounds = min(n_rounds, min(list.heavy, first_left) / members);
     const int light_rounds = n_rounds - heavy_rounds;
     // round * light_rounds / n_rounds by multiplication (any spacing does that takes every light round once, in order)
     const uint32_t light_step = n_rounds > 0 ? (uint32_t)(((uint64_t)(uint32_t)light_rounds << 32) / (uint32_t)n_rounds) + 1u : 0u;
-    auto light_before = [&](int round) { return light_rounds == n_rounds ? round : (int)__umulhi((uint32_t)round, light_step); };
+    auto light_before = [&](int round) GG_LAMBDA { return light_rounds == n_rounds ? round : (int)__umulhi((uint32_t)round, light_step); };
     // Item `item` of XCD `from`, see above.
-    auto decode = [&](int item, int from, typename G::Item& t) __attribute__((always_inline)) {
+    auto decode = [&](int item, int from, typename G::Item& t) GG_LAMBDA {
         int tile_index, part = 0;
         if (item >= n_whole) {
             const int rem = left_of(from), q = item - n_whole;  // piece number
@@ -898,7 +995,7 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
             t.k_steps = KT;
         }
         int unit;
-        list.find(tile_index, t.e, t.slot0, t.rows, t.ft, unit);
+        list.find(tile_index, t.rank, t.e, t.slot0, t.rows, t.ft, unit);
         t.slot0 = uniform(t.slot0);
         t.rows = uniform(t.rows);
         t.ft = uniform(t.ft);
@@ -913,17 +1010,17 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
         }
     };
     // The counters hand out items `members`, `members` + 1, ...; a workgroup's first one is its member number.
-    auto claim = [&](int from) __attribute__((always_inline)) {
+    auto claim = [&](int from) GG_LAMBDA {
         int counter = from;
         asm volatile("" : "+v"(counter));  // (at an address that the compiler knows to be uniform it reads the result at once, and waits)
         return __hip_atomic_fetch_add(&a.sync[counter], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    auto settle_claim = [&](int claimed, int& item, int& from) __attribute__((always_inline)) {
+    auto settle_claim = [&](int claimed, int& item, int& from) GG_LAMBDA {
         item = members + __builtin_amdgcn_readfirstlane(claimed);
         if (item < n_whole + left_of(from) * parts) return;
         // That XCD's items are all handed out: go on with one of the XCD that has most left.
         item = -1;
-        if (KT < kMinStealKSteps) return;
+        if (KT < kMinStealKSteps && !(G::kLinked && G::kMats == 2)) return;
         const int lane = threadIdx.x & 63;
         const int items = lane < kXcds ? n_whole + left_of(lane) * parts - members : 0;
         for (;;) {  // a try that loses the race has seen the victim's last item go: the sum of `open` falls every time
@@ -958,17 +1055,33 @@ __device__ inline void persistent(const GemmArgs& a, unsigned char* lds) {
         item = __builtin_amdgcn_readfirstlane(handoff[0]);
         from = __builtin_amdgcn_readfirstlane(handoff[1]);
         lds_barrier();  // (loads into this memory follow)
-        if (item < 0) return;
+        if (item < 0) return slots;
     }
     typename G::Item first;
     decode(item, from, first);
-    G::run(a, lds, first, claim, settle_claim, decode);
+    G::run(a, lds, first, claim, settle_claim, decode, link);
+    return slots;
 }
 
 template <class G>
 __global__ __launch_bounds__(G::kThreads, 1) void grouped_gemm_kernel(GemmArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_dyn[];
-    persistent<G>(a, lds_dyn);
+    if ((int)blockIdx.x / kXcds >= min((int)gridDim.x / kXcds, kMaxWgsPerXcd)) return;
+    Link link{};
+    persistent<G>(a, lds_dyn, TileList(a.offs, a.E), link);
+}
+
+// Both GEMMs, see Link.  First: Gemm<2, ALT, false, false, true>.
+template <class First>
+__global__ __launch_bounds__(First::kThreads, 1) void linked_grouped_gemm_kernel(GemmArgs a, GemmArgs b, int32_t* done, uint32_t* status, int spin_limit) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds_dyn[];
+    if ((int)blockIdx.x / kXcds >= min((int)gridDim.x / kXcds, kMaxWgsPerXcd)) return;
+    const TileList list(a.offs, a.E);
+    Link link{done, status, spin_limit, 0, 0, 0, false};
+    const int slots = persistent<First>(a, lds_dyn, list, link);
+    link.need = list.slot_tiles(slots) * ((a.N + First::kBF - 1) / First::kBF);
+    link.expert = list.count > 0 ? list.expert : 0;
+    persistent<Gemm<1, false, false, false, true>>(b, lds_dyn, list, link);
 }
 
 }  // namespace gg

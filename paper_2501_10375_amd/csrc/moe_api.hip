@@ -214,7 +214,7 @@ hipError_t run_ffn(const moe_shape_t& s, int tokens, const void* x, const int32_
                               static_cast<const float*>(w3), static_cast<const float*>(w2), static_cast<float*>(y),
                               ws.offs, ws.row_of_slot, ws.slot_of, static_cast<float*>(ws.act), ws.out, alt, stream);
     return launch_ffn_bf16(s, tokens, x, idx, w, w1, w3, w2, y, ws.offs, ws.row_of_slot, ws.slot_of, ws.act, ws.out,
-                           ws.sync, ws.partial, alt, stream);
+                           ws.sync, ws.dec_flags + kDecodeStatusWord, ws.partial, alt, stream);
 }
 
 // Expert execution on a carved workspace from selections made earlier (arguments already checked).

@@ -82,8 +82,8 @@ hipError_t launch_hist_from_idx(const moe_shape_t& s, int tokens, const int32_t*
 // Sum block histograms into counts (counts may be null), and when
 // row_of_slot/slot_of are given build offs and the stable token->expert
 // permutation.
-// Counters of the persistent grouped GEMMs (see grouped_gemm_bf16.h): per launch 8 tile hand-out counters, one per XCD, on
-// cache lines of their own.  (With this block the smallest workspace has the 4096 bytes that moe_decode_status asks for.)
+// Counters of the persistent grouped GEMMs (see grouped_gemm_bf16.h): per GEMM 8 tile hand-out counters, one per XCD, and behind the
+// first GEMM's the tiles that are stored, one per expert.  (With this block the smallest workspace has the 4096 bytes that moe_decode_status asks for.)
 constexpr int kGemmSyncInts = 80;
 constexpr int kSyncInts = 2 * kGemmSyncInts;  // gemm1 and gemm2
 // Scratch memory of the GEMMs for the pieces of K-split tiles and the table of where they are.
@@ -117,7 +117,7 @@ hipError_t launch_ffn_f32(const moe_shape_t& s, int tokens, const float* x, cons
 hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, const int32_t* topk_idx, const float* topk_w,
                            const void* w1, const void* w3, const void* w2, void* y,
                            const int32_t* offs, const int32_t* row_of_slot, const int32_t* slot_of,
-                           void* act, float* out, int32_t* sync, float* partial, const StaleInput& alt,
+                           void* act, float* out, int32_t* sync, uint32_t* status, float* partial, const StaleInput& alt,
                            hipStream_t stream);
 
 // Number of compute units of the current device (cached per device).
