@@ -198,7 +198,7 @@ __global__ __launch_bounds__(kSmallRouteThreads) void predict_degraded_kernel(co
     __shared__ float part[kRoutePartFloats];
     const int t0 = blockIdx.x * per_block;
     const int n = min(per_block, T - t0);
-    route_tokens_wg<scalar_t>(x + (size_t)t0 * H, wg, bias, n, H, E, k, sm, part, on_gpu);
+    route_tokens_wg<scalar_t>(x + (size_t)t0 * H, wg, bias, n, H, E, k, sm, part, false, on_gpu);  // (the same for any per_block)
     const int tid = threadIdx.x;
     if (tid < n * k) {
         idx[(size_t)t0 * k + tid] = sm.idx[tid];

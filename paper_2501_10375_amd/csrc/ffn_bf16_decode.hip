@@ -311,7 +311,7 @@ template <int NC>
 struct Smem {
     int idx[16 * NC * 8];     // selections of the call (expert per assignment) ...
     float w[16 * NC * 8];     // ... and their weights
-    RouteSmem route;          // scratch of the in-kernel routing (NC == 1 only)
+    RouteSmem route;          // results of the in-kernel routing (NC == 1 only)
     Groups<NC> g;
     // partial tiles of the 8 wavefronts; double-buffered over consecutive tiles while that fits
     static constexpr int kRedBufs = NC >= 4 ? 1 : 2;
@@ -791,25 +791,26 @@ __global__ __launch_bounds__(kThreads) void decode_layer_kernel(DecodeArgs p) {
     if (ROUTE) {
         // Every workgroup routes the call itself (identical arithmetic, identical result), which
         // costs a few microseconds of latency instead of a kernel boundary; workgroup 0 publishes.
-        int old_count = 0;
         const bool publish = blockIdx.x == 0;
-        if (publish && tid < p.E && p.accumulate) old_count = p.counts[tid];
         static_assert(sizeof(sm.red) >= kRoutePartFloats * sizeof(float), "routing borrows the reduction buffer");
-        route_tokens_wg<uint16_t>(p.x, p.wg, p.bias, p.T, p.H, p.E, p.k, sm.route,
-                                  reinterpret_cast<float*>(&sm.red[0][0][0][0][0]));
-        if (tid < A) {
-            sm.idx[tid] = sm.route.idx[tid];
-            sm.w[tid] = sm.route.w[tid];
-        }
-        if (publish) {
+        // The prediction for the next layer, which nothing in this call waits for, is the same routine with the next gate: the last
+        // workgroup does it before its share of the experts (where not all take part in phase 1 it is idle
+        // then; else a call ends with it either way).
+        const bool predicts = p.wg_next != nullptr && blockIdx.x == gridDim.x - 1;
+        for (int pass = 0; pass <= (predicts ? 1 : 0); ++pass) {
+            route_tokens_wg<uint16_t>(p.x, pass > 0 ? p.wg_next : p.wg, pass > 0 ? p.bias_next : p.bias, p.T, p.H, p.E, p.k, sm.route,
+                                      reinterpret_cast<float*>(&sm.red[0][0][0][0][0]), route_on_mfma(p.T, p.H));
             if (tid < A) {
-                p.idx_out[tid] = sm.route.idx[tid];
-                p.w_out[tid] = sm.route.w[tid];
-            }
-            if (tid < p.E) {
-                int c = 0;
-                for (int a = 0; a < A; ++a) c += sm.route.idx[a] == tid;
-                p.counts[tid] = old_count + c;
+                if (pass > 0) {
+                    p.pred_out[tid] = sm.route.idx[tid];
+                } else {
+                    sm.idx[tid] = sm.route.idx[tid];
+                    sm.w[tid] = sm.route.w[tid];
+                    if (publish) {
+                        p.idx_out[tid] = sm.route.idx[tid];
+                        p.w_out[tid] = sm.route.w[tid];
+                    }
+                }
             }
         }
     } else {
@@ -820,8 +821,7 @@ __global__ __launch_bounds__(kThreads) void decode_layer_kernel(DecodeArgs p) {
         }
     }
     __syncthreads();
-    if (!ROUTE && p.counts != nullptr && blockIdx.x == 0 && tid < p.E) {
-        // activation counts of selections made by a routing kernel before this one (17 to 32 tokens)
+    if (p.counts != nullptr && blockIdx.x == 0 && tid < p.E) {  // activation counts
         int c = p.accumulate ? p.counts[tid] : 0;
         for (int a = 0; a < A; ++a) c += sm.idx[a] == tid;
         p.counts[tid] = c;
@@ -835,15 +835,6 @@ __global__ __launch_bounds__(kThreads) void decode_layer_kernel(DecodeArgs p) {
     gemm2_phase<P2, NC>(p, sm, epoch, a_open);
     if (blockIdx.x == 0 && tid == 0)  // the next launch counts on from here
         __hip_atomic_store(&p.flags[kEpochIndex], count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (ROUTE && p.wg_next != nullptr && blockIdx.x == gridDim.x - 1) {
-        // The prediction for the next layer, which nothing in this call waits for: one workgroup
-        // evaluates the next gate once its share of the experts is done (same routine as the routing
-        // above, so the result is the one a separate routing call gives).
-        __syncthreads();  // the reduction buffer is free
-        route_tokens_wg<uint16_t>(p.x, p.wg_next, p.bias_next, p.T, p.H, p.E, p.k, sm.route,
-                                  reinterpret_cast<float*>(&sm.red[0][0][0][0][0]));
-        if (tid < A) p.pred_out[tid] = sm.route.idx[tid];
-    }
 }
 
 }  // namespace

@@ -179,7 +179,8 @@ __global__ __launch_bounds__(kSmallRouteThreads) void route_small_kernel(RoutePa
     if (tid < E && p.accumulate && p.counts != nullptr) old_count = p.counts[tid];
     for (int g = 0; g < p.n_gates; ++g) {
         route_tokens_wg<scalar_t>(static_cast<const scalar_t*>(p.x), static_cast<const scalar_t*>(p.gate[g].w),
-                                  p.gate[g].bias, p.tokens, p.hidden, E, p.top_k, sm, part);
+                                  p.gate[g].bias, p.tokens, p.hidden, E, p.top_k, sm, part,
+                                  sizeof(scalar_t) == 2 && route_on_mfma(p.tokens, p.hidden));
         if (tid < A) {
             p.gate[g].idx[tid] = sm.idx[tid];
             if (p.gate[g].wts != nullptr) p.gate[g].wts[tid] = sm.w[tid];

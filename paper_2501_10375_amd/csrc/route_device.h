@@ -140,7 +140,7 @@ struct RouteSmem {
     int idx[kSmallRouteMaxTokens * 8];
     float w[kSmallRouteMaxTokens * 8];
 };
-// Floats of LDS scratch route_tokens_wg needs: [wavefront][token][expert] partial logits.
+// Floats of LDS scratch route_tokens_wg needs: [wavefront][token][expert] partial logits (bf16: the same as MFMA results).
 constexpr int kRoutePartFloats = 8 * kSmallRouteMaxTokens * 64;
 
 // Sums acc[0..8) over the 64 lanes with a halving exchange: after the three exchange steps each
@@ -176,63 +176,128 @@ __device__ inline float reduce8_scatter(const float (&acc)[8], int lane) {
 // renormalised weight of selection j of token t, in descending probability, ties to the lower
 // index.  The arithmetic depends only on (T, H, E, k), never on the workgroup, so any number of
 // workgroups computing the same call agree bit for bit.  `part` is kRoutePartFloats of LDS.
-// With `on_gpu` (uint8 [E]) the selection is degraded gracefully, see select_topk_lanes.
+// `on_mfma`: route_on_mfma() of the call (fp32: false).  With `on_gpu` (uint8 [E]) the selection is degraded gracefully, see select_topk_lanes.
 //
-// The 8 wavefronts split the hidden dimension in interleaved 512-element chunks, so the gate and
-// x are read once per workgroup whatever T is; a wavefront walks the tokens two at a time over
+// bf16, three tokens or more: partial_logits_mfma().  Else the 8 wavefronts split the hidden dimension in interleaved 512-element chunks, so the
+// gate and x are read once per workgroup whatever T is; a wavefront walks the tokens two at a time over
 // its chunks (the gate pieces of later tokens come from the vector cache).  Per-wavefront partial
-// logits are summed in wavefront order through LDS; the softmax and the k arg-max passes run
+// logits are summed through LDS in a fixed order; the softmax and the k arg-max passes run
 // across the lanes of one wavefront, lane e holding expert e.
+// bf16 logits of more than two tokens on the matrix cores: the tokens are the 16 rows of an MFMA, 16 experts its columns, and the 8
+// wavefronts split the hidden dimension in interleaved 64-element pieces.  All loads of up to 16 K steps of 32 are requested before the first
+// one is used, so 16 experts cost one memory round trip whatever the number of tokens.  The loads go through buffer descriptors that end with
+// the operands: rows and steps that do not exist read as zeros and cost nothing in the vector cache (re-read rows would: a call is 256 KB
+// of pieces then: Mixtral shape, one token 120 -> 122 us).  Eight sums, added in a tree, keep the MFMAs apart and the result as close to the exact one as the sums of vector lanes.
+// One or two tokens are one or two rows of the sixteen: the vector lanes need less of the cache for them (Phi
+// shape, one token 63.5 us, 64.2 on the matrix cores; eight tokens of the Mixtral shape are four passes over the gate on the vector lanes: 296 -> 290 us).
+typedef __attribute__((ext_vector_type(8))) __bf16 route_bf16x8;
+typedef __attribute__((ext_vector_type(4))) float route_f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t route_u32x4;
+
+// (beyond, 32-bit offsets do not reach 64 rows)
+constexpr int kRouteMfmaMaxHidden = 1 << 24;
+__device__ inline bool route_on_mfma(int T, int H) { return T > 2 && H <= kRouteMfmaMaxHidden; }
+
+template <int PAIRS>
+__device__ inline void logits_chunk(__amdgpu_buffer_rsrc_t x, __amdgpu_buffer_rsrc_t w, uint32_t xrow, uint32_t wrow, int pair0, int n_pairs,
+                                    route_f32x4 (&acc)[8]) {
+    route_u32x4 xa[2 * PAIRS], wa[2 * PAIRS];
+#pragma unroll
+    for (int i = 0; i < PAIRS; ++i) {
+        const int pair = pair0 + 8 * i;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t off = (uint32_t)pair * 128u + h * 64u;
+            wa[2 * i + h] = __builtin_amdgcn_raw_buffer_load_b128(w, pair < n_pairs ? wrow + off : ~15u, 0, 0);
+            xa[2 * i + h] = __builtin_amdgcn_raw_buffer_load_b128(x, pair < n_pairs ? xrow + off : ~15u, 0, 0);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < 2 * PAIRS; ++i)
+        acc[i & 7] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(route_bf16x8, xa[i]), __builtin_bit_cast(route_bf16x8, wa[i]),
+                                                             acc[i & 7], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// part[(wave * blocks + b) * 256 + 4 * lane + r]: expert 16 b + lane % 16, token 4 * (lane / 16) + r.
+__device__ __attribute__((always_inline)) inline void partial_logits_mfma(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int T, int H, int E,
+                                           float* part) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const uint32_t row_bytes = (uint32_t)H * 2u, lane_off = (uint32_t)(lane & 15) * row_bytes + (uint32_t)(lane >> 4) * 16u;
+    const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x), 0, (int)((uint32_t)T * row_bytes), 0x00020000);
+    const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(wg), 0, (int)((uint32_t)E * row_bytes), 0x00020000);
+    const int n_pairs = H / 64, blocks = (E + 15) / 16;
+    for (int b = 0; b < blocks; ++b) {
+        route_f32x4 acc[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) acc[q] = route_f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int pair0 = wave; pair0 < n_pairs; pair0 += 64) {
+            if (n_pairs - pair0 > 32) logits_chunk<8>(xr, wr, lane_off, lane_off + (uint32_t)b * 16u * row_bytes, pair0, n_pairs, acc);
+            else logits_chunk<4>(xr, wr, lane_off, lane_off + (uint32_t)b * 16u * row_bytes, pair0, n_pairs, acc);
+        }
+        route_f32x4 sum;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            sum[r] = ((acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r])) + ((acc[4][r] + acc[5][r]) + (acc[6][r] + acc[7][r]));
+        *reinterpret_cast<route_f32x4*>(part + (size_t)(wave * blocks + b) * 256 + lane * 4) = sum;
+    }
+}
+
 template <typename scalar_t>
-__device__ inline void route_tokens_wg(const scalar_t* __restrict__ x, const scalar_t* __restrict__ wg,
+__device__ __attribute__((always_inline)) inline void route_tokens_wg(const scalar_t* __restrict__ x, const scalar_t* __restrict__ wg,
                                        const float* __restrict__ bias, int T, int H, int E, int k, RouteSmem& sm,
-                                       float* part, const uint8_t* __restrict__ on_gpu = nullptr) {
+                                       float* part, bool on_mfma, const uint8_t* __restrict__ on_gpu = nullptr) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // requested first so that it arrives together with the gate rows
     const float my_bias = (bias != nullptr && lane < E) ? bias[lane] : 0.f;
     const bool resident = on_gpu != nullptr && lane < E && on_gpu[lane] != 0;
-    const int n_blocks = (E + 7) / 8;
-    const int esub = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
-    for (int t = 0; t < T; t += 2) {
-        const bool two = t + 1 < T;
-        const scalar_t* x0 = x + (size_t)t * H;
-        const scalar_t* x1 = x + (size_t)(two ? t + 1 : t) * H;
-        for (int eb = 0; eb < n_blocks; ++eb) {
-            const int ne = min(8, E - eb * 8);
-            const scalar_t* wrow = wg + (size_t)eb * 8 * H;
-            float acc0[8], acc1[8];
-#pragma unroll
-            for (int r = 0; r < 8; ++r) acc0[r] = acc1[r] = 0.f;
-            for (int h = (wave * 64 + lane) * 8; h < H; h += 8 * 512) {
-                // All loads of the step first, unconditionally (rows past the last expert re-read it;
-                // their sums are never looked at), and nothing else scheduled between them: a load
-                // under a branch, or one the scheduler leaves next to its use, costs a memory round
-                // trip of its own, ten in a row instead of one.
-                Raw8<scalar_t> xr0, xr1, wr[8];
-                xr0.load(x0 + h);
-                xr1.load(x1 + h);
-#pragma unroll
-                for (int r = 0; r < 8; ++r) wr[r].load(wrow + (size_t)min(r, ne - 1) * H + h);
-                __builtin_amdgcn_sched_barrier(0);
-                float xv0[8], xv1[8];
-                xr0.get(xv0);
-                xr1.get(xv1);
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    float wv[8];
-                    wr[r].get(wv);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        acc0[r] = fmaf(xv0[i], wv[i], acc0[r]);
-                        acc1[r] = fmaf(xv1[i], wv[i], acc1[r]);
+    if constexpr (sizeof(scalar_t) == 2)
+        if (on_mfma) partial_logits_mfma(x, wg, T, H, E, part);
+    if (!on_mfma) {
+        const int n_blocks = (E + 7) / 8;
+        const int esub = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);
+        for (int t = 0; t < T; t += 2) {
+            const bool two = t + 1 < T;
+            const scalar_t* x0 = x + (size_t)t * H;
+            const scalar_t* x1 = x + (size_t)(two ? t + 1 : t) * H;
+            for (int eb = 0; eb < n_blocks; ++eb) {
+                const int ne = min(8, E - eb * 8);
+                const scalar_t* wrow = wg + (size_t)eb * 8 * H;
+                float acc0[8], acc1[8];
+    #pragma unroll
+                for (int r = 0; r < 8; ++r) acc0[r] = acc1[r] = 0.f;
+                for (int h = (wave * 64 + lane) * 8; h < H; h += 8 * 512) {
+                    // All loads of the step first, unconditionally (rows past the last expert re-read it;
+                    // their sums are never looked at), and nothing else scheduled between them: a load
+                    // under a branch, or one the scheduler leaves next to its use, costs a memory round
+                    // trip of its own, ten in a row instead of one.
+                    Raw8<scalar_t> xr0, xr1, wr[8];
+                    xr0.load(x0 + h);
+                    xr1.load(x1 + h);
+    #pragma unroll
+                    for (int r = 0; r < 8; ++r) wr[r].load(wrow + (size_t)min(r, ne - 1) * H + h);
+                    __builtin_amdgcn_sched_barrier(0);
+                    float xv0[8], xv1[8];
+                    xr0.get(xv0);
+                    xr1.get(xv1);
+    #pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        float wv[8];
+                        wr[r].get(wv);
+    #pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            acc0[r] = fmaf(xv0[i], wv[i], acc0[r]);
+                            acc1[r] = fmaf(xv1[i], wv[i], acc1[r]);
+                        }
                     }
                 }
-            }
-            const float v0 = reduce8_scatter(acc0, lane);
-            const float v1 = reduce8_scatter(acc1, lane);
-            if ((lane & 7) == 0) {
-                part[(wave * T + t) * 64 + eb * 8 + esub] = v0;
-                if (two) part[(wave * T + t + 1) * 64 + eb * 8 + esub] = v1;
+                const float v0 = reduce8_scatter(acc0, lane);
+                const float v1 = reduce8_scatter(acc1, lane);
+                if ((lane & 7) == 0) {
+                    part[(wave * T + t) * 64 + eb * 8 + esub] = v0;
+                    if (two) part[(wave * T + t + 1) * 64 + eb * 8 + esub] = v1;
+                }
             }
         }
     }
@@ -240,9 +305,17 @@ __device__ inline void route_tokens_wg(const scalar_t* __restrict__ x, const sca
     for (int t = wave; t < T; t += 8) {
         float z = -INFINITY;
         if (lane < E) {
-            float s = 0.f;
-            for (int w = 0; w < 8; ++w) s += part[(w * T + t) * 64 + lane];
-            z = s + my_bias;
+            if (on_mfma) {
+                const int blocks = (E + 15) / 16;
+                float v[8];
+#pragma unroll
+                for (int w = 0; w < 8; ++w) v[w] = part[(w * blocks + (lane >> 4)) * 256 + ((t >> 2) * 16 + (lane & 15)) * 4 + (t & 3)];
+                z = (((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]))) + my_bias;
+            } else {
+                float s = 0.f;
+                for (int w = 0; w < 8; ++w) s += part[(w * T + t) * 64 + lane];
+                z = s + my_bias;
+            }
         }
         int my_sel;
         float my_w;
