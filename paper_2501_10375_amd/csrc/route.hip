@@ -4,7 +4,7 @@
 // which is the same computation with the next layer's gate on the same x).
 //
 // Prefill-size calls: a 16-token x 16-expert MFMA tile per workgroup and gate with the hidden dimension split
-// over 16 wavefronts (route_mfma_kernel).
+// over its wavefronts (route_mfma_kernel).
 //
 // Decode-size calls (at most 16 tokens) are a chain of memory latencies rather
 // than a stream: one workgroup routes the whole call with the hidden dimension
@@ -26,45 +26,53 @@ struct RouteParams {
     int accumulate;
 };
 
-// The gate GEMM on the matrix cores.  One workgroup of 16 wavefronts owns 16 tokens: they
+// The gate GEMM on the matrix cores.  One workgroup owns 16 tokens: they
 // are the 16 rows of an MFMA whose 16 columns are a block of 16 experts, and the wavefronts split the hidden
-// dimension in contiguous runs of 64-byte steps, 16 bytes a lane: one v_mfma_f32_16x16x32_bf16, or for fp32 storage
+// dimension in contiguous runs of 128-byte units, two MFMA steps each, 16 bytes a lane: one v_mfma_f32_16x16x32_bf16, or for fp32 storage
 // four v_mfma_f32_16x16x4_f32, element q of every lane's four going to the q-th (the same K elements in both operands).
-// The wavefronts' partial 16 x 16 tiles are summed through LDS in a fixed order; then wavefront i takes token i with
+// A load instruction covers 8 rows x 128 bytes, consecutive lanes on consecutive addresses, and each wavefront turns its units in 4 KB of
+// LDS of its own: in the layout that the MFMA wants, every quad of lanes is on four rows, which costs the address path 64 cycles an
+// instruction instead of 16 (kernel, 2048 tokens of hidden 4096, 16 experts 11.4 -> 6.8 us; 77 tokens 9.6 -> 7.6; 1003 tokens of hidden
+// 2048, 64 experts 14.4 -> 11.4).
+// The wavefronts' partial 16 x 16 tiles are summed through LDS in a fixed order; then each token is one wavefront's, with
 // expert e on lane e for the softmax and the top-k.
 //
 // At these sizes (a gate of 64 to 512 KB, 16 tokens a workgroup) the kernel is a chain of latencies, so every load of
-// up to kChunk steps is requested before the first one is used, and unconditionally: rows that do not exist re-read one that
-// does (a load under a branch waits for its own memory round trip).  There is a version for every number of steps, so that a
-// wavefront of a short hidden dimension asks for no step twice (all eight always, one gate, 8 experts: hidden 512 11.7 -> 6.9 us,
-// 2048 11.7 -> 9.1) and addresses are constants from the row's start (with an address a step, 64 experts spilled registers:
-// hidden 2048, 1003 tokens 19.3 -> 16.2 us; fp32 with 64 experts has registers for one step only, hidden 1024 21.0 -> 17.0).
+// up to kChunk units is requested before the first one is used, and unconditionally: rows that do not exist re-read one that
+// does (a load under a branch waits for its own memory round trip).  There is a version for every number of units, so that a
+// wavefront of a short hidden dimension asks for no unit twice, and addresses are constants from the row's start (with an address a
+// step, 64 experts spilled registers; fp32 with 64 experts has registers for one unit only).
 // The two gates of a call go to different workgroups (x comes from the L2 the second time) while those fit the chip at one a CU, and
 // are done one after the other by the same workgroup beyond that (4096 tokens: 23 us so, 27 us in two rounds).
-// Measured, both gates: 1003 tokens, 64 experts, hidden 2048: 28 -> 17 us; 32 and 77 tokens, 8 experts, hidden 4096:
-// 17 -> 12 us; fp32, 512 tokens, 64 experts, hidden 1024: 208 -> 20 us (a wavefront per token read the whole gate).
 // NBG = number of 16-expert blocks.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-// acc[q] += a . b over a step.  fp32 storage keeps the four element positions apart until the end, and adds partial sums in
-// a tree: one running sum was 1.2 to 1.6 times as far from the 64-bit gate weights as lanes with 8-element sums of
+// acc += a . b over step h of a unit.  fp32 storage keeps the four element positions of the two steps apart until the end, and adds partial
+// sums in a tree: one running sum was 1.2 to 1.6 times as far from the 64-bit gate weights as lanes with 8-element sums of
 // their own had been (1.77e-7 against 1.13e-7 at a hidden dimension of 1024), this is no further than those.
-__device__ inline void mfma_step(u32x4 a, u32x4 b, f32x4 (&acc)[1]) {
+__device__ inline void mfma_step(u32x4 a, u32x4 b, int, f32x4 (&acc)[1]) {
     acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc[0], 0, 0, 0);
 }
-__device__ inline void mfma_step(u32x4 a, u32x4 b, f32x4 (&acc)[4]) {
+__device__ inline void mfma_step(u32x4 a, u32x4 b, int h, f32x4 (&acc)[8]) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-        acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[q]), __uint_as_float(b[q]), acc[q], 0, 0, 0);
+        acc[h * 4 + q] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[q]), __uint_as_float(b[q]), acc[h * 4 + q], 0, 0, 0);
 }
 __device__ inline f32x4 total_of(const f32x4 (&acc)[1]) { return acc[0]; }
-__device__ inline f32x4 total_of(const f32x4 (&acc)[4]) {
+__device__ inline f32x4 total_of(const f32x4 (&acc)[8]) {
     f32x4 r;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) r[i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]);
+    for (int i = 0; i < 4; ++i)
+        r[i] = ((acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i])) + ((acc[4][i] + acc[5][i]) + (acc[6][i] + acc[7][i]));
     return r;
+}
+// Orders a wavefront's own LDS traffic (which the hardware does by itself; this is for the compiler).
+__device__ inline void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 // f(n) with n, at most N, as a constant.
 template <int N, class F>
@@ -73,59 +81,88 @@ __device__ inline void for_count(int n, F f) {
     else if constexpr (N > 1) for_count<N - 1>(n, f);
 }
 
+// Wavefronts: 16, or 8 for more than 16 experts, which then have registers for four units (two in fp32 with 64 experts).
+template <int NBG>
+constexpr int kRouteWaves = NBG == 1 ? 16 : 8;
 template <typename scalar_t, int NBG>
-__global__ __launch_bounds__(1024) void route_mfma_kernel(RouteParams p) {
+__global__ __launch_bounds__(kRouteWaves<NBG> * 64) void route_mfma_kernel(RouteParams p) {
     constexpr bool kF32 = sizeof(scalar_t) == 4;
-    constexpr int kSums = kF32 ? 4 : 1;
-    constexpr int kChunk = NBG == 1 ? 8 : NBG == 4 && kF32 ? 1 : 4;  // steps whose operands are in registers at a time
-    constexpr int kStep = 64 / (int)sizeof(scalar_t), kLane = 16 / (int)sizeof(scalar_t);
+    constexpr int kSums = kF32 ? 8 : 1, kWaves = kRouteWaves<NBG>;
+    constexpr int kChunk = !kF32 || NBG == 2 ? 4 : NBG == 1 ? 2 : 1;  // units whose operands are in registers at a time
+    constexpr int kUnit = 128 / (int)sizeof(scalar_t), kLane = 16 / (int)sizeof(scalar_t);
+    __shared__ __attribute__((aligned(256))) unsigned char turn[kWaves][4096];  // per wavefront a unit of 16 tokens and of 16 experts
     __shared__ int hist[2][64];
-    __shared__ f32x4 part[16][NBG][64];
+    __shared__ f32x4 part[kWaves][NBG][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid < 128) hist[tid >> 6][tid & 63] = 0;
     const int H = p.hidden, E = p.n_experts, T = p.tokens;
     const int t0 = blockIdx.x * kRouteTokensPerBlock;
-    const int row = lane & 15, kq = lane >> 4;
-    const scalar_t* xrow = static_cast<const scalar_t*>(p.x) + (size_t)min(t0 + row, T - 1) * H + kq * kLane;
-    const int k_steps = H / kStep;
-    const int per = (k_steps + 15) / 16;
-    const int s_begin = wave * per;
-    const int s_end = min(k_steps, s_begin + per);
+    // loads: lane l has piece l % 8 of rows l / 8 and 8 + l / 8 of a unit, which goes to position (l % 8) ^ (row / 2 % 8) of the row;
+    // operands: row l % 16, piece l / 16 (+ 4 for the second step)
+    const int row = lane >> 3, piece = lane & 7;
+    const scalar_t* x_lo = static_cast<const scalar_t*>(p.x) + (size_t)min(t0 + row, T - 1) * H + piece * kLane;
+    const scalar_t* x_hi = static_cast<const scalar_t*>(p.x) + (size_t)min(t0 + row + 8, T - 1) * H + piece * kLane;
+    unsigned char* mine = turn[wave];
+    const int put_lo = row * 128 + ((piece ^ (row >> 1)) << 4), put_hi = (row + 8) * 128 + ((piece ^ (4 + (row >> 1))) << 4);
+    const int get = (lane & 15) * 128 + (((lane >> 4) ^ ((lane >> 1) & 7)) << 4);  // (second step: ^ 64)
+    const int n_units = H / kUnit;
+    const int per = (n_units + kWaves - 1) / kWaves;
+    const int u_begin = wave * per;
+    const int u_end = min(n_units, u_begin + per);
 
-    const int t = t0 + wave;  // the token this wavefront selects for
     const int g_begin = gridDim.y > 1 ? blockIdx.y : 0, g_end = gridDim.y > 1 ? blockIdx.y + 1 : p.n_gates;
     for (int g = g_begin; g < g_end; ++g) {
         const GateArgs gate = p.gate[g];
         const float my_bias = gate.bias != nullptr && lane < E ? gate.bias[lane] : 0.f;
-        const scalar_t* wrow[NBG];  // columns past the last expert compute a logit that nobody reads
+        // rows 16 nb + lane / 8 and 8 further on; columns past the last expert compute a logit that nobody reads
+        const scalar_t *w_lo[NBG], *w_hi[NBG];
 #pragma unroll
-        for (int nb = 0; nb < NBG; ++nb) wrow[nb] = static_cast<const scalar_t*>(gate.w) + (size_t)min(nb * 16 + row, E - 1) * H + kq * kLane;
+        for (int nb = 0; nb < NBG; ++nb) {
+            w_lo[nb] = static_cast<const scalar_t*>(gate.w) + (size_t)min(nb * 16 + row, E - 1) * H + piece * kLane;
+            w_hi[nb] = static_cast<const scalar_t*>(gate.w) + (size_t)min(nb * 16 + row + 8, E - 1) * H + piece * kLane;
+        }
 
         f32x4 acc[NBG][kSums];
 #pragma unroll
         for (int nb = 0; nb < NBG; ++nb)
 #pragma unroll
             for (int q = 0; q < kSums; ++q) acc[nb][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        auto steps = [&](auto n_c, int s0) {
+        auto units = [&](auto n_c, int u0) {
             constexpr int N = decltype(n_c)::value;
-            u32x4 xa[N], wb[NBG][N];
-            const scalar_t* xs = xrow + (size_t)s0 * kStep;
+            u32x4 xl[N], xh[N], wl[NBG][N], wh[NBG][N];
+            const size_t off = (size_t)u0 * kUnit;
 #pragma unroll
-            for (int i = 0; i < N; ++i) xa[i] = *reinterpret_cast<const u32x4*>(xs + i * kStep);
+            for (int i = 0; i < N; ++i) {
+                xl[i] = *reinterpret_cast<const u32x4*>(x_lo + off + i * kUnit);
+                xh[i] = *reinterpret_cast<const u32x4*>(x_hi + off + i * kUnit);
 #pragma unroll
-            for (int nb = 0; nb < NBG; ++nb) {
-                const scalar_t* ws = wrow[nb] + (size_t)s0 * kStep;
-#pragma unroll
-                for (int i = 0; i < N; ++i) wb[nb][i] = *reinterpret_cast<const u32x4*>(ws + i * kStep);
+                for (int nb = 0; nb < NBG; ++nb) {
+                    wl[nb][i] = *reinterpret_cast<const u32x4*>(w_lo[nb] + off + i * kUnit);
+                    wh[nb][i] = *reinterpret_cast<const u32x4*>(w_hi[nb] + off + i * kUnit);
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < N; ++i)
+            for (int i = 0; i < N; ++i) {
+                *reinterpret_cast<u32x4*>(mine + put_lo) = xl[i];
+                *reinterpret_cast<u32x4*>(mine + put_hi) = xh[i];
+                u32x4 xa[2];
 #pragma unroll
-                for (int nb = 0; nb < NBG; ++nb) mfma_step(xa[i], wb[nb][i], acc[nb]);
+                for (int nb = 0; nb < NBG; ++nb) {
+                    *reinterpret_cast<u32x4*>(mine + 2048 + put_lo) = wl[nb][i];
+                    *reinterpret_cast<u32x4*>(mine + 2048 + put_hi) = wh[nb][i];
+                    wave_order();
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        if (nb == 0) xa[h] = *reinterpret_cast<const u32x4*>(mine + (get ^ (h * 64)));
+                        mfma_step(xa[h], *reinterpret_cast<const u32x4*>(mine + 2048 + (get ^ (h * 64))), h, acc[nb]);
+                    }
+                    wave_order();
+                }
+            }
         };
-        for (int s0 = s_begin; s0 < s_end; s0 += kChunk) {
-            for_count<kChunk>(min(kChunk, s_end - s0), [&](auto n) { steps(n, s0); });
+        for (int u0 = u_begin; u0 < u_end; u0 += kChunk) {
+            for_count<kChunk>(min(kChunk, u_end - u0), [&](auto n) { units(n, u0); });
         }
 
         // MFMA result: lane holds column (expert in block) lane & 15 and rows (tokens) 4 * (lane / 16) + r.
@@ -133,21 +170,22 @@ __global__ __launch_bounds__(1024) void route_mfma_kernel(RouteParams p) {
 #pragma unroll
         for (int nb = 0; nb < NBG; ++nb) part[wave][nb][lane] = total_of(acc[nb]);
         __syncthreads();
-        if (t < T) {
+        for (int i = wave; i < kRouteTokensPerBlock && t0 + i < T; i += kWaves) {  // token t0 + i, by one wavefront
+            const int t = t0 + i;
             float z = -INFINITY;
             if (lane < E) {
-                const int nb = lane >> 4, src = (wave >> 2) * 16 + (lane & 15), r = wave & 3;
-                float v[16];
+                const int nb = lane >> 4, src = (i >> 2) * 16 + (lane & 15), r = i & 3;
+                float v[kWaves];
 #pragma unroll
-                for (int w = 0; w < 16; ++w) v[w] = part[w][nb][src][r];
+                for (int w = 0; w < kWaves; ++w) v[w] = part[w][nb][src][r];
                 if constexpr (kF32) {
 #pragma unroll
-                    for (int d = 8; d > 0; d /= 2)
+                    for (int d = kWaves / 2; d > 0; d /= 2)
 #pragma unroll
                         for (int w = 0; w < d; ++w) v[w] += v[w + d];
                 } else {
 #pragma unroll
-                    for (int w = 1; w < 16; ++w) v[0] += v[w];
+                    for (int w = 1; w < kWaves; ++w) v[0] += v[w];
                 }
                 z = v[0] + my_bias;
             }
@@ -199,9 +237,9 @@ template <typename scalar_t>
 void launch_mfma(const RouteParams& p, hipStream_t stream) {
     const int blocks = route_blocks(p.tokens);
     const dim3 grid(blocks, blocks * p.n_gates <= compute_units() ? p.n_gates : 1);
-    if (p.n_experts <= 16) route_mfma_kernel<scalar_t, 1><<<grid, 1024, 0, stream>>>(p);
-    else if (p.n_experts <= 32) route_mfma_kernel<scalar_t, 2><<<grid, 1024, 0, stream>>>(p);
-    else route_mfma_kernel<scalar_t, 4><<<grid, 1024, 0, stream>>>(p);
+    if (p.n_experts <= 16) route_mfma_kernel<scalar_t, 1><<<grid, kRouteWaves<1> * 64, 0, stream>>>(p);
+    else if (p.n_experts <= 32) route_mfma_kernel<scalar_t, 2><<<grid, kRouteWaves<2> * 64, 0, stream>>>(p);
+    else route_mfma_kernel<scalar_t, 4><<<grid, kRouteWaves<4> * 64, 0, stream>>>(p);
 }
 
 RouteParams make_params(const moe_shape_t& s, int tokens, const void* x, const GateArgs* gates, int n_gates) {

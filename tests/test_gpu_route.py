@@ -1,0 +1,93 @@
+"""Routing at the edges of its kernels: blocks of 16 tokens and 16 experts, units of 128 bytes dealt to the wavefronts, the decode-size
+routine on the vector lanes (up to two tokens) and on the matrix cores, and predictions made in the same call."""
+import pytest
+import torch
+
+from paper_2501_10375_amd import moe, synth
+from parity_util import check_routing, host
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _route(oracle, T, H, E, k, dtype):
+    d = synth.moe_layer_inputs(T, H, 64, E, dtype, DEV, seed=T + H + E, zipf_s=0.7, with_next=True)
+    shape = moe.make_shape(H, 64, E, k, dtype)
+    idx = torch.full((T, k), -1, dtype=torch.int32, device=DEV)
+    w = torch.full((T, k), -1.0, device=DEV)
+    counts = torch.full((E,), 7, dtype=torch.int32, device=DEV)
+    pidx, pw, pcounts = torch.full_like(idx, -1), torch.full_like(w, -1.0), torch.full_like(counts, 7)
+    ws = moe.alloc_workspace(shape, T, route_only=True)
+    h = host(d)
+    for fill in (0, 0xFF):
+        ws.fill_(fill)
+        for _ in range(2):
+            moe.moe_route(shape, d["x"], d["wg"], d["bias"], idx, w, counts, False, ws)
+            moe.moe_predict_next(shape, d["x"], d["wg_next"], d["bias_next"], pidx, pw, pcounts, ws)
+        torch.cuda.synchronize()
+        check_routing(idx, w, counts, oracle.route(h["x"], h["wg"], h["bias"], k), E, f"T={T} H={H} E={E}")
+        check_routing(pidx, pw, pcounts, oracle.predict_next(h["x"], h["wg_next"], h["bias_next"], k), E, f"T={T} H={H} E={E} next")
+    before = counts.clone()
+    moe.moe_route(shape, d["x"], d["wg"], d["bias"], idx, w, counts, True, ws)
+    assert torch.equal(counts, 2 * before)
+    # the whole layer makes the same choices, bit for bit
+    out = moe.LayerOutputs(shape, T, dtype, DEV, predict=True)
+    res = moe.run_layer(shape, d, out)
+    torch.cuda.synchronize()
+    assert torch.equal(res["idx"], idx) and torch.equal(res["w"], w) and torch.equal(res["counts"], before)
+    assert torch.equal(res["pred_idx"], pidx)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("T,H,E,k", [
+    (17, 64, 16, 2),       # one or two units for 16 wavefronts
+    (33, 192, 17, 2),      # one expert in the second block
+    (40, 1088, 33, 3),     # units that do not divide the wavefronts; one expert in the third block
+    (50, 4096, 48, 8),     # three of four blocks
+    (31, 8256, 8, 1),      # several chunks a wavefront and a rest
+    (70, 2112, 64, 8),
+    (100, 4160, 32, 4),
+    (530, 128, 5, 2),      # more than 512 selections
+    (1040, 64, 3, 2),      # more than 2048, in 65 blocks
+])
+def test_prefill_sizes(oracle, T, H, E, k, dtype):
+    _route(oracle, T, H, E, k, dtype)
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 9, 16])
+@pytest.mark.parametrize("H,E,k", [
+    (64, 16, 2),           # one piece for eight wavefronts
+    (320, 17, 2),
+    (2112, 33, 8),         # half a chunk and a rest
+    (4096, 8, 2),
+    (4160, 64, 6),         # a chunk and a rest
+    (8192, 24, 1),
+])
+def test_decode_sizes(oracle, T, H, E, k):
+    _route(oracle, T, H, E, k, torch.bfloat16)
+
+
+def test_values_that_are_not_finite_stay_where_they_are():
+    """An infinite gate weight, or a token with one, concerns that expert or token only, also where loads are padded."""
+    T, H, E, k = 9, 320, 12, 2
+    d = synth.moe_layer_inputs(T, H, 64, E, torch.bfloat16, DEV, seed=3, zipf_s=0.0, with_next=False)
+    d["x"][4, 0] = float("inf")
+    shape = moe.make_shape(H, 64, E, k, torch.bfloat16)
+    idx, w = torch.empty((T, k), dtype=torch.int32, device=DEV), torch.empty((T, k), device=DEV)
+    counts, ws = torch.empty(E, dtype=torch.int32, device=DEV), moe.alloc_workspace(shape, 40, route_only=True)
+    moe.moe_route(shape, d["x"], d["wg"], None, idx, w, counts, False, ws)
+    p = (d["x"].double() @ d["wg"].double().T).softmax(-1)
+    torch.cuda.synchronize()
+    for t in (0, 3, 5, 8):
+        ref = p[t].gather(0, idx[t].long())
+        assert torch.allclose(w[t].double(), ref / ref.sum(), atol=1e-5) and p[t].topk(k).indices.sort().values.tolist() == sorted(idx[t].tolist())
+    d["x"][4, 0] = 1.0
+    d["wg"][11, 0] = -float("inf")
+    d["x"][:, 0] = d["x"][:, 0].abs() + 0.5          # that expert's logit is -inf, the others are what they are
+    for n in (9, 1):
+        moe.moe_route(shape, d["x"][:n].contiguous(), d["wg"], None, idx[:n], w[:n], counts, False, ws)
+        p = (d["x"].double() @ d["wg"].double().T).softmax(-1)
+        torch.cuda.synchronize()
+        assert not (idx[:n] == 11).any() and torch.isfinite(w[:n]).all()
+        ref = p[:n].gather(1, idx[:n].long())
+        assert torch.allclose(w[:n].double(), ref / ref.sum(1, keepdim=True), atol=1e-5)
