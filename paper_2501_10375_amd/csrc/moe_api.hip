@@ -185,9 +185,16 @@ hipError_t run_route(const moe_shape_t& s, int tokens, const void* x, GateArgs* 
         stage_mark(stream, kStagePermute);
         return e;
     }
+    if ((counts != nullptr || permute) && counts_next == nullptr && route_finishes(s, tokens, permute)) {
+        const RouteFinish finish = {counts, accumulate, permute ? ws.offs : nullptr, permute ? ws.row_of_slot : nullptr,
+                                    permute ? ws.slot_of : nullptr, permute ? ws.sync : nullptr, reinterpret_cast<uint64_t*>(ws.hist)};
+        const hipError_t e = launch_route(s, tokens, x, gates, n_gates, &finish, stream);
+        stage_mark(stream, kStageRoute);
+        return e;
+    }
     gates[0].hist = ws.hist;
     if (n_gates > 1) gates[1].hist = counts_next != nullptr ? ws.hist_next : nullptr;
-    hipError_t e = launch_route(s, tokens, x, gates, n_gates, stream);
+    hipError_t e = launch_route(s, tokens, x, gates, n_gates, nullptr, stream);
     stage_mark(stream, kStageRoute);
     if (e != hipSuccess) return e;
     if (counts != nullptr || permute)  // (a caller whose expert kernel counts the selections itself passes neither)

@@ -33,7 +33,7 @@ struct WorkspaceLayout {
     size_t dec_flags;    // uint32 [kDecodeFlagInts]  arrival flags, launch count and status word of the decode kernel's two grid-wide rendezvous
     size_t sync;         // int32 [kSyncInts]    tile hand-out counters of the two grouped GEMMs
     size_t hist;         // int32 [n_blocks, E]  per-block selection histogram
-    size_t hist_next;    // int32 [n_blocks, E]  same for the next-layer gate
+    size_t hist_next;    // int32 [n_blocks, E]  same for the next-layer gate; both together also hold RouteFinish::words
     size_t offs;         // int32 [E + 1]        exclusive scan of counts
     size_t row_of_slot;  // int32 [A]            slot -> assignment index t*k + j
     size_t slot_of;      // int32 [A]            assignment index -> slot
@@ -70,10 +70,20 @@ void stage_mark(hipStream_t stream, int stage);
 
 // ---- launchers (each returns hipGetLastError() after enqueueing) ----------
 
+// What the routing kernel's last workgroup makes of the first gate's selections, where it does so (route_finishes()): counts (may be
+// null) and, with row_of_slot, what launch_finalize() leaves for the experts' kernels.
+struct RouteFinish {
+    int32_t* counts;
+    int accumulate;
+    int32_t *offs, *row_of_slot, *slot_of, *sync;
+    uint64_t* words;   // [n_blocks, E] scratch: the memory of both histograms
+};
+bool route_finishes(const moe_shape_t& s, int tokens, bool permute);
+
 // Gate GEMM + softmax + top-k for up to two gates that share x.  Per-block
-// histograms go to gate.hist.
+// histograms go to gate.hist.  `finish` may be null.
 hipError_t launch_route(const moe_shape_t& s, int tokens, const void* x, const GateArgs* gates,
-                        int n_gates, hipStream_t stream);
+                        int n_gates, const RouteFinish* finish, hipStream_t stream);
 
 // Per-block histogram of caller-provided indices (moe_expert_ffn entry).
 hipError_t launch_hist_from_idx(const moe_shape_t& s, int tokens, const int32_t* idx, int32_t* hist,

@@ -48,7 +48,10 @@ def _route(oracle, T, H, E, k, dtype):
     (70, 2112, 64, 8),
     (100, 4160, 32, 4),
     (530, 128, 5, 2),      # more than 512 selections
-    (1040, 64, 3, 2),      # more than 2048, in 65 blocks
+    (512, 64, 16, 2),      # 1024 selections: the last workgroup permutes them
+    (513, 64, 16, 2),      # one more than it takes
+    (1040, 64, 3, 2),      # 65 blocks
+    (2100, 64, 64, 1),     # more counts than one workgroup adds
 ])
 def test_prefill_sizes(oracle, T, H, E, k, dtype):
     _route(oracle, T, H, E, k, dtype)
