@@ -184,9 +184,9 @@ __global__ __launch_bounds__(256) void memory_init_kernel(int L, int E, const in
 }
 
 // ---- prediction with graceful degradation --------------------------------------------------------
-// One workgroup per `per_block` tokens (2 or 16, see daop_predict_degraded), the decode-size routing code with the placement
+// One workgroup per `per_block` tokens (see daop_predict_degraded), the decode-size routing code with the placement
 // mask.
-template <typename scalar_t>
+template <typename scalar_t, bool MFMA>
 __global__ __launch_bounds__(kSmallRouteThreads) void predict_degraded_kernel(const scalar_t* __restrict__ x,
                                                                                const scalar_t* __restrict__ wg,
                                                                                const float* __restrict__ bias,
@@ -196,9 +196,10 @@ __global__ __launch_bounds__(kSmallRouteThreads) void predict_degraded_kernel(co
                                                                                float* __restrict__ w) {
     __shared__ RouteSmem sm;
     __shared__ float part[kRoutePartFloats];
+    __shared__ __attribute__((aligned(256))) unsigned char turn[MFMA ? kRouteTurnBytes : 16];
     const int t0 = blockIdx.x * per_block;
     const int n = min(per_block, T - t0);
-    route_tokens_wg<scalar_t>(x + (size_t)t0 * H, wg, bias, n, H, E, k, sm, part, false, on_gpu);  // (the same for any per_block)
+    route_tokens_wg<scalar_t>(x + (size_t)t0 * H, wg, bias, n, H, E, k, sm, part, MFMA ? turn : nullptr, on_gpu);
     const int tid = threadIdx.x;
     if (tid < n * k) {
         idx[(size_t)t0 * k + tid] = sm.idx[tid];
@@ -287,19 +288,21 @@ int daop_predict_degraded(const moe_shape_t* shape, int32_t tokens, const void* 
         if (p != nullptr && misaligned16(p)) return MOE_ERR_ALIGN;
     if (tokens == 0) return MOE_OK;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    // Two tokens a workgroup as long as that takes a CU three of them at most: every two tokens are a pass over the gate, a
-    // memory round trip, and a workgroup makes its passes one after the other.  Longer calls share what a workgroup
-    // has read of the gate between 16.  (A token's result does not depend on its neighbours.)  Hidden 4096, 8 experts,
-    // 16 / 2 tokens a workgroup: 4 tokens 5.4 / 4.2 us, 64 tokens 14.7 / 4.2, 1500 tokens 16.1 / 8.3; hidden 2048, 64
-    // experts: 64 tokens 78 / 12.6, 1500 tokens 79 / 27.
-    const int per_block = tokens <= 6 * compute_units() ? 2 : kSmallRouteMaxTokens;
+    // More than eight experts: on the matrix cores, where 16 tokens are as many passes over the gate as one, and eight of them a selection
+    // for every wavefront.  Up to eight are one pass on the vector lanes, which is faster (4 tokens of hidden 4096 and the experts
+    // behind them 229.2 us so, 230.4 on the matrix cores), two tokens a workgroup as long as that takes a CU three of them at most:
+    // every two tokens are a pass over the gate, a memory round trip, and a workgroup makes its passes one after the other.  Longer
+    // calls share what a workgroup has read of the gate between 16.  (A token's result does not depend on its neighbours.)  On the vector lanes, hidden 4096, 8
+    // experts, 16 / 2 tokens a workgroup: 4 tokens 5.4 / 4.2 us, 64 tokens 14.7 / 4.2, 1500 tokens 16.1 / 8.3.
+    const bool mfma = shape->dtype == MOE_BF16 && shape->n_experts > 8 && route_on_mfma(shape->hidden);
+    const int per_block = mfma ? 8 : tokens <= 6 * compute_units() ? 2 : kSmallRouteMaxTokens;
     const int grid = (tokens + per_block - 1) / per_block;
     if (shape->dtype == MOE_F32)
-        predict_degraded_kernel<float><<<grid, kSmallRouteThreads, 0, stream>>>(
+        predict_degraded_kernel<float, false><<<grid, kSmallRouteThreads, 0, stream>>>(
             static_cast<const float*>(x), static_cast<const float*>(w_gate_next), gate_bias_next, on_gpu, tokens,
             shape->hidden, shape->n_experts, shape->top_k, per_block, pred_idx, pred_w);
     else
-        predict_degraded_kernel<uint16_t><<<grid, kSmallRouteThreads, 0, stream>>>(
+        (mfma ? predict_degraded_kernel<uint16_t, true> : predict_degraded_kernel<uint16_t, false>)<<<grid, kSmallRouteThreads, 0, stream>>>(
             static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w_gate_next), gate_bias_next, on_gpu, tokens,
             shape->hidden, shape->n_experts, shape->top_k, per_block, pred_idx, pred_w);
     return done();

@@ -311,6 +311,7 @@ template <int NC>
 struct Smem {
     int idx[16 * NC * 8];     // selections of the call (expert per assignment) ...
     float w[16 * NC * 8];     // ... and their weights
+    __attribute__((aligned(256))) unsigned char turn[NC == 1 ? kRouteTurnBytes : 16];
     RouteSmem route;          // results of the in-kernel routing (NC == 1 only)
     Groups<NC> g;
     // partial tiles of the 8 wavefronts; double-buffered over consecutive tiles while that fits
@@ -460,9 +461,9 @@ __device__ inline void gemm1_phase(const DecodeArgs& p, Smem<NC>& sm, uint32_t e
     }
 }
 
-// ---- phase 1 when a wavefront's K slice is at most kXSteps steps (hidden <= 4096): the token
+// ---- phase 1 when a wavefront's K slice is at most STEPS steps (8: hidden <= 4096, 4: hidden <= 2048): the token
 // operand of an expert is the same for every feature tile, so its fragments are loaded once per
-// expert and stay in registers; only weights stream.  A tile is exactly kXSteps steps (statically
+// expert and stay in registers; only weights stream.  A tile is exactly STEPS steps (statically
 // indexed fragments), steps past the slice multiply zeros.
 //
 // Tiles are dealt to the workgroups round-robin (tile b + n * grid), so every XCD reads from every
@@ -471,7 +472,7 @@ __device__ inline void gemm1_phase(const DecodeArgs& p, Smem<NC>& sm, uint32_t e
 // from ticket counters was measured and lost: a unit has to be claimed a unit or two ahead to keep
 // the load pipeline full, which is as coarse as the imbalance it is meant to remove, and the
 // counters cost more than they saved.)
-constexpr int kXSteps = 8;
+constexpr int kXSteps = 8;  // the most that are held
 // Workgroups that take part in phase 1: as many as are needed for the busiest one's tile count,
 // ceil(tiles / ceil(tiles / grid)); 800 tiles go to 200 workgroups with 4 each rather than to 256
 // with 3 or 4.  The HBM stream is the shared resource, so a balanced share over fewer workgroups
@@ -482,16 +483,24 @@ __device__ inline int phase1_participants(int total_tiles, int grid) {
     const int busiest = (total_tiles + grid - 1) / grid;
     return (total_tiles + busiest - 1) / max(busiest, 1);
 }
-template <int P, int NC, bool ALT>
+//
+// (Of eight steps always, a hidden dimension of 2048 spends half of them on zeros: 64 experts of ffn 1408, 12 tokens 187 -> 164 us, 25
+// tokens 291 -> 256; hidden 1024, ffn 2048, 6 tokens 41 -> 35.)
+//
+// LOW: tiles of 8 features instead of 16, whose operand is 8 rows of w1 and 8 of w3 (half the loads a step, so more steps in flight).  A
+// tile is half as long, so the tiles divide more evenly: see low_tiles().
+template <int P, int NC, bool ALT, bool LOW, int STEPS>
 __device__ inline void gemm1_phase_xreg(const DecodeArgs& p, Smem<NC>& sm, uint32_t epoch, bool& a_open) {
-    static_assert(kXSteps % P == 0, "the weight ring must divide a tile");
+    static_assert(STEPS % P == 0, "the weight ring must divide a tile");
+    static_assert(!LOW || NC == 1, "one column group");
+    constexpr int kFeatures = LOW ? 8 : 16;
     const Groups<NC>& g = sm.g;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15;
     const LaneMap lm(lane);
     const int H = p.H, F = p.F, k = p.k;
 
-    const int tiles_per_expert = F / 16;
+    const int tiles_per_expert = F / kFeatures;
     const int total_tiles = g.n_active * tiles_per_expert;
     // This workgroup's tiles, numbered n = 0 .. n_mine - 1 in ascending tile order.
     // Only as many workgroups take part as are needed for the busiest one's tile count (see
@@ -508,7 +517,7 @@ __device__ inline void gemm1_phase_xreg(const DecodeArgs& p, Smem<NC>& sm, uint3
     const int n_mine = bx < grid ? full_rounds + (full_rounds * grid + slot_in_round(full_rounds) < total_tiles ? 1 : 0) : 0;
     auto tile_id = [&](int n) { return n * grid + slot_in_round(n); };
 
-    const KSplit ks(H / 64, wave);  // ks.per <= kXSteps
+    const KSplit ks(H / 64, wave);  // ks.per <= STEPS
     const int n_valid = ks.n_valid, kstride = ks.stride;
     const size_t k0 = n_valid > 0 ? ks.k0 : 0;  // a wavefront without steps re-reads the row's start
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -522,7 +531,7 @@ __device__ inline void gemm1_phase_xreg(const DecodeArgs& p, Smem<NC>& sm, uint3
     auto enter_tile = [&]() {
         const int id = tile_id(min(itile, n_mine - 1));
         const int d = id / tiles_per_expert;
-        const size_t row0 = (size_t)g.expert[d] * F + (id - d * tiles_per_expert) * 16;
+        const size_t row0 = (size_t)g.expert[d] * F + (id - d * tiles_per_expert) * kFeatures;
         wlo = (row0 + lm.row_lo) * H + k0 + lm.k_ld;
         whi = (row0 + lm.row_hi) * H + k0 + lm.k_ld;
     };
@@ -530,10 +539,14 @@ __device__ inline void gemm1_phase_xreg(const DecodeArgs& p, Smem<NC>& sm, uint3
     auto issue = [&](int i) {
         const size_t off = (size_t)(is < n_valid ? is : 0) * kstride;
         lo1[i] = load16(p.w1 + wlo + off);
-        hi1[i] = load16(p.w1 + whi + off);
-        lo3[i] = load16(p.w3 + wlo + off);
-        hi3[i] = load16(p.w3 + whi + off);
-        if (++is == kXSteps) {
+        if constexpr (LOW) {
+            hi1[i] = load16(p.w3 + wlo + off);
+        } else {
+            hi1[i] = load16(p.w1 + whi + off);
+            lo3[i] = load16(p.w3 + wlo + off);
+            hi3[i] = load16(p.w3 + whi + off);
+        }
+        if (++is == STEPS) {
             is = 0;
             ++itile;
             enter_tile();
@@ -542,13 +555,13 @@ __device__ inline void gemm1_phase_xreg(const DecodeArgs& p, Smem<NC>& sm, uint3
 #pragma unroll
     for (int i = 0; i < P; ++i) issue(i);
 
-    u32x4 xr[kXSteps][NC][2];  // token fragments of the current expert
+    u32x4 xr[STEPS][NC][2];  // token fragments of the current expert
     const int d_a = (g.n_active + 1) / 2;  // experts [0, d_a) of the active list are group A
     int cur_d = -1, par = 0;
     for (int ctile = 0; ctile < n_mine; ++ctile) {
         const int id = tile_id(ctile);
         const int d = id / tiles_per_expert;
-        const int f0 = (id - d * tiles_per_expert) * 16;
+        const int f0 = (id - d * tiles_per_expert) * kFeatures;
         const int cnt = g.cnt[d];
         if (a_open && d >= d_a) {  // this workgroup's part of group A is complete
             announce(&p.flags[blockIdx.x], epoch);
@@ -561,7 +574,7 @@ __device__ inline void gemm1_phase_xreg(const DecodeArgs& p, Smem<NC>& sm, uint3
                 // columns without a token read the expert's first token (their results are unused)
                 const uint16_t* xp = token_row<ALT, NC>(p, sm, g.assign[d][col + 16 * c < cnt ? col + 16 * c : 0]) + k0 + lm.kq8;
 #pragma unroll
-                for (int s = 0; s < kXSteps; ++s) {
+                for (int s = 0; s < STEPS; ++s) {
                     const size_t off = (size_t)(s < n_valid ? s : 0) * kstride;
                     xr[s][c][0] = keep_if(s < n_valid, load16(xp + off));
                     xr[s][c][1] = keep_if(s < n_valid, load16(xp + off + 32));
@@ -572,19 +585,21 @@ __device__ inline void gemm1_phase_xreg(const DecodeArgs& p, Smem<NC>& sm, uint3
 #pragma unroll
         for (int c = 0; c < NC; ++c) g1[c] = g2[c] = u1[c] = u2[c] = zero;
 #pragma unroll
-        for (int s = 0; s < kXSteps; ++s) {
+        for (int s = 0; s < STEPS; ++s) {
             const int i = s % P;
             bf16x8 a1, a2, a3, a4;
             mfma_operands(lm, lo1[i], hi1[i], a1, a2);
-            mfma_operands(lm, lo3[i], hi3[i], a3, a4);
+            if constexpr (!LOW) mfma_operands(lm, lo3[i], hi3[i], a3, a4);
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const bf16x8 b1 = __builtin_bit_cast(bf16x8, xr[s][c][0]);
                 const bf16x8 b2 = __builtin_bit_cast(bf16x8, xr[s][c][1]);
                 g1[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b1, g1[c], 0, 0, 0);
                 g2[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2, b2, g2[c], 0, 0, 0);
-                u1[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a3, b1, u1[c], 0, 0, 0);
-                u2[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a4, b2, u2[c], 0, 0, 0);
+                if constexpr (!LOW) {
+                    u1[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a3, b1, u1[c], 0, 0, 0);
+                    u2[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a4, b2, u2[c], 0, 0, 0);
+                }
             }
             issue(i);
         }
@@ -593,11 +608,13 @@ __device__ inline void gemm1_phase_xreg(const DecodeArgs& p, Smem<NC>& sm, uint3
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             sm.red[par][wave][0][c][lane] = fold_halves(g1[c], g2[c]);
-            sm.red[par][wave][1][c][lane] = fold_halves(u1[c], u2[c]);
+            if constexpr (!LOW) sm.red[par][wave][1][c][lane] = fold_halves(u1[c], u2[c]);
         }
         lds_barrier();
-        for (int item = tid; item < 128 * NC; item += kThreads) {
-            const int c = item >> 7, pl = item & 63, rp = (item >> 6) & 1;
+        // LOW: MFMA rows 0 to 7 (lanes 0 to 31) are w1's, rows 8 to 15 (32 lanes on) w3's
+        constexpr int kItems = LOW ? 64 : 128 * NC;
+        for (int item = tid; item < kItems; item += kThreads) {
+            const int c = item >> 7, pl = LOW ? item & 31 : item & 63, rp = LOW ? item >> 5 : (item >> 6) & 1;
             const int tok = (pl & 15) + 16 * c;
             if (tok < cnt) {
                 float o[2];
@@ -607,7 +624,7 @@ __device__ inline void gemm1_phase_xreg(const DecodeArgs& p, Smem<NC>& sm, uint3
 #pragma unroll
                     for (int w = 0; w < kWaves; ++w) {
                         gs += sm.red[par][w][0][c][pl][2 * rp + h];
-                        us += sm.red[par][w][1][c][pl][2 * rp + h];
+                        us += LOW ? sm.red[par][w][0][c][pl + 32][2 * rp + h] : sm.red[par][w][1][c][pl][2 * rp + h];
                     }
                     o[h] = swiglu(gs, us);
                 }
@@ -773,10 +790,14 @@ __device__ inline void gemm2_phase(const DecodeArgs& p, Smem<NC>& sm, uint32_t e
 // The whole MoE layer of a decode-size call in one launch (NC = 1, ROUTE), or the expert FFN of a
 // call of up to 16 * NC tokens whose selections were made earlier.  Every workgroup must be
 // resident at the same time (grid <= number of compute units, one 512-thread workgroup each).
-template <int P1, int P2, bool ROUTE, int NC, bool ALT = false>
+//
+// ROUTE: kVector or kMatrix, see route_on_mfma() (in one kernel the two would share its registers).
+enum Routing { kRouted, kVector, kMatrix };
+// STEPS: K steps of a wavefront in a tile of phase 1 where they are a constant (see kXSteps), 0: any.
+template <int P1, int P2, int ROUTE, int NC, int STEPS, bool ALT = false, bool LOW = false>
 __global__ __launch_bounds__(kThreads) void decode_layer_kernel(DecodeArgs p) {
-    static_assert(!ROUTE || NC == 1, "in-kernel routing serves at most 16 tokens");
-    static_assert(!(ROUTE && ALT), "pre-calculated selections come with their routing");
+    static_assert(ROUTE == kRouted || NC == 1, "in-kernel routing serves at most 16 tokens");
+    static_assert(!(ROUTE != kRouted && ALT), "pre-calculated selections come with their routing");
     __shared__ Smem<NC> sm;
     const int tid = threadIdx.x;
     const int A = p.T * p.k;
@@ -788,7 +809,7 @@ __global__ __launch_bounds__(kThreads) void decode_layer_kernel(DecodeArgs p) {
     asm volatile("" ::: "memory");
     for (int i = tid; i < 16 * NC * 16; i += kThreads) sm.yacc[i >> 4][i & 15] = 0.f;
     if (tid == 0) sm.failed = 0;
-    if (ROUTE) {
+    if (ROUTE != kRouted) {
         // Every workgroup routes the call itself (identical arithmetic, identical result), which
         // costs a few microseconds of latency instead of a kernel boundary; workgroup 0 publishes.
         const bool publish = blockIdx.x == 0;
@@ -796,22 +817,22 @@ __global__ __launch_bounds__(kThreads) void decode_layer_kernel(DecodeArgs p) {
         // The prediction for the next layer, which nothing in this call waits for, is the same routine with the next gate: the last
         // workgroup does it before its share of the experts (where not all take part in phase 1 it is idle
         // then; else a call ends with it either way).
-        const bool predicts = p.wg_next != nullptr && blockIdx.x == gridDim.x - 1;
-        for (int pass = 0; pass <= (predicts ? 1 : 0); ++pass) {
-            route_tokens_wg<uint16_t>(p.x, pass > 0 ? p.wg_next : p.wg, pass > 0 ? p.bias_next : p.bias, p.T, p.H, p.E, p.k, sm.route,
-                                      reinterpret_cast<float*>(&sm.red[0][0][0][0][0]), route_on_mfma(p.T, p.H));
-            if (tid < A) {
-                if (pass > 0) {
-                    p.pred_out[tid] = sm.route.idx[tid];
-                } else {
-                    sm.idx[tid] = sm.route.idx[tid];
-                    sm.w[tid] = sm.route.w[tid];
-                    if (publish) {
-                        p.idx_out[tid] = sm.route.idx[tid];
-                        p.w_out[tid] = sm.route.w[tid];
-                    }
-                }
+        auto route = [&](const uint16_t* gate, const float* bias) __attribute__((always_inline)) {
+            route_tokens_wg<uint16_t>(p.x, gate, bias, p.T, p.H, p.E, p.k, sm.route, reinterpret_cast<float*>(&sm.red[0][0][0][0][0]),
+                                      ROUTE == kMatrix ? sm.turn : nullptr);
+        };
+        route(p.wg, p.bias);
+        if (tid < A) {
+            sm.idx[tid] = sm.route.idx[tid];
+            sm.w[tid] = sm.route.w[tid];
+            if (publish) {
+                p.idx_out[tid] = sm.route.idx[tid];
+                p.w_out[tid] = sm.route.w[tid];
             }
+        }
+        if (p.wg_next != nullptr && blockIdx.x == gridDim.x - 1) {
+            route(p.wg_next, p.bias_next);
+            if (tid < A) p.pred_out[tid] = sm.route.idx[tid];
         }
     } else {
         for (int i = tid; i < A; i += kThreads) {
@@ -830,7 +851,7 @@ __global__ __launch_bounds__(kThreads) void decode_layer_kernel(DecodeArgs p) {
     const uint32_t count = (uint32_t)__builtin_amdgcn_readfirstlane((int)last_count) + 1u;
     const uint32_t epoch = count ^ 0x9E3779B9u;
     bool a_open = true;  // flag A not raised yet
-    if (p.H <= 64 * kXSteps * kWaves) gemm1_phase_xreg<P1, NC, ALT>(p, sm, epoch, a_open);
+    if constexpr (STEPS > 0) gemm1_phase_xreg<LOW ? 4 * P1 : P1, NC, ALT, LOW, STEPS>(p, sm, epoch, a_open);
     else gemm1_phase<P1, NC, ALT>(p, sm, epoch, a_open);
     gemm2_phase<P2, NC>(p, sm, epoch, a_open);
     if (blockIdx.x == 0 && tid == 0)  // the next launch counts on from here
@@ -838,6 +859,21 @@ __global__ __launch_bounds__(kThreads) void decode_layer_kernel(DecodeArgs p) {
 }
 
 }  // namespace
+
+template <int ROUTE, int NC, bool ALT, bool LOW = false>
+static void launch_for_hidden(const DecodeArgs& p, int grid, hipStream_t stream) {
+    if (p.H <= 64 * kXSteps / 2 * kWaves) decode_layer_kernel<kP1, kP2, ROUTE, NC, kXSteps / 2, ALT, LOW><<<grid, kThreads, 0, stream>>>(p);
+    else if (p.H <= 64 * kXSteps * kWaves) decode_layer_kernel<kP1, kP2, ROUTE, NC, kXSteps, ALT, LOW><<<grid, kThreads, 0, stream>>>(p);
+    else decode_layer_kernel<kP1, kP2, ROUTE, NC, 0, ALT><<<grid, kThreads, 0, stream>>>(p);
+}
+
+// Whether phase 1 of a one-token call (whose experts are known to be top_k) takes low tiles: while a workgroup has fewer than six of the tall ones, half
+// a tile is what the busiest has too much or the phase ends with (one token, tall / low: hidden 4096, ffn 6400, 2 of 16 experts, 3.1
+// tiles 58.4 / 57.8 us, ffn 4096, 2 experts, 2 tiles 41.0 / 38.4, hidden 2048, ffn 8192, 4 tiles 41.4 / 39.5; but hidden 4096, ffn
+// 14336, 7 tiles 117.8 / 119.1), and while K is long enough for a tile to be more than its reduction (hidden 1024, ffn 2048 16.6 / 17.4).
+static bool low_tiles(const moe_shape_t& s, int tokens, int grid) {
+    return tokens == 1 && s.hidden >= 2048 && s.hidden <= 64 * kXSteps * kWaves && s.top_k * (s.ffn / 16) < 6 * grid;
+}
 
 hipError_t launch_decode_layer(const moe_shape_t& s, int tokens, const void* x, const DecodeRoute* route,
                                const int32_t* topk_idx, const float* topk_w, const void* w1, const void* w3,
@@ -878,14 +914,21 @@ hipError_t launch_decode_layer(const moe_shape_t& s, int tokens, const void* x, 
     const int max_tiles1 = min(s.n_experts, tokens * s.top_k) * (s.ffn / 16);
     const int grid = min(min(compute_units(), kFlagStride), max(max_tiles1, s.hidden / 16));
     if (route != nullptr) {
-        decode_layer_kernel<kP1, kP2, true, 1><<<grid, kThreads, 0, stream>>>(p);
+        const bool low = low_tiles(s, tokens, grid);
+        if (decode_routes_on_mfma(tokens, s.hidden, s.n_experts)) {
+            if (low) launch_for_hidden<kMatrix, 1, false, true>(p, grid, stream);
+            else launch_for_hidden<kMatrix, 1, false>(p, grid, stream);
+        } else {
+            if (low) launch_for_hidden<kVector, 1, false, true>(p, grid, stream);
+            else launch_for_hidden<kVector, 1, false>(p, grid, stream);
+        }
     } else if (alt.stale != nullptr) {
-        if (tokens <= 16) decode_layer_kernel<kP1, kP2, false, 1, true><<<grid, kThreads, 0, stream>>>(p);
-        else decode_layer_kernel<kP1, kP2, false, 2, true><<<grid, kThreads, 0, stream>>>(p);
+        if (tokens <= 16) launch_for_hidden<kRouted, 1, true>(p, grid, stream);
+        else launch_for_hidden<kRouted, 2, true>(p, grid, stream);
     } else if (tokens <= 16) {
-        decode_layer_kernel<kP1, kP2, false, 1><<<grid, kThreads, 0, stream>>>(p);
+        launch_for_hidden<kRouted, 1, false>(p, grid, stream);
     } else {
-        decode_layer_kernel<kP1, kP2, false, 2><<<grid, kThreads, 0, stream>>>(p);
+        launch_for_hidden<kRouted, 2, false>(p, grid, stream);
     }
     stage_mark(stream, kStageFused);
     return hipGetLastError();

@@ -292,18 +292,18 @@ __global__ __launch_bounds__(kRouteWaves<NBG> * 64) void route_mfma_kernel(Route
 
 // One workgroup routes a decode-size call against up to two gates and writes indices, weights
 // and counts.
-template <typename scalar_t>
+template <typename scalar_t, bool MFMA>
 __global__ __launch_bounds__(kSmallRouteThreads) void route_small_kernel(RouteParams p) {
     __shared__ RouteSmem sm;
     __shared__ float part[kRoutePartFloats];
+    __shared__ __attribute__((aligned(256))) unsigned char turn[MFMA ? kRouteTurnBytes : 16];
     const int tid = threadIdx.x;
     const int E = p.n_experts, A = p.tokens * p.top_k;
     int old_count = 0;  // requested before the gate rows so that its latency is hidden
     if (tid < E && p.accumulate && p.counts != nullptr) old_count = p.counts[tid];
     for (int g = 0; g < p.n_gates; ++g) {
         route_tokens_wg<scalar_t>(static_cast<const scalar_t*>(p.x), static_cast<const scalar_t*>(p.gate[g].w),
-                                  p.gate[g].bias, p.tokens, p.hidden, E, p.top_k, sm, part,
-                                  sizeof(scalar_t) == 2 && route_on_mfma(p.tokens, p.hidden));
+                                  p.gate[g].bias, p.tokens, p.hidden, E, p.top_k, sm, part, MFMA ? turn : nullptr);
         if (tid < A) {
             p.gate[g].idx[tid] = sm.idx[tid];
             if (p.gate[g].wts != nullptr) p.gate[g].wts[tid] = sm.w[tid];
@@ -362,8 +362,9 @@ hipError_t launch_route_small(const moe_shape_t& s, int tokens, const void* x, c
     p.counts = counts;
     p.counts_next = counts_next;
     p.accumulate = accumulate;
-    if (s.dtype == MOE_F32) route_small_kernel<float><<<1, kSmallRouteThreads, 0, stream>>>(p);
-    else route_small_kernel<uint16_t><<<1, kSmallRouteThreads, 0, stream>>>(p);
+    if (s.dtype == MOE_F32) route_small_kernel<float, false><<<1, kSmallRouteThreads, 0, stream>>>(p);
+    else if (decode_routes_on_mfma(tokens, s.hidden, s.n_experts)) route_small_kernel<uint16_t, true><<<1, kSmallRouteThreads, 0, stream>>>(p);
+    else route_small_kernel<uint16_t, false><<<1, kSmallRouteThreads, 0, stream>>>(p);
     return hipGetLastError();
 }
 

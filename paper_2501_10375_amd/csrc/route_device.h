@@ -176,65 +176,92 @@ __device__ inline float reduce8_scatter(const float (&acc)[8], int lane) {
 // renormalised weight of selection j of token t, in descending probability, ties to the lower
 // index.  The arithmetic depends only on (T, H, E, k), never on the workgroup, so any number of
 // workgroups computing the same call agree bit for bit.  `part` is kRoutePartFloats of LDS.
-// `on_mfma`: route_on_mfma() of the call (fp32: false).  With `on_gpu` (uint8 [E]) the selection is degraded gracefully, see select_topk_lanes.
+// `turn` (kRouteTurnBytes of LDS): bf16 on the matrix cores; null: on the vector lanes.  With `on_gpu` (uint8 [E]) the selection is degraded gracefully, see select_topk_lanes.
 //
-// bf16, three tokens or more: partial_logits_mfma().  Else the 8 wavefronts split the hidden dimension in interleaved 512-element chunks, so the
+// With `turn`: partial_logits_mfma().  Else the 8 wavefronts split the hidden dimension in interleaved 512-element chunks, so the
 // gate and x are read once per workgroup whatever T is; a wavefront walks the tokens two at a time over
 // its chunks (the gate pieces of later tokens come from the vector cache).  Per-wavefront partial
 // logits are summed through LDS in a fixed order; the softmax and the k arg-max passes run
 // across the lanes of one wavefront, lane e holding expert e.
-// bf16 logits of more than two tokens on the matrix cores: the tokens are the 16 rows of an MFMA, 16 experts its columns, and the 8
-// wavefronts split the hidden dimension in interleaved 64-element pieces.  All loads of up to 16 K steps of 32 are requested before the first
-// one is used, so 16 experts cost one memory round trip whatever the number of tokens.  The loads go through buffer descriptors that end with
-// the operands: rows and steps that do not exist read as zeros and cost nothing in the vector cache (re-read rows would: a call is 256 KB
-// of pieces then: Mixtral shape, one token 120 -> 122 us).  Eight sums, added in a tree, keep the MFMAs apart and the result as close to the exact one as the sums of vector lanes.
-// One or two tokens are one or two rows of the sixteen: the vector lanes need less of the cache for them (Phi
-// shape, one token 63.5 us, 64.2 on the matrix cores; eight tokens of the Mixtral shape are four passes over the gate on the vector lanes: 296 -> 290 us).
+// bf16 logits on the matrix cores: the tokens are the 16 rows of an MFMA, 16 experts its columns, and the 8 wavefronts split the hidden
+// dimension in interleaved units of 64 elements.  All loads of up to 8 units are requested before the first one is used, so 16 experts cost
+// one memory round trip whatever the number of tokens.  A load covers 8 rows x 128 bytes, consecutive lanes on consecutive addresses,
+// and each wavefront turns its units in 4 KB of LDS of its own (see route_mfma_kernel).  The loads go through buffer descriptors that end
+// with the operands: rows and units that do not exist read as zeros and cost nothing in the vector cache.  Eight sums, added in a tree, keep
+// the MFMAs apart and the result as close to the exact one as the sums of vector lanes.
+// Layer calls of a few tokens, vector lanes two tokens and eight experts a round trip / so: Mixtral shape, 16 tokens 416 / 404 us, 8 tokens
+// 405 / 401; Phi shape, 8 tokens 128 / 119; 64 experts of hidden 2048, ffn 1408, 3 tokens 85 / 69, 12 tokens 241 / 187.
 typedef __attribute__((ext_vector_type(8))) __bf16 route_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float route_f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t route_u32x4;
 
 // (beyond, 32-bit offsets do not reach 64 rows)
 constexpr int kRouteMfmaMaxHidden = 1 << 24;
-__device__ inline bool route_on_mfma(int T, int H) { return T > 2 && H <= kRouteMfmaMaxHidden; }
+__host__ __device__ inline bool route_on_mfma(int H) { return H <= kRouteMfmaMaxHidden; }
+// One or two tokens and up to eight experts are a single pass on the vector lanes, which is faster.
+__host__ __device__ inline bool decode_routes_on_mfma(int T, int H, int E) { return (T > 2 || E > 8) && route_on_mfma(H); }
+constexpr int kRouteTurnBytes = 8 * 4096;
 
-template <int PAIRS>
-__device__ inline void logits_chunk(__amdgpu_buffer_rsrc_t x, __amdgpu_buffer_rsrc_t w, uint32_t xrow, uint32_t wrow, int pair0, int n_pairs,
-                                    route_f32x4 (&acc)[8]) {
-    route_u32x4 xa[2 * PAIRS], wa[2 * PAIRS];
+__device__ inline void route_wave_order() {  // a wavefront's LDS accesses stay in order (for the compiler; the hardware keeps it)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// Units u0, u0 + 8, ... (UNITS of them).  xoff / woff: byte offset of this lane's piece of the first 8 rows in unit 0.
+template <int UNITS>
+__device__ __attribute__((always_inline)) inline void logits_chunk(__amdgpu_buffer_rsrc_t x, __amdgpu_buffer_rsrc_t w, uint32_t xoff, uint32_t woff,
+                                                                   uint32_t rows8, int u0, int n_units, unsigned char* mine, route_f32x4 (&acc)[8]) {
+    const int lane = threadIdx.x & 63, row = lane >> 3, piece = lane & 7;
+    route_u32x4 v[UNITS][4];  // x rows 0 to 7, 8 to 15, w rows 0 to 7, 8 to 15
 #pragma unroll
-    for (int i = 0; i < PAIRS; ++i) {
-        const int pair = pair0 + 8 * i;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t off = (uint32_t)pair * 128u + h * 64u;
-            wa[2 * i + h] = __builtin_amdgcn_raw_buffer_load_b128(w, pair < n_pairs ? wrow + off : ~15u, 0, 0);
-            xa[2 * i + h] = __builtin_amdgcn_raw_buffer_load_b128(x, pair < n_pairs ? xrow + off : ~15u, 0, 0);
-        }
+    for (int i = 0; i < UNITS; ++i) {
+        const int u = u0 + 8 * i;
+        const uint32_t at = (uint32_t)u * 128u;
+        const bool on = u < n_units;
+        v[i][2] = __builtin_amdgcn_raw_buffer_load_b128(w, on ? woff + at : ~15u, 0, 0);
+        v[i][3] = __builtin_amdgcn_raw_buffer_load_b128(w, on ? woff + rows8 + at : ~15u, 0, 0);
+        v[i][0] = __builtin_amdgcn_raw_buffer_load_b128(x, on ? xoff + at : ~15u, 0, 0);
+        v[i][1] = __builtin_amdgcn_raw_buffer_load_b128(x, on ? xoff + rows8 + at : ~15u, 0, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
+    // piece p of row r stands at position p ^ (r / 2 % 8) of its 128 bytes
+    const int put_lo = row * 128 + ((piece ^ (row >> 1)) << 4), put_hi = (row + 8) * 128 + ((piece ^ (4 + (row >> 1))) << 4);
+    const int get = (lane & 15) * 128 + (((lane >> 4) ^ ((lane >> 1) & 7)) << 4);
 #pragma unroll
-    for (int i = 0; i < 2 * PAIRS; ++i)
-        acc[i & 7] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(route_bf16x8, xa[i]), __builtin_bit_cast(route_bf16x8, wa[i]),
-                                                             acc[i & 7], 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
+    for (int i = 0; i < UNITS; ++i) {
+        *reinterpret_cast<route_u32x4*>(mine + put_lo) = v[i][0];
+        *reinterpret_cast<route_u32x4*>(mine + put_hi) = v[i][1];
+        *reinterpret_cast<route_u32x4*>(mine + 2048 + put_lo) = v[i][2];
+        *reinterpret_cast<route_u32x4*>(mine + 2048 + put_hi) = v[i][3];
+        route_wave_order();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const route_u32x4 a = *reinterpret_cast<const route_u32x4*>(mine + (get ^ (h * 64)));
+            const route_u32x4 b = *reinterpret_cast<const route_u32x4*>(mine + 2048 + (get ^ (h * 64)));
+            route_f32x4& sum = acc[(2 * i + h) & 7];
+            sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(route_bf16x8, a), __builtin_bit_cast(route_bf16x8, b), sum, 0, 0, 0);
+        }
+        route_wave_order();
+    }
 }
 
 // part[(wave * blocks + b) * 256 + 4 * lane + r]: expert 16 b + lane % 16, token 4 * (lane / 16) + r.
-__device__ __attribute__((always_inline)) inline void partial_logits_mfma(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int T, int H, int E,
-                                           float* part) {
+__device__ __attribute__((always_inline)) inline void partial_logits_mfma(const uint16_t* __restrict__ x, const uint16_t* __restrict__ wg, int T, int H,
+                                                                          int E, float* part, unsigned char* turn) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const uint32_t row_bytes = (uint32_t)H * 2u, lane_off = (uint32_t)(lane & 15) * row_bytes + (uint32_t)(lane >> 4) * 16u;
+    const uint32_t row_bytes = (uint32_t)H * 2u, off = (uint32_t)(lane >> 3) * row_bytes + (uint32_t)(lane & 7) * 16u;
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x), 0, (int)((uint32_t)T * row_bytes), 0x00020000);
     const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(wg), 0, (int)((uint32_t)E * row_bytes), 0x00020000);
-    const int n_pairs = H / 64, blocks = (E + 15) / 16;
+    const int n_units = H / 64, blocks = (E + 15) / 16;
     for (int b = 0; b < blocks; ++b) {
         route_f32x4 acc[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc[q] = route_f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int pair0 = wave; pair0 < n_pairs; pair0 += 64) {
-            if (n_pairs - pair0 > 32) logits_chunk<8>(xr, wr, lane_off, lane_off + (uint32_t)b * 16u * row_bytes, pair0, n_pairs, acc);
-            else logits_chunk<4>(xr, wr, lane_off, lane_off + (uint32_t)b * 16u * row_bytes, pair0, n_pairs, acc);
+        for (int u0 = wave; u0 < n_units; u0 += 64) {
+            const uint32_t woff = off + (uint32_t)b * 16u * row_bytes;
+            if (n_units - u0 > 32) logits_chunk<8>(xr, wr, off, woff, 8u * row_bytes, u0, n_units, turn + wave * 4096, acc);
+            else logits_chunk<4>(xr, wr, off, woff, 8u * row_bytes, u0, n_units, turn + wave * 4096, acc);
         }
         route_f32x4 sum;
 #pragma unroll
@@ -247,13 +274,14 @@ __device__ __attribute__((always_inline)) inline void partial_logits_mfma(const 
 template <typename scalar_t>
 __device__ __attribute__((always_inline)) inline void route_tokens_wg(const scalar_t* __restrict__ x, const scalar_t* __restrict__ wg,
                                        const float* __restrict__ bias, int T, int H, int E, int k, RouteSmem& sm,
-                                       float* part, bool on_mfma, const uint8_t* __restrict__ on_gpu = nullptr) {
+                                       float* part, unsigned char* turn, const uint8_t* __restrict__ on_gpu = nullptr) {
+    const bool on_mfma = turn != nullptr;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // requested first so that it arrives together with the gate rows
     const float my_bias = (bias != nullptr && lane < E) ? bias[lane] : 0.f;
     const bool resident = on_gpu != nullptr && lane < E && on_gpu[lane] != 0;
     if constexpr (sizeof(scalar_t) == 2)
-        if (on_mfma) partial_logits_mfma(x, wg, T, H, E, part);
+        if (on_mfma) partial_logits_mfma(x, wg, T, H, E, part, turn);
     if (!on_mfma) {
         const int n_blocks = (E + 7) / 8;
         const int esub = ((lane >> 5) & 1) * 4 + ((lane >> 4) & 1) * 2 + ((lane >> 3) & 1);

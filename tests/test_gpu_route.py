@@ -4,7 +4,7 @@ import pytest
 import torch
 
 from paper_2501_10375_amd import moe, synth
-from parity_util import check_routing, host
+from parity_util import check_layer, check_routing, host
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -94,3 +94,18 @@ def test_values_that_are_not_finite_stay_where_they_are():
         assert not (idx[:n] == 11).any() and torch.isfinite(w[:n]).all()
         ref = p[:n].gather(1, idx[:n].long())
         assert torch.allclose(w[:n].double(), ref / ref.sum(1, keepdim=True), atol=1e-5)
+
+
+@pytest.mark.parametrize("T", [1, 2, 16, 24])
+@pytest.mark.parametrize("H,F,E,k", [
+    (2048, 320, 20, 3),    # phase 1 of a decode step with four K steps a wavefront; one token: tiles of 8 features, fewer than workgroups
+    (2112, 192, 9, 2),     # eight K steps, one of them there
+    (4096, 2752, 8, 2),    # one token: 8-feature tiles, more than two rounds
+    (1984, 128, 8, 2),     # just below what takes 8-feature tiles
+    (4160, 128, 12, 2),    # longer than the token operand that registers hold
+])
+def test_decode_step_tiles(oracle, T, H, F, E, k):
+    d = synth.moe_layer_inputs(T, H, F, E, torch.bfloat16, DEV, seed=T + F, zipf_s=0.7, with_next=True)
+    shape = moe.make_shape(H, F, E, k, torch.bfloat16)
+    out = moe.LayerOutputs(shape, T, torch.bfloat16, DEV, predict=True)
+    check_layer(oracle, d, shape, moe.run_layer(shape, d, out), torch.bfloat16, label=f"decode T={T} H={H} F={F}")
