@@ -791,7 +791,7 @@ __device__ inline void gemm2_phase(const DecodeArgs& p, Smem<NC>& sm, uint32_t e
 // call of up to 16 * NC tokens whose selections were made earlier.  Every workgroup must be
 // resident at the same time (grid <= number of compute units, one 512-thread workgroup each).
 //
-// ROUTE: kVector or kMatrix, see route_on_mfma() (in one kernel the two would share its registers).
+// ROUTE: kVector or kMatrix, see decode_routes_on_mfma() (in one kernel the two would share its registers).
 enum Routing { kRouted, kVector, kMatrix };
 // STEPS: K steps of a wavefront in a tile of phase 1 where they are a constant (see kXSteps), 0: any.
 template <int P1, int P2, int ROUTE, int NC, int STEPS, bool ALT = false, bool LOW = false>

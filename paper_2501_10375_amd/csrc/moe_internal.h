@@ -21,8 +21,8 @@ constexpr int kDecodeMaxTokens = 16;
 // phases (routing, counts and prediction then come from the prefill-size routing kernels): below
 // this size the layer is bound by reading each selected expert once, and the streaming kernel needs no
 // permutation, no pieces and one launch.  Whole layer, 32 tokens streamed / 33 through the grouped GEMMs:
-// Mixtral shape 442 / 450 us, Phi shape 202 / 220.  With experts of a few MB the GEMMs are the faster ones (64
-// experts, hidden 2048, ffn 1408: 314 / 209; 8 experts, hidden 1024, ffn 2048: 72 / 45), but their 64 MiB of
+// Mixtral shape 463 / 475 us, Phi shape 206 / 235.  With experts of a few MB the GEMMs are the faster ones (64
+// experts, hidden 2048, ffn 1408: 281 / 213; 8 experts, hidden 1024, ffn 2048: 59 / 46), but their 64 MiB of
 // scratch memory are not part of what a call of 32 tokens asks for, and do not fit the static buffer.
 constexpr int kStreamMaxTokens = 32;
 
