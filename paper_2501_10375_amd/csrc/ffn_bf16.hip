@@ -299,7 +299,9 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
     hipError_t e;
     const bool wide2 = gg::needs_wide(0, 256, s.ffn), wide1 = wide2 || gg::needs_wide((size_t)tokens * s.hidden * 2, gg::Gemm<2>::kBF, s.hidden);
     const bool cut = !wide1 && most_tiles <= gg::kMaxCutTiles && s.hidden / 64 >= gg::kMinCutKSteps;
-    const bool link = !wide1 && most_tiles * 4 > persistent_grid() * 5 && (double)routed * s.hidden * s.ffn <= gg::kMaxLinkedMacs;
+    const bool many_tiles = most_tiles > persistent_grid() * 2 ||
+                            (most_tiles * 4 > persistent_grid() * 5 && routed >= gg::kMinLinkedRows * min(s.n_experts, routed));
+    const bool link = !wide1 && many_tiles && (double)routed * s.hidden * s.ffn <= gg::kMaxLinkedMacs;
     if (link) {
         int32_t* done = sync + gg::kXcds;
         e = alternate ? launch_linked<true>(g1, g2, done, status, stream) : launch_linked<false>(g1, g2, done, status, stream);

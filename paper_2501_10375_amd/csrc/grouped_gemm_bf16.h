@@ -258,14 +258,19 @@ __device__ GG_INLINE int swizzled(int row, int chunk) { return chunk ^ ((row >> 
 // resident.  It is bounded all the same (memory that an overlapping call clears must not hang the GPU): when it runs out
 // the status word is raised and the tile's results are NaN.
 //
-// Which calls: those whose first GEMM has more than five quarters of a round of tiles (with about one there is nothing to fill, and handing act
-// over costs 3 to 8 us: hidden 3584, ffn 1088, 2000 tokens 143 us apart / 151 linked; hidden and ffn 2048, 16 experts, 500 tokens, 1.1
-// rounds 137 / 139; 1.4 rounds, hidden 4096, ffn 2048, 1000 tokens 203 / 200) and at most 1.6e11 products of a routed row and a weight.  Beyond, the chip is at its power
+// Which calls: those whose first GEMM has more than two rounds of tiles, or more than five quarters of one and 48 rows an expert (with about one
+// there is nothing to fill, and handing act over costs 3 to 8 us: hidden 3584, ffn 1088, 2000 tokens 143 us apart / 151 linked; hidden and ffn 2048, 16 experts, 500 tokens, 1.1
+// rounds 137 / 139; 1.4 rounds, hidden 4096, ffn 2048, 1000 tokens 203 / 200; with few rows an expert the tiles of a
+// partial second round stream faster the fewer they are, and nothing is idle that could be filled: hidden 2432, ffn 2624, 16 experts, 1.3 rounds, 14 rows
+// 143 / 150, 38 rows 149 / 156, 32 experts, 2.6 rounds 241 / 241; hidden 1024, ffn 4096, 12 experts, 1.5 rounds, 17 rows 82 / 89; hidden 4096, ffn 2048,
+// 16 experts, 1.3 rounds, 88 rows 218 / 205; hidden 2048, ffn 2816, 16 experts, 1.6 rounds, 63 rows 157 / 155; hidden and ffn 2048, 16 experts, 1.9 rounds, 250 rows
+// 171 / 155; hidden 3008, ffn 5632, 12 experts, 2.1 rounds, 6 rows 259 / 246), and at most 1.6e11 products of a routed row and a weight.  Beyond, the chip is at its power
 // limit, where time that is saved comes back as clock that is lost, and workgroups that enter the second GEMM at different times share
 // fewer lines of its tall tiles.  Whole layer, apart / linked: Mixtral shape 200 tokens 526 / 511 us, 512 616 / 593, 1024 776 / 764,
 // but 1400 (1.64e11) 932 / 945, 2048 1214 / 1235; Phi shape 700 tokens 481 / 474, 2048 757 / 749, 3500 1037 / 1024, 6000 1622 / 1624; 64 experts of
 // hidden 2048 and ffn 1408, 1003 tokens 276 / 269, 3000 429 / 413; hidden 3008, ffn 5632, 12 experts, 200 tokens 290 / 261.
 constexpr double kMaxLinkedMacs = 1.6e11;
+constexpr int kMinLinkedRows = 48;
 struct Link {
     int32_t* done;       // tiles of the first GEMM that are stored, per expert (null: not linked)
     uint32_t* status;

@@ -12,8 +12,11 @@ DEV, DTYPE = "cuda", torch.bfloat16
 
 
 def _layer(T, H, F, E, k, zipf=1.2):
-    # the route: more than five quarters of a round of the first GEMM's tiles (256 compute units), whatever the routing
-    assert -(-F // 128) * (T * k // 256 + min(E, T * k)) * 4 > 256 * 5 and T * k * H * F <= 1.6e11 and T > 32
+    # the route: more than two rounds of the first GEMM's tiles (256 compute units), whatever the routing, or more than five quarters of
+    # one with 48 rows an expert
+    tiles = -(-F // 128) * (T * k // 256 + min(E, T * k))
+    assert tiles > 512 or (tiles > 320 and T * k >= 48 * E), tiles
+    assert T * k * H * F <= 1.6e11 and T > 32
     d = synth.moe_layer_inputs(T, H, F, E, DTYPE, DEV, seed=T + H, zipf_s=zipf, with_next=True)
     shape = moe.make_shape(H, F, E, k, DTYPE)
     out = moe.LayerOutputs(shape, T, DTYPE, DEV, predict=True)
@@ -28,10 +31,10 @@ def _stages(shape, d, out):
 
 
 @pytest.mark.parametrize("T,H,F,E,k", [
-    (40, 64, 640, 64, 8),      # first GEMM of one K step: nothing to overlap in a tile
-    (40, 128, 704, 64, 8),     # two K steps; half a feature tile at the end
-    (40, 192, 640, 64, 8),     # three
-    (45, 256, 640, 64, 8),     # four; experts with a handful of rows
+    (40, 64, 1024, 64, 8),     # first GEMM of one K step: nothing to overlap in a tile
+    (40, 128, 1088, 64, 8),    # two K steps; half a feature tile at the end
+    (40, 192, 1024, 64, 8),    # three
+    (45, 256, 1024, 64, 8),    # four; experts with a handful of rows
     (300, 320, 4160, 8, 2),    # second GEMM: a quarter of a feature tile at the end, 65 K steps
     (600, 512, 8192, 4, 2),    # tall and low tiles; work is taken over between XCDs
     (1500, 256, 2944, 3, 2),   # full tiles of several slot groups
