@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "bf16_utils.h"
+#include "hand_out.h"
 #include "moe_internal.h"
 
 // Everything is compiled into its kernel: what a call would return counts as different from lane to lane.
@@ -43,7 +44,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
-constexpr int kXcds = 8;
 constexpr int kMaxWgsPerXcd = 32;  // persistent grid: at most 8 x 32 workgroups
 
 // A launch uses kXcds counters (`sync`): the tiles handed out so far in each XCD (see persistent()); all zero when it starts.
@@ -253,10 +253,10 @@ __device__ GG_INLINE int swizzled(int row, int chunk) { return chunk ^ ((row >> 
 // slot rows (its weights are on their way by then).  act is stored through to memory, a tile is counted when all of its stores
 // have been acknowledged, and act is not read by anybody in this launch before that, so that no cache can hold an older copy.
 //
-// A workgroup only waits for tiles that others have already taken, and they wait for nobody in the first GEMM: in every XCD's list and,
-// when that is empty, the others', there is no tile left when it goes on.  So the wait ends whatever part of the grid is
-// resident.  It is bounded all the same (memory that an overlapping call clears must not hang the GPU): when it runs out
-// the status word is raised and the tile's results are NaN.
+// A workgroup only waits for tiles that others have already taken, and they wait for nobody in the first GEMM: every one of its tiles, a
+// workgroup's first included, is claimed from a counter (see owns_first()), and when a workgroup goes on, nothing is left to claim in any
+// XCD's list.  So the wait ends whatever part of the grid is resident.  It is bounded all the same (memory that an overlapping call
+// clears must not hang the GPU): when it runs out the status word is raised and the tile's results are NaN.
 //
 // Which calls: those whose first GEMM has more than two rounds of tiles, or more than five quarters of one and 48 rows an expert (with about one
 // there is nothing to fill, and handing act over costs 3 to 8 us: hidden 3584, ffn 1088, 2000 tokens 143 us apart / 151 linked; hidden and ffn 2048, 16 experts, 500 tokens, 1.1
@@ -883,9 +883,9 @@ __device__ GG_INLINE void choose_cut(const TileList& list, int N, int KT, int me
 // through the tile list in rounds of `members` consecutive tiles, so that its workgroups work on
 // tiles that share operand lines at about the same time and most lines are pulled into the
 // XCD's L2 once per round instead of once per workgroup.  A workgroup starts with the tile of
-// its member number and then takes the XCD's next tile from a counter whenever it has finished
+// its member number (or, see owns_first(), with one that it claims) and then takes the XCD's next tile from a counter whenever it has finished
 // one: tiles differ in cost (ragged slot tiles skip the MFMAs of their empty fragments, tiles
-// of cold experts wait for memory), and nobody waits for anybody.  Letting the members drift
+// of cold experts wait for memory), and the members of a round don't wait for each other.  Letting the members drift
 // apart by a fraction of a K step is also faster than holding them in step, because fewer of
 // them then ask for the same line at the same moment.
 //
@@ -913,9 +913,10 @@ __device__ GG_INLINE void choose_cut(const TileList& list, int N, int KT, int me
 // 64-expert shape at 1003 tokens, first GEMM 100.5 -> 103 us with it.  Between 32 and 64 K steps it does not matter (eight
 // shapes, hidden and ffn 2048 to 3584: within 2 % either way).  With 64 and 100 of the Phi shape, 700 tokens, 523 -> 509 us; 64 and
 // 224 of the Mixtral shape, 512 tokens, 630 -> 625, 4096 tokens, both GEMMs, 2168 -> 2164.
-// Returns the slots per tile.
+// claimed: thread 0's first claim of its XCD's counter, where workgroups don't own their first item (see owns_first()).  Returns the
+// slots per tile.
 template <class G>
-__device__ GG_INLINE int persistent(const GemmArgs& a, unsigned char* lds, TileList list, Link& link) {
+__device__ GG_INLINE int persistent(const GemmArgs& a, unsigned char* lds, TileList list, Link& link, int claimed = 0) {
     list.n_ft = (a.N + G::kBF - 1) / G::kBF;
     const int KT = a.K / 64;
     const int xcd = blockIdx.x % kXcds, member = blockIdx.x / kXcds;
@@ -971,7 +972,8 @@ __device__ GG_INLINE int persistent(const GemmArgs& a, unsigned char* lds, TileL
     }
     // Work items of an XCD in hand-out order: its whole tiles, then the pieces of its leftover tiles.
     const int n_whole = full_rounds * members;
-    auto left_of = [&](int x) GG_LAMBDA { return max(0, min(left, (x + 1) * chunk) - x * chunk); };
+    constexpr bool kOwnsFirst = owns_first(G::kLinked, G::kMats);
+    const HandOut<kOwnsFirst> hand{members, n_whole, left, chunk, parts};
     // rounds of `members` whole tiles that lie in the heavy part of the list / in the rest
     const int n_rounds = full_rounds * kXcds;
     const int heavy_rounds = min(n_rounds, min(list.heavy, first_left) / members);
@@ -983,7 +985,7 @@ __device__ GG_INLINE int persistent(const GemmArgs& a, unsigned char* lds, TileL
     auto decode = [&](int item, int from, typename G::Item& t) GG_LAMBDA {
         int tile_index, part = 0;
         if (item >= n_whole) {
-            const int rem = left_of(from), q = item - n_whole;  // piece number
+            const int rem = hand.left_of(from), q = item - n_whole;  // piece number
             part = q / rem;
             tile_index = first_left + from * chunk + q - part * rem;
             t.kt_begin = uniform(KT * part / parts);
@@ -1014,43 +1016,37 @@ __device__ GG_INLINE int persistent(const GemmArgs& a, unsigned char* lds, TileL
             }
         }
     };
-    // The counters hand out items `members`, `members` + 1, ...; a workgroup's first one is its member number.
     auto claim = [&](int from) GG_LAMBDA {
         int counter = from;
         asm volatile("" : "+v"(counter));  // (at an address that the compiler knows to be uniform it reads the result at once, and waits)
         return __hip_atomic_fetch_add(&a.sync[counter], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    auto settle_claim = [&](int claimed, int& item, int& from) GG_LAMBDA {
-        item = members + __builtin_amdgcn_readfirstlane(claimed);
-        if (item < n_whole + left_of(from) * parts) return;
+    auto settle_claim = [&](int n, int& item, int& from) GG_LAMBDA {
+        item = hand.claimed(__builtin_amdgcn_readfirstlane(n), from);
+        if (item >= 0) return;
         // That XCD's items are all handed out: go on with one of the XCD that has most left.
-        item = -1;
         if (KT < kMinStealKSteps && !(G::kLinked && G::kMats == 2)) return;
         const int lane = threadIdx.x & 63;
-        const int items = lane < kXcds ? n_whole + left_of(lane) * parts - members : 0;
         for (;;) {  // a try that loses the race has seen the victim's last item go: the sum of `open` falls every time
-            int open = lane < kXcds ? items - __hip_atomic_load(&a.sync[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+            int open = lane < kXcds ? hand.open(lane, __hip_atomic_load(&a.sync[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0;
             int most = 0;
             for (int x = 0; x < kXcds; ++x) {
                 const int o = __builtin_amdgcn_readlane(open, x);
                 if (o > most) { most = o; from = x; }
             }
             if (most == 0) return;
-            int n = 0;
-            if (lane == 0) n = __hip_atomic_fetch_add(&a.sync[from], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            n = __builtin_amdgcn_readfirstlane(n);
-            if (n < __builtin_amdgcn_readlane(items, from)) {
-                item = members + n;
-                return;
-            }
+            int got = 0;
+            if (lane == 0) got = __hip_atomic_fetch_add(&a.sync[from], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            item = hand.claimed(__builtin_amdgcn_readfirstlane(got), from);
+            if (item >= 0) return;
         }
     };
-    int item = member, from = xcd;
-    if (item >= n_whole + left_of(from) * parts) {
-        // (the XCD has fewer items than workgroups: this one looks elsewhere at once)
+    int item = hand.first(member, xcd), from = xcd;
+    if (item < 0) {
+        // (no item of its own: it takes one like everybody's second, or, where the XCD has fewer items than workgroups, looks elsewhere at once)
         int* handoff = reinterpret_cast<int*>(lds);
         if (threadIdx.x < 64) {
-            settle_claim(item - members, item, from);
+            settle_claim(kOwnsFirst ? hand.items(xcd) : claimed, item, from);
             if (threadIdx.x == 0) {
                 handoff[0] = item;
                 handoff[1] = from;
@@ -1081,9 +1077,11 @@ template <class First>
 __global__ __launch_bounds__(First::kThreads, 1) void linked_grouped_gemm_kernel(GemmArgs a, GemmArgs b, int32_t* done, uint32_t* status, int spin_limit) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds_dyn[];
     if ((int)blockIdx.x / kXcds >= min((int)gridDim.x / kXcds, kMaxWgsPerXcd)) return;
+    int claimed = 0;  // (requested before the list is built)
+    if (threadIdx.x == 0) claimed = __hip_atomic_fetch_add(&a.sync[blockIdx.x % kXcds], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const TileList list(a.offs, a.E);
     Link link{done, status, spin_limit, 0, 0, 0, false};
-    const int slots = persistent<First>(a, lds_dyn, list, link);
+    const int slots = persistent<First>(a, lds_dyn, list, link, claimed);
     link.need = list.slot_tiles(slots) * ((a.N + First::kBF - 1) / First::kBF);
     link.expert = list.count > 0 ? list.expert : 0;
     persistent<Gemm<1, false, false, false, true>>(b, lds_dyn, list, link);

@@ -106,3 +106,19 @@ def test_replays_from_a_graph():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(call.result["y"].view(torch.int16), ref.view(torch.int16)), step
+
+
+def test_two_streams_at_once():
+    """Two calls that share the chip, each with a workspace of its own: whatever part of a grid is resident at a time, a call ends and is right."""
+    d, shape, out = _layer(600, 512, 8192, 4, 2)
+    good = moe.run_layer(shape, d, out)["y"].clone()
+    calls = [(torch.cuda.Stream(), moe.LayerOutputs(shape, 600, DTYPE, DEV, predict=True)) for _ in range(2)]
+    torch.cuda.synchronize()
+    for _ in range(8):
+        for stream, o in calls:
+            with torch.cuda.stream(stream):
+                moe.run_layer(shape, d, o)
+        torch.cuda.synchronize()
+        for _, o in calls:
+            assert torch.equal(o.y.view(torch.int16), good.view(torch.int16))
+            assert not moe.moe_decode_status(o.workspace)
