@@ -276,21 +276,29 @@ struct Link {
     uint32_t* status;
     int spin_limit;
     int need, expert;    // lane r: of the expert of rank r
-    uint64_t ready;      // ranks whose act is complete
-    bool gave_up;
+    uint64_t ready;      // ranks whose act is complete (the same in all wavefronts)
+    unsigned char* told; // 8 bytes of LDS for share()
 
     __device__ GG_INLINE void finish(int e) { __hip_atomic_fetch_add(&done[e], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-    __device__ GG_INLINE void await(int rank) {
-        for (int n = 0; (ready >> rank & 1) == 0; ++n) {
-            if (n == spin_limit) {
-                if (threadIdx.x == 0) __hip_atomic_store(status, kDecodeGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                gave_up = true;
-                break;
-            }
-            if (n > 0) __builtin_amdgcn_s_sleep(8);
-            ready = __ballot(need == 0 || __hip_atomic_load(&done[expert], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= need);
-        }
+    __device__ GG_INLINE bool is_first() const { return threadIdx.x < 64; }
+    __device__ GG_INLINE void pause() const { __builtin_amdgcn_s_sleep(8); }
+    __device__ GG_INLINE uint64_t look() const {
+        return __ballot(need == 0 || __hip_atomic_load(&done[expert], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= need);
+    }
+    __device__ GG_INLINE void report() const {
+        if (threadIdx.x == 0) __hip_atomic_store(status, kDecodeGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ GG_INLINE uint64_t share(uint64_t r) const {
+        if (threadIdx.x == 0) *reinterpret_cast<uint64_t*>(told) = r;
+        lds_barrier();
+        r = *reinterpret_cast<const uint64_t*>(told);
+        return (uint64_t)(uint32_t)uniform((int)(r >> 32)) << 32 | (uint32_t)uniform((int)(uint32_t)r);
+    }
+    __device__ GG_INLINE bool await(int rank, unsigned char* lds_words) {
+        told = lds_words;
+        const bool complete = await_rank(rank, ready, spin_limit, *this);
         asm volatile("" ::: "memory");
+        return complete;
     }
 };
 
@@ -342,6 +350,7 @@ struct Gemm {
     static constexpr uint32_t kSlotBase = 3 * kStage; // weights: three stages from 0, slots: two stages from here
     static constexpr int kLdsBytes = 5 * kStage;
     static constexpr int kRowsOffset = 1024;          // row numbers of the next item's slots, 256 bytes a wavefront, behind the item's number
+    static constexpr int kToldOffset = 16;            // see Link::await()
 
     typedef __attribute__((address_space(3))) const unsigned char* lds_ptr;
     using Yes = std::true_type;
@@ -401,6 +410,7 @@ struct Gemm {
         float* out;          // where fp32 rows go
         uint32_t out_stride;
         int from;            // XCD whose list it is from
+        bool incomplete;     // second GEMM, LINKED: the wait for its slot rows ran out
     };
 
     // Works through items, beginning with `item`.  claim(from) takes the number of the next one off a list (one lane), settle_claim(n, item,
@@ -461,7 +471,7 @@ struct Gemm {
         };
         // First requests of an item: the row numbers of its slots (first GEMM), which go to the weight stage `w0` + 2 (not used
         // before its third K step), and its first weights, into stage w0.  The second GEMM's slot rows are consecutive rows: the first ones go out as well.
-        auto request_first = [&](const Item& t, uint32_t w0) GG_LAMBDA {
+        auto request_first = [&](Item& t, uint32_t w0) GG_LAMBDA {
             int tid = threadIdx.x;
             asm volatile("" : "+v"(tid));
             const int lane = tid & 63;
@@ -496,7 +506,7 @@ struct Gemm {
                     else
                         s_off[q] = (uint32_t)r * row_bytes + (uint32_t)chunk * 16;
                 }
-                if constexpr (LINKED) link.await(t.rank);
+                if constexpr (LINKED) t.incomplete = !link.await(t.rank, lds + next_w(next_w(w0)) + kToldOffset);
                 slot_stage0(t);
             }
         };
@@ -770,7 +780,7 @@ struct Gemm {
                         const int row = (2 * i + wt) * 16 + lr;
                         f32x4 v = *reinterpret_cast<const f32x4*>(own + lr * 512 + ((unit ^ lr) << 4));
                         if constexpr (LINKED)
-                            if (link.gave_up) v = f32x4{NAN, NAN, NAN, NAN};
+                            if (cur.incomplete) v = f32x4{NAN, NAN, NAN, NAN};
                         if (row < cur.rows && stores) *reinterpret_cast<f32x4*>(cur.out + (size_t)row * cur.out_stride + col) = v;
                     }
                     wave_order();
@@ -1080,7 +1090,7 @@ __global__ __launch_bounds__(First::kThreads, 1) void linked_grouped_gemm_kernel
     int claimed = 0;  // (requested before the list is built)
     if (threadIdx.x == 0) claimed = __hip_atomic_fetch_add(&a.sync[blockIdx.x % kXcds], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const TileList list(a.offs, a.E);
-    Link link{done, status, spin_limit, 0, 0, 0, false};
+    Link link{done, status, spin_limit, 0, 0, 0, nullptr};
     const int slots = persistent<First>(a, lds_dyn, list, link, claimed);
     link.need = list.slot_tiles(slots) * ((a.N + First::kBF - 1) / First::kBF);
     link.expert = list.count > 0 ? list.expert : 0;

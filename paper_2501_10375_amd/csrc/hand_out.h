@@ -1,5 +1,8 @@
-// Who computes which work item of a grouped GEMM: arithmetic alone, for the kernels and for a model of them on the host.
+// Who computes which work item of a grouped GEMM, and how a workgroup waits for items of others: without anything of the device, for the
+// kernels and for a model of them on the host.
 #pragma once
+
+#include <stdint.h>
 
 namespace moe {
 namespace gg {
@@ -36,6 +39,28 @@ struct HandOut {
     // What an XCD's counter, standing at `count`, has still to hand out (0 or less: nothing).
     __host__ __device__ __attribute__((always_inline)) int open(int xcd, int count) const { return items(xcd) - reserved() - count; }
 };
+
+// Waits until the expert of this rank is ready, in all wavefronts of a workgroup alike; false: the wait ran out.  Every wavefront multiplies
+// the rows that each of them loads, so there is one answer for all: the first wavefront looks (`ready`: ranks that are) and shares what it
+// has seen.  A workgroup that gave up once looks once from then on.
+template <class Wavefront>
+__host__ __device__ __attribute__((always_inline)) inline bool await_rank(int rank, uint64_t& ready, int& spin_limit, Wavefront& wavefront) {
+    if ((ready >> rank & 1) != 0) return true;
+    if (wavefront.is_first()) {
+        for (int n = 0; (ready >> rank & 1) == 0; ++n) {
+            if (n >= spin_limit) {
+                wavefront.report();
+                break;
+            }
+            if (n > 0) wavefront.pause();
+            ready = wavefront.look();
+        }
+    }
+    ready = wavefront.share(ready);
+    if ((ready >> rank & 1) != 0) return true;
+    if (spin_limit > 1) spin_limit = 1;
+    return false;
+}
 
 }  // namespace gg
 }  // namespace moe

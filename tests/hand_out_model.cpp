@@ -3,7 +3,10 @@
 #define __device__
 #include <stdint.h>
 
+#include <condition_variable>
+#include <mutex>
 #include <random>
+#include <thread>
 #include <vector>
 
 #include "hand_out.h"
@@ -70,7 +73,52 @@ void run(int members, int n_whole, int left, int parts, const unsigned char* res
     }
 }
 
+// Four wavefronts that each see the rank ready at another look of their own.
+struct Workgroup4 {
+    std::mutex m;
+    std::condition_variable all;
+    int arrived = 0, reports = 0;
+    uint64_t told = 0;
+};
+struct Wavefront {
+    Workgroup4& wg;
+    int number, ready_at, looks;
+    uint64_t bit;
+
+    bool is_first() const { return number == 0; }
+    void pause() const {}
+    uint64_t look() { return ++looks >= ready_at ? bit : 0; }
+    void report() const {
+        std::lock_guard<std::mutex> l(wg.m);
+        ++wg.reports;
+    }
+    uint64_t share(uint64_t r) const {
+        std::unique_lock<std::mutex> l(wg.m);
+        if (number == 0) wg.told = r;
+        ++wg.arrived;
+        wg.all.notify_all();
+        wg.all.wait(l, [&] { return wg.arrived % 4 == 0; });
+        return wg.told;
+    }
+};
+
 }  // namespace
+
+// Lets four wavefronts wait for one rank; answers[w]: what wavefront w goes on with.  Returns how many have reported a wait that ran out.
+extern "C" int await_model(int rank, int spin_limit, const int* ready_at, int* answers, int* limit_after) {
+    Workgroup4 wg;
+    std::vector<std::thread> threads;
+    for (int w = 0; w < 4; ++w)
+        threads.emplace_back([&, w] {
+            Wavefront f{wg, w, ready_at[w], 0, (uint64_t)1 << rank};
+            uint64_t ready = 0;
+            int limit = spin_limit;
+            answers[w] = await_rank(rank, ready, limit, f) ? 1 : 0;
+            limit_after[w] = limit;
+        });
+    for (std::thread& t : threads) t.join();
+    return wg.reports;
+}
 
 // Lets the workgroups with resident[block] != 0 work until each finds nothing more; done[xcd * stride + item] counts what they have computed.
 extern "C" int hand_out_model(int linked, int mats, int members, int n_whole, int left, int parts, const unsigned char* resident, int steal,

@@ -88,6 +88,29 @@ def test_reports_when_a_wait_runs_out():
     assert not moe.moe_decode_status(out.workspace)
 
 
+@pytest.mark.parametrize("T,H,F,E,k", [(300, 256, 4160, 8, 2), (600, 512, 8192, 4, 2)])
+def test_what_is_not_right_is_nan_and_reported(T, H, F, E, k):
+    """Waits that run out for some workgroups and not for others, and close to the moment when the rows are complete."""
+    d, shape, out = _layer(T, H, F, E, k)
+    good = moe.run_layer(shape, d, out)["y"].clone()
+    assert not moe.moe_decode_status(out.workspace, reset=True)
+    reported = 0
+    try:
+        for limit in [*range(1, 25)] * 6:
+            moe.moe_measure_set_decode_spin_limit(limit)
+            out.workspace.fill_(0x3F)   # rows that are read too early are finite and wrong
+            y = moe.run_layer(shape, d, out)["y"]
+            torch.cuda.synchronize()
+            nan = torch.isnan(y.float())
+            assert bool(((y.view(torch.int16) == good.view(torch.int16)) | nan).all()), limit
+            raised = moe.moe_decode_status(out.workspace, reset=True)
+            assert raised == bool(nan.any()), limit
+            reported += raised
+    finally:
+        moe.moe_measure_set_decode_spin_limit(1 << 22)
+    assert reported > 0
+
+
 def test_replays_from_a_graph():
     d, shape, out = _layer(300, 256, 4160, 8, 2)
     x = d["x"].clone()

@@ -1,6 +1,7 @@
 """Where both grouped GEMMs run in one launch, workgroups of the second wait for tiles of the first.  That ends whatever part of the grid is
 resident (another stream or a CU mask may hold the rest back) only if the resident workgroups alone can come to every tile of the
-first GEMM.  A host model of the hand-out, on the arithmetic that the kernels use, looks at that."""
+first GEMM.  A host model of the hand-out, on the arithmetic that the kernels use, looks at that.  Where a wait runs out all the same, the
+wavefronts of a workgroup, which multiply each other's rows, have to agree about it."""
 import ctypes
 import os
 import random
@@ -15,11 +16,15 @@ XCDS = 8
 
 
 @pytest.fixture(scope="module")
-def model(tmp_path_factory):
+def library(tmp_path_factory):
     path = str(tmp_path_factory.mktemp("hand_out") / "model.so")
-    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", path, os.path.join(HERE, "hand_out_model.cpp")], check=True)
-    lib = ctypes.CDLL(path)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-pthread", "-I", CSRC, "-o", path, os.path.join(HERE, "hand_out_model.cpp")],
+                   check=True)
+    return ctypes.CDLL(path)
 
+
+@pytest.fixture(scope="module")
+def model(library):
     def run(linked, mats, members, tiles, parts, resident, seed, steal=True):
         """How often each item is computed by the resident workgroups, [XCD][item]; items that no list has are -1."""
         rounds = tiles // (XCDS * members)
@@ -29,7 +34,7 @@ def model(tmp_path_factory):
         stride = max(items) + 1
         done = np.zeros((XCDS, stride), dtype=np.int32)
         mask = (ctypes.c_ubyte * (XCDS * members))(*resident)
-        lib.hand_out_model(int(linked), mats, members, rounds * members, left, parts, mask, int(steal), ctypes.c_uint(seed),
+        library.hand_out_model(int(linked), mats, members, rounds * members, left, parts, mask, int(steal), ctypes.c_uint(seed),
                            done.ctypes.data_as(ctypes.c_void_p), stride)
         for x in range(XCDS):
             assert (done[x, items[x]:] == 0).all()
@@ -75,3 +80,14 @@ def test_the_model_sees_items_that_nobody_holds(model):
     """Where a workgroup's first item is its own (launches in which nobody waits), half of the grid leaves the other half's."""
     done = model(False, 2, 32, 1008, 1, [int(i < 128) for i in range(256)], 1)
     assert (done == 0).sum() == 128 and (done <= 1).all()
+
+
+@pytest.mark.parametrize("ready_at", [(1, 1, 1, 1), (1, 9, 1, 1), (9, 1, 1, 1), (1, 9, 9, 9), (4, 5, 4, 5), (5, 4, 5, 4), (99, 99, 99, 99)])
+@pytest.mark.parametrize("limit", [0, 1, 4])
+def test_the_wavefronts_of_a_workgroup_give_up_together(library, ready_at, limit):
+    answers, after = (ctypes.c_int * 4)(), (ctypes.c_int * 4)()
+    reports = library.await_model(63, limit, (ctypes.c_int * 4)(*ready_at), answers, after)
+    assert len(set(answers)) == 1 and len(set(after)) == 1
+    assert reports == (0 if answers[0] else 1)
+    assert answers[0] == (ready_at[0] <= limit)
+    assert after[0] == (limit if answers[0] else min(limit, 1))
