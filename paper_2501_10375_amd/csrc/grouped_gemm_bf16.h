@@ -413,8 +413,11 @@ struct Gemm {
         bool incomplete;     // second GEMM, LINKED: the wait for its slot rows ran out
     };
 
-    // Works through items, beginning with `item`.  claim(from) takes the number of the next one off a list (one lane), settle_claim(n, item,
+    // Works through items, beginning with `cur`.  claim(from) takes the number of the next one off a list (one lane), settle_claim(n, item,
     // from) turns it into an item's number and its list (wavefront 0; -1: none left), and decode(item, from, Item&) says what that is.
+    // claims: whether the lists have anything to claim.  In a GEMM of one round they have not, and the claim and the look at the other
+    // lists would stand between a tile's last MFMA and its stores (hidden 4096, ffn 3584, 8 experts, 64 tokens, first GEMM 88.8 -> 83.0 us, second
+    // 54.5 -> 48.1; hidden 4096, ffn 512, 16 experts, 200 tokens, first 51.2 -> 44.2).
     //
     // The wavefronts go from tile to tile without emptying the memory pipe: the next item is claimed two K steps before the end of a
     // tile; when the last operands have been read, its first weights, the row numbers of its slots and then its first slot rows are
@@ -425,7 +428,7 @@ struct Gemm {
     // tokens 381 -> 368 us, 64 experts of hidden 2048 and ffn 1408, 3000 tokens 437 -> 429, Mixtral shape 512 to 4096 tokens 0.3 to 0.7 %.)
     template <class Claim, class SettleClaim, class Decode>
     static __device__ GG_INLINE void run(const GemmArgs& a, unsigned char* lds, Item cur, const Claim& claim, const SettleClaim& settle_claim,
-                                      const Decode& decode, Link& link) {
+                                      const Decode& decode, bool claims, Link& link) {
         const int N = a.N, K = a.K;
         const lds_ptr lds3 = (lds_ptr)lds;
         const uint32_t lds0 = (uint32_t)(uintptr_t)lds3;
@@ -663,7 +666,7 @@ struct Gemm {
                           wave_lds + w2, k_off);
                 // Outstanding, oldest first: weights of K step kt + 1, its slots, weights of K step kt + 2, or the first wavefront's claim.
                 if constexpr (decltype(more)::value) wait_vmcnt<8>();
-                else if (wave == 0) wait_vmcnt<1>();
+                else if (wave == 0 && claims) wait_vmcnt<1>();
                 else wait_vmcnt<0>();
                 lds_barrier();
                 half_step(Yes{}, Buf1{}, Yes{}, 0, w1, s1, std::conditional_t<decltype(more)::value, Slots, None>{},
@@ -684,7 +687,7 @@ struct Gemm {
             }
             // The next item is claimed now; the answer is needed after the last K step.
             int claimed = 0;
-            if (tid == 0) claimed = claim(cur.from);
+            if (claims && tid == 0) claimed = claim(cur.from);
             if (KT > 1) k_step(No{});
             half_step(Yes{}, Buf0{}, Yes{}, 1, w_stage, s_stage, None{}, 0u, 0u);
             half_step(Yes{}, Buf1{}, No{}, 0, 0u, 0u, None{}, 0u, 0u);
@@ -699,8 +702,8 @@ struct Gemm {
             const uint32_t handoff = next_w(w_stage);
             asm volatile("" ::"v"(claimed));  // (every wavefront waits here: where the answer may be outstanding, the main loop gets waits for it)
             if (wave == 0) {
-                int item, from = cur.from;
-                settle_claim(claimed, item, from);
+                int item = -1, from = cur.from;
+                if (claims) settle_claim(claimed, item, from);
                 if (tid == 0) *reinterpret_cast<int2*>(lds + handoff) = make_int2(item, from);
             }
             lds_barrier();  // every wavefront is done reading operand tiles; no load is outstanding
@@ -1055,6 +1058,7 @@ __device__ GG_INLINE int persistent(const GemmArgs& a, unsigned char* lds, TileL
     if (item < 0) {
         // (no item of its own: it takes one like everybody's second, or, where the XCD has fewer items than workgroups, looks elsewhere at once)
         int* handoff = reinterpret_cast<int*>(lds);
+        if (!hand.any()) return slots;
         if (threadIdx.x < 64) {
             settle_claim(kOwnsFirst ? hand.items(xcd) : claimed, item, from);
             if (threadIdx.x == 0) {
@@ -1070,7 +1074,7 @@ __device__ GG_INLINE int persistent(const GemmArgs& a, unsigned char* lds, TileL
     }
     typename G::Item first;
     decode(item, from, first);
-    G::run(a, lds, first, claim, settle_claim, decode, link);
+    G::run(a, lds, first, claim, settle_claim, decode, hand.any(), link);
     return slots;
 }
 

@@ -38,6 +38,8 @@ struct HandOut {
     }
     // What an XCD's counter, standing at `count`, has still to hand out (0 or less: nothing).
     __host__ __device__ __attribute__((always_inline)) int open(int xcd, int count) const { return items(xcd) - reserved() - count; }
+    // Whether the counters have anything to hand out (the first XCD's list is the longest).
+    __host__ __device__ __attribute__((always_inline)) bool any() const { return items(0) > reserved(); }
 };
 
 // Waits until the expert of this rank is ready, in all wavefronts of a workgroup alike; false: the wait ran out.  Every wavefront multiplies

@@ -22,11 +22,12 @@ struct Workgroup {
 
 // One step of a workgroup, at most one access to the counters in each (the kernel's settle_claim()).
 template <bool OWN>
-void step(Workgroup& w, const HandOut<OWN>& hand, int (&counter)[kXcds], bool steal, int* done, int stride) {
+void step(Workgroup& w, const HandOut<OWN>& hand, int (&counter)[kXcds], bool steal, int* done, int stride, int& accesses) {
+    if (w.state != kItem) ++accesses;
     switch (w.state) {
         case kItem:
             ++done[w.from * stride + w.item];
-            w.state = kOwn;
+            w.state = hand.any() ? kOwn : kEnd;
             break;
         case kOwn: {
             w.item = hand.claimed(counter[w.from]++, w.from);
@@ -51,26 +52,27 @@ void step(Workgroup& w, const HandOut<OWN>& hand, int (&counter)[kXcds], bool st
 }
 
 template <bool OWN>
-void run(int members, int n_whole, int left, int parts, const unsigned char* resident, bool steal, unsigned seed, int* done, int stride) {
+int run(int members, int n_whole, int left, int parts, const unsigned char* resident, bool steal, unsigned seed, int* done, int stride) {
     const HandOut<OWN> hand{members, n_whole, left, (left + kXcds - 1) / kXcds, parts};
-    int counter[kXcds] = {0};
+    int counter[kXcds] = {0}, accesses = 0;
     std::mt19937 rng(seed);
     std::vector<Workgroup> live;
     for (int b = 0; b < members * kXcds; ++b) {
         if (!resident[b]) continue;
         Workgroup w{b % kXcds, b / kXcds, kOwn, hand.first(b / kXcds, b % kXcds), b % kXcds};
         if (w.item >= 0) w.state = kItem;
-        else if (OWN) w.state = steal ? kLook : kEnd;  // (more workgroups than items)
-        live.push_back(w);
+        else if (OWN) w.state = steal && hand.any() ? kLook : kEnd;  // (more workgroups than items)
+        if (w.state != kEnd) live.push_back(w);
     }
     while (!live.empty()) {
         const size_t i = rng() % live.size();
-        step(live[i], hand, counter, steal, done, stride);
+        step(live[i], hand, counter, steal, done, stride, accesses);
         if (live[i].state == kEnd) {
             live[i] = live.back();
             live.pop_back();
         }
     }
+    return accesses;
 }
 
 // Four wavefronts that each see the rank ready at another look of their own.
@@ -121,10 +123,10 @@ extern "C" int await_model(int rank, int spin_limit, const int* ready_at, int* a
 }
 
 // Lets the workgroups with resident[block] != 0 work until each finds nothing more; done[xcd * stride + item] counts what they have computed.
+// Returns how often they have been at the counters.
 extern "C" int hand_out_model(int linked, int mats, int members, int n_whole, int left, int parts, const unsigned char* resident, int steal,
                               unsigned seed, int* done, int stride) {
     const bool own = linked ? (mats == 2 ? owns_first(true, 2) : owns_first(true, 1)) : owns_first(false, mats);
-    if (own) run<true>(members, n_whole, left, parts, resident, steal != 0, seed, done, stride);
-    else run<false>(members, n_whole, left, parts, resident, steal != 0, seed, done, stride);
-    return own ? 1 : 0;
+    return own ? run<true>(members, n_whole, left, parts, resident, steal != 0, seed, done, stride)
+               : run<false>(members, n_whole, left, parts, resident, steal != 0, seed, done, stride);
 }

@@ -34,7 +34,7 @@ def model(library):
         stride = max(items) + 1
         done = np.zeros((XCDS, stride), dtype=np.int32)
         mask = (ctypes.c_ubyte * (XCDS * members))(*resident)
-        library.hand_out_model(int(linked), mats, members, rounds * members, left, parts, mask, int(steal), ctypes.c_uint(seed),
+        run.accesses = library.hand_out_model(int(linked), mats, members, rounds * members, left, parts, mask, int(steal), ctypes.c_uint(seed),
                            done.ctypes.data_as(ctypes.c_void_p), stride)
         for x in range(XCDS):
             assert (done[x, items[x]:] == 0).all()
@@ -80,6 +80,13 @@ def test_the_model_sees_items_that_nobody_holds(model):
     """Where a workgroup's first item is its own (launches in which nobody waits), half of the grid leaves the other half's."""
     done = model(False, 2, 32, 1008, 1, [int(i < 128) for i in range(256)], 1)
     assert (done == 0).sum() == 128 and (done <= 1).all()
+
+
+@pytest.mark.parametrize("mats", [1, 2])
+@pytest.mark.parametrize("tiles,parts,accesses", [(5, 1, 0), (128, 2, 0), (256, 1, 0), (129, 2, 1), (257, 1, 1), (512, 1, 1)])
+def test_one_round_does_without_the_counters(model, mats, tiles, parts, accesses):
+    model(False, mats, 32, tiles, parts, [1] * 256, 3)
+    assert (model.accesses > 0) == accesses
 
 
 @pytest.mark.parametrize("ready_at", [(1, 1, 1, 1), (1, 9, 1, 1), (9, 1, 1, 1), (1, 9, 9, 9), (4, 5, 4, 5), (5, 4, 5, 4), (99, 99, 99, 99)])
