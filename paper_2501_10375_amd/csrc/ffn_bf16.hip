@@ -295,14 +295,12 @@ hipError_t launch_ffn_bf16(const moe_shape_t& s, int tokens, const void* x, cons
     g2.table = g1.table + 1;
     const bool alternate = alt.stale != nullptr;
     const int routed = tokens * s.top_k;
-    const long most_tiles = (long)((s.ffn + 127) / 128) * (routed / 256 + min(s.n_experts, routed));
+    const long slot_tiles = routed / 256 + min(s.n_experts, routed);  // at most
+    const long most_tiles = (s.ffn + 127) / 128 * slot_tiles;
     hipError_t e;
     const bool wide2 = gg::needs_wide(0, 256, s.ffn), wide1 = wide2 || gg::needs_wide((size_t)tokens * s.hidden * 2, gg::Gemm<2>::kBF, s.hidden);
     const bool cut = !wide1 && most_tiles <= gg::kMaxCutTiles && s.hidden / 64 >= gg::kMinCutKSteps;
-    const bool many_tiles = most_tiles > persistent_grid() * 2 ||
-                            (most_tiles * 4 > persistent_grid() * 5 && routed >= gg::kMinLinkedRows * min(s.n_experts, routed));
-    const bool link = !wide1 && many_tiles && (double)routed * s.hidden * s.ffn <= gg::kMaxLinkedMacs;
-    if (link) {
+    if (!wide1 && gg::links(most_tiles, (s.hidden + 255) / 256 * slot_tiles, persistent_grid(), routed, s.n_experts, s.hidden, s.ffn)) {
         int32_t* done = sync + gg::kXcds;
         e = alternate ? launch_linked<true>(g1, g2, done, status, stream) : launch_linked<false>(g1, g2, done, status, stream);
         stage_mark(stream, kStageFused);

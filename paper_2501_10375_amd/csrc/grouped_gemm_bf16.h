@@ -258,19 +258,7 @@ __device__ GG_INLINE int swizzled(int row, int chunk) { return chunk ^ ((row >> 
 // XCD's list.  So the wait ends whatever part of the grid is resident.  It is bounded all the same (memory that an overlapping call
 // clears must not hang the GPU): when it runs out the status word is raised and the tile's results are NaN.
 //
-// Which calls: those whose first GEMM has more than two rounds of tiles, or more than five quarters of one and 48 rows an expert (with about one
-// there is nothing to fill, and handing act over costs 3 to 8 us: hidden 3584, ffn 1088, 2000 tokens 143 us apart / 151 linked; hidden and ffn 2048, 16 experts, 500 tokens, 1.1
-// rounds 137 / 139; 1.4 rounds, hidden 4096, ffn 2048, 1000 tokens 203 / 200; with few rows an expert the tiles of a
-// partial second round stream faster the fewer they are, and nothing is idle that could be filled: hidden 2432, ffn 2624, 16 experts, 1.3 rounds, 14 rows
-// 143 / 150, 38 rows 149 / 156, 32 experts, 2.6 rounds 241 / 241; hidden 1024, ffn 4096, 12 experts, 1.5 rounds, 17 rows 82 / 89; hidden 4096, ffn 2048,
-// 16 experts, 1.3 rounds, 88 rows 218 / 205; hidden 2048, ffn 2816, 16 experts, 1.6 rounds, 63 rows 157 / 155; hidden and ffn 2048, 16 experts, 1.9 rounds, 250 rows
-// 171 / 155; hidden 3008, ffn 5632, 12 experts, 2.1 rounds, 6 rows 259 / 246), and at most 1.6e11 products of a routed row and a weight.  Beyond, the chip is at its power
-// limit, where time that is saved comes back as clock that is lost, and workgroups that enter the second GEMM at different times share
-// fewer lines of its tall tiles.  Whole layer, apart / linked: Mixtral shape 200 tokens 526 / 511 us, 512 616 / 593, 1024 776 / 764,
-// but 1400 (1.64e11) 932 / 945, 2048 1214 / 1235; Phi shape 700 tokens 481 / 474, 2048 757 / 749, 3500 1037 / 1024, 6000 1622 / 1624; 64 experts of
-// hidden 2048 and ffn 1408, 1003 tokens 276 / 269, 3000 429 / 413; hidden 3008, ffn 5632, 12 experts, 200 tokens 290 / 261.
-constexpr double kMaxLinkedMacs = 1.6e11;
-constexpr int kMinLinkedRows = 48;
+// Which calls: see links().
 struct Link {
     int32_t* done;       // tiles of the first GEMM that are stored, per expert (null: not linked)
     uint32_t* status;
@@ -301,6 +289,31 @@ struct Link {
         return complete;
     }
 };
+
+// Whether a call runs both GEMMs in one launch.  first, second: tiles of 256 slots that the two can have at most, grid: workgroups.  Handing act
+// over costs 5 to 15 us; what it gives is the end of the first GEMM, filled with tiles of the second whose experts are complete.  So:
+//   * more than two and a half rounds of the first GEMM (else little else is running while an expert completes), three quarters of a round of the
+//     second, and 4e5 routed elements of the hidden dimension (with fewer the second GEMM is over as soon as it begins).  With 2e10 products of a
+//     routed row and a weight, which take half a millisecond, nine sixteenths of a round of the second will do;
+//   * or more than five quarters of a round of the first with 48 rows an expert, if the second has more than a round;
+//   * in both cases at most 300 rows an expert, beyond which the second GEMM waits for too many tiles at a time, and 1.6e11 products, beyond
+//     which the chip is at its power limit: time that is saved comes back as clock that is lost.
+// Whole layer in us, apart / linked (hidden, ffn, experts, top-k, tokens; 184 sizes were timed).  Linked: 2048, 1408, 64, 6, 40 207 / 199, 400 248 / 236,
+// 1003 284 / 277, 2500 375 / 363; 4096, 14336, 8, 2, 200 505 / 483, 512 617 / 594, 1024 783 / 768; 4096, 6400, 16, 2, 200 380 / 378, 2048 763 / 752; 2112, 5888, 16, 4,
+// 349 +3.4 %; 4096, 2048, 16, 2, 700 238 / 223; 3456, 2624, 16, 1, 1616 +3.8 %.  On 90 sizes drawn after the rule was made, 25 of them linked, those are
+// 2.6 % faster so on average, the worst is 1024, 1472, 64, 3, 1187 with 146 / 150.  Apart, few rounds or rows:
+// 2432, 2624, 16, 2, 108 142 / 154, 300 150 / 158, 800 173 / 178; 1024, 4096, 12, 2, 100 78 / 86; 1536, 1984, 32, 3, 100 124 / 130; 3008, 5632, 16, 1, 100
+// 292 / 305; 64, 1024, 64, 8, 40 43 / 47; little of the second: 640, 5824, 16, 3, 46 84 / 92; 1600, 4544, 16, 1, 47 75 / 88; 1024, 4032, 12, 2, 1052 113 / 120;
+// 4096, 14336, 8, 2, 50 497 / 501, 77 512 / 514; many rows: 1664, 5888, 4, 4, 885 206 / 216; 3328, 7744, 4, 2, 1865 477 / 485; 896, 1792, 16, 4, 1554 106 / 121;
+// long: 4096, 14336, 8, 2, 1400 932 / 945, 2048 1214 / 1235.  What this gives away: 3008, 5632, 12, 1, 66 259 / 242; 3648, 1664, 32, 1, 290 218 / 203.
+constexpr bool links(long first, long second, int grid, long routed, int experts, long hidden, long ffn) {
+    const long active = routed < experts ? routed : experts;
+    const double macs = (double)routed * hidden * ffn;
+    if (routed > 300 * active || macs > 1.6e11) return false;
+    const bool long_first = first * 2 > grid * 5L && routed * hidden >= 400000 &&
+                            (second * 4 >= grid * 3L || (second * 16 >= grid * 9L && macs >= 2e10));
+    return long_first || (first * 4 > grid * 5L && second * 6 >= grid * 7L && routed >= 48 * active);
+}
 
 // ---- one tile: up to 256 slots x 256 weight rows, one wavefront per SIMD.
 //

@@ -11,12 +11,13 @@ pytestmark = pytest.mark.gpu
 DEV, DTYPE = "cuda", torch.bfloat16
 
 
-def _layer(T, H, F, E, k, zipf=1.2):
-    # the route: more than two rounds of the first GEMM's tiles (256 compute units), whatever the routing, or more than five quarters of
-    # one with 48 rows an expert
-    tiles = -(-F // 128) * (T * k // 256 + min(E, T * k))
-    assert tiles > 512 or (tiles > 320 and T * k >= 48 * E), tiles
-    assert T * k * H * F <= 1.6e11 and T > 32
+def _layer(T, H, F, E, k, zipf=1.2, linked=True):
+    # the route (256 compute units), whatever the routing: two and a half rounds of the first GEMM's tiles and three quarters of the second's,
+    # or five quarters of both with 48 rows an expert; 300 rows an expert at most
+    slot_tiles = T * k // 256 + min(E, T * k)
+    first, second = -(-F // 128) * slot_tiles, -(-H // 256) * slot_tiles
+    route = (first > 640 and second >= 192 and T * k * H >= 4e5) or (first > 320 and second >= 300 and T * k >= 48 * E)
+    assert linked == (route and T * k <= 300 * E and T * k * H * F <= 1.6e11 and T > 32), (first, second)
     d = synth.moe_layer_inputs(T, H, F, E, DTYPE, DEV, seed=T + H, zipf_s=zipf, with_next=True)
     shape = moe.make_shape(H, F, E, k, DTYPE)
     out = moe.LayerOutputs(shape, T, DTYPE, DEV, predict=True)
@@ -31,6 +32,19 @@ def _stages(shape, d, out):
 
 
 @pytest.mark.parametrize("T,H,F,E,k", [
+    (1024, 320, 896, 64, 8),   # five K steps in the first GEMM: the fewest; a quarter of a feature tile at the end of the second
+    (88, 576, 1344, 64, 8),    # nine K steps; half a feature tile at the end; experts with a handful of rows
+    (100, 1088, 1728, 48, 4),
+    (600, 2048, 1024, 32, 4),  # little more than a round of both
+    (512, 2560, 4160, 16, 2),  # tall and low tiles, 65 K steps in the second GEMM; work is taken over between XCDs
+    (1500, 1536, 2560, 16, 3), # full tiles of several slot groups
+    (900, 576, 1600, 64, 1),   # skewed routing over many experts, some without rows
+])
+def test_every_token(oracle, T, H, F, E, k):
+    _every_token(oracle, T, H, F, E, k, True)
+
+
+@pytest.mark.parametrize("T,H,F,E,k", [
     (40, 64, 1024, 64, 8),     # first GEMM of one K step: nothing to overlap in a tile
     (40, 128, 1088, 64, 8),    # two K steps; half a feature tile at the end
     (40, 192, 1024, 64, 8),    # three
@@ -40,10 +54,15 @@ def _stages(shape, d, out):
     (1500, 256, 2944, 3, 2),   # full tiles of several slot groups
     (900, 192, 1600, 64, 1),   # skewed routing over many experts, some without rows
 ])
-def test_every_token(oracle, T, H, F, E, k):
-    d, shape, out = _layer(T, H, F, E, k, zipf=3.0 if k == 1 else 1.2)
+def test_every_token_of_two_launches(oracle, T, H, F, E, k):
+    """Two rounds of the first GEMM with too little of the second for one launch."""
+    _every_token(oracle, T, H, F, E, k, False)
+
+
+def _every_token(oracle, T, H, F, E, k, linked):
+    d, shape, out = _layer(T, H, F, E, k, zipf=3.0 if k == 1 else 1.2, linked=linked)
     res, stages = _stages(shape, d, out)
-    assert stages["fused"][1] == 1 and stages["gemm1"][1] == stages["gemm2"][1] == 0, stages
+    assert stages["fused"][1] == linked and stages["gemm1"][1] == stages["gemm2"][1] == (not linked), stages
     r = check_layer(oracle, d, shape, res, DTYPE, label=f"linked T={T}")
     print(r)
     assert r["compared_tokens"] >= T - r["excluded"] - 2
@@ -71,7 +90,7 @@ def test_every_token(oracle, T, H, F, E, k):
 
 def test_reports_when_a_wait_runs_out():
     """With no polling round allowed (every kernel still runs to its end) the output is NaN and the status word is raised."""
-    d, shape, out = _layer(300, 256, 4160, 8, 2)
+    d, shape, out = _layer(88, 576, 1344, 64, 8)
     good = moe.run_layer(shape, d, out)["y"].clone()
     assert not moe.moe_decode_status(out.workspace, reset=True)
     try:
@@ -88,7 +107,7 @@ def test_reports_when_a_wait_runs_out():
     assert not moe.moe_decode_status(out.workspace)
 
 
-@pytest.mark.parametrize("T,H,F,E,k", [(300, 256, 4160, 8, 2), (600, 512, 8192, 4, 2)])
+@pytest.mark.parametrize("T,H,F,E,k", [(88, 576, 1344, 64, 8), (512, 2560, 4160, 16, 2)])
 def test_what_is_not_right_is_nan_and_reported(T, H, F, E, k):
     """Waits that run out for some workgroups and not for others, and close to the moment when the rows are complete."""
     d, shape, out = _layer(T, H, F, E, k)
@@ -112,17 +131,17 @@ def test_what_is_not_right_is_nan_and_reported(T, H, F, E, k):
 
 
 def test_replays_from_a_graph():
-    d, shape, out = _layer(300, 256, 4160, 8, 2)
+    d, shape, out = _layer(88, 576, 1344, 64, 8)
     x = d["x"].clone()
     call = moe.PreparedLayerCall(shape, dict(d, x=x), out)
-    eager = moe.LayerOutputs(shape, 300, DTYPE, DEV, predict=True)
+    eager = moe.LayerOutputs(shape, 88, DTYPE, DEV, predict=True)
     call()
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
         call()
     for step in range(4):
-        xs = synth.normal((300, 256), 700 + step, synth.TID_X, 1.0, DTYPE, DEV)
+        xs = synth.normal((88, 576), 700 + step, synth.TID_X, 1.0, DTYPE, DEV)
         ref = moe.run_layer(shape, dict(d, x=xs), eager)["y"].clone()
         torch.cuda.synchronize()
         x.copy_(xs)
@@ -133,9 +152,9 @@ def test_replays_from_a_graph():
 
 def test_two_streams_at_once():
     """Two calls that share the chip, each with a workspace of its own: whatever part of a grid is resident at a time, a call ends and is right."""
-    d, shape, out = _layer(600, 512, 8192, 4, 2)
+    d, shape, out = _layer(512, 2560, 4160, 16, 2)
     good = moe.run_layer(shape, d, out)["y"].clone()
-    calls = [(torch.cuda.Stream(), moe.LayerOutputs(shape, 600, DTYPE, DEV, predict=True)) for _ in range(2)]
+    calls = [(torch.cuda.Stream(), moe.LayerOutputs(shape, 512, DTYPE, DEV, predict=True)) for _ in range(2)]
     torch.cuda.synchronize()
     for _ in range(8):
         for stream, o in calls:
