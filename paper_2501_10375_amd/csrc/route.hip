@@ -98,8 +98,15 @@ constexpr int kRouteWaves = NBG == 1 ? 16 : 8;
 // selections: fp32, hidden 256, 64 tokens 25.9 -> 23.0 us, 500 tokens 37.1 -> 36.7; bf16, 1024 by 1024, 500 tokens 53.5 -> 53.0, Mixtral shape
 // 512 tokens 606.7 -> 604.1.  More passes, or 8 wavefronts of more than 16 experts, are no faster than workgroups that share it:
 // 2048 selections 773.6 -> 778.1, 64 experts, 1800 selections 251.8 -> 254.2, fp32 179.2 -> 182.3.
+//
+// Every workgroup reads all words, so the time grows with their number and with that of the workgroups.  Up to 3072 words and 256 workgroups
+// (what the chip holds at one a CU) a call that waits for the host gains up to 3 us and one that does not is as fast as with another launch;
+// beyond, it loses.  moe_route in us, another launch / so, replayed from a graph and called in a row: 8 experts, hidden 4096, 2048 tokens 9.6 / 9.7 and 12.5 / 9.7,
+// 4096 tokens 12.5 / 12.8 and 12.6 / 12.6, 8192 tokens 21.7 / 23.9, 16384 tokens 38.2 / 49.8; 16 experts, 3000 tokens 11.9 / 11.4 and 12.0 / 11.2, 4096 tokens
+// 13.6 / 14.0 and 13.6 / 13.7; 32 experts, hidden 2048, 1500 tokens 10.8 / 11.0 and 12.0 / 11.0, 2048 tokens 10.8 / 12.1; 64 experts, 500 tokens 12.1 / 12.3 and
+// 12.8 / 12.5, 1000 tokens 13.0 / 13.8, 2048 tokens 14.3 / 17.4; fp32, 8 experts, hidden 1024, 4096 tokens 9.9 / 10.3 and 11.8 / 10.1, 8192 tokens 16.7 / 20.2.
 constexpr uint64_t kWordTag = 0x9E3779B97F4A7Cull << 8;
-constexpr int kFinishMaxWords = 8192, kFinishMaxSelections = 1024, kFinishMaxExperts = 16;
+constexpr int kFinishMaxWords = 3072, kFinishMaxBlocks = 256, kFinishMaxSelections = 1024, kFinishMaxExperts = 16;
 
 template <int WAVES>
 __device__ inline void finish_routing(const RouteFinish& f, const int32_t* idx, int n_blocks, int E, int A, const int* hist) {
@@ -342,7 +349,7 @@ RouteParams make_params(const moe_shape_t& s, int tokens, const void* x, const G
 }  // namespace
 
 bool route_finishes(const moe_shape_t& s, int tokens, bool permute) {
-    return (int64_t)route_blocks(tokens) * s.n_experts <= kFinishMaxWords &&
+    return route_blocks(tokens) <= kFinishMaxBlocks && (int64_t)route_blocks(tokens) * s.n_experts <= kFinishMaxWords &&
            (!permute || ((int64_t)tokens * s.top_k <= kFinishMaxSelections && s.n_experts <= kFinishMaxExperts));
 }
 

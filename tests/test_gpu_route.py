@@ -51,6 +51,8 @@ def _route(oracle, T, H, E, k, dtype):
     (512, 64, 16, 2),      # 1024 selections: the last workgroup permutes them
     (513, 64, 16, 2),      # one more than it takes
     (1040, 64, 3, 2),      # 65 blocks
+    (768, 64, 64, 1),      # 3072 counts: the most that the last workgroup adds
+    (4096, 64, 6, 1),      # 256 blocks: the most whose counts it adds
     (2100, 64, 64, 1),     # more counts than one workgroup adds
 ])
 def test_prefill_sizes(oracle, T, H, E, k, dtype):
@@ -109,3 +111,17 @@ def test_decode_step_tiles(oracle, T, H, F, E, k):
     shape = moe.make_shape(H, F, E, k, torch.bfloat16)
     out = moe.LayerOutputs(shape, T, torch.bfloat16, DEV, predict=True)
     check_layer(oracle, d, shape, moe.run_layer(shape, d, out), torch.bfloat16, label=f"decode T={T} H={H} F={F}")
+
+
+@pytest.mark.parametrize("T,E,launches", [(17, 8, 1), (4096, 8, 1), (4097, 8, 2), (768, 64, 1), (769, 64, 2), (16384, 8, 2)])
+def test_counts_of_long_calls_are_another_kernels(T, E, launches):
+    """Where every workgroup would read very many counts, that takes longer than a launch."""
+    d = synth.moe_layer_inputs(T, 64, 64, E, torch.bfloat16, DEV, seed=T, zipf_s=0.7, with_next=False)
+    shape = moe.make_shape(64, 64, E, 1, torch.bfloat16)
+    idx, w = torch.empty((T, 1), dtype=torch.int32, device=DEV), torch.empty((T, 1), device=DEV)
+    counts, ws = torch.empty(E, dtype=torch.int32, device=DEV), moe.alloc_workspace(shape, T, route_only=True)
+    moe.moe_stage_timing_begin(1)
+    moe.moe_route(shape, d["x"], d["wg"], d["bias"], idx, w, counts, False, ws)
+    stages = moe.moe_stage_timing_end()
+    assert stages["route"][1] + stages["permute"][1] == launches
+    assert torch.equal(counts, torch.bincount(idx.flatten(), minlength=E).int())
