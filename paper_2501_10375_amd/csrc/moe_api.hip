@@ -24,8 +24,7 @@ WorkspaceLayout workspace_layout(const moe_shape_t& s, int tokens) {
     size_t off = 0;
     L.dec_flags = off;   off = align_up(off + kDecodeFlagInts * sizeof(uint32_t));
     L.sync = off;        off = align_up(off + kSyncInts * sizeof(int32_t));
-    L.hist = off;        off = align_up(off + nb * s.n_experts * sizeof(int32_t));
-    L.hist_next = off;   off = align_up(off + nb * s.n_experts * sizeof(int32_t));
+    L.hist = off;        off += 2 * align_up(nb * s.n_experts * sizeof(int32_t));  // (RouteFinish::words are twice as wide)
     L.offs = off;        off = align_up(off + (size_t)(s.n_experts + 1) * sizeof(int32_t));
     L.row_of_slot = off; off = align_up(off + A * sizeof(int32_t));
     L.slot_of = off;     off = align_up(off + A * sizeof(int32_t));
@@ -147,7 +146,7 @@ bool decode_path(const moe_shape_t& s, int tokens) { return s.dtype == MOE_BF16 
 bool stream_path(const moe_shape_t& s, int tokens) { return s.dtype == MOE_BF16 && tokens <= kStreamMaxTokens; }
 
 struct Ws {
-    int32_t *hist, *hist_next, *offs, *row_of_slot, *slot_of, *sync;
+    int32_t *hist, *offs, *row_of_slot, *slot_of, *sync;
     uint32_t* dec_flags;
     void* act;
     float* out;
@@ -158,7 +157,6 @@ Ws carve(void* workspace, const WorkspaceLayout& L) {
     char* b = static_cast<char*>(workspace);
     Ws w;
     w.hist = reinterpret_cast<int32_t*>(b + L.hist);
-    w.hist_next = reinterpret_cast<int32_t*>(b + L.hist_next);
     w.offs = reinterpret_cast<int32_t*>(b + L.offs);
     w.row_of_slot = reinterpret_cast<int32_t*>(b + L.row_of_slot);
     w.slot_of = reinterpret_cast<int32_t*>(b + L.slot_of);
@@ -170,13 +168,13 @@ Ws carve(void* workspace, const WorkspaceLayout& L) {
     return w;
 }
 
-// Routing for one or two gates.  With `permute`, also leaves offs / row_of_slot / slot_of in
+// Routing for one or two gates; counts (may be null) of the first one's selections.  With `permute`, also leaves offs / row_of_slot / slot_of in
 // the workspace for the grouped GEMMs.
 hipError_t run_route(const moe_shape_t& s, int tokens, const void* x, GateArgs* gates, int n_gates, int32_t* counts,
-                     int accumulate, int32_t* counts_next, bool permute, const Ws& ws, hipStream_t stream) {
+                     int accumulate, bool permute, const Ws& ws, hipStream_t stream) {
     if (tokens <= kDecodeMaxTokens) {
         // Decode-size calls: one workgroup routes every token and writes the counts itself.
-        hipError_t e = launch_route_small(s, tokens, x, gates, n_gates, counts, accumulate, counts_next, stream);
+        hipError_t e = launch_route_small(s, tokens, x, gates, n_gates, counts, accumulate, stream);
         stage_mark(stream, kStageRoute);
         if (e != hipSuccess || !permute) return e;
         e = launch_hist_from_idx(s, tokens, gates[0].idx, ws.hist, stream);
@@ -185,25 +183,23 @@ hipError_t run_route(const moe_shape_t& s, int tokens, const void* x, GateArgs* 
         stage_mark(stream, kStagePermute);
         return e;
     }
-    if ((counts != nullptr || permute) && counts_next == nullptr && route_finishes(s, tokens, permute)) {
+    if ((counts != nullptr || permute) && route_finishes(s, tokens, permute)) {
         const RouteFinish finish = {counts, accumulate, permute ? ws.offs : nullptr, permute ? ws.row_of_slot : nullptr,
                                     permute ? ws.slot_of : nullptr, permute ? ws.sync : nullptr, reinterpret_cast<uint64_t*>(ws.hist)};
         const hipError_t e = launch_route(s, tokens, x, gates, n_gates, &finish, stream);
         stage_mark(stream, kStageRoute);
         return e;
     }
-    gates[0].hist = ws.hist;
-    if (n_gates > 1) gates[1].hist = counts_next != nullptr ? ws.hist_next : nullptr;
+    // (a caller whose expert kernel counts the selections itself asks for neither)
+    const bool count = counts != nullptr || permute;
+    if (count) gates[0].hist = ws.hist;
     hipError_t e = launch_route(s, tokens, x, gates, n_gates, nullptr, stream);
     stage_mark(stream, kStageRoute);
     if (e != hipSuccess) return e;
-    if (counts != nullptr || permute)  // (a caller whose expert kernel counts the selections itself passes neither)
+    if (count)
         e = launch_finalize(s, tokens, ws.hist, gates[0].idx, counts, accumulate, permute ? ws.offs : nullptr,
                             permute ? ws.row_of_slot : nullptr, permute ? ws.slot_of : nullptr,
                             permute ? ws.sync : nullptr, stream);
-    if (e != hipSuccess) return e;
-    if (n_gates > 1 && counts_next != nullptr)
-        e = launch_finalize(s, tokens, ws.hist_next, gates[1].idx, counts_next, 0, nullptr, nullptr, nullptr, nullptr, stream);
     stage_mark(stream, kStagePermute);
     return e;
 }
@@ -274,7 +270,7 @@ int enqueue_layer(const moe_shape_t& s, int32_t tokens, const void* x, const voi
     const int n_gates = w_gate_next != nullptr ? 2 : 1;
     // 17 to 32 tokens: the weight-streaming kernel needs no permutation and counts the selections itself.
     const bool streaming = stream_path(s, tokens);
-    hipError_t e = run_route(s, tokens, x, g, n_gates, streaming ? nullptr : counts, accumulate, nullptr, !streaming, ws, stream);
+    hipError_t e = run_route(s, tokens, x, g, n_gates, streaming ? nullptr : counts, accumulate, !streaming, ws, stream);
     if (e != hipSuccess) return MOE_ERR_DEVICE;
     return dev(run_ffn(s, tokens, x, topk_idx, topk_w, w1, w3, w2, y, ws, stream, kNoStaleInput, streaming ? counts : nullptr,
                        accumulate));
@@ -336,7 +332,7 @@ int moe_route(const moe_shape_t* shape, int32_t tokens, const void* x, const voi
         return dev(launch_finalize(*shape, 0, ws.hist, nullptr, counts, accumulate, nullptr, nullptr, nullptr, nullptr, stream));
     stage_call_begin(stream);
     GateArgs g[1] = {{w_gate, gate_bias, topk_idx, topk_w, nullptr}};
-    return dev(run_route(*shape, tokens, x, g, 1, counts, accumulate, nullptr, false, ws, stream));
+    return dev(run_route(*shape, tokens, x, g, 1, counts, accumulate, false, ws, stream));
 }
 
 int moe_predict_next(const moe_shape_t* shape, int32_t tokens, const void* x, const void* w_gate_next,
@@ -360,7 +356,7 @@ int moe_predict_next(const moe_shape_t* shape, int32_t tokens, const void* x, co
     }
     stage_call_begin(stream);
     GateArgs g[1] = {{w_gate_next, gate_bias_next, pred_idx, pred_w, nullptr}};
-    return dev(run_route(*shape, tokens, x, g, 1, pred_counts, 0, nullptr, false, ws, stream));
+    return dev(run_route(*shape, tokens, x, g, 1, pred_counts, 0, false, ws, stream));
 }
 
 int moe_expert_ffn(const moe_shape_t* shape, int32_t tokens, const void* x, const int32_t* topk_idx,

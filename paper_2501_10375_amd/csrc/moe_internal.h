@@ -32,8 +32,7 @@ constexpr int kStreamMaxTokens = 32;
 struct WorkspaceLayout {
     size_t dec_flags;    // uint32 [kDecodeFlagInts]  arrival flags, launch count and status word of the decode kernel's two grid-wide rendezvous
     size_t sync;         // int32 [kSyncInts]    tile hand-out counters of the two grouped GEMMs
-    size_t hist;         // int32 [n_blocks, E]  per-block selection histogram
-    size_t hist_next;    // int32 [n_blocks, E]  same for the next-layer gate; both together also hold RouteFinish::words
+    size_t hist;         // int32 [n_blocks, E]  per-block selection histogram, or uint64 [n_blocks, E] RouteFinish::words
     size_t offs;         // int32 [E + 1]        exclusive scan of counts
     size_t row_of_slot;  // int32 [A]            slot -> assignment index t*k + j
     size_t slot_of;      // int32 [A]            assignment index -> slot
@@ -76,7 +75,7 @@ struct RouteFinish {
     int32_t* counts;
     int accumulate;
     int32_t *offs, *row_of_slot, *slot_of, *sync;
-    uint64_t* words;   // [n_blocks, E] scratch: the memory of both histograms
+    uint64_t* words;   // [n_blocks, E] scratch: the memory of the histograms
 };
 bool route_finishes(const moe_shape_t& s, int tokens, bool permute);
 
@@ -104,11 +103,10 @@ hipError_t launch_finalize(const moe_shape_t& s, int tokens, int32_t* hist, cons
                            int32_t* counts, int accumulate, int32_t* offs, int32_t* row_of_slot,
                            int32_t* slot_of, int32_t* sync, hipStream_t stream);
 
-// Decode path (tokens <= kDecodeMaxTokens): routing for up to two gates with
-// counts written directly, in one workgroup.
+// Decode path (tokens <= kDecodeMaxTokens): routing for up to two gates in one workgroup, which writes the
+// first gate's counts (may be null) as well.
 hipError_t launch_route_small(const moe_shape_t& s, int tokens, const void* x, const GateArgs* gates,
-                              int n_gates, int32_t* counts, int accumulate, int32_t* counts_next,
-                              hipStream_t stream);
+                              int n_gates, int32_t* counts, int accumulate, hipStream_t stream);
 
 // Expert execution with pre-calculated selections (moe_expert_ffn_precalc): selection a = t * k + j
 // reads its input row from x_stale instead of x when stale[a] != 0.  Both null: the plain layer.

@@ -22,7 +22,6 @@ struct RouteParams {
     int tokens, hidden, n_experts, top_k, n_gates;
     GateArgs gate[2];
     int32_t* counts;       // decode-size calls only
-    int32_t* counts_next;  // decode-size calls only
     int accumulate;
     RouteFinish finish;    // words == null: left to other kernels
 };
@@ -298,7 +297,7 @@ __global__ __launch_bounds__(kRouteWaves<NBG> * 64) void route_mfma_kernel(Route
 }
 
 // One workgroup routes a decode-size call against up to two gates and writes indices, weights
-// and counts.
+// and the first gate's counts.
 template <typename scalar_t, bool MFMA>
 __global__ __launch_bounds__(kSmallRouteThreads) void route_small_kernel(RouteParams p) {
     __shared__ RouteSmem sm;
@@ -315,11 +314,10 @@ __global__ __launch_bounds__(kSmallRouteThreads) void route_small_kernel(RoutePa
             p.gate[g].idx[tid] = sm.idx[tid];
             if (p.gate[g].wts != nullptr) p.gate[g].wts[tid] = sm.w[tid];
         }
-        int32_t* counts = g == 0 ? p.counts : p.counts_next;
-        if (tid < E && counts != nullptr) {
+        if (g == 0 && tid < E && p.counts != nullptr) {
             int c = 0;
             for (int a = 0; a < A; ++a) c += sm.idx[a] == tid;
-            counts[tid] = (g == 0 ? old_count : 0) + c;
+            p.counts[tid] = old_count + c;
         }
         __syncthreads();  // sm is reused by the next gate
     }
@@ -363,11 +361,9 @@ hipError_t launch_route(const moe_shape_t& s, int tokens, const void* x, const G
 }
 
 hipError_t launch_route_small(const moe_shape_t& s, int tokens, const void* x, const GateArgs* gates,
-                              int n_gates, int32_t* counts, int accumulate, int32_t* counts_next,
-                              hipStream_t stream) {
+                              int n_gates, int32_t* counts, int accumulate, hipStream_t stream) {
     RouteParams p = make_params(s, tokens, x, gates, n_gates);
     p.counts = counts;
-    p.counts_next = counts_next;
     p.accumulate = accumulate;
     if (s.dtype == MOE_F32) route_small_kernel<float, false><<<1, kSmallRouteThreads, 0, stream>>>(p);
     else if (decode_routes_on_mfma(tokens, s.hidden, s.n_experts)) route_small_kernel<uint16_t, true><<<1, kSmallRouteThreads, 0, stream>>>(p);
