@@ -43,8 +43,13 @@ struct RouteParams {
 // wavefront of a short hidden dimension asks for no unit twice, and addresses are constants from the row's start (with an address a
 // step, 64 experts spilled registers; fp32 with 64 experts has registers for one unit only).
 // The two gates of a call go to different workgroups (x comes from the L2 the second time) while those fit the chip at one a CU, and
-// are done one after the other by the same workgroup beyond that (4096 tokens: 23 us so, 27 us in two rounds).
-// NBG = number of 16-expert blocks.
+// are done one after the other by the same workgroup beyond that (whole layer of hidden 4096, ffn 64, 8 experts, 4096 tokens 116.6 us so,
+// 117.7 with different workgroups; hidden 2048, 64 experts, 2500 tokens 83.8 / 84.8).
+// NBG = number of 16-expert blocks.  SHARERS: where more than 32 experts meet a hidden dimension of at most four units, a wavefront makes one
+// unit for NBG / SHARERS of the blocks.  (A wavefront's chain of blocks, each through LDS and in fp32 eight MFMAs a step, is what such a
+// call waits for while other wavefronts have no unit.  moe_route, 64 experts top-6, 200 tokens, a unit a wavefront / shared: fp32, hidden 64
+// 9.0 / 8.4 us, 128 top-4, 100 tokens 8.0 / 7.9; bf16, hidden 64 8.3 / 8.1, 192 top-4, 100 tokens 7.3 / 7.2; with 17 to 32 experts a chain is two
+// blocks, and sharing is no faster: fp32, hidden 64 7.1 / 7.1, bf16, hidden 256 7.0 / 7.1.)
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -170,7 +175,50 @@ __device__ inline void finish_routing(const RouteFinish& f, const int32_t* idx, 
     }
 }
 
-template <typename scalar_t, int NBG>
+// Adds the products of N units with NB blocks of experts, requested together.  x, w: lane l's piece of rows l / 8 (lo) and 8 + l / 8 (hi) of
+// the first unit, piece l % 8, which goes to position (l % 8) ^ (row / 2 % 8) of the row in `mine` (4 KB); operands: row l % 16, piece l / 16
+// (+ 4 for the second step).
+template <int N, typename scalar_t, int NB, int SUMS>
+__device__ __attribute__((always_inline)) inline void add_units(const scalar_t* x_lo, const scalar_t* x_hi, const scalar_t* const (&w_lo)[NB],
+                                                                const scalar_t* const (&w_hi)[NB], size_t off, unsigned char* mine,
+                                                                f32x4 (&acc)[NB][SUMS]) {
+    constexpr int kUnit = 128 / (int)sizeof(scalar_t);
+    const int lane = threadIdx.x & 63, row = lane >> 3, piece = lane & 7;
+    const int put_lo = row * 128 + ((piece ^ (row >> 1)) << 4), put_hi = (row + 8) * 128 + ((piece ^ (4 + (row >> 1))) << 4);
+    const int get = (lane & 15) * 128 + (((lane >> 4) ^ ((lane >> 1) & 7)) << 4);  // (second step: ^ 64)
+    u32x4 xl[N], xh[N], wl[NB][N], wh[NB][N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        xl[i] = *reinterpret_cast<const u32x4*>(x_lo + off + i * kUnit);
+        xh[i] = *reinterpret_cast<const u32x4*>(x_hi + off + i * kUnit);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            wl[nb][i] = *reinterpret_cast<const u32x4*>(w_lo[nb] + off + i * kUnit);
+            wh[nb][i] = *reinterpret_cast<const u32x4*>(w_hi[nb] + off + i * kUnit);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        *reinterpret_cast<u32x4*>(mine + put_lo) = xl[i];
+        *reinterpret_cast<u32x4*>(mine + put_hi) = xh[i];
+        u32x4 xa[2];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            *reinterpret_cast<u32x4*>(mine + 2048 + put_lo) = wl[nb][i];
+            *reinterpret_cast<u32x4*>(mine + 2048 + put_hi) = wh[nb][i];
+            wave_order();
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (nb == 0) xa[h] = *reinterpret_cast<const u32x4*>(mine + (get ^ (h * 64)));
+                mfma_step(xa[h], *reinterpret_cast<const u32x4*>(mine + 2048 + (get ^ (h * 64))), h, acc[nb]);
+            }
+            wave_order();
+        }
+    }
+}
+
+template <typename scalar_t, int NBG, int SHARERS>
 __global__ __launch_bounds__(kRouteWaves<NBG> * 64) void route_mfma_kernel(RouteParams p) {
     constexpr bool kF32 = sizeof(scalar_t) == 4;
     constexpr int kSums = kF32 ? 8 : 1, kWaves = kRouteWaves<NBG>;
@@ -183,78 +231,45 @@ __global__ __launch_bounds__(kRouteWaves<NBG> * 64) void route_mfma_kernel(Route
     if (tid < 128) hist[tid >> 6][tid & 63] = 0;
     const int H = p.hidden, E = p.n_experts, T = p.tokens;
     const int t0 = blockIdx.x * kRouteTokensPerBlock;
-    // loads: lane l has piece l % 8 of rows l / 8 and 8 + l / 8 of a unit, which goes to position (l % 8) ^ (row / 2 % 8) of the row;
-    // operands: row l % 16, piece l / 16 (+ 4 for the second step)
-    const int row = lane >> 3, piece = lane & 7;
+    const int row = lane >> 3, piece = lane & 7;  // see add_units()
     const scalar_t* x_lo = static_cast<const scalar_t*>(p.x) + (size_t)min(t0 + row, T - 1) * H + piece * kLane;
     const scalar_t* x_hi = static_cast<const scalar_t*>(p.x) + (size_t)min(t0 + row + 8, T - 1) * H + piece * kLane;
     unsigned char* mine = turn[wave];
-    const int put_lo = row * 128 + ((piece ^ (row >> 1)) << 4), put_hi = (row + 8) * 128 + ((piece ^ (4 + (row >> 1))) << 4);
-    const int get = (lane & 15) * 128 + (((lane >> 4) ^ ((lane >> 1) & 7)) << 4);  // (second step: ^ 64)
     const int n_units = H / kUnit;
-    const int per = (n_units + kWaves - 1) / kWaves;
-    const int u_begin = wave * per;
-    const int u_end = min(n_units, u_begin + per);
+    // This wavefront's units and blocks of experts, and the partial tile that they go to.
+    const int per = SHARERS > 1 ? 1 : (n_units + kWaves - 1) / kWaves;
+    const int slot = wave / SHARERS, slots = SHARERS > 1 ? n_units : kWaves;
+    const int u_begin = slot * per, u_end = min(n_units, u_begin + per);
+    constexpr int NB = NBG / SHARERS, kChunkUnits = SHARERS > 1 ? 1 : kChunk;
+    const int first = wave % SHARERS * NB;
 
     const int g_begin = gridDim.y > 1 ? blockIdx.y : 0, g_end = gridDim.y > 1 ? blockIdx.y + 1 : p.n_gates;
     for (int g = g_begin; g < g_end; ++g) {
         const GateArgs gate = p.gate[g];
         const float my_bias = gate.bias != nullptr && lane < E ? gate.bias[lane] : 0.f;
         // rows 16 nb + lane / 8 and 8 further on; columns past the last expert compute a logit that nobody reads
-        const scalar_t *w_lo[NBG], *w_hi[NBG];
+        const scalar_t *w_lo[NB], *w_hi[NB];
 #pragma unroll
-        for (int nb = 0; nb < NBG; ++nb) {
-            w_lo[nb] = static_cast<const scalar_t*>(gate.w) + (size_t)min(nb * 16 + row, E - 1) * H + piece * kLane;
-            w_hi[nb] = static_cast<const scalar_t*>(gate.w) + (size_t)min(nb * 16 + row + 8, E - 1) * H + piece * kLane;
+        for (int nb = 0; nb < NB; ++nb) {
+            w_lo[nb] = static_cast<const scalar_t*>(gate.w) + (size_t)min((first + nb) * 16 + row, E - 1) * H + piece * kLane;
+            w_hi[nb] = static_cast<const scalar_t*>(gate.w) + (size_t)min((first + nb) * 16 + row + 8, E - 1) * H + piece * kLane;
         }
-
-        f32x4 acc[NBG][kSums];
+        f32x4 acc[NB][kSums];
 #pragma unroll
-        for (int nb = 0; nb < NBG; ++nb)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
             for (int q = 0; q < kSums; ++q) acc[nb][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        auto units = [&](auto n_c, int u0) {
-            constexpr int N = decltype(n_c)::value;
-            u32x4 xl[N], xh[N], wl[NBG][N], wh[NBG][N];
-            const size_t off = (size_t)u0 * kUnit;
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                xl[i] = *reinterpret_cast<const u32x4*>(x_lo + off + i * kUnit);
-                xh[i] = *reinterpret_cast<const u32x4*>(x_hi + off + i * kUnit);
-#pragma unroll
-                for (int nb = 0; nb < NBG; ++nb) {
-                    wl[nb][i] = *reinterpret_cast<const u32x4*>(w_lo[nb] + off + i * kUnit);
-                    wh[nb][i] = *reinterpret_cast<const u32x4*>(w_hi[nb] + off + i * kUnit);
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                *reinterpret_cast<u32x4*>(mine + put_lo) = xl[i];
-                *reinterpret_cast<u32x4*>(mine + put_hi) = xh[i];
-                u32x4 xa[2];
-#pragma unroll
-                for (int nb = 0; nb < NBG; ++nb) {
-                    *reinterpret_cast<u32x4*>(mine + 2048 + put_lo) = wl[nb][i];
-                    *reinterpret_cast<u32x4*>(mine + 2048 + put_hi) = wh[nb][i];
-                    wave_order();
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        if (nb == 0) xa[h] = *reinterpret_cast<const u32x4*>(mine + (get ^ (h * 64)));
-                        mfma_step(xa[h], *reinterpret_cast<const u32x4*>(mine + 2048 + (get ^ (h * 64))), h, acc[nb]);
-                    }
-                    wave_order();
-                }
-            }
-        };
-        for (int u0 = u_begin; u0 < u_end; u0 += kChunk) {
-            for_count<kChunk>(min(kChunk, u_end - u0), [&](auto n) { units(n, u0); });
-        }
+        for (int u0 = u_begin; u0 < u_end; u0 += kChunkUnits)
+            for_count<kChunkUnits>(min(kChunkUnits, u_end - u0), [&](auto n) {
+                add_units<decltype(n)::value>(x_lo, x_hi, w_lo, w_hi, (size_t)u0 * kUnit, mine, acc);
+            });
 
         // MFMA result: lane holds column (expert in block) lane & 15 and rows (tokens) 4 * (lane / 16) + r.
         if (g > g_begin) __syncthreads();  // the previous gate's partial tiles have been read
+        if (SHARERS == 1 || slot < slots) {
 #pragma unroll
-        for (int nb = 0; nb < NBG; ++nb) part[wave][nb][lane] = total_of(acc[nb]);
+            for (int nb = 0; nb < NB; ++nb) part[slot][first + nb][lane] = total_of(acc[nb]);
+        }
         __syncthreads();
         for (int i = wave; i < kRouteTokensPerBlock && t0 + i < T; i += kWaves) {  // token t0 + i, by one wavefront
             const int t = t0 + i;
@@ -263,7 +278,7 @@ __global__ __launch_bounds__(kRouteWaves<NBG> * 64) void route_mfma_kernel(Route
                 const int nb = lane >> 4, src = (i >> 2) * 16 + (lane & 15), r = i & 3;
                 float v[kWaves];
 #pragma unroll
-                for (int w = 0; w < kWaves; ++w) v[w] = part[w][nb][src][r];
+                for (int w = 0; w < kWaves; ++w) v[w] = SHARERS == 1 || w < slots ? part[w][nb][src][r] : 0.f;
                 if constexpr (kF32) {
 #pragma unroll
                     for (int d = kWaves / 2; d > 0; d /= 2)
@@ -327,9 +342,19 @@ template <typename scalar_t>
 void launch_mfma(const RouteParams& p, hipStream_t stream) {
     const int blocks = route_blocks(p.tokens);
     const dim3 grid(blocks, blocks * p.n_gates <= compute_units() ? p.n_gates : 1);
-    if (p.n_experts <= 16) route_mfma_kernel<scalar_t, 1><<<grid, kRouteWaves<1> * 64, 0, stream>>>(p);
-    else if (p.n_experts <= 32) route_mfma_kernel<scalar_t, 2><<<grid, kRouteWaves<2> * 64, 0, stream>>>(p);
-    else route_mfma_kernel<scalar_t, 4><<<grid, kRouteWaves<4> * 64, 0, stream>>>(p);
+    auto launch = [&](auto nbg, auto sharers) {
+        constexpr int kBlocks = decltype(nbg)::value;
+        route_mfma_kernel<scalar_t, kBlocks, decltype(sharers)::value><<<grid, kRouteWaves<kBlocks> * 64, 0, stream>>>(p);
+    };
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    using Four = std::integral_constant<int, 4>;
+    const int units = p.hidden / (128 / (int)sizeof(scalar_t));
+    if (p.n_experts <= 16) launch(One{}, One{});
+    else if (p.n_experts <= 32) launch(Two{}, One{});
+    else if (units <= 2) launch(Four{}, Four{});
+    else if (units <= 4) launch(Four{}, Two{});
+    else launch(Four{}, One{});
 }
 
 RouteParams make_params(const moe_shape_t& s, int tokens, const void* x, const GateArgs* gates, int n_gates) {

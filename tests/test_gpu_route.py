@@ -44,6 +44,11 @@ def _route(oracle, T, H, E, k, dtype):
     (33, 192, 17, 2),      # one expert in the second block
     (40, 1088, 33, 3),     # units that do not divide the wavefronts; one expert in the third block
     (50, 4096, 48, 8),     # three of four blocks
+    (33, 64, 33, 2),       # one or two units, each shared by four wavefronts
+    (50, 128, 64, 8),      # two (shared by four) or four (by two)
+    (17, 192, 48, 3),      # three shared by two, or six
+    (40, 256, 64, 6),      # four shared by two, or eight
+    (24, 320, 40, 4),      # five and ten: not shared
     (31, 8256, 8, 1),      # several chunks a wavefront and a rest
     (70, 2112, 64, 8),
     (100, 4160, 32, 4),
