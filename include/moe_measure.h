@@ -27,7 +27,10 @@ extern "C" {
  * SwiGLU, 3 grouped GEMM2, 4 combine, 5 a kernel that runs both GEMMs: of a bf16
  * call of at most 16 tokens everything (routing when the entry point routes,
  * combine), of one of at most 32 tokens the combine, and in longer calls of
- * middle size just the two grouped GEMMs (stages 2 and 3 are not recorded then).  begin allocates events for up to max_calls calls (later calls
+ * middle size just the two grouped GEMMs (stages 2 and 3 are not recorded then).
+ * Where the routing kernel makes the counts, and in shorter calls the
+ * permutation, too, their time is in stage 0 and stage 1 is not recorded.
+ * begin allocates events for up to max_calls calls (later calls
  * are not recorded); end synchronises with the last recorded event, writes
  * the mean milliseconds per launch of each stage and the number of launches
  * averaged (either pointer may be NULL), and frees the events.
@@ -84,9 +87,10 @@ int moe_calibrate_read_stream(const void* device_buffer, size_t bytes, float* mi
 /*
  * Test aid: the number of polling rounds that a rendezvous of the decode-size
  * kernel, or a workgroup of a kernel that runs both grouped GEMMs, waits before
- * it gives up (process-wide; default 4194304).  With 0 every one gives up at once, which lets a test see the failure report
- * of moe_decode_status while every kernel still runs to its end: the affected
- * calls write NaN into y and raise the status word.  Not for production use.
+ * it gives up (process-wide; default 4194304).  With 0 every one gives up at
+ * once, which lets a test see the failure report of moe_decode_status while
+ * every kernel still runs to its end: the affected calls write NaN into y and
+ * raise the status word.  Not for production use.
  * Errors: MOE_ERR_SHAPE (negative).
  */
 int moe_measure_set_decode_spin_limit(int32_t polling_rounds);

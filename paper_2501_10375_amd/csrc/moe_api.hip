@@ -260,8 +260,7 @@ int enqueue_layer(const moe_shape_t& s, int32_t tokens, const void* x, const voi
         return dev(launch_finalize(s, 0, ws.hist, nullptr, counts, accumulate, nullptr, nullptr, nullptr, nullptr, stream));
     stage_call_begin(stream);
     if (decode_path(s, tokens)) {
-        // One kernel routes, runs the experts and (in one of its workgroups, at the end) evaluates the
-        // prediction gate.
+        // One kernel routes, evaluates the prediction gate (in one of its workgroups) and runs the experts.
         const DecodeRoute r = {w_gate, gate_bias, topk_idx, topk_w, counts, accumulate, w_gate_next, gate_bias_next, pred_idx};
         return dev(launch_decode_layer(s, tokens, x, &r, nullptr, nullptr, w1, w3, w2, y, ws.act, ws.dec_flags, kNoStaleInput,
                                        stream));

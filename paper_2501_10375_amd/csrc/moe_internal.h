@@ -61,7 +61,7 @@ struct GateArgs {
 // Stage ids of the optional per-stage timing (moe_stage_timing_begin/end in moe_measure.h).
 enum Stage {
     kStageRoute = 0, kStagePermute = 1, kStageGemm1 = 2, kStageGemm2 = 3, kStageCombine = 4,
-    kStageFused = 5,  // the single kernel of a decode-size bf16 call
+    kStageFused = 5,  // a kernel that runs both GEMMs (moe_measure.h)
 };
 static_assert(kStageFused + 1 == MOE_NUM_STAGES, "moe_measure.h lists the stages");
 // Records "stage `stage` ends here" on `stream`; a no-op unless timing is active on this thread.
@@ -151,7 +151,7 @@ struct DecodeRoute {
     int32_t* counts;
     int accumulate;
     // optional prediction (the next layer's gate on the same hidden states): evaluated by one
-    // workgroup after its share of the experts; pred_idx [tokens, top_k]
+    // workgroup before its share of the experts; pred_idx [tokens, top_k]
     const void* w_gate_next;
     const float* bias_next;
     int32_t* pred_idx;

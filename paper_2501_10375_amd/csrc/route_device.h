@@ -171,18 +171,6 @@ __device__ inline float reduce8_scatter(const float (&acc)[8], int lane) {
     return v;
 }
 
-// Routes tokens 0..T (T <= 16) against one gate; every thread of the 512-thread workgroup calls
-// it.  On return (after a workgroup barrier) sm.idx[t*k + j] / sm.w[t*k + j] hold expert and
-// renormalised weight of selection j of token t, in descending probability, ties to the lower
-// index.  The arithmetic depends only on (T, H, E, k), never on the workgroup, so any number of
-// workgroups computing the same call agree bit for bit.  `part` is kRoutePartFloats of LDS.
-// `turn` (kRouteTurnBytes of LDS): bf16 on the matrix cores; null: on the vector lanes.  With `on_gpu` (uint8 [E]) the selection is degraded gracefully, see select_topk_lanes.
-//
-// With `turn`: partial_logits_mfma().  Else the 8 wavefronts split the hidden dimension in interleaved 512-element chunks, so the
-// gate and x are read once per workgroup whatever T is; a wavefront walks the tokens two at a time over
-// its chunks (the gate pieces of later tokens come from the vector cache).  Per-wavefront partial
-// logits are summed through LDS in a fixed order; the softmax and the k arg-max passes run
-// across the lanes of one wavefront, lane e holding expert e.
 // bf16 logits on the matrix cores: the tokens are the 16 rows of an MFMA, 16 experts its columns, and the 8 wavefronts split the hidden
 // dimension in interleaved units of 64 elements.  All loads of up to 8 units are requested before the first one is used, so 16 experts cost
 // one memory round trip whatever the number of tokens.  A load covers 8 rows x 128 bytes, consecutive lanes on consecutive addresses,
@@ -271,6 +259,19 @@ __device__ __attribute__((always_inline)) inline void partial_logits_mfma(const 
     }
 }
 
+// Routes tokens 0..T (T <= 16) against one gate; every thread of the 512-thread workgroup calls
+// it.  On return (after a workgroup barrier) sm.idx[t*k + j] / sm.w[t*k + j] hold expert and
+// renormalised weight of selection j of token t, in descending probability, ties to the lower
+// index.  The arithmetic depends only on (T, H, E, k), never on the workgroup, so any number of
+// workgroups computing the same call agree bit for bit.  `part` is kRoutePartFloats of LDS.
+// `turn` (kRouteTurnBytes of LDS): bf16 on the matrix cores; null: on the vector lanes.  With `on_gpu` (uint8 [E]) the selection
+// is degraded gracefully, see select_topk_lanes.
+//
+// With `turn`: partial_logits_mfma().  Else the 8 wavefronts split the hidden dimension in interleaved 512-element chunks, so the
+// gate and x are read once per workgroup whatever T is; a wavefront walks the tokens two at a time over
+// its chunks (the gate pieces of later tokens come from the vector cache).  Per-wavefront partial
+// logits are summed through LDS in a fixed order; the softmax and the k arg-max passes run
+// across the lanes of one wavefront, lane e holding expert e.
 template <typename scalar_t>
 __device__ __attribute__((always_inline)) inline void route_tokens_wg(const scalar_t* __restrict__ x, const scalar_t* __restrict__ wg,
                                        const float* __restrict__ bias, int T, int H, int E, int k, RouteSmem& sm,
