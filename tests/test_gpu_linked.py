@@ -33,6 +33,7 @@ def _stages(shape, d, out):
 
 @pytest.mark.parametrize("T,H,F,E,k", [
     (1024, 320, 896, 64, 8),   # five K steps in the first GEMM: the fewest; a quarter of a feature tile at the end of the second
+    (2400, 768, 320, 64, 8),   # five K steps in the second GEMM: the fewest; 300 rows an expert: the most
     (88, 576, 1344, 64, 8),    # nine K steps; half a feature tile at the end; experts with a handful of rows
     (100, 1088, 1728, 48, 4),
     (600, 2048, 1024, 32, 4),  # little more than a round of both
